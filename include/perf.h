@@ -92,8 +92,9 @@ perf_status perf_layernorm(const void *x, const void *gamma, const void *beta, v
  *   (strides >= 0; strideC must be >= the extent of one C when batch > 1).
  * The bf16 MFMA path is taken for bf16 operands with A row-major and B column-major (both
  * K-contiguous), K a multiple of 32, lda/ldb/strides multiples of 8 and 16-byte aligned
- * pointers; every other legal combination (fp32 operands, other layouts, any K) runs a kernel
- * built on the fp32 matrix instruction.
+ * pointers; every other legal combination (fp32 operands, other layouts, any K) passes its
+ * operands through registers on the way to the same matrix instruction; an fp32 operand is split
+ * exactly into three bf16 and a product computed as six of theirs (what is left out is below 2^-23 of it).
  * Errors: NULL, SHAPE, DTYPE, LAYOUT, ALIGN (pointer not aligned to its element size),
  * UNSUPPORTED (f32 operands with bf16 C), LAUNCH. */
 perf_status perf_gemm(const void *A, const void *B, void *C, int64_t M, int64_t N, int64_t K,

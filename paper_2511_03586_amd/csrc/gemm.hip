@@ -4,11 +4,11 @@
 //  * gemm_mfma_kernel: bf16 operands, A row-major and B column-major (both K-contiguous),
 //    K a multiple of 32.  256x256, 128x128 or 64x64 workgroup tile; the K-step-64 loop of
 //    mfma_tile.h when K is a multiple of 64, else its K-step-32 loop.
-//  * f32mfma_kernel (f32mfma.h): any layout / dtype / size (fp32 operands, other layouts, odd K):
-//    the fp32 matrix instruction on operands staged through LDS as fp32.
+//  * staged_kernel (staged.h, launched by staged_gemm.hip): any layout / dtype / size / alignment (fp32 operands,
+//    other layouts, odd K), on the bf16 matrix instruction as well.
 #include <atomic>
 #include "mfma_tile.h"
-#include "f32mfma.h"
+#include "staged.h"
 #include "host_utils.h"
 #include "timeline.h"
 
@@ -111,15 +111,6 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_mfma_kernel(const uint16_t 
     }
 }
 
-struct GemmArgs {
-    const void *A, *B;
-    void *C;
-    int64_t M, N, K, lda, ldb, ldc, batch, strideA, strideB, strideC;
-    int la, lb;
-    float alpha;
-    hipStream_t st;
-};
-
 template <int TM, int TN, int WM, int WN, bool K64, typename CT, int NS = kStages, bool MI32 = false>
 static perf_status launch_mfma(const GemmArgs &g)
 {
@@ -145,28 +136,6 @@ static perf_status launch_mfma(const GemmArgs &g)
     }
     return launch_status();
 }
-
-template <typename T, typename CT>
-static perf_status launch_general(const GemmArgs &g)
-{
-    const int64_t a_sm = g.la == PERF_ROW_MAJOR ? g.lda : 1, a_sk = g.la == PERF_ROW_MAJOR ? 1 : g.lda;
-    const int64_t b_sk = g.lb == PERF_ROW_MAJOR ? g.ldb : 1, b_sn = g.lb == PERF_ROW_MAJOR ? 1 : g.ldb;
-    // 128 x 128 tiles when they give every CU a workgroup, else 64 x 64
-    const bool big = ((g.M + 127) / 128) * ((g.N + 127) / 128) * g.batch >= 256;
-    const int64_t edge = big ? 128 : 64;
-    const int64_t gx = (g.M + edge - 1) / edge, gy = (g.N + edge - 1) / edge;
-    if (gx > kMaxGridX || gy > kMaxGridYZ) return PERF_ERR_UNSUPPORTED;
-    const unsigned gz = (unsigned)(g.batch < kMaxGridYZ ? g.batch : kMaxGridYZ);
-    const DenseRows<T> a_src{(const T *)g.A, a_sm, a_sk, g.M, g.K};
-    auto kern = big ? f32mfma_kernel<2, 2, DenseRows<T>, T, CT> : f32mfma_kernel<1, 1, DenseRows<T>, T, CT>;
-    hipLaunchKernelGGL(kern, dim3((unsigned)gx, (unsigned)gy, gz), dim3(256), 0, g.st, a_src, (const T *)g.B, (CT *)g.C,
-                       g.M, g.N, g.K, b_sk, b_sn, g.ldc, g.strideA, g.strideB, g.strideC, g.batch, g.alpha);
-    return launch_status();
-}
-
-}  // namespace perf
-
-namespace perf {
 
 template <int TM, int TN, int WM, int WN>
 static perf_status launch_mfma_rt(const GemmArgs &g, bool k64, bool c_f32)
@@ -246,9 +215,7 @@ static perf_status gemm_impl(const void *A, const void *B, void *C, int64_t M, i
         if (tile == 128) return launch_mfma_rt<2, 2, 2, 2>(g, k64, c_f32);
         return launch_mfma_rt<1, 1, 2, 2>(g, k64, c_f32);
     }
-    if (ab_dt == PERF_BF16)
-        return c_dt == PERF_F32 ? launch_general<uint16_t, float>(g) : launch_general<uint16_t, uint16_t>(g);
-    return launch_general<float, float>(g);
+    return launch_staged_gemm(g, ab_dt, c_dt);
 }
 
 }  // namespace perf

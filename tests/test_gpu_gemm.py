@@ -123,6 +123,55 @@ def test_general_kernel_layouts_exact_integers(a_col, b_col, M, N, K):
     assert np.array_equal(c16.astype(np.float64), ref) and np.array_equal(c32.astype(np.float64), ref)
 
 
+@pytest.mark.parametrize("ab_bf16,c_bf16", [(True, False), (True, True), (False, False)])
+@pytest.mark.parametrize("a_col,b_col", [(False, False), (True, False), (True, True), (False, True)])
+@pytest.mark.parametrize("M,N,K,batch,pad", [
+    (1, 1, 1, 1, 0), (7, 3, 5, 2, 0), (3, 300, 7, 1, 1),       # extents below a 16-byte load: element loads
+    (8, 9, 8, 1, 0), (64, 64, 64, 1, 0), (65, 71, 130, 2, 3),    # 64 x 64 tile: exact, ragged in every extent, odd ld
+    (100, 70, 643, 1, 1), (64, 130, 1024, 1, 0), (9, 10, 257, 3, 1),   # several wave groups: odd and even step counts
+    (257, 131, 97, 64, 0), (130, 250, 64, 96, 5),                # 128 x 128 (bf16), 256 x 128 (fp32)
+    (40, 33, 521, 200, 1), (300, 261, 512, 100, 0),              # 256 x 256 (bf16): ragged first and second tiles
+])
+def test_staged_kernel_edges(M, N, K, batch, pad, a_col, b_col, ab_bf16, c_bf16):
+    """Every layout and type of the register-staged contraction at the edges of its tiles, K-steps and loads."""
+    g = np.random.default_rng(M * 1000 + N + K)
+    lda, ldb = (M if a_col else K) + pad, (K if b_col else N) + pad
+    a = g.uniform(-1, 1, (batch, K if a_col else M, lda)).astype(np.float32)
+    b = g.uniform(-1, 1, (batch, N if b_col else K, ldb)).astype(np.float32)
+    if ab_bf16:
+        a, b = _bits(a), _bits(b)
+    c = G.run_gemm(a, b, M, N, K, a_col=a_col, b_col=b_col, batch=batch, ab_bf16=ab_bf16, c_bf16=c_bf16, lda=lda, ldb=ldb,
+                   ldc=N + pad, alpha=0.75)
+    for i in sorted({0, batch // 2, batch - 1}):
+        ai, bi = oracle.widen(a[i], ab_bf16), oracle.widen(b[i], ab_bf16)
+        ref = oracle.gemm(ai, bi, M, N, K, a_col=a_col, b_col=b_col, alpha=0.75, lda=lda, ldb=ldb)
+        A = ai[:, :M].T if a_col else ai[:, :K]
+        B = bi[:, :K].T if b_col else bi[:, :N]
+        absdot = 0.75 * (np.abs(A) @ np.abs(B))
+        # fp32 operands: the products that the split leaves out are below 2^-23 of |a||b| each (K + 1 in the bound)
+        P.assert_contraction_close(P.bf16_to_f64(c[i]) if c_bf16 else c[i], ref, absdot, K + 1, out_bf16=c_bf16)
+
+
+@pytest.mark.parametrize("a_col,b_col", [(False, False), (True, True)])
+@pytest.mark.parametrize("M,N,K,batch", [(70, 65, 33, 1), (96, 64, 300, 1), (130, 250, 64, 96), (7, 3, 5, 1)])
+def test_fp32_range_ends(M, N, K, batch, a_col, b_col):
+    """fp32 operands at both ends of the range: values around 2^-118 (below what the three-way split holds), one of
+    them among ordinary ones, and values next to the largest. Bounds as for any fp32 accumulation order."""
+    g = np.random.default_rng(K)
+    for scale, where in ((2.0 ** -118, None), (2.0 ** -118, 3), (1.9 * 2.0 ** 126, None)):
+        a = g.uniform(0.5, 1, (batch, K, M) if a_col else (batch, M, K))
+        b = g.uniform(0.5, 1, (batch, N, K) if b_col else (batch, K, N)) / (1 if where is None and scale < 1 else 4 * K)
+        if where is None:
+            a = a * scale
+        else:
+            a.reshape(batch, -1)[:, where] *= scale
+        a, b = a.astype(np.float32), b.astype(np.float32)
+        c = G.run_gemm(a, b, M, N, K, a_col=a_col, b_col=b_col, batch=batch, ab_bf16=False)
+        for i in (0, batch - 1):
+            ref = oracle.gemm(a[i], b[i], M, N, K, a_col=a_col, b_col=b_col)
+            P.assert_contraction_close(c[i], ref, oracle.gemm_absdot(a[i], b[i], M, N, K, a_col=a_col, b_col=b_col), K + 1)
+
+
 def test_mfma_exact_integers_identity_permutation_ones():
     g = np.random.default_rng(3)
     M, N, K = 200, 136, 192
