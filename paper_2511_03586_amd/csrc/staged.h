@@ -630,10 +630,10 @@ __global__ __launch_bounds__(64 * WM * WN * KG, (StagedShape<T, TM, TN, WM, WN, 
     // register set (it + 1) % D to the other stage, and that set is refilled with step it + 1 + D.  Rounds are
     // straight-line code with no conditions around their loads (one that is issued on one of two paths makes
     // the compiler wait for all of them).
-    // EDGE = false rounds: all that have only whole steps to fetch and park; if K is whole, every full round (what
-    // they fetch past the end is the last step once more, never used).
-    const bool clean = a_src.whole() && b_src.whole(), even = K % BK == 0;
-    const int64_t fast_rounds = !clean ? 0 : even ? nsteps / KG : K / BK / KG - D - 1;
+    // EDGE = false rounds: all that have only whole steps to fetch and park; if the rounds divide K, every one (what
+    // they fetch past the end is the last step once more, never multiplied).
+    const bool clean = a_src.whole() && b_src.whole(), even = K % (BK * KG) == 0;
+    const int64_t fast_rounds = !clean ? 0 : even ? rounds : K / BK / KG - D - 1;
     auto step_k = [&](int64_t it) { return (it * KG + group) * BK; };
     auto round = [&](auto u, auto edge, int64_t it) {
         constexpr int slot = (u + 1) % D, buf = u & 1;
@@ -725,6 +725,17 @@ struct GemmArgs {
     float alpha;
     hipStream_t st;
 };
+
+// A convolution as launch_staged_conv takes it: NHWC x, KRSC w, NPQK y.
+struct StagedConv {
+    const void *x, *w;
+    void *y;
+    int N, H, W, C, K, R, S, sh, sw, ph, pw, P, Q;
+    hipStream_t st;
+};
+
+// Any stride, padding, channel count and type (staged_conv.hip).
+perf_status launch_staged_conv(const StagedConv &c, int xw_dt, int y_dt);
 
 // Any layout, type (ab: bf16 or fp32 operands), size and alignment (staged_gemm.hip).
 perf_status launch_staged_gemm(const GemmArgs &g, int ab_dt, int c_dt);

@@ -128,7 +128,8 @@ def test_general_kernel_layouts_exact_integers(a_col, b_col, M, N, K):
 @pytest.mark.parametrize("M,N,K,batch,pad", [
     (1, 1, 1, 1, 0), (7, 3, 5, 2, 0), (3, 300, 7, 1, 1),       # extents below a 16-byte load: element loads
     (8, 9, 8, 1, 0), (64, 64, 64, 1, 0), (65, 71, 130, 2, 3),    # 64 x 64 tile: exact, ragged in every extent, odd ld
-    (100, 70, 643, 1, 1), (64, 130, 1024, 1, 0), (9, 10, 257, 3, 1),   # several wave groups: odd and even step counts
+    (100, 70, 643, 1, 1), (64, 130, 1024, 1, 0), (9, 10, 257, 3, 1),   # several wave groups
+    (64, 72, 704, 1, 0), (72, 64, 288, 1, 0), (64, 64, 1216, 1, 0),    # ... whole K-steps that the groups do not divide
     (257, 131, 97, 64, 0), (130, 250, 64, 96, 5),                # 128 x 128 (bf16), 256 x 128 (fp32)
     (40, 33, 521, 200, 1), (300, 261, 512, 100, 0),              # 256 x 256 (bf16): ragged first and second tiles
 ])
