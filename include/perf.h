@@ -110,8 +110,8 @@ perf_status perf_gemm(const void *A, const void *B, void *C, int64_t M, int64_t 
  *   x  device, NHWC dense;  w  device, KRSC dense;  y  device, NPQK dense
  *   xw_dt  dtype of x and w (bf16 or f32);  y_dt  f32 or bf16;  fp32 accumulation.
  * The bf16 MFMA path is taken for bf16 x/w with C a multiple of 32 and 16-byte aligned
- * pointers; fp32 x/w (and bf16 with other channel counts) with at least 32 output channels run
- * an implicit GEMM on the fp32 matrix instruction; the remaining cases run direct kernels.
+ * pointers; fp32 x/w (and bf16 with other channel counts from 8 on) with at least 32 output channels run
+ * an implicit GEMM that treats its operands as perf_gemm does; the remaining cases run direct kernels.
  * Errors: NULL, SHAPE (any dim < 1, stride < 1, pad < 0, filter larger than the padded
  * image, more than 2^31-1 output pixels), DTYPE, ALIGN, LAUNCH. */
 perf_status perf_conv2d(const void *x, const void *w, void *y, int64_t N, int64_t H, int64_t W,
@@ -234,7 +234,7 @@ perf_status perf_eltwise(perf_eltwise_op op, const void *a, const void *b, void 
  *     stride 1, few input channels: 5x5 with 3 channels, 3x3 with 3 or 4; W*C even),
  *     6 = variant 1 with the input rows under a workgroup's pixel range resident in LDS
  *     (stride 1; N*P*Q / 256 pixels per range must divide P*Q, and the rows must fit),
- *     7 = implicit GEMM on the fp32 matrix instruction (any dtype, stride, padding, channel count),
+ *     7 = implicit GEMM through registers (any dtype, stride, padding, channel count),
  *     8 = weights in registers with a workgroup per (pixel range, slab of 64 output channels)
  *     and the input rows passing through a ring in LDS (3x3, 64 input channels, bf16, stride 1,
  *     K any multiple of 64, 32 <= Q and a ring of at least 5 rows of 144 Q + 512 bytes within

@@ -17,10 +17,11 @@
 //    layer of the paper's "conv 1"): one filter row per 16-wide MFMA K-step, stride 1.
 //  * conv2d_smallc_kernel: other few-channel cases: one thread per output pixel and block of
 //    KB output channels, weights broadcast from LDS, fp32 FMAs.
+//  * staged_kernel (staged.h, launched by staged_conv.hip): fp32, and other channel counts from 8 on.
 //  * conv2d_direct_kernel: any other legal case; one thread per output element.
 #include <atomic>
 #include "mfma_tile.h"
-#include "f32mfma.h"
+#include "staged.h"
 #include "host_utils.h"
 #include "timeline.h"
 #include <algorithm>
@@ -1613,25 +1614,8 @@ namespace perf {
 
 enum ConvVariant {
     kConvAuto = 0, kConvWreg = 1, kConvMfma = 2, kConvSmallC = 3, kConvDirect = 4, kConvRowMfma = 5, kConvWres = 6,
-    kConvF32Mfma = 7, kConvWsplit = 8
+    kConvStaged = 7, kConvWsplit = 8
 };
-
-// Implicit GEMM on the fp32 matrix instruction: any dtype, stride, padding and channel count.
-template <typename T, typename CT>
-static perf_status launch_conv_f32mfma(const void *x, const void *w, void *y, const ConvGeom &g, hipStream_t st)
-{
-    const int64_t M = (int64_t)g.N * g.P * g.Q, Kred = (int64_t)g.R * g.S * g.C;
-    const bool big = ((M + 127) / 128) * ((g.K + 127) / 128) >= 256;
-    const int64_t edge = big ? 128 : 64;
-    const int64_t gx = (M + edge - 1) / edge, gy = (g.K + edge - 1) / edge;
-    if (gx > kMaxGridX || gy > kMaxGridYZ) return PERF_ERR_UNSUPPORTED;
-    const ConvRows<T> rows{(const T *)x, g.H, g.W, g.C, g.S, g.sh, g.sw, g.ph, g.pw, g.P, g.Q, M, Kred};
-    auto kern = big ? f32mfma_kernel<2, 2, ConvRows<T>, T, CT> : f32mfma_kernel<1, 1, ConvRows<T>, T, CT>;
-    // B(k, n) = w[n][k]: the KRSC filter of output channel n is a row of R*S*C values
-    hipLaunchKernelGGL(kern, dim3((unsigned)gx, (unsigned)gy, 1), dim3(256), 0, st, rows, (const T *)w, (CT *)y, M,
-                       (int64_t)g.K, Kred, (int64_t)1, Kred, (int64_t)g.K, (int64_t)0, (int64_t)0, (int64_t)0, (int64_t)1, 1.0f);
-    return launch_status();
-}
 
 // variant: kConvAuto = chosen here from the shape; otherwise the caller's choice (perf_conv2d_variant).
 static perf_status conv2d_impl(const void *x, const void *w, void *y, int64_t N, int64_t H, int64_t W, int64_t C,
@@ -1712,8 +1696,13 @@ static perf_status conv2d_impl(const void *x, const void *w, void *y, int64_t N,
                             ((R == 5 && S == 5 && C == 3) || (R == 3 && S == 3 && (C == 3 || C == 4))) &&
                             N * H * W * C < (int64_t(1) << 31) && N * ((P + 31) / 32) * ((Q + 63) / 64) <= kMaxGridX &&
                             (K + 15) / 16 <= kMaxGridYZ;
-    // fp32 matrix instruction: worth it from 32 output channels on (a 64-wide tile is then at least half used)
-    const bool f32mfma_ok = K >= 32 && R * S * C >= 16;
+    // staged implicit GEMM: worth it from 32 output channels on (a 64-wide tile is then at least half used); bf16 with
+    // fewer than 8 channels loads element by element there (8x224x224x3->64 62 us against 34 a filter row at a time)
+    const bool staged_ok = K >= 32 && (xw_dt == PERF_F32 || (C >= 8 && R * S * C >= 16));
+    // a filter of one tap on every pixel is a plain GEMM (32x28x28 256->256 bf16: 12.1 us as a convolution)
+    if (variant == kConvAuto && R == 1 && S == 1 && stride_h == 1 && stride_w == 1 && pad_h == 0 && pad_w == 0 && K >= 16 &&
+        C >= 8 && K <= 64 * kMaxGridYZ && !(xw_dt == PERF_F32 && y_dt == PERF_BF16))
+        return perf_gemm(x, w, y, N * P * Q, K, C, PERF_ROW_MAJOR, C, PERF_COL_MAJOR, C, K, 1, 0, 0, 0, 1.0f, xw_dt, y_dt, stream);
     if (variant == kConvAuto)
         // (the channel-blocked kernel has one thread per pixel: below ~64 workgroups of pixels the
         // thread-per-output kernel has more parallelism and measured faster)
@@ -1725,7 +1714,7 @@ static perf_status conv2d_impl(const void *x, const void *w, void *y, int64_t N,
                   : (wres_ok && wres_rounds <= 2) ? kConvWres
                   : wreg_ok                     ? kConvWreg
                   : mfma_ok ? kConvMfma
-                  : (f32mfma_ok && (xw_dt == PERF_F32 || C >= 32)) ? kConvF32Mfma
+                  : staged_ok ? kConvStaged
                   : (rowmfma_ok && N * P * Q >= 16384)          ? kConvRowMfma
                   : (C < 32 && smallc_ok && N * P * Q >= 16384) ? kConvSmallC
                                                                 : kConvDirect;
@@ -1737,13 +1726,9 @@ static perf_status conv2d_impl(const void *x, const void *w, void *y, int64_t N,
     if (variant == kConvWsplit)
         return y_dt == PERF_F32 ? launch_conv_wsplit<3, 3, 64, float>(x, w, y, g, wsplit, st)
                                 : launch_conv_wsplit<3, 3, 64, uint16_t>(x, w, y, g, wsplit, st);
-    if (variant == kConvF32Mfma) {
-        if (xw_dt == PERF_BF16)
-            return y_dt == PERF_F32 ? launch_conv_f32mfma<uint16_t, float>(x, w, y, g, st)
-                                    : launch_conv_f32mfma<uint16_t, uint16_t>(x, w, y, g, st);
-        return y_dt == PERF_F32 ? launch_conv_f32mfma<float, float>(x, w, y, g, st)
-                                : launch_conv_f32mfma<float, uint16_t>(x, w, y, g, st);
-    }
+    if (variant == kConvStaged)
+        return launch_staged_conv(StagedConv{x, w, y, g.N, g.H, g.W, g.C, g.K, g.R, g.S, g.sh, g.sw, g.ph, g.pw, g.P, g.Q, st}, xw_dt,
+                                  y_dt);
     if (variant == kConvWres)
         return y_dt == PERF_F32 ? launch_conv_wres<3, 3, 64, float>(x, w, y, g, wres_px, wres_rows, wres_lds, st)
                                 : launch_conv_wres<3, 3, 64, uint16_t>(x, w, y, g, wres_px, wres_rows, wres_lds, st);

@@ -261,3 +261,32 @@ def test_deterministic():
     a = G.run_conv2d(d["x_bf16"], d["w_bf16"], (1, 1), (1, 1))
     b = G.run_conv2d(d["x_bf16"], d["w_bf16"], (1, 1), (1, 1))
     assert np.array_equal(a, b)
+
+
+@pytest.mark.parametrize("kw", [
+    dict(N=1, H=9, W=8, C=3, K=33, R=1, S=1, pad=0),          # a reduction shorter than a load
+    dict(N=2, H=13, W=9, C=5, K=40, R=3, S=2, pad=1, stride=2),   # element loads, ragged everything
+    dict(N=1, H=17, W=16, C=12, K=64, R=5, S=5, pad=0),
+    dict(N=8, H=56, W=57, C=8, K=70, R=3, S=3, pad=1),         # 128 x 64 tiles (fp32), ragged; K-step of several taps
+    dict(N=1, H=10, W=11, C=72, K=40, R=3, S=3, pad=2),        # two groups of waves that do not divide the K-steps
+    dict(N=1, H=8, W=8, C=64, K=64, R=3, S=3, pad=1),
+    dict(N=3, H=7, W=5, C=24, K=17, R=1, S=1, pad=0),          # one tap on every pixel: the GEMM
+    dict(N=2, H=9, W=9, C=96, K=64, R=1, S=1, pad=0),
+    dict(N=2, H=9, W=9, C=40, K=64, R=1, S=1, pad=0, stride=2),   # one tap, strided: no plain GEMM
+])
+def test_staged_conv_edges(kw):
+    """The register-staged implicit GEMM and the one-tap route, bf16 and fp32 operands, by the library's own choice."""
+    wl = configs.ConvWorkload(**kw)
+    _check(wl)
+    _check(wl, y_bf16=False)
+    d = wl.make()
+    x, w = rng.bf16_bits_to_f32(d["x_bf16"]) * np.float32(1.001), rng.bf16_bits_to_f32(d["w_bf16"]) * np.float32(0.999)
+    for tiny in (False, True):
+        xs = x * np.float32(2.0 ** -119) if tiny else x  # below what the three-way split holds
+        for y_bf16 in (False, True):
+            y = G.run_conv2d(xs, w, (wl.stride, wl.stride), (wl.pad, wl.pad), xw_bf16=False, y_bf16=y_bf16)
+            ref, ad = oracle.conv2d(xs.astype(np.float64), w.astype(np.float64), (wl.stride, wl.stride), (wl.pad, wl.pad),
+                                    want_absdot=True)
+            yg = P.bf16_to_f64(y) if y_bf16 else y
+            # (+ half the smallest subnormal per addition: the tiny results are near the end of the range)
+            P.assert_contraction_close(yg, ref, ad + 2.0 ** -126, wl.R * wl.S * wl.C + 1, out_bf16=y_bf16)
