@@ -10,7 +10,8 @@
 //    16-byte aligned).  Reductions are DPP / permlane butterflies, no LDS, no barrier.
 //  * softmax_wgrow_kernel: rows of 8 .. 128 KiB, one workgroup (4 or 16 waves) per row, the
 //    row in the workgroup's registers, the next row's loads in flight meanwhile.
-//  * softmax_wide_kernel: still longer or unaligned rows, one workgroup per row:
+//    Both take rows of any length and 4-byte alignment as well (RAG).
+//  * softmax_wide_kernel: still longer rows, one workgroup per row:
 //    the row goes to LDS (up to 144 KiB, 16-byte accesses when aligned) and is read from HBM
 //    once; what a longer row has beyond that is read twice.
 #include <atomic>
@@ -19,7 +20,29 @@
 
 namespace perf {
 
-template <int NV, int RPW>
+typedef float float4_at4 __attribute__((ext_vector_type(4), aligned(4)));
+template <bool RAG>
+__device__ __forceinline__ float4_t load_vec(const float *p)
+{
+    if constexpr (RAG) return __builtin_nontemporal_load(reinterpret_cast<const float4_at4 *>(p));
+    else return __builtin_nontemporal_load(reinterpret_cast<const float4_t *>(p));
+}
+template <bool RAG>
+__device__ __forceinline__ void store_vec(float *p, float4_t v)
+{
+    if constexpr (RAG) __builtin_nontemporal_store(v, reinterpret_cast<float4_at4 *>(p));
+    else __builtin_nontemporal_store(v, reinterpret_cast<float4_t *>(p));
+}
+// First element of the vector that covers element c of a row.
+template <bool RAG>
+__device__ __forceinline__ int vec_start(int c, int cols)
+{
+    return RAG ? min(c, cols - 4) : c;
+}
+
+// RAG: rows of any length from 4 on and any 4-byte alignment.  A row's last vector starts 4 elements before its end, so
+// that no access leaves the row; what it shares with the vector before is computed twice and summed once.
+template <int NV, int RPW, bool RAG = false>
 __global__ __launch_bounds__(256) void softmax_rows_kernel(const float *__restrict__ x, float *__restrict__ y,
                                                            int64_t rows, int cols, int64_t ldx, int64_t ldy,
                                                            ExpConst k)
@@ -37,7 +60,7 @@ __global__ __launch_bounds__(256) void softmax_rows_kernel(const float *__restri
             for (int j = 0; j < NV; ++j) {
                 const int c = (j * 64 + lane) * 4;
                 if (r < rows && c < cols)
-                    v[i][j] = __builtin_nontemporal_load(reinterpret_cast<const float4_t *>(x + r * ldx + c));
+                    v[i][j] = load_vec<RAG>(x + r * ldx + vec_start<RAG>(c, cols));
                 else
                     v[i][j] = float4_t{-FLT_MAX, -FLT_MAX, -FLT_MAX, -FLT_MAX} * k.sign;
             }
@@ -56,12 +79,13 @@ __global__ __launch_bounds__(256) void softmax_rows_kernel(const float *__restri
             float z = 0.f;
 #pragma unroll
             for (int j = 0; j < NV; ++j) {
-                const bool valid = (j * 64 + lane) * 4 < cols;
+                const int c = (j * 64 + lane) * 4;
+                const bool valid = c < cols;
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
                     float t = exp_scaled(v[i][j][e] - m, k.c_hi, k.c_lo);
                     v[i][j][e] = valid ? t : 0.f;
-                    z += v[i][j][e];
+                    z += !RAG || e >= c - vec_start<RAG>(c, cols) ? v[i][j][e] : 0.f;
                 }
             }
             z = wave_allreduce(z, OpSum{});
@@ -70,8 +94,7 @@ __global__ __launch_bounds__(256) void softmax_rows_kernel(const float *__restri
 #pragma unroll
                 for (int j = 0; j < NV; ++j) {
                     const int c = (j * 64 + lane) * 4;
-                    if (c < cols)
-                        __builtin_nontemporal_store(v[i][j] * inv, reinterpret_cast<float4_t *>(y + r * ldy + c));
+                    if (c < cols) store_vec<RAG>(y + r * ldy + vec_start<RAG>(c, cols), v[i][j] * inv);
                 }
             }
         }
@@ -112,20 +135,20 @@ __device__ __forceinline__ float block_reduce_sum(float v, float *red)
 // registers (NV 16-byte vectors per thread), LDS only for the two cross-wave reductions.  The
 // next row's loads are issued before this row's arithmetic, so a workgroup always has a row in
 // flight and reads, exponentials and writes of different rows overlap.
-template <int THREADS, int NV>
+template <int THREADS, int NV, bool RAG = false>
 __global__ __launch_bounds__(THREADS) void softmax_wgrow_kernel(const float *__restrict__ x, float *__restrict__ y,
                                                                 int64_t rows, int cols, int64_t ldx, int64_t ldy,
                                                                 ExpConst k)
 {
     __shared__ float red[THREADS / 64];
-    const int tid = threadIdx.x, n4 = cols / 4;
+    const int tid = threadIdx.x, n4 = RAG ? (cols + 3) / 4 : cols / 4;
     float4_t cur[NV], nxt[NV];
     auto load_row = [&](float4_t (&v)[NV], int64_t r) {
-        const float4_t *xr = reinterpret_cast<const float4_t *>(x + r * ldx);
+        const float *xr = x + r * ldx;
 #pragma unroll
         for (int j = 0; j < NV; ++j) {
             const int c = j * THREADS + tid;
-            if (c < n4) v[j] = __builtin_nontemporal_load(xr + c);
+            if (c < n4) v[j] = load_vec<RAG>(xr + vec_start<RAG>(4 * c, cols));
             else v[j] = float4_t{-FLT_MAX, -FLT_MAX, -FLT_MAX, -FLT_MAX} * k.sign;
         }
     };
@@ -143,27 +166,28 @@ __global__ __launch_bounds__(THREADS) void softmax_wgrow_kernel(const float *__r
         float z = 0.f;
 #pragma unroll
         for (int j = 0; j < NV; ++j) {
+            const int c = 4 * (j * THREADS + tid);
             const bool valid = j * THREADS + tid < n4;
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
                 const float t = exp_scaled(cur[j][e] - m, k.c_hi, k.c_lo);
                 cur[j][e] = valid ? t : 0.f;
-                z += cur[j][e];
+                z += !RAG || e >= c - vec_start<RAG>(c, cols) ? cur[j][e] : 0.f;
             }
         }
         const float inv = 1.0f / block_reduce_sum<THREADS>(z, red);
-        float4_t *yr = reinterpret_cast<float4_t *>(y + r * ldy);
+        float *yr = y + r * ldy;
 #pragma unroll
         for (int j = 0; j < NV; ++j) {
             const int c = j * THREADS + tid;
-            if (c < n4) __builtin_nontemporal_store(cur[j] * inv, yr + c);
+            if (c < n4) store_vec<RAG>(yr + vec_start<RAG>(4 * c, cols), cur[j] * inv);
         }
 #pragma unroll
         for (int j = 0; j < NV; ++j) cur[j] = nxt[j];
     }
 }
 
-template <int THREADS, int NV>
+template <int THREADS, int NV, bool RAG = false>
 static perf_status launch_wgrow(const float *x, float *y, int64_t rows, int cols, int64_t ldx, int64_t ldy, ExpConst k,
                                 hipStream_t st, int64_t grid = 0)
 {
@@ -171,7 +195,7 @@ static perf_status launch_wgrow(const float *x, float *y, int64_t rows, int cols
     // 200 with just the resident ones on 8192 x 16384)
     int64_t blocks = rows < 256 * 16 ? rows : 256 * 16;
     if (grid > 0) blocks = grid < rows ? grid : rows;
-    hipLaunchKernelGGL((softmax_wgrow_kernel<THREADS, NV>), dim3((unsigned)blocks), dim3(THREADS), 0, st, x, y, rows, cols,
+    hipLaunchKernelGGL((softmax_wgrow_kernel<THREADS, NV, RAG>), dim3((unsigned)blocks), dim3(THREADS), 0, st, x, y, rows, cols,
                        ldx, ldy, k);
     return launch_status();
 }
@@ -279,7 +303,7 @@ static perf_status launch_wide(const float *x, float *y, int64_t rows, int64_t c
     return launch_status();
 }
 
-template <int NV, int RPW>
+template <int NV, int RPW, bool RAG = false>
 static void launch_rows(const float *x, float *y, int64_t rows, int cols, int64_t ldx, int64_t ldy, ExpConst k,
                         hipStream_t st, int64_t grid = 0)
 {
@@ -287,7 +311,7 @@ static void launch_rows(const float *x, float *y, int64_t rows, int cols, int64_
     // (one pass up to 256K workgroups: 167.5 us against 170.8 on 131072 x 1024 with waves looping over two rows each)
     if (blocks > 256 * 1024) blocks = 256 * 1024;  // then waves loop over rows
     if (grid > 0 && grid < blocks) blocks = grid;  // (a caller's choice of a persistent grid)
-    hipLaunchKernelGGL((softmax_rows_kernel<NV, RPW>), dim3((unsigned)blocks), dim3(256), 0, st, x, y, rows, cols, ldx,
+    hipLaunchKernelGGL((softmax_rows_kernel<NV, RPW, RAG>), dim3((unsigned)blocks), dim3(256), 0, st, x, y, rows, cols, ldx,
                        ldy, k);
 }
 
@@ -358,7 +382,24 @@ static perf_status softmax_impl(const void *x, void *y, int64_t rows, int64_t co
                      : launch_wgrow<1024, 8>(xp, yp, rows, c, ldx, ldy, k, st, grid);
     }
     if (variant) return PERF_ERR_UNSUPPORTED;
-    // rows beyond 128 KiB, or nothing aligned: a workgroup per row through LDS
+    // Rows that are not whole aligned vectors: the same two kernels with ragged vectors, as many registers as the row
+    // needs (slots without an element cost occupancy: 4099 x 10007 takes 58.5 us with 5 or 6 vectors per thread of
+    // 512, 86 with 8, 83 with 4 of 1024; element accesses through LDS took 103).  Up to 2048 columns, against that
+    // kernel: 57600 x 777 62 us (126), 131072 x 101 31 us (100); one pass (a persistent grid: 68 on 57600 x 777).
+    if (!vec && cols >= 4 && cols <= 32768) {
+        const int c = (int)cols;
+        if (c > 24576) return launch_wgrow<1024, 8, true>(xp, yp, rows, c, ldx, ldy, k, st);
+        if (c > 16384) return launch_wgrow<1024, 6, true>(xp, yp, rows, c, ldx, ldy, k, st);
+        if (c > 12288) return launch_wgrow<512, 8, true>(xp, yp, rows, c, ldx, ldy, k, st);
+        if (c > 8192) return launch_wgrow<512, 6, true>(xp, yp, rows, c, ldx, ldy, k, st);
+        if (c > 2048) return launch_wgrow<512, 4, true>(xp, yp, rows, c, ldx, ldy, k, st);
+        if (c > 1024) launch_rows<8, 1, true>(xp, yp, rows, c, ldx, ldy, k, st);
+        else if (c > 512) launch_rows<4, 1, true>(xp, yp, rows, c, ldx, ldy, k, st);
+        else if (c > 256) launch_rows<2, 1, true>(xp, yp, rows, c, ldx, ldy, k, st);
+        else launch_rows<1, 4, true>(xp, yp, rows, c, ldx, ldy, k, st);
+        return launch_status();
+    }
+    // rows beyond 128 KiB (or shorter than a vector): a workgroup per row through LDS
     if (cols > 8192) return vec ? launch_wide<1024, true>(xp, yp, rows, cols, ldx, ldy, k, st)
                                 : launch_wide<1024, false>(xp, yp, rows, cols, ldx, ldy, k, st);
     return vec ? launch_wide<256, true>(xp, yp, rows, cols, ldx, ldy, k, st)

@@ -67,6 +67,16 @@ def test_padded_rows_unaligned_base_and_inplace():
     _check(x, ldx=203, inplace=True)
 
 
+@pytest.mark.parametrize("cols", [4, 5, 7, 255, 257, 511, 515, 1023, 1025, 2047, 2049, 2051, 8191, 8193, 12289, 16385, 24578,
+                                  32767, 32769])
+def test_ragged_rows(cols):
+    # rows that are no whole aligned vectors, at the edges of each register shape; odd strides, shifted bases, in place
+    x = configs.SoftmaxWorkload(rows=5, cols=cols).make()["x"]
+    _check(x, offset=1)
+    _check(x, ldx=cols + 1, ldy=cols + 3, scale=-0.5)
+    _check(x, ldx=cols + 1, inplace=True)
+
+
 def test_wide_dynamic_range():
     g = np.random.default_rng(11)
     x = g.uniform(-80.0, 0.0, (16, 1024)).astype(np.float32)
