@@ -25,8 +25,9 @@ constexpr int kLnThreads = 256;  // 256 threads x 1536 workgroups measured best 
 constexpr int kLnWaves = kLnThreads / 64;
 
 // XT, YT: element types of x and y; PT: element type of gamma/beta; NC: 16-byte chunks of
-// the row held per lane (cols <= NC * 64 * E); EVEN: cols == NC * 64 * E exactly.
-template <typename XT, typename PT, typename YT, int NC, bool EVEN>
+// the row held per lane (cols <= NC * 64 * E); EVEN: cols == NC * 64 * E exactly; RAG: rows that are no whole
+// aligned chunks (row_io.h).
+template <typename XT, typename PT, typename YT, int NC, bool EVEN, bool RAG = false>
 __global__ __launch_bounds__(kLnThreads) void layernorm_rows_kernel(const XT *__restrict__ x,
                                                                     const PT *__restrict__ gamma,
                                                                     const PT *__restrict__ beta, YT *__restrict__ y,
@@ -43,9 +44,9 @@ __global__ __launch_bounds__(kLnThreads) void layernorm_rows_kernel(const XT *__
     float4_t *b_lds = lds + (E / 4) * NCH;       // [E/4][NCH]
     for (int i = threadIdx.x; i < (E / 4) * NCH; i += kLnThreads) {
         const int q = i / NCH, c = i % NCH;
-        const int col = c * E + 4 * q;
+        const int col = chunk_start<RAG, E>(c * E, cols) + 4 * q;
         float4_t g = {0.f, 0.f, 0.f, 0.f}, b = {0.f, 0.f, 0.f, 0.f};
-        if (col < cols) {  // cols is a multiple of E, so a chunk is entirely valid or not
+        if (c * E < cols) {  // a chunk is entirely valid or not
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
                 g[e] = Elem<PT>::load1(gamma + col + e);
@@ -69,7 +70,7 @@ __global__ __launch_bounds__(kLnThreads) void layernorm_rows_kernel(const XT *__
         for (int j = 0; j < NC; ++j) {
             const int c = (j * 64 + lane) * E;
             if (EVEN || c < cols)
-                raw[j] = *reinterpret_cast<const uint4_t *>(xr + c);  // (plain loads measured 6 % faster here than non-temporal ones)
+                raw[j] = load_chunk<RAG>(xr + chunk_start<RAG, E>(c, cols));  // (plain loads measured 6 % faster here than non-temporal ones)
             else
                 raw[j] = uint4_t{0u, 0u, 0u, 0u};
         }
@@ -83,7 +84,8 @@ __global__ __launch_bounds__(kLnThreads) void layernorm_rows_kernel(const XT *__
         for (int j = 0; j < NC; ++j) {
             Elem<XT>::unpack(raw[j], v[j]);
 #pragma unroll
-            for (int e = 0; e < E; ++e) s += v[j][e];  // padding chunks hold zeros
+            for (int e = 0; e < E; ++e)  // (padding chunks hold zeros)
+                s += !RAG || e >= (j * 64 + lane) * E - chunk_start<RAG, E>((j * 64 + lane) * E, cols) ? v[j][e] : 0.f;
         }
         // the raw registers are free again: the next row's loads fly during this row's arithmetic
         if (r + nwaves < rows) load_row(r + nwaves);
@@ -94,13 +96,15 @@ __global__ __launch_bounds__(kLnThreads) void layernorm_rows_kernel(const XT *__
         float s1 = 0.f, s2 = 0.f;
 #pragma unroll
         for (int j = 0; j < NC; ++j) {
-            const bool valid = EVEN || (j * 64 + lane) * E < cols;
+            const int c = (j * 64 + lane) * E;
+            const bool valid = EVEN || c < cols;
 #pragma unroll
             for (int e = 0; e < E; ++e) {
                 const float d = valid ? v[j][e] - mean0 : 0.f;
                 v[j][e] = d;
-                s1 += d;
-                s2 = __builtin_fmaf(d, d, s2);
+                const float once = !RAG || e >= c - chunk_start<RAG, E>(c, cols) ? d : 0.f;
+                s1 += once;
+                s2 = __builtin_fmaf(once, once, s2);
             }
         }
         s1 = wave_allreduce(s1, OpSum{});
@@ -127,7 +131,7 @@ __global__ __launch_bounds__(kLnThreads) void layernorm_rows_kernel(const XT *__
                     for (int e = 0; e < 4; ++e)
                         o[4 * q + e] = __builtin_fmaf((v[j][4 * q + e] - dm) * rstd, g[e], b[e]);
                 }
-                store_chunk<YT, E>(yr + ch * E, o);
+                store_row_chunk<RAG, YT, E>(yr + chunk_start<RAG, E>(ch * E, cols), o);
             }
             // keeps the LDS reads of gamma / beta chunk by chunk; hoisted together they
             // double the register count and halve the occupancy
@@ -195,7 +199,7 @@ struct LnArgs {
     int failed;         // 0 = launched, 1 = a HIP call failed, 2 = the chosen kernel cannot run the rows
 };
 
-template <typename XT, typename PT, typename YT, int NC>
+template <typename XT, typename PT, typename YT, int NC, bool RAG = false>
 static void launch_rows_nc(const LnArgs &a)
 {
     constexpr int E = Elem<XT>::kPerChunk;
@@ -204,7 +208,8 @@ static void launch_rows_nc(const LnArgs &a)
     const int64_t cap = a.grid > 0 ? a.grid : 1536;  // six workgroups per CU (two rounds of the three that are resident); waves then loop over rows
     if (blocks > cap) blocks = cap;
     const bool even = a.cols == (int64_t)NC * 64 * E;
-    auto kern = even ? layernorm_rows_kernel<XT, PT, YT, NC, true> : layernorm_rows_kernel<XT, PT, YT, NC, false>;
+    auto kern = RAG ? layernorm_rows_kernel<XT, PT, YT, NC, false, RAG>
+                    : even ? layernorm_rows_kernel<XT, PT, YT, NC, true> : layernorm_rows_kernel<XT, PT, YT, NC, false>;
     hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(kLnThreads), lds_bytes, a.st, (const XT *)a.x,
                        (const PT *)a.gamma, (const PT *)a.beta, (YT *)a.y, a.mean_out, a.rstd_out, a.rows, (int)a.cols,
                        a.ldx, a.ldy, a.eps);
@@ -230,6 +235,17 @@ static void launch_typed(LnArgs &a, bool vec_ok)
         // longer rows: a workgroup per row, the row in its registers or parked in LDS (one read of HBM)
         a.failed = launch_norm_wide<XT, PT, YT, false>(a.x, a.gamma, a.beta, a.y, a.mean_out, a.rstd_out, a.rows, a.cols,
                                                        a.ldx, a.ldy, a.eps, a.st, a.waves_per_row, a.grid);
+    } else if (a.cols >= E && chunks <= 8) {
+        // no whole aligned chunks: the same kernel with ragged ones (6007 x 1023 fp32: 9.9 us; element accesses in
+        // three passes took 16.7), up to 8 per lane: beyond that a workgroup per row is ahead (6000 x 7001 bf16 44
+        // against 62)
+        if (chunks <= 1) launch_rows_nc<XT, PT, YT, 1, true>(a);
+        else if (chunks <= 2) launch_rows_nc<XT, PT, YT, 2, true>(a);
+        else if (chunks <= 4) launch_rows_nc<XT, PT, YT, 4, true>(a);
+        else launch_rows_nc<XT, PT, YT, 8, true>(a);
+    } else if (a.cols >= E && a.cols <= wide_ragged_max<XT>()) {
+        launch_norm_ragged<XT, PT, YT, false>(a.x, a.gamma, a.beta, a.y, a.mean_out, a.rstd_out, a.rows, a.cols, a.ldx, a.ldy,
+                                              a.eps, a.st);
     } else {
         int64_t blocks = a.rows < 65536 ? a.rows : 65536;
         hipLaunchKernelGGL((layernorm_block_kernel<XT, PT, YT>), dim3((unsigned)blocks), dim3(256), 0, a.st,

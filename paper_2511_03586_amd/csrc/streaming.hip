@@ -21,8 +21,8 @@ namespace perf {
 constexpr int kRmsThreads = 256;
 constexpr int kRmsWaves = kRmsThreads / 64;
 
-// NC: 16-byte chunks of the row held per lane (cols <= NC * 64 * E).
-template <typename XT, typename PT, typename YT, int NC>
+// NC: 16-byte chunks of the row held per lane (cols <= NC * 64 * E); RAG: rows that are no whole aligned chunks (row_io.h).
+template <typename XT, typename PT, typename YT, int NC, bool RAG = false>
 __global__ __launch_bounds__(kRmsThreads) void rmsnorm_rows_kernel(const XT *__restrict__ x, const PT *__restrict__ gamma,
                                                                    YT *__restrict__ y, float *__restrict__ rrms_out,
                                                                    int64_t rows, int cols, int64_t ldx, int64_t ldy,
@@ -34,9 +34,9 @@ __global__ __launch_bounds__(kRmsThreads) void rmsnorm_rows_kernel(const XT *__r
     extern __shared__ float4_t lds[];
     for (int i = threadIdx.x; i < (E / 4) * NCH; i += kRmsThreads) {
         const int q = i / NCH, c = i % NCH;
-        const int col = c * E + 4 * q;
+        const int col = chunk_start<RAG, E>(c * E, cols) + 4 * q;
         float4_t g = {0.f, 0.f, 0.f, 0.f};
-        if (col < cols) {  // cols is a multiple of E
+        if (c * E < cols) {
 #pragma unroll
             for (int e = 0; e < 4; ++e) g[e] = Elem<PT>::load1(gamma + col + e);
         }
@@ -55,7 +55,7 @@ __global__ __launch_bounds__(kRmsThreads) void rmsnorm_rows_kernel(const XT *__r
 #pragma unroll
         for (int j = 0; j < NC; ++j) {
             const int c = (j * 64 + lane) * E;
-            raw[j] = c < cols ? __builtin_nontemporal_load(reinterpret_cast<const uint4_t *>(xr + c)) : uint4_t{0u, 0u, 0u, 0u};
+            raw[j] = c < cols ? load_chunk_nt<RAG>(xr + chunk_start<RAG, E>(c, cols)) : uint4_t{0u, 0u, 0u, 0u};
         }
     };
     if (wave < rows) load_row(wave);
@@ -66,7 +66,10 @@ __global__ __launch_bounds__(kRmsThreads) void rmsnorm_rows_kernel(const XT *__r
         for (int j = 0; j < NC; ++j) {
             Elem<XT>::unpack(raw[j], v[j]);
 #pragma unroll
-            for (int e = 0; e < E; ++e) ss = __builtin_fmaf(v[j][e], v[j][e], ss);  // padding chunks hold zeros
+            for (int e = 0; e < E; ++e) {  // (padding chunks hold zeros)
+                const float once = !RAG || e >= (j * 64 + lane) * E - chunk_start<RAG, E>((j * 64 + lane) * E, cols) ? v[j][e] : 0.f;
+                ss = __builtin_fmaf(once, once, ss);
+            }
         }
         if (r + nwaves < rows) load_row(r + nwaves);  // next row's loads fly during this row's arithmetic
         ss = wave_allreduce(ss, OpSum{});
@@ -84,7 +87,7 @@ __global__ __launch_bounds__(kRmsThreads) void rmsnorm_rows_kernel(const XT *__r
 #pragma unroll
                     for (int e = 0; e < 4; ++e) o[4 * q + e] = v[j][4 * q + e] * rr * g[e];
                 }
-                store_chunk<YT, E>(yr + ch * E, o);
+                store_row_chunk<RAG, YT, E>(yr + chunk_start<RAG, E>(ch * E, cols), o);
             }
             __builtin_amdgcn_sched_barrier(0);  // keeps the gamma reads chunk by chunk (register count)
         }
@@ -133,14 +136,14 @@ struct RmsArgs {
     bool failed;
 };
 
-template <typename XT, typename PT, typename YT, int NC>
+template <typename XT, typename PT, typename YT, int NC, bool RAG = false>
 static void launch_rms_nc(const RmsArgs &a)
 {
     constexpr int E = Elem<XT>::kPerChunk;
     const size_t lds_bytes = (size_t)(E / 4) * NC * 64 * sizeof(float4_t);
     int64_t blocks = (a.rows + kRmsWaves - 1) / kRmsWaves;
     if (blocks > 512) blocks = 512;  // two workgroups per CU; waves then loop over rows
-    hipLaunchKernelGGL((rmsnorm_rows_kernel<XT, PT, YT, NC>), dim3((unsigned)blocks), dim3(kRmsThreads), lds_bytes, a.st,
+    hipLaunchKernelGGL((rmsnorm_rows_kernel<XT, PT, YT, NC, RAG>), dim3((unsigned)blocks), dim3(kRmsThreads), lds_bytes, a.st,
                        (const XT *)a.x, (const PT *)a.gamma, (YT *)a.y, a.rrms, a.rows, (int)a.cols, a.ldx, a.ldy, a.eps);
 }
 
@@ -157,6 +160,16 @@ static void launch_rms_typed(RmsArgs &a, bool vec_ok)
         // longer rows: a workgroup per row, the row parked in LDS (one read of HBM)
         a.failed = launch_norm_wide<XT, PT, YT, true>(a.x, a.gamma, a.gamma, a.y, nullptr, a.rrms, a.rows, a.cols, a.ldx,
                                                       a.ldy, a.eps, a.st) != 0;
+    } else if (a.cols >= E && chunks <= (E == 8 ? 16 : 8)) {
+        // no whole aligned chunks: the same kernel with ragged ones (20000 x 1999 fp32: 58 us, element accesses in two
+        // passes took 108; 9000 x 4999 bf16: 36 us, 42 with a workgroup per row)
+        if (chunks <= 2) launch_rms_nc<XT, PT, YT, 2, true>(a);
+        else if (chunks <= 4) launch_rms_nc<XT, PT, YT, 4, true>(a);
+        else if (chunks <= 8) launch_rms_nc<XT, PT, YT, 8, true>(a);
+        else if constexpr (E == 8) launch_rms_nc<XT, PT, YT, 16, true>(a);
+    } else if (a.cols >= E && a.cols <= wide_ragged_max<XT>()) {
+        launch_norm_ragged<XT, PT, YT, true>(a.x, a.gamma, a.gamma, a.y, nullptr, a.rrms, a.rows, a.cols, a.ldx, a.ldy, a.eps,
+                                             a.st);
     } else {
         const int64_t blocks = a.rows < 65536 ? a.rows : 65536;
         hipLaunchKernelGGL((rmsnorm_block_kernel<XT, PT, YT>), dim3((unsigned)blocks), dim3(256), 0, a.st,

@@ -25,11 +25,16 @@ __device__ __forceinline__ float wide_block_sum(float v, float *red)
     return r;
 }
 
-// E parameters starting at element `col` (a multiple of E; p is 16-byte aligned) as fp32
-template <typename PT, int E>
+// E parameters starting at element `col` (a multiple of E and p 16-byte aligned, or ANY column and alignment) as fp32
+template <typename PT, int E, bool ANY = false>
 __device__ __forceinline__ void load_params(const PT *p, int64_t col, float *out)
 {
-    if constexpr (sizeof(PT) == 4) {
+    if constexpr (ANY) {
+        PT v[E];
+        __builtin_memcpy(v, p + col, sizeof(v));
+#pragma unroll
+        for (int e = 0; e < E; ++e) out[e] = Elem<PT>::load1(v + e);
+    } else if constexpr (sizeof(PT) == 4) {
 #pragma unroll
         for (int q = 0; q < E / 4; ++q) {
             const float4_t g = *reinterpret_cast<const float4_t *>(p + col + 4 * q);
@@ -144,7 +149,8 @@ __global__ __launch_bounds__(THREADS) void norm_wide_kernel(const XT *__restrict
 // Rows of 16 .. 128 KiB of input: one workgroup of THREADS per row, the row in the workgroup's
 // registers (NC 16-byte chunks per thread), LDS only for the cross-wave sums.  The next row's
 // loads are issued as soon as this row is unpacked, so a workgroup always has a row in flight.
-template <typename XT, typename PT, typename YT, int THREADS, int NC, bool RMS>
+// RAG: rows that are no whole aligned chunks (row_io.h), parameters of any alignment.
+template <typename XT, typename PT, typename YT, int THREADS, int NC, bool RMS, bool RAG = false>
 __global__ __launch_bounds__(THREADS) void norm_wgrow_kernel(const XT *__restrict__ x, const PT *__restrict__ gamma,
                                                              const PT *__restrict__ beta, YT *__restrict__ y,
                                                              float *__restrict__ stat0, float *__restrict__ stat1,
@@ -152,15 +158,17 @@ __global__ __launch_bounds__(THREADS) void norm_wgrow_kernel(const XT *__restric
 {
     constexpr int E = Elem<XT>::kPerChunk;
     __shared__ float red[THREADS / 64];
-    const int tid = threadIdx.x, nch = cols / E;
+    const int tid = threadIdx.x, nch = RAG ? (cols + E - 1) / E : cols / E;
+    auto start = [&](int c) { return chunk_start<RAG, E>(c * E, cols); };
+    auto counts = [&](int c, int e) { return !RAG || e >= c * E - start(c); };  // (not shared with the chunk before)
     const float inv_cols = 1.0f / (float)cols;
     uint4_t raw[NC];
     auto load_row = [&](int64_t r) {
-        const uint4_t *xr = reinterpret_cast<const uint4_t *>(x + r * ldx);
+        const XT *xr = x + r * ldx;
 #pragma unroll
         for (int j = 0; j < NC; ++j) {
             const int c = j * THREADS + tid;
-            raw[j] = c < nch ? __builtin_nontemporal_load(xr + c) : uint4_t{0u, 0u, 0u, 0u};
+            raw[j] = c < nch ? load_chunk_nt<RAG>(xr + start(c)) : uint4_t{0u, 0u, 0u, 0u};
         }
     };
     int64_t r = blockIdx.x;
@@ -172,7 +180,10 @@ __global__ __launch_bounds__(THREADS) void norm_wgrow_kernel(const XT *__restric
         for (int j = 0; j < NC; ++j) {
             Elem<XT>::unpack(raw[j], v[j]);
 #pragma unroll
-            for (int e = 0; e < E; ++e) s = RMS ? __builtin_fmaf(v[j][e], v[j][e], s) : s + v[j][e];  // padding chunks hold zeros
+            for (int e = 0; e < E; ++e) {  // (padding chunks hold zeros)
+                const float once = counts(j * THREADS + tid, e) ? v[j][e] : 0.f;
+                s = RMS ? __builtin_fmaf(once, once, s) : s + once;
+            }
         }
         if (r + gridDim.x < rows) load_row(r + gridDim.x);  // flies during this row's arithmetic and stores
         s = wide_block_sum<THREADS>(s, red);
@@ -190,8 +201,9 @@ __global__ __launch_bounds__(THREADS) void norm_wgrow_kernel(const XT *__restric
                 for (int e = 0; e < E; ++e) {
                     const float d = valid ? v[j][e] - mean0 : 0.f;
                     v[j][e] = d;
-                    s1 += d;
-                    s2 = __builtin_fmaf(d, d, s2);
+                    const float once = counts(j * THREADS + tid, e) ? d : 0.f;
+                    s1 += once;
+                    s2 = __builtin_fmaf(once, once, s2);
                 }
             }
             s1 = wide_block_sum<THREADS>(s1, red);
@@ -210,21 +222,45 @@ __global__ __launch_bounds__(THREADS) void norm_wgrow_kernel(const XT *__restric
             const int c = j * THREADS + tid;
             if (c < nch) {
                 float g[E], o[E];
-                load_params<PT, E>(gamma, (int64_t)c * E, g);
+                load_params<PT, E, RAG>(gamma, start(c), g);
                 if constexpr (RMS) {
 #pragma unroll
                     for (int e = 0; e < E; ++e) o[e] = v[j][e] * scale * g[e];
                 } else {
                     float b[E];
-                    load_params<PT, E>(beta, (int64_t)c * E, b);
+                    load_params<PT, E, RAG>(beta, start(c), b);
 #pragma unroll
                     for (int e = 0; e < E; ++e) o[e] = __builtin_fmaf((v[j][e] - dm) * scale, g[e], b[e]);
                 }
-                store_chunk<YT, E>(yr + (int64_t)c * E, o);
+                store_row_chunk<RAG, YT, E>(yr + start(c), o);
             }
             __builtin_amdgcn_sched_barrier(0);  // keeps the parameter loads chunk by chunk (register count)
         }
     }
+}
+
+// Longest ragged row that a workgroup's registers hold (elements), and its launch: 4 waves per row, 16 beyond 8 chunks
+// per thread of those.
+template <typename XT>
+constexpr int64_t wide_ragged_max()
+{
+    return (int64_t)Elem<XT>::kPerChunk * (Elem<XT>::kPerChunk == 8 ? 4 : 8) * 1024;
+}
+template <typename XT, typename PT, typename YT, bool RMS>
+static void launch_norm_ragged(const void *x, const void *gamma, const void *beta, void *y, float *stat0, float *stat1,
+                               int64_t rows, int64_t cols, int64_t ldx, int64_t ldy, float eps, hipStream_t st)
+{
+    constexpr int E = Elem<XT>::kPerChunk;
+    const int64_t nch = (cols + E - 1) / E;
+    const unsigned blocks = (unsigned)(rows < 256 * 16 ? rows : 256 * 16);
+    auto go = [&](auto kern, int threads) {
+        hipLaunchKernelGGL(kern, dim3(blocks), dim3(threads), 0, st, (const XT *)x, (const PT *)gamma, (const PT *)beta, (YT *)y,
+                           stat0, stat1, rows, (int)cols, ldx, ldy, eps);
+    };
+    if (nch <= 4 * 256) return go(norm_wgrow_kernel<XT, PT, YT, 256, 4, RMS, true>, 256);
+    if (nch <= 8 * 256) return go(norm_wgrow_kernel<XT, PT, YT, 256, 8, RMS, true>, 256);
+    if (E == 8 || nch <= 4 * 1024) return go(norm_wgrow_kernel<XT, PT, YT, 1024, 4, RMS, true>, 1024);
+    if constexpr (E == 4) go(norm_wgrow_kernel<XT, PT, YT, 1024, 8, RMS, true>, 1024);
 }
 
 // Launch: rows of up to 128 KiB in a workgroup's registers (4 waves up to 32 KiB, 16 beyond); longer

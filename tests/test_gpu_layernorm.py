@@ -144,3 +144,16 @@ def test_deterministic():
     a = G.run_layernorm(d["x_bf16"], d["gamma"], d["beta"], 1e-5, True, False, True)
     b = G.run_layernorm(d["x_bf16"], d["gamma"], d["beta"], 1e-5, True, False, True)
     assert all(np.array_equal(u, v) for u, v in zip(a, b))
+
+
+@pytest.mark.parametrize("x_bf16,p_bf16,y_bf16", [(False, False, False), (True, False, True), (True, True, False), (False, True, True)])
+@pytest.mark.parametrize("cols", [4, 9, 255, 257, 513, 515, 1023, 2049, 4095, 4097, 8191, 8195, 16385, 32767, 32771])
+def test_ragged_rows(cols, x_bf16, p_bf16, y_bf16):
+    # rows that are no whole aligned chunks, at the edges of each register shape; odd strides and shifted bases
+    d = configs.LayerNormWorkload(rows=5, cols=cols).make()
+    x = d["x_bf16"] if x_bf16 else rng.bf16_bits_to_f32(d["x_bf16"]) * np.float32(1.001)
+    gamma, beta = _params(cols, p_bf16)
+    _check(x, gamma, beta, 1e-5, x_bf16, p_bf16, y_bf16, offset=1)
+    _check(x, gamma, beta, 1e-5, x_bf16, p_bf16, y_bf16, ldx=cols + 1, ldy=cols + 3)
+    if x_bf16 == y_bf16:
+        _check(x, gamma, beta, 1e-5, x_bf16, p_bf16, y_bf16, ldx=cols + 1, inplace=True)

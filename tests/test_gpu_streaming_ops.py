@@ -70,6 +70,14 @@ def test_rmsnorm_rows_beyond_the_register_kernel():
     _check_rmsnorm(5, 16384, ldx=16392, ldy=16400)
 
 
+@pytest.mark.parametrize("x_bf16,p_bf16,y_bf16", [(False, False, False), (True, False, True), (True, True, False)])
+@pytest.mark.parametrize("cols", [4, 9, 513, 1023, 2049, 4097, 8195, 16385, 32771])
+def test_rmsnorm_ragged_rows(cols, x_bf16, p_bf16, y_bf16):
+    # rows that are no whole aligned chunks, at the edges of each register shape
+    _check_rmsnorm(5, cols, x_bf16, p_bf16, y_bf16)
+    _check_rmsnorm(5, cols, x_bf16, p_bf16, y_bf16, ldx=cols + 1, ldy=cols + 3)
+
+
 def test_rmsnorm_dtypes_padding_inplace():
     _check_rmsnorm(40, 2048, x_bf16=False, y_bf16=False)
     _check_rmsnorm(40, 4096, x_bf16=False, y_bf16=False)        # 16 chunks of fp32 per lane
