@@ -51,13 +51,19 @@ LAYERNORM_AXES = {"waves_per_row": (1, 4, 16), "grid_per_cu": (2, 4, 6, 8, 12, 1
 
 
 def _time(launch, nsets, iters, warmup):
-    """Mean microseconds per launch over ``iters`` launches on rotated buffer sets."""
+    """Mean microseconds per launch over ``iters`` launches on rotated buffer sets.  The launches are replayed from
+    a graph: one by one the host issues them more slowly than a small kernel runs, and all variants look alike."""
     for i in range(warmup):
         launch(i % nsets)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        for i in range(iters):
+            launch((warmup + i) % nsets)
+    graph.replay()
     e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
     e0.record()
-    for i in range(iters):
-        launch((warmup + i) % nsets)
+    graph.replay()
     e1.record()
     torch.cuda.synchronize()
     return e0.elapsed_time(e1) / iters * 1e3
