@@ -127,10 +127,11 @@ perf_status perf_conv2d(const void *x, const void *w, void *y, int64_t N, int64_
  * followed by perf_softmax (scale 1) on every row of the M x N result, with the same
  * arithmetic (fp32 accumulation, fp32 softmax) and the same max convention.
  *   A, B     device, bf16 or f32 (ab_dt);  P  device, M x N, row stride ldp, f32 or bf16
- * For bf16 operands with K = 64 or 128, N <= 512 and 16-byte aligned rows the scores never
- * reach memory (one kernel; its exponential is exp2 of a plain fp32 product, relative error
- * about 2^-24 times the exponent); other legal cases run the two operators one
- * after the other through P, which then must be f32 (bf16 P: UNSUPPORTED).
+ * For bf16 operands with K a multiple of 8 up to 512, N <= 1024 and 16-byte aligned rows the scores never
+ * reach memory (one kernel; for K = 64 and N = 128, 256 or 512 its exponential is exp2 of a plain fp32
+ * product, relative error about 2^-24 times the exponent); other legal cases, and few rows of more than
+ * 512 columns, run the two operators one after the other through P.  bf16 P takes K = 64 or 128 and
+ * N <= 512 in one kernel (UNSUPPORTED otherwise).
  * Errors: NULL, SHAPE (dimension < 1, ld too small, negative stride, batches overlapping in
  * P, alpha not finite), DTYPE, ALIGN, UNSUPPORTED, LAUNCH. */
 perf_status perf_gemm_softmax(const void *A, const void *B, void *P, int64_t M, int64_t N,

@@ -4,45 +4,46 @@
 // way the paper's fusion moves join producer and consumer scopes, Sections 2.2 and 3.1: the
 // score matrix never goes to memory, so the traffic is the operands plus one write of P).
 //
-//  * gemm_softmax_kernel: bf16 operands, both K-contiguous, N <= 512, K = 64 or 128.  A
-//    workgroup of 4 waves owns 64 rows x all N columns of one matrix; each wave 16 rows x N
+//  * gemm_softmax_kernel: bf16 operands, both K-contiguous, K = 64, N = 128, 256 or 512, fp32 P.  A
+//    workgroup of 8 waves takes strips of 128 rows x all N columns of one matrix; each wave 16 rows x N
 //    as up to 32 accumulators of 16x16 (128 registers), computed with B as the MFMA's row
 //    operand, so that a lane holds 4 consecutive columns per accumulator and all of a
 //    lane's values belong to ONE row: the row reductions are in-lane plus two lane
-//    exchanges, and the write-out is 16 bytes per lane in whole 128-byte segments.  The
-//    operand strips and all of B go to LDS (global->LDS loads, the swizzled 128-byte rows
+//    exchanges.  The operand strips and all of B go to LDS (global->LDS loads, the swizzled 128-byte rows
 //    of mfma_tile.h): B once per workgroup, which then walks over several row strips of the
-//    matrix with the next strip's rows in flight.  With K = 64 two workgroups fit a CU
-//    (80 KiB of LDS, <= 256 registers), so one's exponentials overlap the other's stores.
+//    matrix with the next strip's rows in flight.
+//  * gemm_softmax_wide_kernel: bf16 operands, any K that is a multiple of 8 up to 512, N <= 1024, P of any
+//    alignment: strips of 32 rows, B streamed through the LDS.
 //  * any other legal case: perf_gemm into P followed by perf_softmax in place.
 #include <atomic>
 #include "mfma_tile.h"
+#include "row_io.h"
 #include "softmax_math.h"
 #include "host_utils.h"
 
 namespace perf {
 
-// T16N: 16-column accumulators per wave (N <= 16 * T16N); MASK: N < 16 * T16N.
+// T16N: 16-column accumulators per wave (N = 16 * T16N, a multiple of 128).
 // A workgroup takes `group` consecutive row strips of one matrix: B goes to LDS once per
 // workgroup, and a wave's 16 rows of the next strip are fetched (into the other of two
 // buffers; the rows are the wave's own, so no barrier is involved) while it works on the
 // present one, so its stores follow each other without a load latency in between.
-// STAGED (8 waves, one workgroup per CU, K = 64, N a multiple of 128, fp32 P): the probabilities leave through
-// a private 8 KiB LDS region per wave, 128 columns at a time, so that a store instruction writes 2 rows x
+// One workgroup per CU: the probabilities leave through a private 8 KiB LDS region per wave, 128 columns at a time, so that a store instruction writes 2 rows x
 // 512 contiguous bytes instead of 8 rows x 128.  A write-only probe of this output (a wave writing its 16
 // rows of 2 KiB per strip) moves 5.6 TB/s in the first shape and 6.3 in the second (6.4 with 1 KiB per row,
 // for which the LDS has no room): the shape of the store instruction, not the exponentials, held the
 // kernel at 0.68 of the HBM peak.
-template <int T16N, bool MASK, typename PT, int NW = 4, bool STAGED = false>
-__global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void gemm_softmax_kernel(const uint16_t *__restrict__ A,
-                                                              const uint16_t *__restrict__ B, PT *__restrict__ P,
+constexpr int kFusedWaves = 8;
+template <int T16N>
+__global__ __launch_bounds__(64 * kFusedWaves, 1) void gemm_softmax_kernel(const uint16_t *__restrict__ A,
+                                                              const uint16_t *__restrict__ B, float *__restrict__ P,
                                                               int M, int N, int K, int64_t lda, int64_t ldb,
                                                               int64_t ldp, int64_t strideA, int64_t strideB,
                                                               int64_t strideP, float sign, float c, int strips,
                                                               int group, int xcd_remap)
 {
-    constexpr int BM = 16 * NW, BN = 16 * T16N;
-    static_assert(!STAGED || (!MASK && T16N % 8 == 0 && sizeof(PT) == 4), "the staged write-out takes whole chunks of 128 fp32 columns");
+    constexpr int NW = kFusedWaves, BM = 16 * NW, BN = 16 * T16N;
+    static_assert(T16N % 8 == 0, "the staged write-out takes whole chunks of 128 columns");
     constexpr int LB = (BN + 8 * NW - 1) / (8 * NW);     // wave loads per K-step of 64 for B (the last one may be partly unused)
     constexpr int kRowsB = LB * 8 * NW;
     constexpr int kStepB = kRowsB * kRowBytes64, kStepA = BM * kRowBytes64;
@@ -67,9 +68,9 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void gemm_softmax_kernel(
     const int ksteps = K / 64;
     const uint16_t *Ab = A + (int64_t)bz * strideA;
     const uint16_t *Bb = B + (int64_t)bz * strideB;
-    PT *Pb = P + (int64_t)bz * strideP;
+    float *Pb = P + (int64_t)bz * strideP;
     char *const smem_a = smem + ksteps * kStepB;  // two buffers of ksteps x BM rows
-    char *const stage = smem_a + 2 * ksteps * kStepA + wave * (16 * 512);  // STAGED: this wave's 16 rows x 128 columns
+    char *const stage = smem_a + 2 * ksteps * kStepA + wave * (16 * 512);  // this wave's 16 rows x 128 columns
 
     // this wave's 16 rows of strip s -> buffer s & 1 (nothing if the rows lie past M)
     auto issue_a = [&](int s) {
@@ -136,8 +137,7 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void gemm_softmax_kernel(
         for (int j = 0; j < T16N; ++j)
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
-                float v = t.acc[0][j][e] * sign;
-                if (MASK) v = (16 * j + 4 * (lane >> 4) + e < N) ? v : -FLT_MAX;
+                const float v = t.acc[0][j][e] * sign;
                 t.acc[0][j][e] = v;
                 m = __builtin_fmaxf(m, v);
             }
@@ -153,8 +153,7 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void gemm_softmax_kernel(
         for (int j = 0; j < T16N; ++j)
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
-                float p = __builtin_amdgcn_exp2f((t.acc[0][j][e] - m) * c);
-                if (MASK) p = (16 * j + 4 * (lane >> 4) + e < N) ? p : 0.f;  // (c == 0 would give masked columns weight 1)
+                const float p = __builtin_amdgcn_exp2f((t.acc[0][j][e] - m) * c);
                 t.acc[0][j][e] = p;
                 z += p;
             }
@@ -170,9 +169,7 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void gemm_softmax_kernel(
         // stores, leaves those in flight across the next strip's MFMAs.  (Letting two strips of stores stay in
         // flight, by waiting for a count at the top of the loop instead, measured no faster.)
         wait_vmem<0>();
-        if constexpr (!STAGED) {
-            store_tile16<1, T16N, PT>(t, Pb, ldp, M, N, m0 + wave * 16, 0, scale, lane);
-        } else {
+        {
             // 128 columns at a time: lane (row r = lane % 16, q = lane / 16) writes its 16-byte pieces 4 jj + q of
             // the chunk to row r of the staging; a row is 32 pieces, piece s at position s ^ r (then both the
             // writes, 16 rows per quarter-wave, and the reads, 16 consecutive pieces of a row, are conflict
@@ -199,17 +196,228 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void gemm_softmax_kernel(
     }
 }
 
-// The staged form: 8 waves, 128-row strips, 160 KiB of LDS (B 64 KiB, two row buffers of 16 KiB, 64 KiB of staging).
+// Longer and ragged rows: N <= 1024, K any multiple of 8, P of any alignment.  A workgroup of 4 waves owns 32 rows x all
+// N columns; wave w the NT tiles of 32 columns from 32 NT w on, as 32x32 accumulators (128 registers at NT = 8) with B as
+// the MFMA's row operand, so that a lane's values belong to ONE row: row maxima and sums are in-lane plus one lane
+// exchange, and one LDS exchange between the waves.  B does not fit the LDS (1024 x 128 bf16 are 256 KiB): both
+// operands pass through it 32 K at a time (global->LDS loads, chunks past K read as zeros), B once per strip from the
+// L2.  At most 80 KiB of LDS, so that two workgroups share a CU and one's loads and exponentials overlap the other's
+// stores; those leave through staging of 8 KiB per wave as 4 rows x 256 bytes per instruction, past the caches
+// only where rows are whole 128-byte lines (a line that two waves or two instructions write is put together in the L2:
+// 96 x (600x777x80) 72 us so, 105 us past the caches).  That shape took 135 us as two launches; its P alone is 28 us
+// of writes at the copy rate, its exponentials about 20 us of vector work.
+// K-steps of operands in the LDS: a second one pays while it costs no workgroup per CU (400 x (200x100x80) 13.9 us
+// against 17.9; 32 x (600x301x64) 17.0 against 13.7 at NT = 4)
+constexpr int wide_stages(int nt) { return nt <= 2 ? 2 : 1; }
+constexpr int wide_chunk(int nt) { return nt < 2 ? nt : 2; }  // tiles of a wave that are staged at a time
+template <int NT, typename PT>
+__global__ __launch_bounds__(256, 2) void gemm_softmax_wide_kernel(const uint16_t *__restrict__ A, const uint16_t *__restrict__ B,
+                                                                   PT *__restrict__ P, int M, int N, int K, int64_t lda,
+                                                                   int64_t ldb, int64_t ldp, int64_t strideA, int64_t strideB,
+                                                                   int64_t strideP, ExpConst ek, float t_min, int strips, int xcd_remap,
+                                                                   int whole_lines)
+{
+    constexpr int kStageB = 128 * NT * kRowBytes, kStageA = 32 * kRowBytes, kStage = kStageB + kStageA;
+    constexpr int NST = wide_stages(NT);
+    constexpr int LB = 2 * NT, kLoads = LB + 1;
+    extern __shared__ __attribute__((aligned(1024))) char smem[];
+    __shared__ float red[2][4][32];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    // (all strips of a matrix on one XCD where the batch allows it: B comes over the fabric once)
+    int si, bz;
+    if (xcd_remap) {
+        const int xcd = blockIdx.x & 7, j = blockIdx.x >> 3;
+        si = j % strips;
+        bz = (j / strips) * 8 + xcd;
+    } else {
+        si = blockIdx.x % strips;
+        bz = blockIdx.x / strips;
+    }
+    const int m0 = si * 32, ksteps = (K + 31) / 32, rows = min(32, M - m0);
+    const uint16_t *Ab = A + (int64_t)bz * strideA + (int64_t)m0 * lda;
+    const uint16_t *Bb = B + (int64_t)bz * strideB;
+    const rsrc_t ra = make_rsrc(Ab, (uint32_t)(((int64_t)(rows - 1) * lda + K) * 2));
+    const rsrc_t rb = make_rsrc(Bb, (uint32_t)(((int64_t)(N - 1) * ldb + K) * 2));
+
+    // load i of wave w: tile rows (4 i + w) * 16 .. +15; lane l row l / 4, the chunk stored at position l % 4
+    const int lrow = lane >> 2;
+    uint32_t vb[LB];
+    int kb;  // first K of this lane's chunk in a step (the swizzle of a row depends on its low four bits only)
+    {
+        const int ch = load_chunk(lrow, lane);
+        kb = ch * 8;
+#pragma unroll
+        for (int i = 0; i < LB; ++i) vb[i] = (uint32_t)(min((i * 4 + wave) * 16 + lrow, N - 1) * ldb * 2) + ch * 16;
+    }
+    const uint32_t va = (uint32_t)(min((wave & 1) * 16 + lrow, rows - 1) * lda * 2) + kb * 2;
+    auto issue = [&](int ks) {
+        char *st = smem + (NST == 2 ? (ks & 1) * kStage : 0);
+        const bool in = ks * 32 + kb < K;
+        const uint32_t so = (uint32_t)ks * kRowBytes;
+#pragma unroll
+        for (int i = 0; i < LB; ++i) issue_load_to(rb, in ? vb[i] : kOutOfRange, so, st + (i * 4 + wave) * 16 * kRowBytes);
+        issue_load_to(ra, in ? va : kOutOfRange, so, st + kStageB + (wave & 1) * 16 * kRowBytes);  // (waves 2, 3: the same again)
+    };
+    float16_t acc[NT];
+#pragma unroll
+    for (int j = 0; j < NT; ++j)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) acc[j][e] = 0.f;
+    issue(0);
+    if (NST == 2 && ksteps > 1) issue(1);
+    for (int ks = 0; ks < ksteps; ++ks) {
+        if (NST == 2 && ks + 1 < ksteps) wait_vmem<kLoads>();
+        else wait_vmem<0>();
+        wg_barrier();
+        const char *st = smem + (NST == 2 ? (ks & 1) * kStage : 0);
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const int chunk = 2 * h + (lane >> 5);
+            const bf16x8_t a = *reinterpret_cast<const bf16x8_t *>(st + kStageB + frag_offset(lane & 31, chunk));
+#pragma unroll
+            for (int j = 0; j < NT; ++j) {
+                const bf16x8_t b = *reinterpret_cast<const bf16x8_t *>(st + frag_offset((wave * NT + j) * 32 + (lane & 31), chunk));
+                acc[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(b, a, acc[j], 0, 0, 0);
+            }
+        }
+        __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0): this wave is done with the stage
+        wg_barrier();
+        if (ks + NST < ksteps) issue(ks + NST);
+    }
+
+    // acc[j] element e: row m0 + lane % 32, column 32 (wave NT + j) + 8 (e / 4) + 4 (lane / 32) + e % 4
+    const int row = lane & 31, half = lane >> 5, col0 = 32 * wave * NT;
+    if (ek.sign < 0.f) {  // (uniform: the maximum of -v)
+#pragma unroll
+        for (int j = 0; j < NT; ++j)
+#pragma unroll
+            for (int e = 0; e < 16; ++e) acc[j][e] = -acc[j][e];
+    }
+    auto column = [&](int j, int e) { return col0 + 32 * j + 8 * (e >> 2) + 4 * half + (e & 3); };
+    const bool ragged = col0 + 32 * NT > N;  // (uniform) some of this wave's columns lie past N
+    if (ragged) {
+#pragma unroll
+        for (int j = 0; j < NT; ++j)
+#pragma unroll
+            for (int e = 0; e < 16; ++e) acc[j][e] = column(j, e) < N ? acc[j][e] : -FLT_MAX;
+    }
+    float m = -FLT_MAX;
+#pragma unroll
+    for (int j = 0; j < NT; ++j)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) m = __builtin_fmaxf(m, acc[j][e]);
+    float x, y;
+    swap32(m, x, y);
+    red[0][wave][row] = __builtin_fmaxf(x, y);  // (both halves write the same)
+    __syncthreads();
+    m = __builtin_fmaxf(__builtin_fmaxf(red[0][0][row], red[0][1][row]), __builtin_fmaxf(red[0][2][row], red[0][3][row]));
+#pragma unroll
+    for (int j = 0; j < NT; ++j)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) acc[j][e] = exp_scaled_above(acc[j][e] - m, ek.c_hi, ek.c_lo, t_min);
+    if (ragged) {  // (scale 0 would give masked columns weight 1)
+#pragma unroll
+        for (int j = 0; j < NT; ++j)
+#pragma unroll
+            for (int e = 0; e < 16; ++e) acc[j][e] = column(j, e) < N ? acc[j][e] : 0.f;
+    }
+    float z = 0.f;
+#pragma unroll
+    for (int j = 0; j < NT; ++j)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) z += acc[j][e];
+    swap32(z, x, y);
+    red[1][wave][row] = x + y;
+    __syncthreads();  // (the operand stages are free since the last step's barrier)
+    const float inv = 1.0f / ((red[1][0][row] + red[1][1][row]) + (red[1][2][row] + red[1][3][row]));
+
+    // write-out, 4 tiles = 128 columns at a time: 32 pieces of 16 bytes per row, piece s at position s ^ row
+    constexpr int NC = wide_chunk(NT), kPieces = 8 * NC, kRowsPer = 64 / kPieces;
+    char *const stage = smem + wave * (32 * 16 * kPieces);
+    const int piece = lane % kPieces;
+    PT *Pb = P + (int64_t)bz * strideP + (int64_t)m0 * ldp;
+#pragma unroll
+    for (int j0 = 0; j0 < NT; j0 += NC) {
+#pragma unroll
+        for (int j = 0; j < NC; ++j)
+            if (j0 + j < NT) {
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    const float16_t &c = acc[j0 + j < NT ? j0 + j : 0];
+                    const float4_t v = {c[4 * q] * inv, c[4 * q + 1] * inv, c[4 * q + 2] * inv, c[4 * q + 3] * inv};
+                    *reinterpret_cast<float4_t *>(stage + row * (16 * kPieces) + (((8 * j + 2 * q + half) ^ (row & (kPieces - 1))) << 4)) = v;
+                }
+            }
+        __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0): own writes are in LDS (the region is this wave's alone)
+        const int col = col0 + 32 * j0 + 4 * piece;
+        const int left = piece < 8 * (NT - j0) ? N - col : 0;  // columns of this lane's piece that exist
+#pragma unroll
+        for (int i = 0; i < 32 / kRowsPer; ++i) {
+            const int r = kRowsPer * i + lane / kPieces;
+            const float4_t v = *reinterpret_cast<const float4_t *>(stage + r * (16 * kPieces) + ((piece ^ (r & (kPieces - 1))) << 4));
+            PT *dst = Pb + (int64_t)r * ldp + col;
+            if (r < rows && left >= 4) {
+                if constexpr (sizeof(PT) == 4) {
+                    typedef float float4_at4 __attribute__((ext_vector_type(4), aligned(4)));
+                    if (whole_lines) __builtin_nontemporal_store(v, reinterpret_cast<float4_at4 *>(dst));
+                    else *reinterpret_cast<float4_at4 *>(dst) = v;
+                } else {
+                    typedef uint32_t uint2_at2 __attribute__((ext_vector_type(2), aligned(2)));
+                    const uint2_t o = {pack_bf16(v[0], v[1]), pack_bf16(v[2], v[3])};
+                    if (whole_lines) __builtin_nontemporal_store(o, reinterpret_cast<uint2_at2 *>(dst));
+                    else *reinterpret_cast<uint2_at2 *>(dst) = o;
+                }
+            } else if (r < rows) {
+#pragma unroll
+                for (int e = 0; e < 3; ++e)
+                    if (e < left) Elem<PT>::store1(dst + e, v[e]);
+            }
+        }
+        __builtin_amdgcn_wave_barrier();  // (the wave's LDS operations execute in order)
+    }
+}
+
+template <int NT, typename PT>
+static perf_status launch_wide(const void *A, const void *B, void *P, int64_t M, int64_t N, int64_t K, int64_t lda, int64_t ldb,
+                               int64_t ldp, int64_t batch, int64_t strideA, int64_t strideB, int64_t strideP, float alpha,
+                               hipStream_t st)
+{
+    constexpr int kStages = wide_stages(NT) * (128 * NT + 32) * kRowBytes, kOut = 4 * 32 * 128 * wide_chunk(NT);
+    constexpr int kLds = kStages > kOut ? kStages : kOut;
+    auto kern = gemm_softmax_wide_kernel<NT, PT>;
+    static std::atomic<bool> attr_done{false};  // (idempotent per-function setting)
+    if (!attr_done) {
+        if (hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, kLds) != hipSuccess)
+            return PERF_ERR_LAUNCH;
+        attr_done = true;
+    }
+    const ExpConst ek = make_exp_const(alpha);
+    const float t_min = ek.c_hi > 0.f ? std::fmax(-200.0f / ek.c_hi, -FLT_MAX) : -FLT_MAX;
+    const int64_t line = 128 / sizeof(PT);
+    const int whole_lines = N % line == 0 && ldp % line == 0 && strideP % line == 0 && aligned(P, 128);
+    const int64_t strips = (M + 31) / 32, per_launch = (kMaxGridX / strips) / 8 * 8;
+    if (per_launch < 8) return PERF_ERR_UNSUPPORTED;
+    for (int64_t b0 = 0; b0 < batch; b0 += per_launch) {
+        const int64_t nb = batch - b0 < per_launch ? batch - b0 : per_launch;
+        hipLaunchKernelGGL(kern, dim3((unsigned)(strips * nb)), dim3(256), kLds, st, (const uint16_t *)A + b0 * strideA,
+                           (const uint16_t *)B + b0 * strideB, (PT *)P + b0 * strideP, (int)M, (int)N, (int)K, lda, ldb, ldp,
+                           strideA, strideB, strideP, ek, t_min, (int)strips, nb % 8 == 0 ? 1 : 0, whole_lines);
+    }
+    return launch_status();
+}
+
+// gemm_softmax_kernel: 8 waves, 128-row strips, 160 KiB of LDS (B 64 KiB, two row buffers of 16 KiB, 64 KiB of staging).
 template <int T16N>
 static perf_status launch_fused_staged(const void *A, const void *B, void *P, int64_t M, int64_t N, int64_t K, int64_t lda,
                                        int64_t ldb, int64_t ldp, int64_t batch, int64_t strideA, int64_t strideB,
                                        int64_t strideP, float alpha, hipStream_t st)
 {
-    constexpr int NW = 8;
+    constexpr int NW = kFusedWaves;
     constexpr int kRowsB = (16 * T16N + 8 * NW - 1) / (8 * NW) * (8 * NW);
     const size_t lds = (size_t)(K / 64) * (2 * 16 * NW + kRowsB) * kRowBytes64 + (size_t)NW * 16 * 512;
     if (lds > 160 * 1024) return PERF_ERR_UNSUPPORTED;
-    auto kern = gemm_softmax_kernel<T16N, false, float, NW, true>;
+    auto kern = gemm_softmax_kernel<T16N>;
     static std::atomic<bool> attr_done{false};  // (idempotent per-function setting)
     if (!attr_done) {
         if (hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
@@ -230,42 +438,6 @@ static perf_status launch_fused_staged(const void *A, const void *B, void *P, in
         const int64_t nb = batch - b0 < per_launch ? batch - b0 : per_launch;
         hipLaunchKernelGGL(kern, dim3((unsigned)(groups * nb)), dim3(64 * NW), lds, st, (const uint16_t *)A + b0 * strideA,
                            (const uint16_t *)B + b0 * strideB, (float *)P + b0 * strideP, (int)M, (int)N, (int)K, lda, ldb,
-                           ldp, strideA, strideB, strideP, sign, c, (int)strips, (int)group, nb % 8 == 0 ? 1 : 0);
-    }
-    return launch_status();
-}
-
-template <int T16N, bool MASK, typename PT>
-static perf_status launch_fused(const void *A, const void *B, void *P, int64_t M, int64_t N, int64_t K, int64_t lda,
-                                int64_t ldb, int64_t ldp, int64_t batch, int64_t strideA, int64_t strideB,
-                                int64_t strideP, float alpha, hipStream_t st)
-{
-    constexpr int kRowsB = (16 * T16N + 31) / 32 * 32;
-    const size_t lds = (size_t)(K / 64) * (2 * 64 + kRowsB) * kRowBytes64;  // B, and two buffers for the row strips
-    auto kern = gemm_softmax_kernel<T16N, MASK, PT>;
-    // the dynamic-LDS cap is a per-function setting: raised once to the CU's 160 KiB (idempotent, so
-    // concurrent first calls are harmless)
-    static std::atomic<bool> attr_done{false};
-    if (!attr_done) {
-        if (hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
-                                160 * 1024) != hipSuccess)
-            return PERF_ERR_LAUNCH;
-        attr_done = true;
-    }
-    const float sign = alpha < 0.f ? -1.f : 1.f;
-    const float c = (float)(std::fabs((double)alpha) * 1.4426950408889634074);  // |alpha| log2(e)
-    const int64_t strips = (M + 63) / 64;
-    // strips per workgroup: as many as still leave two workgroups for every CU
-    int64_t group = strips * batch / 512;
-    group = group < 1 ? 1 : group > strips ? strips : group;
-    const int64_t groups = (strips + group - 1) / group;
-    // one-dimensional grid of strip groups x matrices, in chunks that keep the grid below its limit
-    const int64_t per_launch = (kMaxGridX / groups) / 8 * 8;
-    if (per_launch < 8) return PERF_ERR_UNSUPPORTED;
-    for (int64_t b0 = 0; b0 < batch; b0 += per_launch) {
-        const int64_t nb = batch - b0 < per_launch ? batch - b0 : per_launch;
-        hipLaunchKernelGGL(kern, dim3((unsigned)(groups * nb)), dim3(256), lds, st, (const uint16_t *)A + b0 * strideA,
-                           (const uint16_t *)B + b0 * strideB, (PT *)P + b0 * strideP, (int)M, (int)N, (int)K, lda, ldb,
                            ldp, strideA, strideB, strideP, sign, c, (int)strips, (int)group, nb % 8 == 0 ? 1 : 0);
     }
     return launch_status();
@@ -292,28 +464,37 @@ extern "C" perf_status perf_gemm_softmax(const void *A, const void *B, void *P, 
         return PERF_ERR_ALIGN;
     hipStream_t st = static_cast<hipStream_t>(stream);
 
-    const bool fused = ab_dt == PERF_BF16 && (K == 64 || K == 128) && N <= 512 && lda % 8 == 0 && ldb % 8 == 0 &&
-                       strideA % 8 == 0 && strideB % 8 == 0 && aligned(A, 16) && aligned(B, 16) && lda <= (1 << 21) &&
-                       ldb <= (1 << 21) && M <= (1 << 24);
-    if (fused) {
-#define PERF_FUSED(T, MASK)                                                                                              \
-    (p_dt == PERF_F32                                                                                                    \
-         ? launch_fused<T, MASK, float>(A, B, P, M, N, K, lda, ldb, ldp, batch, strideA, strideB, strideP, alpha, st)    \
-         : launch_fused<T, MASK, uint16_t>(A, B, P, M, N, K, lda, ldb, ldp, batch, strideA, strideB, strideP, alpha, st))
-        // whole chunks of 128 columns, K = 64, fp32 P with 16-byte aligned rows: the staged write-out
-        const bool staged = K == 64 && N % 128 == 0 && p_dt == PERF_F32 && ldp % 4 == 0 && strideP % 4 == 0 && aligned(P, 16);
-        if (staged && N == 512) return launch_fused_staged<32>(A, B, P, M, N, K, lda, ldb, ldp, batch, strideA, strideB, strideP, alpha, st);
-        if (staged && N == 256) return launch_fused_staged<16>(A, B, P, M, N, K, lda, ldb, ldp, batch, strideA, strideB, strideP, alpha, st);
-        if (staged && N == 128) return launch_fused_staged<8>(A, B, P, M, N, K, lda, ldb, ldp, batch, strideA, strideB, strideP, alpha, st);
-        if (N == 512) return PERF_FUSED(32, false);
-        if (N > 256) return PERF_FUSED(32, true);
-        if (N == 256) return PERF_FUSED(16, false);
-        if (N > 128) return PERF_FUSED(16, true);
-        if (N == 128) return PERF_FUSED(8, false);
-        if (N > 64) return PERF_FUSED(8, true);
-        return PERF_FUSED(4, true);
-#undef PERF_FUSED
+    // One kernel (scores never reach memory): operands as the global->LDS loads need them, N up to 1024, fp32 P for any K
+    // that is a multiple of 8 up to 512 (16 x (1024x1024x512): 53 us against 58 in two launches), bf16 P for the K and N that
+    // the header names.
+    const bool loads_ok = ab_dt == PERF_BF16 && K % 8 == 0 && lda % 8 == 0 && ldb % 8 == 0 && strideA % 8 == 0 && strideB % 8 == 0 &&
+                          aligned(A, 16) && aligned(B, 16) && M <= (1 << 24);
+    // whole chunks of 128 columns, K = 64, fp32 P with 16-byte aligned rows: B stays in the LDS for several strips, the staged
+    // write-out (512 x (512x512x64) 104 us against 116 with the strip kernel, 300 x (256x128x64) 13.2 against 14.5)
+    const bool staged = loads_ok && K == 64 && p_dt == PERF_F32 && lda <= (1 << 21) && ldb <= (1 << 21) && ldp % 4 == 0 &&
+                        strideP % 4 == 0 && aligned(P, 16);
+    if (staged && N == 512) return launch_fused_staged<32>(A, B, P, M, N, K, lda, ldb, ldp, batch, strideA, strideB, strideP, alpha, st);
+    if (staged && N == 256) return launch_fused_staged<16>(A, B, P, M, N, K, lda, ldb, ldp, batch, strideA, strideB, strideP, alpha, st);
+    if (staged && N == 128) return launch_fused_staged<8>(A, B, P, M, N, K, lda, ldb, ldp, batch, strideA, strideB, strideP, alpha, st);
+    const int64_t strips = (M + 31) / 32 * batch;
+#define PERF_WIDE(T, PT) return launch_wide<T, PT>(A, B, P, M, N, K, lda, ldb, ldp, batch, strideA, strideB, strideP, alpha, st)
+    if (loads_ok && lda <= (1 << 21) && ldb <= (1 << 21) && p_dt == PERF_BF16 && N <= 512 && (K == 64 || K == 128)) {
+        if (N <= 128) PERF_WIDE(1, uint16_t);
+        if (N <= 256) PERF_WIDE(2, uint16_t);
+        PERF_WIDE(4, uint16_t);
     }
+    // (a few strips of long rows are faster as two launches, which spread the columns over the chip: 100x769x128 8 us
+    // against 13)
+    if (loads_ok && lda <= (1 << 20) && ldb <= (1 << 20) && p_dt == PERF_F32 && N <= 1024 && K <= 512 && (N <= 512 || strips >= 64)) {
+        if (N <= 128) PERF_WIDE(1, float);
+        if (N <= 256) PERF_WIDE(2, float);
+        if (N <= 512) PERF_WIDE(4, float);
+        if (N <= 640) PERF_WIDE(5, float);
+        if (N <= 768) PERF_WIDE(6, float);
+        if (N <= 896) PERF_WIDE(7, float);
+        PERF_WIDE(8, float);
+    }
+#undef PERF_WIDE
     // Unfused: scores into P, then the row softmax in place (fp32 P only).
     if (p_dt != PERF_F32) return PERF_ERR_UNSUPPORTED;
     perf_status s = perf_gemm(A, B, P, M, N, K, PERF_ROW_MAJOR, lda, PERF_COL_MAJOR, ldb, ldp, batch, strideA, strideB,

@@ -22,6 +22,17 @@ __device__ __forceinline__ float exp_scaled(float t, float c_hi, float c_lo)
     return p < -160.f ? 0.f : v;       // also discards the NaN residual of an overflowed p
 }
 
+// The same with the clamp where the result has become 0 (t_min = -200 / c_hi, or -FLT_MAX): nothing overflows, so no
+// result needs to be discarded.
+__device__ __forceinline__ float exp_scaled_above(float t, float c_hi, float c_lo, float t_min)
+{
+    t = __builtin_fmaxf(t, t_min);
+    const float p = t * c_hi;
+    const float r = __builtin_fmaf(t, c_lo, __builtin_fmaf(t, c_hi, -p));
+    const float e = __builtin_amdgcn_exp2f(p);
+    return __builtin_fmaf(e, r * 0.69314718056f, e);
+}
+
 struct ExpConst {
     float sign, c_hi, c_lo;
 };

@@ -90,6 +90,27 @@ def test_staged_write_out_widths_ragged_strips_and_leading_dimensions():
         P.assert_softmax_close(p.reshape(-1, N), ref.reshape(-1, N), tol=TOL)
 
 
+@pytest.mark.parametrize("M,N,K,batch,ldp", [
+    (1, 1, 8, 1, 1), (33, 3, 16, 2, 3), (31, 127, 24, 1, 127), (32, 128, 72, 3, 131), (65, 129, 64, 1, 129), (40, 255, 80, 2, 256),
+    (33, 257, 136, 1, 257), (64, 512, 128, 2, 512), (17, 511, 200, 1, 511), (33, 513, 40, 32, 513), (1, 640, 64, 64, 640),
+    (33, 641, 96, 32, 641), (20, 768, 80, 64, 768), (1, 769, 512, 64, 771), (33, 896, 64, 32, 896), (1, 897, 8, 65, 897),
+    (33, 1023, 80, 32, 1023), (32, 1024, 64, 64, 1024), (2, 1025, 64, 3, 1025),
+])
+def test_strip_kernel_edges(M, N, K, batch, ldp):
+    # N at the edges of each column count per wave, K-steps that are partial, ragged strips, P of any alignment; the last
+    # one is past the kernel's columns.  (Scaled by 1/sqrt(K): a score is a sum of K products of N(0,1) values, typically
+    # off by sqrt(K) 2^-24 of its size sqrt(K), at most K 2^-24 sum |q||k|, and a probability by alpha times that: with
+    # alpha = -0.5 at K = 512 fp32 accumulation alone costs 2e-5, 1.87e-5 was seen.)
+    for alpha in (K ** -0.5, -2 * K ** -0.5):
+        _check(M, N, K, alpha=alpha, batch=batch, ldp=ldp)
+    _check(M, N, K, alpha=0.0, batch=batch, ldp=ldp)
+
+
+@pytest.mark.parametrize("M,N,K", [(33, 5, 64), (40, 130, 128), (64, 512, 64), (1, 301, 128)])
+def test_strip_kernel_bf16_output(M, N, K):
+    _check(M, N, K, batch=3, p_bf16=True)
+
+
 def test_argmax_matches_scores():
     M, N, K = 256, 512, 64
     a, b = _inputs(M, N, K, 1, seed=7)
