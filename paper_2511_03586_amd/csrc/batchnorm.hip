@@ -3,16 +3,19 @@
 // are computed first, then a streaming kernel normalises).  x is NCHW; a channel's data are
 // N planes of H*W contiguous elements.
 //
-//  * bn_partial_kernel: a workgroup reduces one segment (<= 16384 elements) of one plane,
-//    held in registers: provisional mean, then first and second moments of the shifted data
-//    (the corrected two-pass form of the LayerNorm kernel), written as (mean_hi, mean_lo, M2).
-//  * bn_finalize_kernel: one workgroup per channel merges the segments' (count, mean, M2) in
-//    double precision (the pairwise update of parallel variance algorithms), and writes mean,
-//    rstd and the per-channel scale rstd*gamma.
-//  * bn_apply_kernel: streaming y = (x - mean) * scale + beta, 16-byte accesses.
+//  * bn_partial_kernel: a workgroup reduces one segment (<= 16384 elements) of a channel, held in registers:
+//    part of a plane, or several whole planes where they are small; provisional mean, then first and second
+//    moments of the shifted data (the corrected two-pass form of the LayerNorm kernel), written as
+//    (mean_hi, mean_lo, M2).
+//  * bn_apply_kernel: streaming y = (x - mean) * scale + beta, 16-byte accesses, on the same segments.  The channel's
+//    segments are merged in double precision, by every workgroup while its loads fly if there are at most
+//    256 of them, else by bn_finalize_kernel (one workgroup per channel).
+// Planes of any size and alignment use 16-byte loads (row_io.h: the chunk that would overhang a plane starts
+// early and its shared elements count once).
 // The partials live in a caller-supplied workspace (perf_batchnorm_workspace_bytes): no
 // atomics, results bit-identical from run to run.
 #include <atomic>
+#include <type_traits>
 #include "row_io.h"
 #include "host_utils.h"
 
@@ -29,92 +32,120 @@ __device__ __forceinline__ float bn_block_sum(float v, float *red)
     return (red[0] + red[1]) + (red[2] + red[3]);
 }
 
-// grid: (segments per plane, N*C planes).  VEC: plane size and base allow 16-byte loads.
-template <typename XT, bool VEC>
-__global__ __launch_bounds__(256) void bn_partial_kernel(const XT *__restrict__ x, float *__restrict__ partial, int64_t HW,
-                                                         int C, int segs)
+constexpr int kBnFuseSegs = 256;  // segments per channel up to which the apply kernel merges them itself
+
+// How a channel is cut.  Planes of more than half a segment are split (spp segments each); smaller ones are grouped,
+// G to a segment.  An item is a chunk of 16 bytes of x; a segment's items are numbered through its planes.
+struct BnGeom {
+    int64_t HW;
+    int C, N;
+    int64_t cpp;   // chunks per plane
+    int G, spp;    // planes per segment (0: split), segments per plane when split
+    int segs;      // segments per channel
+    uint32_t m_cpp;
+    __device__ __forceinline__ int64_t count(int s) const  // elements of segment s
+    {
+        return G ? (int64_t)min(G, N - s * G) * HW : min((int64_t)kBnSeg, HW - (int64_t)(s % spp) * kBnSeg);
+    }
+};
+
+template <typename T, int NJ, bool RAG>
+struct BnItems {  // this thread's items of a segment
+    static constexpr int E = Elem<T>::kPerChunk;
+    const BnGeom &g;
+    int64_t base, c0;  // first element of the segment's first plane (channel c); first chunk when split
+    int total;         // items of the segment
+    __device__ __forceinline__ BnItems(const BnGeom &g_, int c, int s) : g(g_)
+    {
+        const int n0 = g.G ? s * g.G : s / g.spp, part = g.G ? 0 : s % g.spp;
+        base = ((int64_t)n0 * g.C + c) * g.HW;
+        c0 = (int64_t)part * (kBnSeg / E);
+        total = g.G ? min(g.G, g.N - n0) * (int)g.cpp : (int)min((int64_t)(kBnSeg / E), g.cpp - c0);
+    }
+    __device__ __forceinline__ bool all() const { return total == NJ * 256; }
+    __device__ __forceinline__ bool valid(int j) const { return j * 256 + (int)threadIdx.x < total; }
+    // element offset of item j from `base`; `dup`: its first elements that the chunk before holds as well
+    __device__ __forceinline__ int64_t at(int j, int &dup) const
+    {
+        const int i = min(j * 256 + (int)threadIdx.x, total - 1);
+        const int p = g.G ? fast_quot(i, (int)g.cpp, g.m_cpp) : 0;
+        const int64_t first = (g.G ? i - p * (int)g.cpp : c0 + i) * E, start = RAG ? min(first, g.HW - E) : first;
+        dup = (int)(first - start);
+        return (int64_t)p * g.C * g.HW + start;
+    }
+    __device__ static __forceinline__ int fast_quot(int n, int d, uint32_t m)
+    {
+        const uint32_t q = __umulhi((uint32_t)n, m);
+        return (int)((uint32_t)n - q * (uint32_t)d >= (uint32_t)d ? q + 1 : q);
+    }
+};
+
+// grid: (segments, C).
+template <typename XT, int NJ, bool RAG>
+__global__ __launch_bounds__(256) void bn_partial_kernel(const XT *__restrict__ x, float *__restrict__ partial, BnGeom g)
 {
     constexpr int E = Elem<XT>::kPerChunk;
-    constexpr int kPerThread = kBnSeg / 256;  // 64
     __shared__ float red[4];
-    const int64_t plane = blockIdx.y;  // n*C + c
-    const int64_t seg0 = (int64_t)blockIdx.x * kBnSeg;
-    const bool full = blockIdx.x + 1 < gridDim.x || HW % kBnSeg == 0;  // every segment but a ragged last one
-    const int64_t len = full ? (int64_t)kBnSeg : HW - seg0;
-    const XT *xp = x + plane * HW + seg0;
-    float v[kPerThread];
-    if (VEC && full) {
-        // full segment (uniform): straight-line loads, all in flight together; with a bounds
-        // test around each load the compiler waits for the loads two at a time
+    const int s = blockIdx.x, c = blockIdx.y;
+    const BnItems<XT, NJ, RAG> items(g, c, s);
+    const XT *xp = x + items.base;
+    uint4_t raw[NJ];
+    int dup[NJ];
+    // straight-line loads from clamped addresses, all in flight together (with a bounds test around each load the compiler
+    // waits for the loads two at a time); plain (cacheable) ones: what the last-level cache keeps of x is read
+    // from there by the apply kernel (8x64x300x300 fp32: 107 -> 89 us)
 #pragma unroll
-        for (int j = 0; j < kPerThread / E; ++j)
-            Elem<XT>::unpack(*reinterpret_cast<const uint4_t *>(xp + ((int64_t)j * 256 + threadIdx.x) * E), v + j * E);
-    } else if (VEC) {
+    for (int j = 0; j < NJ; ++j) raw[j] = load_chunk<RAG>(xp + items.at(j, dup[j]));
+    float v[NJ][E];
+    auto reduce = [&](auto masked) {
+        constexpr bool kMasked = decltype(masked)::value;
+        auto counts = [&](int j, int e) { return !kMasked || (items.valid(j) && (!RAG || e >= dup[j])); };
+        float sum = 0.f;
 #pragma unroll
-        for (int j = 0; j < kPerThread / E; ++j) {
-            const int64_t e0 = ((int64_t)j * 256 + threadIdx.x) * E;
-            if (e0 < len) {  // HW is a multiple of E: a chunk is entirely inside or outside
-                // plain (cacheable) load: what the last-level cache keeps of x is read from there by the
-                // apply kernel (8x64x300x300 fp32: 107 -> 89 us)
-                Elem<XT>::unpack(*reinterpret_cast<const uint4_t *>(xp + e0), v + j * E);
-            } else {
+        for (int j = 0; j < NJ; ++j) {
+            Elem<XT>::unpack(raw[j], v[j]);
 #pragma unroll
-                for (int e = 0; e < E; ++e) v[j * E + e] = 0.f;
+            for (int e = 0; e < E; ++e) sum += counts(j, e) ? v[j][e] : 0.f;
+        }
+        const float len = (float)g.count(s), inv = 1.0f / len;
+        const float mean0 = bn_block_sum(sum, red) * inv;
+        float s1 = 0.f, s2 = 0.f;
+#pragma unroll
+        for (int j = 0; j < NJ; ++j)
+#pragma unroll
+            for (int e = 0; e < E; ++e) {
+                const float d = counts(j, e) ? v[j][e] - mean0 : 0.f;
+                s1 += d;
+                s2 = __builtin_fmaf(d, d, s2);
             }
+        s1 = bn_block_sum(s1, red);
+        s2 = bn_block_sum(s2, red);
+        if (threadIdx.x == 0) {
+            const float dm = s1 * inv;
+            // segment statistics: mean = mean0 + dm (kept as two floats), M2 = sum (x - mean)^2
+            float *p = partial + ((int64_t)c * g.segs + s) * 3;
+            p[0] = mean0;
+            p[1] = dm;
+            p[2] = __builtin_fmaxf(__builtin_fmaf(-dm * len, dm, s2), 0.f);
         }
-    } else {
-#pragma unroll
-        for (int j = 0; j < kPerThread; ++j) {
-            const int64_t e0 = (int64_t)j * 256 + threadIdx.x;
-            v[j] = e0 < len ? Elem<XT>::load1(xp + e0) : 0.f;
-        }
-    }
-    auto inside = [&](int j) {  // is register j a real element?
-        const int64_t e0 = VEC ? ((int64_t)(j / E) * 256 + threadIdx.x) * E + j % E : (int64_t)j * 256 + threadIdx.x;
-        return e0 < len;
     };
-    float s = 0.f;
-#pragma unroll
-    for (int j = 0; j < kPerThread; ++j) s += v[j];  // padding registers hold zeros
-    const float inv = 1.0f / (float)len;
-    const float mean0 = bn_block_sum(s, red) * inv;
-    float s1 = 0.f, s2 = 0.f;
-#pragma unroll
-    for (int j = 0; j < kPerThread; ++j) {
-        const float d = inside(j) ? v[j] - mean0 : 0.f;
-        s1 += d;
-        s2 = __builtin_fmaf(d, d, s2);
-    }
-    s1 = bn_block_sum(s1, red);
-    s2 = bn_block_sum(s2, red);
-    if (threadIdx.x == 0) {
-        const float dm = s1 * inv;
-        // segment statistics: mean = mean0 + dm (kept as two floats), M2 = sum (x - mean)^2
-        const int c = (int)(plane % C);
-        const int64_t n = plane / C;
-        float *p = partial + (((int64_t)c * gridDim.y / C + n) * segs + blockIdx.x) * 3;
-        p[0] = mean0;
-        p[1] = dm;
-        p[2] = __builtin_fmaxf(__builtin_fmaf(-dm * (float)len, dm, s2), 0.f);
-    }
+    if (!RAG && items.all()) reduce(std::false_type{});
+    else reduce(std::true_type{});
 }
 
 // grid: C workgroups.  coef[c] = rstd*gamma, coef[C + c] = mean.
 template <typename PT>
 __global__ __launch_bounds__(256) void bn_finalize_kernel(const float *__restrict__ partial, const PT *__restrict__ gamma,
                                                           float *__restrict__ coef, float *__restrict__ mean_out,
-                                                          float *__restrict__ rstd_out, int64_t HW, int C, int N, int segs,
-                                                          float eps)
+                                                          float *__restrict__ rstd_out, BnGeom g, float eps)
 {
     __shared__ double sh_n[256], sh_mean[256], sh_m2[256];
     const int c = blockIdx.x;
-    const int64_t total = (int64_t)N * segs;
-    const float *p = partial + (int64_t)c * total * 3;
+    const float *p = partial + (int64_t)c * g.segs * 3;
     // each thread folds its share of the segments in order, then a tree over the threads
     double cnt = 0.0, mean = 0.0, m2 = 0.0;
-    for (int64_t i = threadIdx.x; i < total; i += 256) {
-        const int64_t sidx = i % segs;
-        const double nb = (double)min((int64_t)kBnSeg, HW - sidx * kBnSeg);
+    for (int i = threadIdx.x; i < g.segs; i += 256) {
+        const double nb = (double)g.count(i);
         const double mb = (double)p[3 * i] + (double)p[3 * i + 1], qb = (double)p[3 * i + 2];
         const double nn = cnt + nb, delta = mb - mean;
         mean += delta * (nb / nn);
@@ -142,64 +173,129 @@ __global__ __launch_bounds__(256) void bn_finalize_kernel(const float *__restric
         const float mu = (float)sh_mean[0];
         const float rstd = (float)(1.0 / sqrt(var + (double)eps));
         coef[c] = rstd * Elem<PT>::load1(gamma + c);
-        coef[C + c] = mu;
+        coef[g.C + c] = mu;
         if (mean_out) mean_out[c] = mu;
         if (rstd_out) rstd_out[c] = rstd;
     }
 }
 
-// grid: (segments per plane, N*C planes).
-template <typename XT, typename PT, typename YT, bool VEC>
-__global__ __launch_bounds__(256) void bn_apply_kernel(const XT *__restrict__ x, const PT *__restrict__ beta,
-                                                       const float *__restrict__ coef, YT *__restrict__ y, int64_t HW, int C)
+__device__ __forceinline__ double bn_block_sum_f64(double v, double *red)
+{
+#pragma unroll
+    for (int step = 32; step > 0; step >>= 1) v += __shfl_xor(v, step);
+    __syncthreads();  // red may still be read from the previous use
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
+    __syncthreads();
+    return (red[0] + red[1]) + (red[2] + red[3]);
+}
+
+// Statistics of channel c from its segments' (mean, M2), at most kBnFuseSegs = one per thread:
+// mean = sum n_i m_i / n, M2 = sum (M2_i + n_i (m_i - mean)^2), in double.
+__device__ __forceinline__ void bn_channel_stats(const float *partial, int c, const BnGeom &g, float eps, double *red, float &mu,
+                                                 float &rstd)
+{
+    static_assert(kBnFuseSegs == 256, "one segment per thread");
+    const int i = threadIdx.x;
+    const bool in = i < g.segs;
+    const float *p = partial + ((int64_t)c * g.segs + (in ? i : 0)) * 3;
+    const double nb = in ? (double)g.count(i) : 0.0, mb = (double)p[0] + (double)p[1], qb = in ? (double)p[2] : 0.0;
+    const double n = (double)g.N * (double)g.HW, mean = bn_block_sum_f64(nb * mb, red) / n;
+    const double var = bn_block_sum_f64(qb + nb * (mb - mean) * (mb - mean), red) / n;
+    mu = (float)mean;
+    rstd = (float)(1.0 / sqrt(var + (double)eps));
+}
+
+// grid: (segments, C).  STATS: the channel's statistics are made here from the segments' (partial, and gamma,
+// mean_out, rstd_out, eps with them): 8x64x300x300 fp32 94 -> 88 us with the launch that made them gone; else coef
+// holds them.
+template <typename XT, typename PT, typename YT, int NJ, bool RAG, bool STATS>
+__global__ __launch_bounds__(256) void bn_apply_kernel(const XT *__restrict__ x, const PT *__restrict__ gamma,
+                                                       const PT *__restrict__ beta, const float *__restrict__ partial,
+                                                       const float *__restrict__ coef, YT *__restrict__ y,
+                                                       float *__restrict__ mean_out, float *__restrict__ rstd_out, BnGeom g,
+                                                       float eps)
 {
     constexpr int E = Elem<XT>::kPerChunk;
-    constexpr int kPerThread = kBnSeg / 256;
-    const int64_t plane = blockIdx.y;
-    const int c = (int)(plane % C);
-    const float scale = coef[c], mu = coef[C + c], b = Elem<PT>::load1(beta + c);
-    const int64_t seg0 = (int64_t)blockIdx.x * kBnSeg;
-    const bool full = blockIdx.x + 1 < gridDim.x || HW % kBnSeg == 0;  // every segment but a ragged last one
-    const int64_t len = full ? (int64_t)kBnSeg : HW - seg0;
-    const XT *xp = x + plane * HW + seg0;
-    YT *yp = y + plane * HW + seg0;
-    if (VEC && full) {
-        // full segment (uniform): straight-line code; with bounds tests the compiler puts a full
-        // wait in front of every store, so each store waits for the one before it
-        uint4_t raw[kPerThread / E];
+    __shared__ double red[4];
+    const int s = blockIdx.x, c = blockIdx.y;
+    const BnItems<XT, NJ, RAG> items(g, c, s);
+    const XT *xp = x + items.base;
+    YT *yp = y + items.base;
+    uint4_t raw[NJ];
 #pragma unroll
-        for (int j = 0; j < kPerThread / E; ++j)
-            raw[j] = __builtin_nontemporal_load(reinterpret_cast<const uint4_t *>(xp + ((int64_t)j * 256 + threadIdx.x) * E));
-#pragma unroll
-        for (int j = 0; j < kPerThread / E; ++j) {
-            float v[E], o[E];
-            Elem<XT>::unpack(raw[j], v);
-#pragma unroll
-            for (int e = 0; e < E; ++e) o[e] = __builtin_fmaf(v[e] - mu, scale, b);
-            store_chunk<YT, E>(yp + ((int64_t)j * 256 + threadIdx.x) * E, o);
-        }
-    } else if (VEC) {
-        uint4_t raw[kPerThread / E];
-#pragma unroll
-        for (int j = 0; j < kPerThread / E; ++j) {
-            const int64_t e0 = ((int64_t)j * 256 + threadIdx.x) * E;
-            if (e0 < len) raw[j] = __builtin_nontemporal_load(reinterpret_cast<const uint4_t *>(xp + e0));
-        }
-#pragma unroll
-        for (int j = 0; j < kPerThread / E; ++j) {
-            const int64_t e0 = ((int64_t)j * 256 + threadIdx.x) * E;
-            if (e0 < len) {
-                float v[E], o[E];
-                Elem<XT>::unpack(raw[j], v);
-#pragma unroll
-                for (int e = 0; e < E; ++e) o[e] = __builtin_fmaf(v[e] - mu, scale, b);
-                store_chunk<YT, E>(yp + e0, o);
-            }
+    for (int j = 0; j < NJ; ++j) {
+        int dup;
+        raw[j] = load_chunk_nt<RAG>(xp + items.at(j, dup));
+    }
+    float scale, mu;
+    const float b = Elem<PT>::load1(beta + c);
+    if constexpr (STATS) {  // (while the loads fly)
+        float rstd;
+        bn_channel_stats(partial, c, g, eps, red, mu, rstd);
+        scale = rstd * Elem<PT>::load1(gamma + c);
+        if (s == 0 && threadIdx.x == 0) {
+            if (mean_out) mean_out[c] = mu;
+            if (rstd_out) rstd_out[c] = rstd;
         }
     } else {
-        for (int64_t e0 = threadIdx.x; e0 < len; e0 += 256)
-            Elem<YT>::store1(yp + e0, __builtin_fmaf(Elem<XT>::load1(xp + e0) - mu, scale, b));
+        scale = coef[c];
+        mu = coef[g.C + c];
     }
+    auto write = [&](auto masked) {
+#pragma unroll
+        for (int j = 0; j < NJ; ++j) {
+            int dup;
+            const int64_t o = items.at(j, dup);
+            float v[E], r[E];
+            Elem<XT>::unpack(raw[j], v);
+#pragma unroll
+            for (int e = 0; e < E; ++e) r[e] = __builtin_fmaf(v[e] - mu, scale, b);
+            if constexpr (!decltype(masked)::value) {
+                store_row_chunk<RAG, YT, E>(yp + o, r);
+            } else if (items.valid(j)) {
+                // (y may be x: the elements shared with the chunk before may have been overwritten when this one was read,
+                // so only that chunk writes them)
+                if (!RAG || dup == 0) {
+                    store_row_chunk<RAG, YT, E>(yp + o, r);
+                } else {
+#pragma unroll
+                    for (int e = 1; e < E; ++e)
+                        if (e >= dup) Elem<YT>::store1(yp + o + e, r[e]);
+                }
+            }
+        }
+    };
+    // full segment (uniform): straight-line code; with bounds tests the compiler puts a full
+    // wait in front of every store, so each store waits for the one before it
+    if (!RAG && items.all()) write(std::false_type{});
+    else write(std::true_type{});
+}
+
+// Planes of fewer elements than a chunk of 16 bytes: a workgroup per channel, an element at a time, sums in double.
+template <typename XT, typename PT, typename YT>
+__global__ __launch_bounds__(256) void bn_small_kernel(const XT *__restrict__ x, const PT *__restrict__ gamma,
+                                                       const PT *__restrict__ beta, YT *__restrict__ y,
+                                                       float *__restrict__ mean_out, float *__restrict__ rstd_out, int HW, int C,
+                                                       int N, float eps)
+{
+    __shared__ double red[4];
+    const int c = blockIdx.x, total = N * HW;
+    auto at = [&](int i) { return ((int64_t)(i / HW) * C + c) * HW + i % HW; };
+    double sum = 0.0, sq = 0.0;
+    for (int i = threadIdx.x; i < total; i += 256) sum += (double)Elem<XT>::load1(x + at(i));
+    const double mean = bn_block_sum_f64(sum, red) / total;
+    for (int i = threadIdx.x; i < total; i += 256) {
+        const double d = (double)Elem<XT>::load1(x + at(i)) - mean;
+        sq += d * d;
+    }
+    const float mu = (float)mean, rstd = (float)(1.0 / sqrt(bn_block_sum_f64(sq, red) / total + (double)eps));
+    const float scale = rstd * Elem<PT>::load1(gamma + c), b = Elem<PT>::load1(beta + c);
+    if (threadIdx.x == 0) {
+        if (mean_out) mean_out[c] = mu;
+        if (rstd_out) rstd_out[c] = rstd;
+    }
+    for (int i = threadIdx.x; i < total; i += 256)
+        Elem<YT>::store1(y + at(i), __builtin_fmaf(Elem<XT>::load1(x + at(i)) - mu, scale, b));
 }
 
 struct BnArgs {
@@ -211,26 +307,62 @@ struct BnArgs {
     hipStream_t st;
 };
 
+// Where a channel is cut: whole segments of 16384 elements from planes of more than half of that; smaller planes in
+// groups, as many to a segment as leave about 1024 workgroups (32x256x7x7 fp32 in one workgroup per plane took 38 us).
+static BnGeom bn_geom(const BnArgs &a, int E)
+{
+    BnGeom g{a.HW, (int)a.C, (int)a.N, (a.HW + E - 1) / E, 0, 1, 0, 0};
+    if (a.HW > kBnSeg / 2) {
+        g.spp = (int)((a.HW + kBnSeg - 1) / kBnSeg);
+        g.segs = g.N * g.spp;
+    } else {
+        int64_t most = (kBnSeg / E) / g.cpp, want = a.N * a.C / 1024;
+        if (want > most) want = most;
+        if (want > a.N) want = a.N;
+        g.G = want < 1 ? 1 : (int)want;
+        g.segs = (g.N + g.G - 1) / g.G;
+        g.m_cpp = g.cpp <= 1 ? 0xFFFFFFFFu : (uint32_t)((1ull << 32) / (uint64_t)g.cpp);
+    }
+    return g;
+}
+
+template <typename XT, typename PT, typename YT, int NJ, bool RAG>
+static void launch_bn_nj(const BnArgs &a, const BnGeom &g)
+{
+    float *partial = a.ws, *coef = a.ws + (int64_t)3 * a.C * g.segs;
+    const dim3 grid((unsigned)g.segs, (unsigned)a.C);
+    hipLaunchKernelGGL((bn_partial_kernel<XT, NJ, RAG>), grid, dim3(256), 0, a.st, (const XT *)a.x, partial, g);
+    const bool fuse = g.segs <= kBnFuseSegs;
+    if (!fuse)
+        hipLaunchKernelGGL((bn_finalize_kernel<PT>), dim3((unsigned)a.C), dim3(256), 0, a.st, partial, (const PT *)a.gamma, coef,
+                           a.mean_out, a.rstd_out, g, a.eps);
+    auto kern = fuse ? bn_apply_kernel<XT, PT, YT, NJ, RAG, true> : bn_apply_kernel<XT, PT, YT, NJ, RAG, false>;
+    hipLaunchKernelGGL(kern, grid, dim3(256), 0, a.st, (const XT *)a.x, (const PT *)a.gamma, (const PT *)a.beta, partial, coef,
+                       (YT *)a.y, a.mean_out, a.rstd_out, g, a.eps);
+}
+
 template <typename XT, typename PT, typename YT>
 static void launch_bn(const BnArgs &a, bool vec)
 {
-    const int segs = (int)((a.HW + kBnSeg - 1) / kBnSeg);
-    const dim3 grid((unsigned)segs, (unsigned)(a.N * a.C));
-    float *partial = a.ws, *coef = a.ws + (int64_t)3 * a.C * a.N * segs;
-    if (vec)
-        hipLaunchKernelGGL((bn_partial_kernel<XT, true>), grid, dim3(256), 0, a.st, (const XT *)a.x, partial, a.HW,
-                           (int)a.C, segs);
-    else
-        hipLaunchKernelGGL((bn_partial_kernel<XT, false>), grid, dim3(256), 0, a.st, (const XT *)a.x, partial, a.HW,
-                           (int)a.C, segs);
-    hipLaunchKernelGGL((bn_finalize_kernel<PT>), dim3((unsigned)a.C), dim3(256), 0, a.st, partial, (const PT *)a.gamma,
-                       coef, a.mean_out, a.rstd_out, a.HW, (int)a.C, (int)a.N, segs, a.eps);
-    if (vec)
-        hipLaunchKernelGGL((bn_apply_kernel<XT, PT, YT, true>), grid, dim3(256), 0, a.st, (const XT *)a.x,
-                           (const PT *)a.beta, coef, (YT *)a.y, a.HW, (int)a.C);
-    else
-        hipLaunchKernelGGL((bn_apply_kernel<XT, PT, YT, false>), grid, dim3(256), 0, a.st, (const XT *)a.x,
-                           (const PT *)a.beta, coef, (YT *)a.y, a.HW, (int)a.C);
+    constexpr int E = Elem<XT>::kPerChunk;
+    if (a.HW < E) {
+        hipLaunchKernelGGL((bn_small_kernel<XT, PT, YT>), dim3((unsigned)a.C), dim3(256), 0, a.st, (const XT *)a.x,
+                           (const PT *)a.gamma, (const PT *)a.beta, (YT *)a.y, a.mean_out, a.rstd_out, (int)a.HW, (int)a.C,
+                           (int)a.N, a.eps);
+        return;
+    }
+    const BnGeom g = bn_geom(a, E);
+    const int64_t items = g.G ? g.G * g.cpp : g.cpp < kBnSeg / E ? g.cpp : kBnSeg / E, slots = (items + 255) / 256;
+    auto go = [&](auto nj) {
+        constexpr int NJ = decltype(nj)::value;
+        if (vec) launch_bn_nj<XT, PT, YT, NJ, false>(a, g);
+        else launch_bn_nj<XT, PT, YT, NJ, true>(a, g);
+    };
+    if (slots <= 1) go(std::integral_constant<int, 1>{});
+    else if (slots <= 2) go(std::integral_constant<int, 2>{});
+    else if (slots <= 4) go(std::integral_constant<int, 4>{});
+    else if (slots <= 8) go(std::integral_constant<int, 8>{});
+    else if constexpr (E == 4) go(std::integral_constant<int, 16>{});
 }
 
 template <typename XT, typename PT>

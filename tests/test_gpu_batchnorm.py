@@ -89,3 +89,17 @@ def test_deterministic():
     a = _run(x, np.ones(6, np.float32), np.zeros(6, np.float32), 1e-5, False, False, False)
     b = _run(x, np.ones(6, np.float32), np.zeros(6, np.float32), 1e-5, False, False, False)
     assert all(np.array_equal(u, v) for u, v in zip(a, b))
+
+
+@pytest.mark.parametrize("N,C,H,W", [
+    (5, 3, 1, 3), (9, 4, 1, 5),              # planes shorter than 16 bytes (both types, bf16 only)
+    (7, 700, 5, 7), (40, 30, 13, 13),        # planes grouped to a segment, a shorter last group, odd planes
+    (6, 512, 16, 16), (3, 4, 90, 91),        # ... whole aligned chunks; one plane to a segment
+    (3, 4, 1, 8193), (2, 3, 1, 16387), (2, 2, 1, 49152),   # split planes: a ragged last segment, one of 3 elements, whole ones
+    (1, 2, 2100, 2000),                      # more than 256 segments per channel: merged by a kernel of their own
+])
+def test_segment_edges(N, C, H, W):
+    _check(N, C, H, W, inplace=True)
+    _check(N, C, H, W, x_bf16=True, y_bf16=True, inplace=True)
+    _check(N, C, H, W, x_bf16=True, p_bf16=True)
+    _check(N, C, H, W, y_bf16=True)
