@@ -14,6 +14,7 @@
 #include "row_io.h"
 #include "wide_rows.h"
 #include "host_utils.h"
+#include <type_traits>
 
 namespace perf {
 
@@ -192,9 +193,10 @@ static void launch_rms_p(RmsArgs &a, bool vec_ok, int p_dt, int y_dt)
 }
 
 // ---- means ---------------------------------------------------------------------------
-// Mean of every row: a wavefront per row; 16-byte loads when VEC (cols, ldx and x suitably
-// aligned), else element loads.
-template <typename XT, typename YT, bool VEC>
+// Mean of every row: a wavefront per row; 16-byte loads, at the elements' own alignment unless ALIGNED, and the few
+// elements that fill no chunk one by one.
+// ELEMENTS: short unaligned rows, element loads only (40000 x 129 bf16: 6.6 us, 10.8 with chunks that leave most lanes idle).
+template <typename XT, typename YT, bool ALIGNED, bool ELEMENTS = false>
 __global__ __launch_bounds__(256) void rowmean_kernel(const XT *__restrict__ x, YT *__restrict__ y, int64_t rows,
                                                       int64_t cols, int64_t ldx)
 {
@@ -205,14 +207,16 @@ __global__ __launch_bounds__(256) void rowmean_kernel(const XT *__restrict__ x, 
     for (int64_t r = wave; r < rows; r += nwaves) {
         const XT *xr = x + r * ldx;
         float s0 = 0.f, s1 = 0.f;
-        if (VEC) {
+        if constexpr (ELEMENTS) {
+            for (int64_t c = lane; c < cols; c += 64) s0 += Elem<XT>::load1(xr + c);
+        } else {
             const int64_t nch = cols / E;
             int64_t c = lane;
             constexpr int kU = 8;  // eight independent 16-byte loads in flight per lane (8 KiB per wave)
             for (; c + 64 * (kU - 1) < nch; c += 64 * kU) {
                 uint4_t raw[kU];
 #pragma unroll
-                for (int u = 0; u < kU; ++u) raw[u] = __builtin_nontemporal_load(reinterpret_cast<const uint4_t *>(xr) + c + 64 * u);
+                for (int u = 0; u < kU; ++u) raw[u] = load_chunk_nt<!ALIGNED>(xr + (c + 64 * u) * E);
 #pragma unroll
                 for (int u = 0; u < kU; ++u) {
                     float v[E];
@@ -225,8 +229,8 @@ __global__ __launch_bounds__(256) void rowmean_kernel(const XT *__restrict__ x, 
                 }
             }
             for (; c + 64 < nch; c += 128) {  // two at a time
-                const uint4_t r0 = __builtin_nontemporal_load(reinterpret_cast<const uint4_t *>(xr) + c);
-                const uint4_t r1 = __builtin_nontemporal_load(reinterpret_cast<const uint4_t *>(xr) + c + 64);
+                const uint4_t r0 = load_chunk_nt<!ALIGNED>(xr + c * E);
+                const uint4_t r1 = load_chunk_nt<!ALIGNED>(xr + (c + 64) * E);
                 float v0[E], v1[E];
                 Elem<XT>::unpack(r0, v0);
                 Elem<XT>::unpack(r1, v1);
@@ -238,12 +242,11 @@ __global__ __launch_bounds__(256) void rowmean_kernel(const XT *__restrict__ x, 
             }
             if (c < nch) {
                 float v0[E];
-                Elem<XT>::unpack(__builtin_nontemporal_load(reinterpret_cast<const uint4_t *>(xr) + c), v0);
+                Elem<XT>::unpack(load_chunk_nt<!ALIGNED>(xr + c * E), v0);
 #pragma unroll
                 for (int e = 0; e < E; ++e) s0 += v0[e];
             }
-        } else {
-            for (int64_t c = lane; c < cols; c += 64) s0 += Elem<XT>::load1(xr + c);
+            if (!ALIGNED && nch * E + lane < cols) s1 += Elem<XT>::load1(xr + nch * E + lane);
         }
         const float s = wave_allreduce(s0 + s1, OpSum{});
         if (lane == 0) Elem<YT>::store1(y + r, s / (float)cols);
@@ -256,7 +259,8 @@ __global__ __launch_bounds__(256) void rowmean_kernel(const XT *__restrict__ x, 
 // workgroups share each line, and the group index is remapped so that they run on the same
 // XCD (workgroup ids are dealt round-robin to the 8 XCDs, whose L2s are private: without the
 // remap both XCDs fetch the line from memory).
-template <typename XT, typename YT, int CW, int THREADS>
+// RAG: columns that are no whole aligned chunks (row_io.h), at least one chunk of them.
+template <typename XT, typename YT, int CW, int THREADS, bool RAG = false>
 __global__ __launch_bounds__(THREADS) void colmean_kernel(const XT *__restrict__ x, YT *__restrict__ y, int64_t rows,
                                                           int64_t cols, int64_t ldx)
 {
@@ -271,14 +275,13 @@ __global__ __launch_bounds__(THREADS) void colmean_kernel(const XT *__restrict__
     float acc[E];
 #pragma unroll
     for (int e = 0; e < E; ++e) acc[e] = 0.f;
-    if (col0 < cols) {  // cols is a multiple of E
-        const XT *xc = x + col0;
+    if (col0 < cols) {  // (a chunk is entirely valid or not)
+        const XT *xc = x + (RAG ? min(col0, cols - E) : col0);
         int64_t r = rl;
         for (; r + kRowLanes * (kUnroll - 1) < rows; r += kRowLanes * kUnroll) {
             uint4_t raw[kUnroll];
 #pragma unroll
-            for (int u = 0; u < kUnroll; ++u)
-                raw[u] = __builtin_nontemporal_load(reinterpret_cast<const uint4_t *>(xc + (r + kRowLanes * u) * ldx));
+            for (int u = 0; u < kUnroll; ++u) raw[u] = load_chunk_nt<RAG>(xc + (r + kRowLanes * u) * ldx);
 #pragma unroll
             for (int u = 0; u < kUnroll; ++u) {
                 float v[E];
@@ -289,7 +292,7 @@ __global__ __launch_bounds__(THREADS) void colmean_kernel(const XT *__restrict__
         }
         for (; r < rows; r += kRowLanes) {
             float v[E];
-            Elem<XT>::unpack(__builtin_nontemporal_load(reinterpret_cast<const uint4_t *>(xc + r * ldx)), v);
+            Elem<XT>::unpack(load_chunk_nt<RAG>(xc + r * ldx), v);
 #pragma unroll
             for (int e = 0; e < E; ++e) acc[e] += v[e];
         }
@@ -315,8 +318,11 @@ __global__ __launch_bounds__(THREADS) void colmean_kernel(const XT *__restrict__
     }
     __syncthreads();
     if (threadIdx.x < kCols) {
-        const int64_t c = group * kCols + threadIdx.x;
-        if (c < cols) Elem<YT>::store1(y + c, part[0][threadIdx.x] / (float)rows);
+        // (element e of a chunk that would overhang the columns is column cols - E + e; those that the chunk before has as well
+        // are written by that one)
+        const int64_t first = group * kCols + threadIdx.x / E * E, start = RAG ? min(first, cols - E) : first;
+        const int64_t c = start + threadIdx.x % E;
+        if (first < cols && c >= first) Elem<YT>::store1(y + c, part[0][threadIdx.x] / (float)rows);
     }
 }
 
@@ -340,7 +346,8 @@ static void launch_mean(const void *x, void *y, int64_t rows, int64_t cols, int6
     if (axis == 1) {
         int64_t blocks = (rows + 3) / 4;
         if (blocks > 256 * 64) blocks = 256 * 64;
-        auto kern = vec ? rowmean_kernel<XT, YT, true> : rowmean_kernel<XT, YT, false>;
+        auto kern = vec ? rowmean_kernel<XT, YT, true>
+                    : cols < 128 * E ? rowmean_kernel<XT, YT, false, true> : rowmean_kernel<XT, YT, false>;
         hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(256), 0, st, (const XT *)x, (YT *)y, rows, cols, ldx);
     } else if (vec) {
         // whole 128-byte lines per workgroup when that still gives every CU a workgroup
@@ -354,6 +361,16 @@ static void launch_mean(const void *x, void *y, int64_t rows, int64_t cols, int6
         else
             hipLaunchKernelGGL((colmean_kernel<XT, YT, 4, 256>), dim3((unsigned)((cols + 4 * E - 1) / (4 * E))), dim3(256),
                                0, st, (const XT *)x, (YT *)y, rows, cols, ldx);
+    } else if (cols >= E) {
+        // (a thread per column, all rows in turn, took 12.4 ms on 51480 x 777 fp32: 168 us; narrower groups where there are few:
+        // 9000 x 2222 bf16 36 us against 40, but 5000 x 4001 fp32 55 against 37)
+        auto go = [&](auto cw) {
+            constexpr int CW = decltype(cw)::value;
+            hipLaunchKernelGGL((colmean_kernel<XT, YT, CW, 256, true>), dim3((unsigned)((cols + CW * E - 1) / (CW * E))), dim3(256), 0,
+                               st, (const XT *)x, (YT *)y, rows, cols, ldx);
+        };
+        if (cols >= 128 * 4 * E) go(std::integral_constant<int, 4>{});
+        else go(std::integral_constant<int, 2>{});
     } else {
         hipLaunchKernelGGL((colmean_scalar_kernel<XT, YT>), dim3((unsigned)((cols + 255) / 256)), dim3(256), 0, st,
                            (const XT *)x, (YT *)y, rows, cols, ldx);
@@ -485,39 +502,43 @@ template <int OP> __device__ __forceinline__ float apply_op(float a, float b)
 
 constexpr int kEltUnroll = 4;
 
-template <int OP, typename T>
+// n elements in nvec whole vectors, and the rest one by one by the last workgroup; ALIGNED: 16-byte aligned operands.
+template <int OP, typename T, bool ALIGNED>
 __global__ __launch_bounds__(256) void eltwise_kernel(const T *__restrict__ a, const T *__restrict__ b, T *__restrict__ y,
-                                                      int64_t nvec)
+                                                      int64_t nvec, int64_t n)
 {
     constexpr int E = Elem<T>::kPerChunk;
     const int64_t block0 = (int64_t)blockIdx.x * 256 * kEltUnroll;
     const int64_t base = block0 + threadIdx.x;
-    const uint4_t *av = reinterpret_cast<const uint4_t *>(a), *bv = reinterpret_cast<const uint4_t *>(b);
+    auto av = [&](int64_t i) { return load_chunk_nt<!ALIGNED>(a + i * E); };
+    auto bv = [&](int64_t i) { return OP != PERF_RELU ? load_chunk_nt<!ALIGNED>(b + i * E) : uint4_t{0u, 0u, 0u, 0u}; };
     auto combine = [&](const uint4_t &xa, const uint4_t &xb, int64_t i) {
         float va[E], vb[E], o[E];
         Elem<T>::unpack(xa, va);
         if (OP != PERF_RELU) Elem<T>::unpack(xb, vb);
 #pragma unroll
         for (int e = 0; e < E; ++e) o[e] = apply_op<OP>(va[e], OP != PERF_RELU ? vb[e] : 0.f);
-        store_chunk<T, E>(y + i * E, o);
+        store_row_chunk<!ALIGNED, T, E>(y + i * E, o);
     };
+    if (blockIdx.x == gridDim.x - 1 && nvec * E + threadIdx.x < n) {  // (fewer than E elements)
+        const int64_t i = nvec * E + threadIdx.x;
+        Elem<T>::store1(y + i, apply_op<OP>(Elem<T>::load1(a + i), OP != PERF_RELU ? Elem<T>::load1(b + i) : 0.f));
+    }
     if (block0 + 256 * kEltUnroll <= nvec) {
         // whole block in range (uniform): straight-line loads, all in flight together.  (With a
         // bounds test around each load the compiler waits for one load before it issues the next.)
         uint4_t ra[kEltUnroll], rb[kEltUnroll];
 #pragma unroll
         for (int u = 0; u < kEltUnroll; ++u) {
-            ra[u] = __builtin_nontemporal_load(av + base + u * 256);
-            rb[u] = OP != PERF_RELU ? __builtin_nontemporal_load(bv + base + u * 256) : uint4_t{0u, 0u, 0u, 0u};
+            ra[u] = av(base + u * 256);
+            rb[u] = bv(base + u * 256);
         }
 #pragma unroll
         for (int u = 0; u < kEltUnroll; ++u) combine(ra[u], rb[u], base + u * 256);
     } else {
         for (int u = 0; u < kEltUnroll; ++u) {
             const int64_t i = base + u * 256;
-            if (i < nvec)
-                combine(__builtin_nontemporal_load(av + i),
-                        OP != PERF_RELU ? __builtin_nontemporal_load(bv + i) : uint4_t{0u, 0u, 0u, 0u}, i);
+            if (i < nvec) combine(av(i), bv(i), i);
         }
     }
 }
@@ -535,19 +556,17 @@ static perf_status launch_eltwise(const void *a, const void *b, void *y, int64_t
 {
     constexpr int E = Elem<T>::kPerChunk;
     const bool vec = aligned(a, 16) && aligned(y, 16) && (OP == PERF_RELU || aligned(b, 16));
-    const int64_t nvec = vec ? n / E : 0;
-    if (nvec > 0) {
-        const int64_t blocks = (nvec + 256 * kEltUnroll - 1) / (256 * kEltUnroll);
-        if (blocks > kMaxGridX) return PERF_ERR_UNSUPPORTED;
-        hipLaunchKernelGGL((eltwise_kernel<OP, T>), dim3((unsigned)blocks), dim3(256), 0, st, (const T *)a, (const T *)b,
-                           (T *)y, nvec);
+    if (!vec && n > (int64_t(1) << 20) * 64) return PERF_ERR_UNSUPPORTED;  // unaligned bulk: not a streaming case
+    const int64_t nvec = n / E;
+    if (nvec == 0) {
+        hipLaunchKernelGGL((eltwise_tail_kernel<OP, T>), dim3(1), dim3(64), 0, st, (const T *)a,
+                           OP != PERF_RELU ? (const T *)b : (const T *)a, (T *)y, n);
+        return launch_status();
     }
-    const int64_t done = nvec * E;
-    if (done < n) {
-        if (n - done > (int64_t(1) << 20) * 64) return PERF_ERR_UNSUPPORTED;  // unaligned bulk: not a streaming case
-        hipLaunchKernelGGL((eltwise_tail_kernel<OP, T>), dim3(1), dim3(64), 0, st, (const T *)a + done,
-                           OP != PERF_RELU ? (const T *)b + done : (const T *)a, (T *)y + done, n - done);
-    }
+    const int64_t blocks = (nvec + 256 * kEltUnroll - 1) / (256 * kEltUnroll);
+    if (blocks > kMaxGridX) return PERF_ERR_UNSUPPORTED;
+    auto kern = vec ? eltwise_kernel<OP, T, true> : eltwise_kernel<OP, T, false>;
+    hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(256), 0, st, (const T *)a, (const T *)b, (T *)y, nvec, n);
     return launch_status();
 }
 

@@ -309,3 +309,45 @@ def test_copy_any_alignment_and_size():
     torch.cuda.synchronize()
     assert time.perf_counter() - t0 < 0.5
     assert torch.equal(out[2:2 + (64 << 20)], big[1:1 + (64 << 20)])
+
+
+@pytest.mark.parametrize("rows,cols,ldx", [(513, 7, 7), (1000, 777, 777), (70, 129, 131), (9000, 9, 9), (40, 12345, 12345),
+                                           (300, 64, 67), (3, 2, 2), (2500, 255, 256)])
+@pytest.mark.parametrize("x_bf16", [False, True])
+@pytest.mark.parametrize("axis", [0, 1])
+def test_reduce_mean_ragged(rows, cols, ldx, x_bf16, axis):
+    # columns that are no whole aligned chunks: overhanging chunks, single elements, odd strides; with a workspace (none is
+    # needed) and without
+    g = np.random.default_rng(rows + cols)
+    x = (g.standard_normal((rows, cols)) * 2 + 0.5).astype(np.float32)
+    xs = rng.f32_to_bf16_bits(x) if x_bf16 else x
+    ref = oracle.reduce_mean(oracle.widen(xs, x_bf16), axis)
+    floor = np.sqrt(np.mean(x.astype(np.float64) ** 2))
+    for ws in (False, True):
+        y = _run_mean(xs, axis, x_bf16, False, ldx=ldx, ws=ws)
+        assert np.max(np.abs(y - ref) / np.maximum(np.abs(ref), floor)) <= 1e-5
+
+
+@pytest.mark.parametrize("op", [perf.PERF_ADD, perf.PERF_MUL, perf.PERF_RELU])
+@pytest.mark.parametrize("n", [1, 3, 4, 7, 1023, 4096, 4099, 8203, 100001])
+@pytest.mark.parametrize("offset", [0, 1])
+@pytest.mark.parametrize("bf16", [False, True])
+def test_eltwise_ragged(op, n, offset, bf16):
+    # lengths that are no whole vectors or blocks, and buffers that are only element-aligned; in place as well
+    g = np.random.default_rng(n)
+    a, b = g.standard_normal(n + offset).astype(np.float32), g.standard_normal(n + offset).astype(np.float32)
+    if bf16:
+        a, b = rng.f32_to_bf16_bits(a), rng.f32_to_bf16_bits(b)
+    size = 2 if bf16 else 4
+    af, bf = oracle.widen(a, bf16)[offset:], oracle.widen(b, bf16)[offset:]
+    ref = (af + bf if op == perf.PERF_ADD else af * bf if op == perf.PERF_MUL else np.maximum(af, 0.0))
+    want = oracle.round_bf16(ref) if bf16 else ref.astype(np.float32)
+    for inplace in (False, True):
+        ad, bd = G.dev(a), G.dev(b)
+        yd = ad if inplace else torch.zeros_like(ad)
+        perf.perf_eltwise(op, ad.data_ptr() + size * offset, bd.data_ptr() + size * offset, yd.data_ptr() + size * offset, n,
+                          G.dt(bf16), G.stream())
+        torch.cuda.synchronize()
+        got = G.host(yd, bf16)
+        assert np.array_equal(got[offset:], want)
+        assert np.array_equal(got[:offset], a[:offset] if inplace else np.zeros_like(a[:offset]))
