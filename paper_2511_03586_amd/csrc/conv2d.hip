@@ -1699,10 +1699,15 @@ static perf_status conv2d_impl(const void *x, const void *w, void *y, int64_t N,
     // staged implicit GEMM: worth it from 32 output channels on (a 64-wide tile is then at least half used); bf16 with
     // fewer than 8 channels loads element by element there (8x224x224x3->64 62 us against 34 a filter row at a time)
     const bool staged_ok = K >= 32 && (xw_dt == PERF_F32 || (C >= 8 && R * S * C >= 16));
-    // a filter of one tap on every pixel is a plain GEMM (32x28x28 256->256 bf16: 12.1 us as a convolution)
+    // a filter of one tap on every pixel is a plain GEMM (32x28x28 256->256 bf16: 12.1 us as a convolution, 9.9 so; where
+    // the GEMM would not take tiles of 128 x 128 either, the convolution kernel stays: 5x17x97 256->128 7.7 us against 8.0)
+    const int64_t tiles128 = ((N * P * Q + 127) / 128) * ((K + 127) / 128);
     if (variant == kConvAuto && R == 1 && S == 1 && stride_h == 1 && stride_w == 1 && pad_h == 0 && pad_w == 0 && K >= 16 &&
-        C >= 8 && K <= 64 * kMaxGridYZ && !(xw_dt == PERF_F32 && y_dt == PERF_BF16))
+        C >= 8 && K <= 64 * kMaxGridYZ && !(xw_dt == PERF_F32 && y_dt == PERF_BF16) && (!mfma_ok || tiles128 >= 192))
         return perf_gemm(x, w, y, N * P * Q, K, C, PERF_ROW_MAJOR, C, PERF_COL_MAJOR, C, K, 1, 0, 0, 0, 1.0f, xw_dt, y_dt, stream);
+    // few tiles with a long reduction: the staged kernel's wave groups share it (8x28x28 256->128 12.8 us against 16.5 on the
+    // shared main loop, 20x20 256->256 12.2 against 16.1, 14x14 128->64 with 5x5 taps about even at 1600)
+    const bool few_long = mfma_ok && staged_ok && R * S * C >= 1600 && ((N * P * Q + 63) / 64) * ((K + 63) / 64) <= 256;
     if (variant == kConvAuto)
         // (the channel-blocked kernel has one thread per pixel: below ~64 workgroups of pixels the
         // thread-per-output kernel has more parallelism and measured faster)
@@ -1713,7 +1718,7 @@ static perf_status conv2d_impl(const void *x, const void *w, void *y, int64_t N,
         variant = wsplit_ok                     ? kConvWsplit
                   : (wres_ok && wres_rounds <= 2) ? kConvWres
                   : wreg_ok                     ? kConvWreg
-                  : mfma_ok ? kConvMfma
+                  : (mfma_ok && !few_long)      ? kConvMfma
                   : staged_ok ? kConvStaged
                   : (rowmfma_ok && N * P * Q >= 16384)          ? kConvRowMfma
                   : (C < 32 && smallc_ok && N * P * Q >= 16384) ? kConvSmallC

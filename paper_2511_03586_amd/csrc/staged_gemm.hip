@@ -61,14 +61,15 @@ static int64_t tiles_of(const GemmArgs &g, int64_t bm, int64_t bn) { return ((g.
 //   * 256 x 256 (8 waves of 128 x 64; 128 KiB of LDS) for a chip full of them and a reduction long enough to pay
 //     for its start: 2999x5003x2048 72 against 80 with 128 x 128; 120 x (125x357x112) 14.7 against 12.8 without it.
 //   * 128 x 128 (4 waves, two workgroups per CU) from 192 such tiles on: 952x3562x489 13.6 against 17.4 with 64 x 64.
-//   * 64 x 64, four register sets of loads in flight; with few tiles and a long reduction instead four groups of waves
-//     that share the K-steps: 984x632x2137 15.1 against 16.2, 3320x41x3541 22 against 40; 245x552x520 9.8 against 8.2.
+//   * 64 x 64, four register sets of loads in flight; with few tiles and a long reduction instead two groups of waves
+//     that share the K-steps: 336x640x1000 7.8 against 9.2 (8.7 with four groups), 256x256x4096 16.2 against 20.4 (16.3),
+//     512x512x512 even.
 template <typename CT>
 static perf_status launch_bf16(const GemmArgs &g, bool big_ok)
 {
     if (big_ok && g.K >= 512 && tiles_of(g, 256, 256) >= 192) return launch_layouts<uint16_t, CT, 4, 2, 2, 4, 1, 1>(g);
     if (big_ok && tiles_of(g, 128, 128) >= 192) return launch_layouts<uint16_t, CT, 2, 2, 2, 2, 1, 2>(g);
-    if (g.K >= 640 && tiles_of(g, 64, 64) <= 256) return launch_layouts<uint16_t, CT, 1, 1, 2, 2, 4, 2>(g);
+    if (g.K >= 512 && tiles_of(g, 64, 64) <= 256) return launch_layouts<uint16_t, CT, 1, 1, 2, 2, 2, 2>(g);
     return launch_layouts<uint16_t, CT, 1, 1, 2, 2, 1, 4>(g);
 }
 
