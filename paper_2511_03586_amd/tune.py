@@ -43,7 +43,7 @@ CONV_AXES = {"variant": (perf.CONV_WRES, perf.CONV_WREG, perf.CONV_WSPLIT, perf.
                          perf.CONV_SMALLC, perf.CONV_DIRECT)}
 CONV_NAMES = {perf.CONV_WRES: "weights-in-regs, input-in-lds", perf.CONV_WREG: "weights-in-registers",
               perf.CONV_WSPLIT: "weights-in-regs, 64-channel slabs",
-              perf.CONV_MFMA: "implicit-gemm", perf.CONV_F32MFMA: "implicit-gemm-fp32-mfma", perf.CONV_ROWMFMA: "filter-row-per-mfma",
+              perf.CONV_MFMA: "implicit-gemm", perf.CONV_F32MFMA: "implicit-gemm-through-registers", perf.CONV_ROWMFMA: "filter-row-per-mfma",
               perf.CONV_SMALLC: "channel-blocked-direct", perf.CONV_DIRECT: "thread-per-output"}
 # grid_per_cu: workgroups per CU of a persistent grid; 0 = the kernel family's own default
 SOFTMAX_AXES = {"waves_per_row": (1, 4, 16), "rows_per_wave": (0, 1, 2, 4, 8), "grid_per_cu": (0, 2, 4, 8, 16)}
@@ -60,13 +60,17 @@ def _time(launch, nsets, iters, warmup):
     with torch.cuda.graph(graph):
         for i in range(iters):
             launch((warmup + i) % nsets)
-    graph.replay()
-    e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
-    e0.record()
-    graph.replay()
-    e1.record()
-    torch.cuda.synchronize()
-    return e0.elapsed_time(e1) / iters * 1e3
+    for _ in range(3):  # (validation on the host leaves the GPU idle, and its clock low)
+        graph.replay()
+    best = float("inf")
+    for _ in range(5):  # the shortest: a replay's own start is a few microseconds that vary
+        e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        e0.record()
+        graph.replay()
+        e1.record()
+        torch.cuda.synchronize()
+        best = min(best, e0.elapsed_time(e1))
+    return best / iters * 1e3
 
 
 def _rotating_sets(bytes_per_set, at_least=2, budget=512 << 20):
