@@ -168,12 +168,14 @@ __global__ __launch_bounds__(THREADS) void softmax_wgrow_kernel(const float *__r
         for (int j = 0; j < NV; ++j) {
             const int c = 4 * (j * THREADS + tid);
             const bool valid = j * THREADS + tid < n4;
+            float part = 0.f;  // a sum per vector first: shorter chains of roundings in a long row
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
                 const float t = exp_scaled(cur[j][e] - m, k.c_hi, k.c_lo);
                 cur[j][e] = valid ? t : 0.f;
-                z += !RAG || e >= c - vec_start<RAG>(c, cols) ? cur[j][e] : 0.f;
+                part += !RAG || e >= c - vec_start<RAG>(c, cols) ? cur[j][e] : 0.f;
             }
+            z += part;
         }
         const float inv = 1.0f / block_reduce_sum<THREADS>(z, red);
         float *yr = y + r * ldy;
