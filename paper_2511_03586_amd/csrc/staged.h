@@ -555,8 +555,9 @@ __global__ __launch_bounds__(64 * WM * WN * KG, (StagedShape<T, TM, TN, WM, WN, 
     const int wm = wave / WN, wn = wave % WN;
     int tm, tn;
     staged_tile(blockIdx.x, tiles_m, tiles_n, tm, tn);
-    // A ragged last tile starts a few rows early if that lets it end on a whole block of its source (the rows it
-    // shares with its neighbour get the same bits from both).
+    // A ragged last tile starts a few rows early if that lets it end on a whole block of its source.  The rows it shares
+    // with its neighbour are the neighbour's to store: the two need not agree on them (one may have met a value that the
+    // split does not hold), and an element has one writer.
     auto origin = [](int64_t r0, int64_t rows, int64_t edge, int block) {
         const int64_t over = rows - r0 < edge ? (rows - r0) % block : 0;
         return over != 0 && r0 > 0 ? r0 - (block - over) : r0;
@@ -714,7 +715,7 @@ __global__ __launch_bounds__(64 * WM * WN * KG, (StagedShape<T, TM, TN, WM, WN, 
     }
     CT *Ct = C + (int64_t)blockIdx.y * strideC + m0 * ldc + n0;
     store_tile<TM, TN, CT>(t, Ct, ldc, (int)min((int64_t)BM, M - m0), (int)min((int64_t)BN, N - n0), wm * 32 * TM, wn * 32 * TN,
-                           alpha, lane);
+                           alpha, lane, (int)((int64_t)tm * BM - m0), (int)((int64_t)tn * BN - n0));
 }
 
 struct GemmArgs {

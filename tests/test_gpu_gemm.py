@@ -173,6 +173,29 @@ def test_fp32_range_ends(M, N, K, batch, a_col, b_col):
             P.assert_contraction_close(c[i], ref, oracle.gemm_absdot(a[i], b[i], M, N, K, a_col=a_col, b_col=b_col), K + 1)
 
 
+@pytest.mark.parametrize("M,N,K,tiny_row,tiny_col", [(70, 70, 300, 5, None), (70, 70, 300, None, 5), (65, 131, 33, 3, 66),
+                                                     (257, 129, 40, None, 128), (199, 67, 1024, 130, 65)])
+def test_rows_shared_by_two_tiles_have_one_writer(M, N, K, tiny_row, tiny_col):
+    """K-strided fp32 operands whose ragged last tile reads rows and columns of its neighbour, with a value under 2^-110
+    in some tiles only (those may take another way): every element carries the bits of the 64 x 64 tile that owns it,
+    in every run. A tile's bits alone come from a call on its rows and columns."""
+    g = np.random.default_rng(M + N)
+    a, b = g.uniform(-1, 1, (K, M)).astype(np.float32), g.uniform(-1, 1, (K, N)).astype(np.float32)
+    if tiny_row is not None:
+        a[7, tiny_row] = 1.7 * 2.0 ** -118
+    if tiny_col is not None:
+        b[9, tiny_col] = 1.7 * 2.0 ** -118
+    c = G.run_gemm(a, b, M, N, K, a_col=True, b_col=False, ab_bf16=False)[0]
+    for _ in range(5):
+        assert np.array_equal(c, G.run_gemm(a, b, M, N, K, a_col=True, b_col=False, ab_bf16=False)[0])
+    for m0 in range(0, M, 64):
+        for n0 in range(0, N, 64):
+            m1, n1 = min(M, m0 + 64), min(N, n0 + 64)
+            m, n = m0 - (m0 - m1) % 4, n0 - (n0 - n1) % 4  # (the tile reads whole blocks of 4)
+            own = G.run_gemm(a[:, m:m1], b[:, n:n1], m1 - m, n1 - n, K, a_col=True, b_col=False, ab_bf16=False)[0]
+            assert np.array_equal(c[m0:m1, n0:n1], own[m0 - m:, n0 - n:])
+
+
 def test_mfma_exact_integers_identity_permutation_ones():
     g = np.random.default_rng(3)
     M, N, K = 200, 136, 192
