@@ -11,12 +11,16 @@
 //     consecutive k-rows and transposes the block with byte permutes.
 //   * convolution activations (ConvRows): the chunk's filter tap is decoded per step; taps in the
 //     zero padding are zeroed.
-//   * fp32: every value is split exactly into three bf16 of 8 mantissa bits each (a = a0 + a1 + a2,
-//     by truncation, so that nothing overflows), and a product is the six MFMAs a0b0, a0b1, a1b0,
-//     a1b1, a0b2, a2b0; what is left out is below 2^-23 of the product.  The fp32 accumulator is
-//     rounded 6/16 times per k instead of once with the fp32 matrix instruction.  The split is exact from
-//     2^-110 on (bf16 ends at 2^-133); a workgroup that met a smaller value other than 0 computes its tile
-//     again with the fp32 matrix instruction, straight from memory.
+//   * fp32: every value is split exactly into three bf16 (a = a0 + a1 + a2, each the nearest bf16 to what the ones
+//     before leave), and a product is the six MFMAs a0b0, a0b1, a1b0, a1b1, a0b2, a2b0.  |a1| <= 2^-8 and |a2| <= 2^-17
+//     of a's power of two, so what is left out is at most 2^-24 of the product, of either sign (by truncation, whose
+//     parts share the sign of the value, it was up to 2^-21 and always towards zero).  The fp32 accumulator is
+//     rounded 6/16 times per k instead of once with the fp32 matrix instruction, which outweighs that from a few k on
+//     (rms error against float64 over sum |a||b|, operands in [-1, 1): K = 1024 1.4e-8 for 2.4e-8, K = 8 1.3e-8 for 2.5e-8,
+//     but K = 1 3.3e-8 for 2.5e-8); K < 8 takes the fp32 instruction.
+//     bf16 ends at 2^-133, so that a value under 2^-110 may not fit, and next to FLT_MAX a0 rounds to infinity; a
+//     workgroup that met the former, or sums that are not finite, computes its tile again with the fp32 matrix
+//     instruction, straight from memory.
 // Pipeline: the values of step s+2 are in flight while step s+1's go from registers to the other
 // LDS stage and step s is multiplied; one barrier per step.  KG > 1 splits the K-steps among KG
 // groups of waves of the workgroup, whose sums are added through LDS in a fixed order.
@@ -55,24 +59,30 @@ template <> struct Split<float> {
     static constexpr int kPlanes = 3, kBK = 32, kVec = 4;
 };
 
-// Smallest magnitude met so far, as 2 * bits - 1 (zero is the largest number, the sign drops out).
-struct Smallest {
-    uint32_t v = 0xffffffffu;
-    __device__ __forceinline__ void meet(uint32_t lo, uint32_t hi) { v = min(v, min(2 * lo - 1, 2 * hi - 1)); }
-    __device__ __forceinline__ bool below_split() const { return v < 2 * ((127u - 110u) << 23) - 1; }  // 2^-110
+// What a split did not hold, as bits of its last residual: a bf16 is the upper half of an fp32.
+struct Lost {
+    uint32_t v = 0;
+    __device__ __forceinline__ bool any() const { return (v & 0xffffu) != 0; }
 };
 
-// Two fp32 values as pairs of bf16: out[p] holds plane p of (lo, hi).
-__device__ __forceinline__ void split_pair(uint32_t lo, uint32_t hi, uint32_t (&out)[3], Smallest &low)
+// One conversion for both values.  (The compiler otherwise converts the upper one a second time to widen it again.)
+__device__ __forceinline__ uint32_t pack_once(float lo, float hi)
 {
-    low.meet(lo, hi);
+    uint32_t v = pack_bf16(lo, hi);
+    asm("" : "+v"(v));
+    return v;
+}
+
+// Two fp32 values as pairs of bf16: out[p] holds plane p of (lo, hi).  (The subtractions are exact.)
+__device__ __forceinline__ void split_pair(uint32_t lo, uint32_t hi, uint32_t (&out)[3], Lost &lost)
+{
     const float l0 = __builtin_bit_cast(float, lo), h0 = __builtin_bit_cast(float, hi);
-    const float l1 = l0 - __builtin_bit_cast(float, lo & 0xffff0000u), h1 = h0 - __builtin_bit_cast(float, hi & 0xffff0000u);
-    const uint32_t l1b = __builtin_bit_cast(uint32_t, l1), h1b = __builtin_bit_cast(uint32_t, h1);
-    const float l2 = l1 - __builtin_bit_cast(float, l1b & 0xffff0000u), h2 = h1 - __builtin_bit_cast(float, h1b & 0xffff0000u);
-    out[0] = __builtin_amdgcn_perm(hi, lo, 0x07060302u);
-    out[1] = __builtin_amdgcn_perm(h1b, l1b, 0x07060302u);
-    out[2] = __builtin_amdgcn_perm(__builtin_bit_cast(uint32_t, h2), __builtin_bit_cast(uint32_t, l2), 0x07060302u);
+    out[0] = pack_once(l0, h0);
+    const float l1 = l0 - bf16_lo(out[0]), h1 = h0 - bf16_hi(out[0]);
+    out[1] = pack_once(l1, h1);
+    const uint32_t l2 = __builtin_bit_cast(uint32_t, l1 - bf16_lo(out[1])), h2 = __builtin_bit_cast(uint32_t, h1 - bf16_hi(out[1]));
+    out[2] = __builtin_amdgcn_perm(h2, l2, 0x07060302u);
+    lost.v |= l2 | h2;
 }
 
 // LDS image of an operand: planes of ROWS rows of BK bf16 (128 or 64 bytes).  Within 16 rows the order is
@@ -129,7 +139,7 @@ __device__ __forceinline__ void shift_down(uint4_t (&v)[V], int sh)
 
 // Park a chunk of 8 K-contiguous elements at offset `o` of every plane.
 template <typename T, int ROWS>
-__device__ __forceinline__ void park_chunk(char *lds, int o, const uint4_t (&r)[8 / Split<T>::kVec], Smallest &low)
+__device__ __forceinline__ void park_chunk(char *lds, int o, const uint4_t (&r)[8 / Split<T>::kVec], Lost &lost)
 {
     if constexpr (Split<T>::kPlanes == 1) {
         *reinterpret_cast<uint4_t *>(lds + o) = r[0];
@@ -139,7 +149,7 @@ __device__ __forceinline__ void park_chunk(char *lds, int o, const uint4_t (&r)[
         for (int d = 0; d < 4; ++d) {
             uint32_t out[3];
             const uint32_t lo = r[d >> 1][2 * (d & 1)], hi = r[d >> 1][2 * (d & 1) + 1];
-            split_pair(lo, hi, out, low);
+            split_pair(lo, hi, out, lost);
 #pragma unroll
             for (int p = 0; p < 3; ++p) pl[p][d] = out[p];
         }
@@ -157,7 +167,7 @@ struct DenseArgs {
 // The operand sources below share an interface: init(), whole() (uniform: no row of the tile needs an
 // edge case), fetch<EDGE>(k0, slot) (loads of the K-step at k0 into register set `slot`) and
 // park<EDGE>(lds, k0, slot).  EDGE = false requires a whole K-step, and whole() where it is parked; past K, EDGE
-// fetches stay inside the operand and EDGE parks zeros.  low: the smallest magnitude parked (fp32).  at(row, k):
+// fetches stay inside the operand and EDGE parks zeros.  lost: what the splits did not hold (fp32).  at(row, k):
 // one element of the tile as fp32, zero outside.
 
 // Rows of K-contiguous elements, K >= 8.  An item is one chunk of 8 elements of a row; a chunk that would
@@ -175,7 +185,7 @@ struct KRows {
     int64_t K;
     int ch, o0, last;
     uint4_t raw[D][PER][V];
-    Smallest low;
+    Lost lost;
 
     __device__ __forceinline__ void init(const Args &a, int64_t b, int64_t r0, int64_t rows, int64_t K_, int tid)
     {
@@ -217,7 +227,7 @@ struct KRows {
         }
 #pragma unroll
         for (int i = 0; i < PER; ++i) {
-            park_chunk<T, ROWS>(lds, stage_step<BK>(o0, i * kRowStep), raw[slot][i], low);
+            park_chunk<T, ROWS>(lds, stage_step<BK>(o0, i * kRowStep), raw[slot][i], lost);
         }
     }
 };
@@ -239,7 +249,7 @@ struct RRows {
     int kq, sh, o0, last, back;
     bool all;
     uint4_t raw[D][KB];
-    Smallest low;
+    Lost lost;
 
     __device__ __forceinline__ void init(const Args &a, int64_t b, int64_t r0, int64_t rows, int64_t K_, int tid)
     {
@@ -302,7 +312,7 @@ struct RRows {
                     pair[h][0] = __builtin_amdgcn_perm(hi, lo, (e & 1) ? 0x07060302u : 0x05040100u);
                 } else {
                     const uint32_t lo = raw[slot][2 * h][e], hi = raw[slot][2 * h + 1][e];
-                    split_pair(lo, hi, pair[h], low);
+                    split_pair(lo, hi, pair[h], lost);
                 }
             }
 #pragma unroll
@@ -328,7 +338,7 @@ struct AnyRows {
     int64_t K;
     int row, ch, last;
     uint4_t raw[D][PER][V];
-    Smallest low;
+    Lost lost;
 
     __device__ __forceinline__ void init(const Args &a, int64_t b, int64_t r0, int64_t rows, int64_t K_, int tid)
     {
@@ -364,7 +374,7 @@ struct AnyRows {
     __device__ __forceinline__ void park(char *lds, int64_t, int slot)
     {
 #pragma unroll
-        for (int i = 0; i < PER; ++i) park_chunk<T, ROWS>(lds, stage_offset<BK>(row + i * kRowStep, ch), raw[slot][i], low);
+        for (int i = 0; i < PER; ++i) park_chunk<T, ROWS>(lds, stage_offset<BK>(row + i * kRowStep, ch), raw[slot][i], lost);
     }
 };
 
@@ -387,7 +397,7 @@ struct ConvRows {
     int ih0[PER], iw0[PER];
     uint4_t raw[D][PER][WHOLE ? V : 2];  // the chunk, or its 8 elements one per word
     uint32_t ok[D];
-    Smallest low;
+    Lost lost;
     int64_t first, pixels;
 
     __device__ __forceinline__ void pixel(int m, int &h0, int &w0, int64_t &o) const
@@ -493,7 +503,7 @@ struct ConvRows {
                     for (int d = 0; d < 8; ++d) v[d >> 2][d & 3] = w[d];
                 }
             }
-            park_chunk<T, ROWS>(lds, stage_step<BK>(o0, i * kRowStep), v, low);
+            park_chunk<T, ROWS>(lds, stage_step<BK>(o0, i * kRowStep), v, lost);
         }
     }
 };
@@ -673,8 +683,17 @@ __global__ __launch_bounds__(64 * WM * WN * KG, (StagedShape<T, TM, TN, WM, WN, 
             }
         });
     }
-    bool again = false;  // a value the split does not hold: the fp32 matrix instruction, operands straight from memory
-    if constexpr (NP > 1) again = __syncthreads_or(a_src.low.below_split() || b_src.low.below_split()) != 0;
+    bool again = false;  // the fp32 matrix instruction, operands straight from memory
+    if constexpr (NP > 1) {
+        float z = 0.f;  // (infinities and NaN make it NaN)
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+            for (int j = 0; j < TN; ++j)
+#pragma unroll
+                for (int e = 0; e < 16; ++e) z = __builtin_fmaf(t.acc[i][j][e], 0.f, z);
+        again = __syncthreads_or(K < 8 || a_src.lost.any() || b_src.lost.any() || z != 0.f) != 0;
+    }
     if (again) {
         if (group > 0) return;
         t.clear();

@@ -8,6 +8,7 @@ import oracle
 from workloads import configs, rng
 from tests import gpu_helpers as G
 from tests import parity as P
+from tests.test_gpu_gemm import split_bound
 
 pytestmark = pytest.mark.gpu
 
@@ -290,3 +291,13 @@ def test_staged_conv_edges(kw):
             yg = P.bf16_to_f64(y) if y_bf16 else y
             # (+ half the smallest subnormal per addition: the tiny results are near the end of the range)
             P.assert_contraction_close(yg, ref, ad + 2.0 ** -126, wl.R * wl.S * wl.C + 1, out_bf16=y_bf16)
+
+
+@pytest.mark.parametrize("C,R,stride", [(1, 1, 2), (2, 1, 2), (7, 1, 2), (1, 3, 1), (8, 1, 2), (40, 3, 1), (64, 5, 1)])
+def test_fp32_operands_that_split_badly(C, R, stride):
+    """As for the GEMM: all operands 1 + 2^-7 - 2^-23, whose lower parts are the largest that truncation leaves."""
+    v = np.float32(1 + 2.0 ** -7 - 2.0 ** -23)
+    y = G.run_conv2d(np.full((2, 12, 11, C), v), np.full((40, R, R, C), v), (stride, stride), (0, 0), xw_bf16=False, y_bf16=False,
+                     variant=7)
+    K = R * R * C
+    assert np.abs(y / (K * np.float64(v) ** 2) - 1).max() <= split_bound(K)

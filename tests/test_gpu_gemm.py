@@ -149,7 +149,7 @@ def test_staged_kernel_edges(M, N, K, batch, pad, a_col, b_col, ab_bf16, c_bf16)
         A = ai[:, :M].T if a_col else ai[:, :K]
         B = bi[:, :K].T if b_col else bi[:, :N]
         absdot = 0.75 * (np.abs(A) @ np.abs(B))
-        # fp32 operands: the products that the split leaves out are below 2^-23 of |a||b| each (K + 1 in the bound)
+        # fp32 operands: the products that the split leaves out are at most 2^-24 of |a||b| each (K + 1 in the bound)
         P.assert_contraction_close(P.bf16_to_f64(c[i]) if c_bf16 else c[i], ref, absdot, K + 1, out_bf16=c_bf16)
 
 
@@ -171,6 +171,60 @@ def test_fp32_range_ends(M, N, K, batch, a_col, b_col):
         for i in (0, batch - 1):
             ref = oracle.gemm(a[i], b[i], M, N, K, a_col=a_col, b_col=b_col)
             P.assert_contraction_close(c[i], ref, oracle.gemm_absdot(a[i], b[i], M, N, K, a_col=a_col, b_col=b_col), K + 1)
+
+
+def split_bound(K):
+    """Largest error over sum |a||b| of an fp32 reduction of K: K roundings of the partial sum with the fp32 instruction
+    (K < 8); else the products that the three-way split leaves out (2^-24 each) and, for every 16 k, six additions to
+    the accumulator that may truncate, of which in the first 16 only the last is to more than 2^-7 of the sum."""
+    return K * 2.0 ** -24 if K < 8 else 2.0 ** -24 + (1.04 + 6 * ((K + 15) // 16 - 1)) * 2.0 ** -23
+
+
+@pytest.mark.parametrize("a_col,b_col", [(False, True), (True, False), (False, False)])
+@pytest.mark.parametrize("K", [1, 2, 7, 8, 16, 33, 300, 4096])
+def test_fp32_operands_that_split_badly(K, a_col, b_col):
+    """fp32 operands whose lower parts are as large as they get for splits by truncation (1 + 2^-7 - 2^-23) and by rounding
+    (1 + 2^-8 - 2^-17), all of one sign: what a split leaves out adds up."""
+    M, N = 70, 130
+    g = np.random.default_rng(K)
+    adv = np.array([1 + 2.0 ** -7 - 2.0 ** -23, 1 + 2.0 ** -8 - 2.0 ** -17 - 2.0 ** -23, 1 + 2.0 ** -8 + 2.0 ** -17, 1.0])
+    for a, b in ((np.full((M, K), adv[0]), np.full((N, K), adv[0])), (adv[g.integers(0, 4, (M, K))], adv[g.integers(0, 4, (N, K))]),
+                 (g.uniform(0.5, 1, (M, K)), g.uniform(0.5, 1, (N, K)))):
+        a, b = a.astype(np.float32), b.astype(np.float32)
+        c = G.run_gemm(np.ascontiguousarray(a.T) if a_col else a, b if b_col else np.ascontiguousarray(b.T), M, N, K, a_col=a_col,
+                       b_col=b_col, ab_bf16=False)[0]
+        ref = a.astype(np.float64) @ b.astype(np.float64).T
+        rel = np.abs(c - ref) / ref
+        assert rel.max() <= split_bound(K), rel.max()
+        if K >= 16 and a.min() < 1:  # random operands: the additions' errors are independent
+            assert np.sqrt(np.mean(rel ** 2)) <= 2.0 ** -24 * np.sqrt(6 * K / 16)
+
+
+@pytest.mark.parametrize("a_col,b_col", [(False, True), (True, False)])
+@pytest.mark.parametrize("M,N,K", [(70, 65, 33), (96, 64, 300), (7, 3, 5), (3, 9, 40)])
+def test_fp32_values_next_to_what_splits(M, N, K, a_col, b_col):
+    """Values whose lowest part just fits a bf16 (2^-109), values that round to infinity in one (next to FLT_MAX), and infinities
+    and NaN, which the fp32 instruction carries through."""
+    g = np.random.default_rng(M)
+    big = np.float32(np.finfo(np.float32).max)
+    run = lambda a, b: G.run_gemm(np.ascontiguousarray(a.T) if a_col else a, b if b_col else np.ascontiguousarray(b.T), M, N, K,  # noqa: E731
+                                  a_col=a_col, b_col=b_col, ab_bf16=False)[0]
+    a0, b = g.uniform(0.5, 1, (M, K)).astype(np.float32), g.uniform(0.5, 1, (N, K)).astype(np.float32)
+    for scale, at, value in ((2.0 ** -109, None, 0), (1, (2, 4), big), (1, (2, 4), -big)):
+        a = a0 * np.float32(scale)
+        if at is not None:
+            a[at] = value
+        ref, ab = a.astype(np.float64) @ b.astype(np.float64).T / K, np.abs(a).astype(np.float64) @ b.astype(np.float64).T / K
+        # (the added 2^-126: half the smallest subnormal per addition)
+        P.assert_contraction_close(run(a, b / np.float32(K)), ref, ab + 2.0 ** -126, K + 2)
+    for value in (np.inf, -np.inf, np.nan):
+        a = a0.copy()
+        a[2, 4] = value
+        c = run(a, b)
+        assert np.all(np.isnan(c[2])) if np.isnan(value) else np.all(c[2] == value)
+        rest = np.arange(M) != 2
+        ref = a0.astype(np.float64) @ b.astype(np.float64).T
+        P.assert_contraction_close(c[rest], ref[rest], ref[rest], K + 1)
 
 
 @pytest.mark.parametrize("M,N,K,tiny_row,tiny_col", [(70, 70, 300, 5, None), (70, 70, 300, None, 5), (65, 131, 33, 3, 66),
