@@ -95,7 +95,7 @@ perf_status perf_layernorm(const void *x, const void *gamma, const void *beta, v
  * pointers; every other legal combination (fp32 operands, other layouts, any K) passes its
  * operands through registers on the way to the same matrix instruction; an fp32 operand is split
  * exactly into three bf16 and a product computed as six of theirs (what is left out is at most 2^-24 of it); K < 8 and
- * operands that do not split (below 2^-110, next to the largest) take the fp32 matrix instruction.
+ * values next to the largest take the fp32 matrix instruction, values below 2^-110 are scaled first where they show.
  * Errors: NULL, SHAPE, DTYPE, LAYOUT, ALIGN (pointer not aligned to its element size),
  * UNSUPPORTED (f32 operands with bf16 C), LAUNCH. */
 perf_status perf_gemm(const void *A, const void *B, void *C, int64_t M, int64_t N, int64_t K,

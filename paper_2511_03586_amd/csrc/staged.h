@@ -18,9 +18,9 @@
 //     rounded 6/16 times per k instead of once with the fp32 matrix instruction, which outweighs that from a few k on
 //     (rms error against float64 over sum |a||b|, operands in [-1, 1): K = 1024 1.4e-8 for 2.4e-8, K = 8 1.3e-8 for 2.5e-8,
 //     but K = 1 3.3e-8 for 2.5e-8); K < 8 takes the fp32 instruction.
-//     bf16 ends at 2^-133, so that a value under 2^-110 may not fit, and next to FLT_MAX a0 rounds to infinity; a
-//     workgroup that met the former, or sums that are not finite, computes its tile again with the fp32 matrix
-//     instruction, straight from memory.
+//     bf16 ends at 2^-133, so that a value under 2^-110 may not fit: a workgroup that met one computes its tile again
+//     with that operand times 2^24 (TIMES), and then every fp32 value fits.  Next to FLT_MAX (2^104 the second time) a0
+//     rounds to infinity: sums that are not finite are computed with the fp32 matrix instruction, straight from memory.
 // Pipeline: the values of step s+2 are in flight while step s+1's go from registers to the other
 // LDS stage and step s is multiplied; one barrier per step.  KG > 1 splits the K-steps among KG
 // groups of waves of the workgroup, whose sums are added through LDS in a fixed order.
@@ -73,10 +73,16 @@ __device__ __forceinline__ uint32_t pack_once(float lo, float hi)
     return v;
 }
 
-// Two fp32 values as pairs of bf16: out[p] holds plane p of (lo, hi).  (The subtractions are exact.)
-__device__ __forceinline__ void split_pair(uint32_t lo, uint32_t hi, uint32_t (&out)[3], Lost &lost)
+// Two fp32 values, times a power of two if TIMES, as pairs of bf16: out[p] holds plane p of (lo, hi).  (The subtractions
+// are exact.)
+template <bool TIMES>
+__device__ __forceinline__ void split_pair(uint32_t lo, uint32_t hi, uint32_t (&out)[3], Lost &lost, float times)
 {
-    const float l0 = __builtin_bit_cast(float, lo), h0 = __builtin_bit_cast(float, hi);
+    float l0 = __builtin_bit_cast(float, lo), h0 = __builtin_bit_cast(float, hi);
+    if constexpr (TIMES) {
+        l0 *= times;
+        h0 *= times;
+    }
     out[0] = pack_once(l0, h0);
     const float l1 = l0 - bf16_lo(out[0]), h1 = h0 - bf16_hi(out[0]);
     out[1] = pack_once(l1, h1);
@@ -138,8 +144,8 @@ __device__ __forceinline__ void shift_down(uint4_t (&v)[V], int sh)
 }
 
 // Park a chunk of 8 K-contiguous elements at offset `o` of every plane.
-template <typename T, int ROWS>
-__device__ __forceinline__ void park_chunk(char *lds, int o, const uint4_t (&r)[8 / Split<T>::kVec], Lost &lost)
+template <typename T, int ROWS, bool TIMES>
+__device__ __forceinline__ void park_chunk(char *lds, int o, const uint4_t (&r)[8 / Split<T>::kVec], Lost &lost, float times)
 {
     if constexpr (Split<T>::kPlanes == 1) {
         *reinterpret_cast<uint4_t *>(lds + o) = r[0];
@@ -149,7 +155,7 @@ __device__ __forceinline__ void park_chunk(char *lds, int o, const uint4_t (&r)[
         for (int d = 0; d < 4; ++d) {
             uint32_t out[3];
             const uint32_t lo = r[d >> 1][2 * (d & 1)], hi = r[d >> 1][2 * (d & 1) + 1];
-            split_pair(lo, hi, out, lost);
+            split_pair<TIMES>(lo, hi, out, lost, times);
 #pragma unroll
             for (int p = 0; p < 3; ++p) pl[p][d] = out[p];
         }
@@ -166,8 +172,8 @@ struct DenseArgs {
 
 // The operand sources below share an interface: init(), whole() (uniform: no row of the tile needs an
 // edge case), fetch<EDGE>(k0, slot) (loads of the K-step at k0 into register set `slot`) and
-// park<EDGE>(lds, k0, slot).  EDGE = false requires a whole K-step, and whole() where it is parked; past K, EDGE
-// fetches stay inside the operand and EDGE parks zeros.  lost: what the splits did not hold (fp32).  at(row, k):
+// park<EDGE, TIMES>(lds, k0, slot).  EDGE = false requires a whole K-step, and whole() where it is parked; past K, EDGE
+// fetches stay inside the operand and EDGE parks zeros.  lost, times: see split_pair (fp32).  at(row, k):
 // one element of the tile as fp32, zero outside.
 
 // Rows of K-contiguous elements, K >= 8.  An item is one chunk of 8 elements of a row; a chunk that would
@@ -175,6 +181,8 @@ struct DenseArgs {
 template <typename T, int ROWS, int THREADS, int D>
 struct KRows {
     using S = Split<T>;
+    using Shallow = KRows<T, ROWS, THREADS, 1>;  // one register set
+    static constexpr int kDepth = D;
     static constexpr int BK = S::kBK, CH = BK / 8, ITEMS = ROWS * CH, PER = ITEMS / THREADS, V = 8 / S::kVec;
     static constexpr int kRowStep = THREADS / CH, kBlock = 1;
     static_assert(ITEMS % THREADS == 0 && kRowStep >= 16, "items divide among the threads, one chunk column per thread");
@@ -186,6 +194,7 @@ struct KRows {
     int ch, o0, last;
     uint4_t raw[D][PER][V];
     Lost lost;
+    float times;
 
     __device__ __forceinline__ void init(const Args &a, int64_t b, int64_t r0, int64_t rows, int64_t K_, int tid)
     {
@@ -215,7 +224,7 @@ struct KRows {
 #pragma unroll
             for (int v = 0; v < V; ++v) raw[slot][i][v] = load16(b + (Off)(off[i] + d) + v * S::kVec);
     }
-    template <bool EDGE>
+    template <bool EDGE, bool TIMES>
     __device__ __forceinline__ void park(char *lds, int64_t k0, int slot)
     {
         if constexpr (EDGE) {
@@ -227,7 +236,7 @@ struct KRows {
         }
 #pragma unroll
         for (int i = 0; i < PER; ++i) {
-            park_chunk<T, ROWS>(lds, stage_step<BK>(o0, i * kRowStep), raw[slot][i], lost);
+            park_chunk<T, ROWS, TIMES>(lds, stage_step<BK>(o0, i * kRowStep), raw[slot][i], lost, times);
         }
     }
 };
@@ -238,6 +247,8 @@ struct KRows {
 template <typename T, int ROWS, int THREADS, int D>
 struct RRows {
     using S = Split<T>;
+    using Shallow = RRows<T, ROWS, THREADS, 1>;  // one register set
+    static constexpr int kDepth = D;
     static constexpr int BK = S::kBK, V = S::kVec, RB = ROWS / V, KB = RB * BK / THREADS;
     static constexpr int kBlock = V;
     static_assert(KB == 2 || KB == 4, "one block per thread");
@@ -250,6 +261,7 @@ struct RRows {
     bool all;
     uint4_t raw[D][KB];
     Lost lost;
+    float times;
 
     __device__ __forceinline__ void init(const Args &a, int64_t b, int64_t r0, int64_t rows, int64_t K_, int tid)
     {
@@ -288,7 +300,7 @@ struct RRows {
             for (int u = 0; u < KB; ++u) raw[slot][u] = load16(b + u * ld + off);
         }
     }
-    template <bool EDGE>
+    template <bool EDGE, bool TIMES>
     __device__ __forceinline__ void park(char *lds, int64_t k0, int slot)
     {
         if constexpr (EDGE) {
@@ -312,7 +324,7 @@ struct RRows {
                     pair[h][0] = __builtin_amdgcn_perm(hi, lo, (e & 1) ? 0x07060302u : 0x05040100u);
                 } else {
                     const uint32_t lo = raw[slot][2 * h][e], hi = raw[slot][2 * h + 1][e];
-                    split_pair(lo, hi, pair[h], lost);
+                    split_pair<TIMES>(lo, hi, pair[h], lost, times);
                 }
             }
 #pragma unroll
@@ -329,6 +341,8 @@ struct RRows {
 template <typename T, int ROWS, int THREADS, int D>
 struct AnyRows {
     using S = Split<T>;
+    using Shallow = AnyRows<T, ROWS, THREADS, 1>;  // one register set
+    static constexpr int kDepth = D;
     static constexpr int BK = S::kBK, CH = BK / 8, PER = ROWS * CH / THREADS, V = 8 / S::kVec, kRowStep = THREADS / CH, kBlock = 1;
     struct Args {
         const T *p;
@@ -339,6 +353,7 @@ struct AnyRows {
     int row, ch, last;
     uint4_t raw[D][PER][V];
     Lost lost;
+    float times;
 
     __device__ __forceinline__ void init(const Args &a, int64_t b, int64_t r0, int64_t rows, int64_t K_, int tid)
     {
@@ -370,12 +385,19 @@ struct AnyRows {
             __builtin_memcpy(&raw[slot][i][0], e, sizeof(e));
         }
     }
-    template <bool EDGE>
+    template <bool EDGE, bool TIMES>
     __device__ __forceinline__ void park(char *lds, int64_t, int slot)
     {
 #pragma unroll
-        for (int i = 0; i < PER; ++i) park_chunk<T, ROWS>(lds, stage_offset<BK>(row + i * kRowStep, ch), raw[slot][i], lost);
+        for (int i = 0; i < PER; ++i) park_chunk<T, ROWS, TIMES>(lds, stage_offset<BK>(row + i * kRowStep, ch), raw[slot][i], lost, times);
     }
+};
+
+template <typename T>
+struct ConvArgs {
+    const T *x;
+    int H, W, C, S, sh, sw, ph, pw, P, Q;
+    uint32_t mC, mS, mPQ, mQ;  // multipliers for div_by
 };
 
 // The implicit im2col matrix of a convolution over NHWC x: row = output pixel (n, p, q), k = (r, s, c) with c
@@ -383,14 +405,12 @@ struct AnyRows {
 template <typename T, int ROWS, int THREADS, int D, bool WHOLE>
 struct ConvRows {
     using S = Split<T>;
+    using Shallow = ConvRows<T, ROWS, THREADS, 1, WHOLE>;  // one register set
+    static constexpr int kDepth = D;
     static constexpr int BK = S::kBK, CH = BK / 8, ITEMS = ROWS * CH, PER = ITEMS / THREADS, V = 8 / S::kVec;
     static constexpr int kRowStep = THREADS / CH, kBlock = 1;
     static_assert(ITEMS % THREADS == 0 && kRowStep >= 16 && PER <= 4, "items divide among the threads, one chunk column per thread");
-    struct Args {
-        const T *x;
-        int H, W, C, S, sh, sw, ph, pw, P, Q;
-        uint32_t mC, mS, mPQ, mQ;
-    };
+    using Args = ConvArgs<T>;
     Args g;
     int K, ch, o0;
     int64_t off[PER];  // element offset of the pixel under tap (0, 0), channel 0 (may lie outside x)
@@ -398,6 +418,7 @@ struct ConvRows {
     uint4_t raw[D][PER][WHOLE ? V : 2];  // the chunk, or its 8 elements one per word
     uint32_t ok[D];
     Lost lost;
+    float times;
     int64_t first, pixels;
 
     __device__ __forceinline__ void pixel(int m, int &h0, int &w0, int64_t &o) const
@@ -481,7 +502,7 @@ struct ConvRows {
         }
         ok[slot] = good;
     }
-    template <bool EDGE>
+    template <bool EDGE, bool TIMES>
     __device__ __forceinline__ void park(char *lds, int64_t, int slot)
     {
 #pragma unroll
@@ -503,7 +524,7 @@ struct ConvRows {
                     for (int d = 0; d < 8; ++d) v[d >> 2][d & 3] = w[d];
                 }
             }
-            park_chunk<T, ROWS>(lds, stage_step<BK>(o0, i * kRowStep), v, lost);
+            park_chunk<T, ROWS, TIMES>(lds, stage_step<BK>(o0, i * kRowStep), v, lost, times);
         }
     }
 };
@@ -579,7 +600,8 @@ __global__ __launch_bounds__(64 * WM * WN * KG, (StagedShape<T, TM, TN, WM, WN, 
     a_src.init(aa, blockIdx.y, m0, M, K, tid - group * Shape::kThreads);
     b_src.init(ba, blockIdx.y, n0, N, K, tid - group * Shape::kThreads);
     char *const mine = smem + group * 2 * Shape::kStage;
-    const int64_t nsteps = (K + BK - 1) / BK, rounds = (nsteps + KG - 1) / KG;
+    const bool few_k = NP > 1 && K < 8;  // (no rounds: computed with the fp32 instruction)
+    const int64_t nsteps = (K + BK - 1) / BK, rounds = few_k ? 0 : (nsteps + KG - 1) / KG;
 
     // Fragment addresses: tile rows 32 R + l, chunk 2 ks + lane / 32 sit at 32 R rows past the address of
     // rows l, chunk 2 (ks ^ R) + lane / 32: one register per k-substep and an immediate per tile.
@@ -646,68 +668,148 @@ __global__ __launch_bounds__(64 * WM * WN * KG, (StagedShape<T, TM, TN, WM, WN, 
     const bool clean = a_src.whole() && b_src.whole(), even = K % (BK * KG) == 0;
     const int64_t fast_rounds = !clean ? 0 : even ? rounds : K / BK / KG - D - 1;
     auto step_k = [&](int64_t it) { return (it * KG + group) * BK; };
-    auto round = [&](auto u, auto edge, int64_t it) {
-        constexpr int slot = (u + 1) % D, buf = u & 1;
-        constexpr bool kEdge = decltype(edge)::value;
-        char *sa = mine + (buf ^ 1) * Shape::kStage, *sb = sa + Shape::kStageA;
-        const int64_t kp = step_k(it + 1), kn = kEdge ? step_k(it + 1 + D) : min(step_k(it + 1 + D), K - BK);
+    auto round = [&](auto &sa, auto &sb, auto u, auto edge, auto times, int64_t it) {
+        constexpr int kD = std::remove_reference_t<decltype(sa)>::kDepth, slot = (u + 1) % kD, buf = u & 1;
+        constexpr bool kEdge = decltype(edge)::value, kTimes = decltype(times)::value;
+        char *la = mine + (buf ^ 1) * Shape::kStage, *lb = la + Shape::kStageA;
+        const int64_t kp = step_k(it + 1), kn = kEdge ? step_k(it + 1 + kD) : min(step_k(it + 1 + kD), K - BK);
         multiply(buf, [&](auto ks) {
             if constexpr (ks == 0) {
-                a_src.template park<kEdge>(sa, kp, slot);
-                a_src.template fetch<kEdge>(kn, slot);
+                sa.template park<kEdge, kTimes>(la, kp, slot);
+                sa.template fetch<kEdge>(kn, slot);
             } else if constexpr (ks == 1) {
-                b_src.template park<kEdge>(sb, kp, slot);
-                b_src.template fetch<kEdge>(kn, slot);
+                sb.template park<kEdge, kTimes>(lb, kp, slot);
+                sb.template fetch<kEdge>(kn, slot);
             }
         });
         __syncthreads();
     };
-    unrolled<D>([&](auto d) {
-        a_src.template fetch<true>(step_k(d), d);
-        b_src.template fetch<true>(step_k(d), d);
-    });
-    a_src.template park<true>(mine, step_k(0), 0);
-    a_src.template fetch<true>(step_k(D), 0);
-    b_src.template park<true>(mine + Shape::kStageA, step_k(0), 0);
-    b_src.template fetch<true>(step_k(D), 0);
-    __syncthreads();
+    auto start = [&](auto &sa, auto &sb, auto times, int64_t it) {
+        constexpr int kD = std::remove_reference_t<decltype(sa)>::kDepth;
+        constexpr bool kTimes = decltype(times)::value;
+        unrolled<kD>([&](auto d) {
+            sa.template fetch<true>(step_k(it + d), d);
+            sb.template fetch<true>(step_k(it + d), d);
+        });
+        sa.template park<true, kTimes>(mine, step_k(it), 0);
+        sa.template fetch<true>(step_k(it + kD), 0);
+        sb.template park<true, kTimes>(mine + Shape::kStageA, step_k(it), 0);
+        sb.template fetch<true>(step_k(it + kD), 0);
+        __syncthreads();
+    };
+    auto edge_rounds = [&](auto &sa, auto &sb, auto times, int64_t it) {
+        constexpr int kD = std::remove_reference_t<decltype(sa)>::kDepth;
+        while (it < rounds) {
+            bool more = true;
+            unrolled<(kD > 2 ? kD : 2)>([&](auto u) {
+                if (more) {
+                    round(sa, sb, u, std::true_type{}, times, it);
+                    more = ++it < rounds;
+                }
+            });
+        }
+    };
+    start(a_src, b_src, std::false_type{}, 0);
     int64_t it = 0;
     for (; it + U <= fast_rounds; it += U)
-        unrolled<U>([&](auto u) { round(u, std::false_type{}, it + u); });
-    while (it < rounds) {
-        bool more = true;
-        unrolled<U>([&](auto u) {
-            if (more) {
-                round(u, std::true_type{}, it);
-                more = ++it < rounds;
-            }
-        });
-    }
-    bool again = false;  // the fp32 matrix instruction, operands straight from memory
+        unrolled<U>([&](auto u) { round(a_src, b_src, u, std::false_type{}, std::false_type{}, it + u); });
+    edge_rounds(a_src, b_src, std::false_type{}, it);
+    bool direct = false;  // the fp32 matrix instruction, operands straight from memory
     if constexpr (NP > 1) {
-        float z = 0.f;  // (infinities and NaN make it NaN)
-#pragma unroll
-        for (int i = 0; i < TM; ++i)
-#pragma unroll
-            for (int j = 0; j < TN; ++j)
-#pragma unroll
-                for (int e = 0; e < 16; ++e) z = __builtin_fmaf(t.acc[i][j][e], 0.f, z);
-        again = __syncthreads_or(K < 8 || a_src.lost.any() || b_src.lost.any() || z != 0.f) != 0;
-    }
-    if (again) {
-        if (group > 0) return;
-        t.clear();
-        for (int64_t k = lane >> 5; k < K + (lane >> 5); k += 2) {  // (the same count in both halves of the wave)
-            float a[TM], b[TN];
-#pragma unroll
-            for (int i = 0; i < TM; ++i) a[i] = a_src.at(aa, (wm * TM + i) * 32 + (lane & 31), k);
-#pragma unroll
-            for (int j = 0; j < TN; ++j) b[j] = b_src.at(ba, (wn * TN + j) * 32 + (lane & 31), k);
+        auto not_finite = [&]() {
+            float z = 0.f;  // (infinities and NaN make it NaN)
 #pragma unroll
             for (int i = 0; i < TM; ++i)
 #pragma unroll
-                for (int j = 0; j < TN; ++j) t.acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[i], b[j], t.acc[i][j], 0, 0, 0);
+                for (int j = 0; j < TN; ++j)
+#pragma unroll
+                    for (int e = 0; e < 16; ++e) z = __builtin_fmaf(t.acc[i][j][e], 0.f, z);
+            return z != 0.f;
+        };
+        const bool lost_a = a_src.lost.any(), lost_b = b_src.lost.any(), no_sum = few_k || not_finite();
+        if (__syncthreads_or(lost_a || lost_b || no_sum)) {
+            const float times_a = __syncthreads_or(lost_a) ? 0x1p24f : 1.f, times_b = __syncthreads_or(lost_b) ? 0x1p24f : 1.f;
+            direct = __syncthreads_or(no_sum) != 0;
+            // (everything anew, from values that the compiler takes for others: what it would keep costs the loop above registers)
+            int tid2 = tid;
+            int64_t K2 = K, first = 0;
+            asm volatile("" : "+v"(tid2), "+s"(K2), "+s"(first));
+            typename ASrc::Shallow a2;
+            typename BSrc::Shallow b2;
+            a2.init(aa, blockIdx.y, m0, M, K2, tid2 - group * Shape::kThreads);
+            b2.init(ba, blockIdx.y, n0, N, K2, tid2 - group * Shape::kThreads);
+            // A value loses less than 2^-133, so a sum less than 2^-133 K max |other operand|: nothing that shows if every sum
+            // is 2^28 times that.  (Probabilities times values: those that underflow stand beside others.)
+            bool again = !direct;
+            if (KG == 1 && again) {
+                auto largest = [&](auto &src) {
+                    float m = 0.f;
+                    for (int64_t k = first; k < K2; k += BK) {
+                        src.template fetch<true>(k, 0);
+                        const uint4_t(&w)[sizeof(src.raw[0]) / 16] = reinterpret_cast<const uint4_t(&)[sizeof(src.raw[0]) / 16]>(src.raw[0]);
+#pragma unroll
+                        for (unsigned i = 0; i < sizeof(src.raw[0]) / 16; ++i)
+#pragma unroll
+                            for (int e = 0; e < 4; ++e) {
+                                const uint32_t bits = w[i][e];
+                                m = __builtin_fmaxf(m, __builtin_fabsf(__builtin_bit_cast(float, bits)));
+                            }
+                    }
+                    return m;
+                };
+                float big = 0.f;
+                if (times_a > 1.f) big = largest(b2);
+                if (times_b > 1.f) big = __builtin_fmaxf(big, largest(a2));
+                big = wave_allreduce(big, OpMax{});
+                float *red = reinterpret_cast<float *>(smem);  // (no stage is read any more)
+                if ((tid2 & 63) == 0) red[wave_all] = big;
+                __syncthreads();
+#pragma unroll
+                for (int w = 0; w < NW; ++w) big = __builtin_fmaxf(big, red[w]);
+                const float least = 0x1p-104f * (float)K * big;  // (2^29 times: both operands may have lost)
+                bool small = false;
+#pragma unroll
+                for (int i = 0; i < TM; ++i)
+#pragma unroll
+                    for (int j = 0; j < TN; ++j)
+#pragma unroll
+                        for (int e = 0; e < 16; ++e) small |= !(__builtin_fabsf(t.acc[i][j][e]) >= least);
+                again = __syncthreads_or(small) != 0;
+            }
+            if (again) {
+                a2.times = times_a;
+                b2.times = times_b;
+                t.clear();
+                start(a2, b2, std::true_type{}, first);
+                edge_rounds(a2, b2, std::true_type{}, first);
+                direct = __syncthreads_or(not_finite()) != 0;
+                const float back = (times_a > 1.f ? 0x1p-24f : 1.f) * (times_b > 1.f ? 0x1p-24f : 1.f);
+#pragma unroll
+                for (int i = 0; i < TM; ++i)
+#pragma unroll
+                    for (int j = 0; j < TN; ++j)
+#pragma unroll
+                        for (int e = 0; e < 16; ++e) t.acc[i][j][e] *= back;
+            }
+            if (direct && group == 0) {
+                const int l = tid2 & 63;
+                t.clear();
+                for (int64_t k = l >> 5; k < K + (l >> 5); k += 2) {  // (the same count in both halves of the wave)
+                    float a[TM], b[TN];
+#pragma unroll
+                    for (int i = 0; i < TM; ++i) a[i] = a2.at(aa, (wm * TM + i) * 32 + (l & 31), k);
+#pragma unroll
+                    for (int j = 0; j < TN; ++j) b[j] = b2.at(ba, (wn * TN + j) * 32 + (l & 31), k);
+#pragma unroll
+                    for (int i = 0; i < TM; ++i)
+#pragma unroll
+                        for (int j = 0; j < TN; ++j) t.acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[i], b[j], t.acc[i][j], 0, 0, 0);
+                }
+            }
         }
+    }
+    if (direct) {
+        if (group > 0) return;
     } else if constexpr (KG > 1) {
         // the groups' sums, added in group order
         float *red = reinterpret_cast<float *>(smem);

@@ -227,6 +227,32 @@ def test_fp32_values_next_to_what_splits(M, N, K, a_col, b_col):
         P.assert_contraction_close(c[rest], ref[rest], ref[rest], K + 1)
 
 
+@pytest.mark.parametrize("a_col,b_col", [(False, True), (True, False)])
+@pytest.mark.parametrize("M,N,K,batch", [(70, 65, 33, 1), (64, 64, 96, 1), (96, 64, 300, 1), (130, 250, 64, 96), (3, 9, 40, 1)])
+def test_fp32_tiny_values(M, N, K, batch, a_col, b_col):
+    """Values under 2^-110 (which need more than the three-way split): beside ordinary ones in sums that they do not
+    show in, alone in the sums of some columns, in both operands, and beside values that leave no room to scale."""
+    g = np.random.default_rng(M + K)
+    t = 2.0 ** -112
+    a0, b0 = g.uniform(0.5, 1, (M, K)), g.uniform(0.5, 1, (N, K))
+    beside, alone = a0.copy(), b0.copy()
+    beside[:, ::2] *= t
+    alone[N // 2:, 1::2] = 0                 # the second half of the columns meets tiny values only
+    room = beside.copy()
+    room[0, 1] = 2.0 ** 120
+    for a, b in ((beside, b0), (beside, alone), (a0 * t, b0), (beside, b0 * np.where(np.arange(K) % 3, 1.0, t)), (room, alone),
+                 (a0, beside[:1] * np.ones((N, 1)))):
+        a, b = a.astype(np.float32), b.astype(np.float32)
+        A, B = np.ascontiguousarray(a.T) if a_col else a, b if b_col else np.ascontiguousarray(b.T)
+        c = G.run_gemm(np.tile(A, (batch, 1)), np.tile(B, (batch, 1)), M, N, K, a_col=a_col, b_col=b_col, batch=batch, ab_bf16=False)
+        ref = a.astype(np.float64) @ b.astype(np.float64).T
+        for i in (0, batch - 1):
+            # (the added 2^-126: half the smallest subnormal per addition)
+            P.assert_contraction_close(c[i], ref, ref + 2.0 ** -126, K + 1)
+            rel = np.abs(c[i] - ref) / np.maximum(ref, K * 2.0 ** -126)
+            assert rel.max() <= (K + 1) * 2.0 ** -23
+
+
 @pytest.mark.parametrize("M,N,K,tiny_row,tiny_col", [(70, 70, 300, 5, None), (70, 70, 300, None, 5), (65, 131, 33, 3, 66),
                                                      (257, 129, 40, None, 128), (199, 67, 1024, 130, 65)])
 def test_rows_shared_by_two_tiles_have_one_writer(M, N, K, tiny_row, tiny_col):
