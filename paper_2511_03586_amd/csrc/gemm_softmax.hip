@@ -396,7 +396,7 @@ static perf_status launch_wide(const void *A, const void *B, void *P, int64_t M,
     const float t_min = ek.c_hi > 0.f ? std::fmax(-200.0f / ek.c_hi, -FLT_MAX) : -FLT_MAX;
     const int64_t line = 128 / sizeof(PT);
     const int whole_lines = N % line == 0 && ldp % line == 0 && strideP % line == 0 && aligned(P, 128);
-    const int64_t strips = (M + 31) / 32, per_launch = (kMaxGridX / strips) / 8 * 8;
+    const int64_t strips = (M + 31) / 32, per_launch = (max_blocks(256) / strips) / 8 * 8;
     if (per_launch < 8) return PERF_ERR_UNSUPPORTED;
     for (int64_t b0 = 0; b0 < batch; b0 += per_launch) {
         const int64_t nb = batch - b0 < per_launch ? batch - b0 : per_launch;
@@ -432,7 +432,7 @@ static perf_status launch_fused_staged(const void *A, const void *B, void *P, in
     int64_t group = strips * batch / 512;
     group = group < 1 ? 1 : group > strips ? strips : group;
     const int64_t groups = (strips + group - 1) / group;
-    const int64_t per_launch = (kMaxGridX / groups) / 8 * 8;
+    const int64_t per_launch = (max_blocks(64 * NW) / groups) / 8 * 8;
     if (per_launch < 8) return PERF_ERR_UNSUPPORTED;
     for (int64_t b0 = 0; b0 < batch; b0 += per_launch) {
         const int64_t nb = batch - b0 < per_launch ? batch - b0 : per_launch;

@@ -19,5 +19,7 @@ inline perf_status launch_status()
 
 constexpr int64_t kMaxGridX = 2147483647;  // HIP grid.x limit
 constexpr int64_t kMaxGridYZ = 65535;
+// A dimension of 2^32 threads or more is not refused at launch but cut short.
+constexpr int64_t max_blocks(int threads) { return 4294967295LL / threads; }
 
 }  // namespace perf

@@ -848,7 +848,8 @@ struct GemmArgs {
     hipStream_t st;
 };
 
-// A convolution as launch_staged_conv takes it: NHWC x, KRSC w, NPQK y.
+// A convolution as launch_staged_conv takes it: NHWC x, KRSC w, NPQK y.  (ph may be negative: rows p0 .. of an image are a
+// convolution with ph - p0 sh.)
 struct StagedConv {
     const void *x, *w;
     void *y;

@@ -65,7 +65,21 @@ perf_status launch_staged_conv(const StagedConv &c, int xw_dt, int y_dt)
 {
     // (the grid limits of the 64- and 128-wide tiles, whatever tile runs)
     const int64_t edge = tiles_of(c, 128, 128) >= 256 ? 128 : 64;
-    if ((c.K + edge - 1) / edge > kMaxGridYZ || tiles_of(c, 64, 64) > kMaxGridX) return PERF_ERR_UNSUPPORTED;
+    if ((c.K + edge - 1) / edge > kMaxGridYZ) return PERF_ERR_UNSUPPORTED;
+    if (tiles_of(c, 64, 64) > max_blocks(256) && (c.N > 1 || c.P > 1)) {  // half the images, or half the rows of one
+        StagedConv lo = c, hi = c;
+        if (c.N > 1) {
+            lo.N = c.N / 2, hi.N = c.N - lo.N;
+            hi.x = (const char *)c.x + (int64_t)lo.N * c.H * c.W * c.C * dtype_size(xw_dt);
+        } else {
+            lo.P = c.P / 2, hi.P = c.P - lo.P;
+            hi.ph = c.ph - lo.P * c.sh;
+        }
+        hi.y = (char *)c.y + (int64_t)lo.N * lo.P * c.Q * c.K * dtype_size(y_dt);
+        const perf_status s = launch_staged_conv(lo, xw_dt, y_dt);
+        return s != PERF_OK ? s : launch_staged_conv(hi, xw_dt, y_dt);
+    }
+    if (tiles_of(c, 64, 64) > max_blocks(256)) return PERF_ERR_UNSUPPORTED;
     if (xw_dt == PERF_BF16) return y_dt == PERF_F32 ? launch_typed<uint16_t, float>(c) : launch_typed<uint16_t, uint16_t>(c);
     return y_dt == PERF_F32 ? launch_typed<float, float>(c) : launch_typed<float, uint16_t>(c);
 }

@@ -88,7 +88,14 @@ perf_status launch_staged_gemm(const GemmArgs &g, int ab_dt, int c_dt)
     // (the grid limits of the 64- and 128-wide tiles, whatever tile runs)
     const int64_t edge = tiles_of(g, 128, 128) >= 256 ? 128 : 64;
     if ((g.M + edge - 1) / edge > kMaxGridX || (g.N + edge - 1) / edge > kMaxGridYZ) return PERF_ERR_UNSUPPORTED;
-    if (tiles_of(g, 64, 64) / g.batch > kMaxGridX) return PERF_ERR_UNSUPPORTED;
+    if (tiles_of(g, 64, 64) / g.batch > max_blocks(256)) {  // (larger tiles and those with wave groups are fewer threads)
+        GemmArgs lo = g, hi = g;
+        lo.M = g.M / 512 * 256, hi.M = g.M - lo.M;  // (M is at least 2^13: N fits grid.y)
+        hi.A = (const char *)g.A + lo.M * (g.la == PERF_ROW_MAJOR ? g.lda : 1) * dtype_size(ab_dt);
+        hi.C = (char *)g.C + lo.M * g.ldc * dtype_size(c_dt);
+        const perf_status s = launch_staged_gemm(lo, ab_dt, c_dt);
+        return s != PERF_OK ? s : launch_staged_gemm(hi, ab_dt, c_dt);
+    }
     // the larger tiles hold 32-bit element offsets
     const int64_t v = ab_dt == PERF_BF16 ? 8 : 4;
     const bool few = (g.la == PERF_ROW_MAJOR ? g.K < 8 : g.M < v) || (g.lb == PERF_COL_MAJOR ? g.K < 8 : g.N < v);

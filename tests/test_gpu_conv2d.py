@@ -301,3 +301,31 @@ def test_fp32_operands_that_split_badly(C, R, stride):
                      variant=7)
     K = R * R * C
     assert np.abs(y / (K * np.float64(v) ** 2) - 1).max() <= split_bound(K)
+
+
+@pytest.mark.parametrize("N,H", [(1, 1 << 15), (3, 11000)])
+def test_more_tiles_than_a_launch_holds(N, H):
+    """2^24 tiles and more of 256 threads (a dimension of 2^32 threads is cut short without an error): the images, or the rows of
+    one, are dealt to several launches. 75 GB."""
+    import torch
+    import paper_2511_03586_amd as perf
+    if torch.cuda.mem_get_info()[0] < (100 << 30):
+        pytest.skip("needs 100 GB of device memory")
+    W, K, rows = 1 << 15, 32, (0, 1, H // 2 - 2, H // 2 - 1, H // 2, H // 2 + 1, H - 1)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(1)
+    x = torch.randint(-4, 5, (N, H, W), generator=g, device="cuda", dtype=torch.int8).float()
+    w = torch.randint(-2, 3, (K, 3, 3), generator=g, device="cuda").float()
+    y = torch.full((N, H, W, K), 7777.0, dtype=torch.bfloat16, device="cuda")
+    perf.perf_conv2d(x.data_ptr(), w.data_ptr(), y.data_ptr(), N, H, W, 1, K, 3, 3, 1, 1, 1, 1, perf.PERF_F32, perf.PERF_BF16, G.stream())
+    for n in range(N):
+        for h in range(0, H, 2048):
+            assert not bool((y[n, h:h + 2048] == 7776.0).any())  # (7777 as bf16)
+        for r in rows:
+            want = torch.zeros((W, K), device="cuda")
+            for i in range(3):
+                if 0 <= r + i - 1 < H:
+                    line = torch.nn.functional.pad(x[n, r + i - 1], (1, 1))
+                    for j in range(3):
+                        want += line[j:j + W, None] * w[None, :, i, j]
+            assert torch.equal(y[n, r], want.to(torch.bfloat16)), (n, r)  # (small integers: exact)

@@ -376,3 +376,18 @@ def test_deterministic():
     c0 = G.run_gemm(d["a_bf16"], d["b_bf16"], 512, 512, 512)
     c1 = G.run_gemm(d["a_bf16"], d["b_bf16"], 512, 512, 512)
     assert np.array_equal(c0, c1)
+
+
+def test_more_tiles_than_a_launch_holds():
+    """2^24 tiles and more of 256 threads (a dimension of 2^32 threads is cut short without an error): B one value."""
+    import torch
+    import paper_2511_03586_amd as perf
+    big = (1 << 30) + 5
+    x = torch.zeros(big, dtype=torch.bfloat16, device="cuda")
+    x[::1 << 20] = 3.0
+    x[-1] = 5.0
+    one = torch.full((8,), 2.0, dtype=torch.bfloat16, device="cuda")
+    c = torch.full((big,), 7.0, dtype=torch.bfloat16, device="cuda")
+    perf.perf_gemm(x.data_ptr(), one.data_ptr(), c.data_ptr(), big, 1, 1, perf.PERF_ROW_MAJOR, 1, perf.PERF_COL_MAJOR, 1, 1, 1, 0, 0, 0,
+                   1.0, perf.PERF_BF16, perf.PERF_BF16, G.stream())
+    assert bool((c == 2.0 * x).all())

@@ -201,3 +201,18 @@ def test_deterministic():
     p1 = G.run_gemm_softmax(a, b, 256, 512, 64, alpha=0.125, batch=2)
     p2 = G.run_gemm_softmax(a, b, 256, 512, 64, alpha=0.125, batch=2)
     assert np.array_equal(p1, p2)
+
+
+def test_more_strips_than_a_launch_holds():
+    """2^24 strips and more of 256 threads (a dimension of 2^32 threads is cut short without an error)."""
+    import torch
+    import paper_2511_03586_amd as perf
+    batch, N, K = (1 << 24) + 3, 8, 8
+    a = torch.ones((batch, K), dtype=torch.bfloat16, device="cuda")
+    b = torch.zeros((N, K), dtype=torch.bfloat16, device="cuda")
+    b[3] = 1.0
+    p = torch.zeros((batch, N), dtype=torch.float32, device="cuda")
+    perf.perf_gemm_softmax(a.data_ptr(), b.data_ptr(), p.data_ptr(), 1, N, K, K, K, N, batch, K, 0, N, 0.25, perf.PERF_BF16, perf.PERF_F32,
+                           G.stream())
+    want = torch.softmax(torch.tensor([0.0, 0, 0, 2, 0, 0, 0, 0], dtype=torch.float64), 0).to("cuda")
+    assert bool(((p - want).abs() <= 1e-6).all())
