@@ -260,14 +260,14 @@ template <> __device__ __forceinline__ void store_c<uint16_t>(uint16_t *p, float
 // Write a wave's accumulators to row-major C.  Accumulator element e of a 32x32 tile is
 // row 8*(e/4) + 4*(lane/32) + e%4, column lane%32, so one store instruction writes two
 // 128-byte row segments.  (row0, col0) is the wave tile's origin in C; rows below row_from and columns below
-// col_from are not written.
-template <int TM, int TN, typename CT>
+// col_from are not written (FROM).
+template <int TM, int TN, typename CT, bool FROM = false>
 __device__ __forceinline__ void store_tile(const WaveTile<TM, TN> &t, CT *C, int64_t ldc, int M, int N, int row0,
                                            int col0, float alpha, int lane, int row_from = 0, int col_from = 0)
 {
     const int r_l = row0 + 4 * (lane >> 5), c_l = col0 + (lane & 31);
     CT *base = C + (int64_t)r_l * ldc + c_l;
-    if (row0 + 32 * TM <= M && col0 + 32 * TN <= N && row0 >= row_from && col0 >= col_from) {
+    if (row0 + 32 * TM <= M && col0 + 32 * TN <= N && (!FROM || (row0 >= row_from && col0 >= col_from))) {
 #pragma unroll
         for (int i = 0; i < TM; ++i)
 #pragma unroll
@@ -285,7 +285,7 @@ __device__ __forceinline__ void store_tile(const WaveTile<TM, TN> &t, CT *C, int
                 CT *p = base + (int64_t)dr * ldc;
 #pragma unroll
                 for (int j = 0; j < TN; ++j)
-                    if (r_l + dr < M && c_l + j * 32 < N && r_l + dr >= row_from && c_l + j * 32 >= col_from)
+                    if (r_l + dr < M && c_l + j * 32 < N && (!FROM || (r_l + dr >= row_from && c_l + j * 32 >= col_from)))
                         store_c<CT>(p + j * 32, alpha * t.acc[i][j][e]);
             }
     }

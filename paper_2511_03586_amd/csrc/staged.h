@@ -835,7 +835,8 @@ __global__ __launch_bounds__(64 * WM * WN * KG, (StagedShape<T, TM, TN, WM, WN, 
                         t.acc[i][j][e] += red[(((h * NW + wave) * TM * TN + i * TN + j) * 16 + e) * 64 + lane];
     }
     CT *Ct = C + (int64_t)blockIdx.y * strideC + m0 * ldc + n0;
-    store_tile<TM, TN, CT>(t, Ct, ldc, (int)min((int64_t)BM, M - m0), (int)min((int64_t)BN, N - n0), wm * 32 * TM, wn * 32 * TN,
+    constexpr bool kEarly = ASrc::kBlock > 1 || BSrc::kBlock > 1;  // (tiles that can start early)
+    store_tile<TM, TN, CT, kEarly>(t, Ct, ldc, (int)min((int64_t)BM, M - m0), (int)min((int64_t)BN, N - n0), wm * 32 * TM, wn * 32 * TN,
                            alpha, lane, (int)((int64_t)tm * BM - m0), (int)((int64_t)tn * BN - n0));
 }
 
