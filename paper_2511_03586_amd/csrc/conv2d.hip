@@ -1698,12 +1698,19 @@ static perf_status conv2d_impl(const void *x, const void *w, void *y, int64_t N,
                             (K + 15) / 16 <= kMaxGridYZ;
     // staged implicit GEMM: worth it from 32 output channels on (a 64-wide tile is then at least half used); bf16 with
     // fewer than 8 channels loads element by element there (8x224x224x3->64 62 us against 34 a filter row at a time)
-    const bool staged_ok = K >= 32 && (xw_dt == PERF_F32 || (C >= 8 && R * S * C >= 16));
-    // a filter of one tap on every pixel is a plain GEMM (32x28x28 256->256 bf16: 12.1 us as a convolution, 9.9 so; where
-    // the GEMM would not take tiles of 128 x 128 either, the convolution kernel stays: 5x17x97 256->128 7.7 us against 8.0)
-    const int64_t tiles128 = ((N * P * Q + 127) / 128) * ((K + 127) / 128);
-    if (variant == kConvAuto && R == 1 && S == 1 && stride_h == 1 && stride_w == 1 && pad_h == 0 && pad_w == 0 && K >= 16 &&
-        C >= 8 && K <= 64 * kMaxGridYZ && !(xw_dt == PERF_F32 && y_dt == PERF_BF16) && (!mfma_ok || tiles128 >= 192))
+    // a filter of one tap on every pixel is a plain GEMM.  Where the convolution has its own MFMA kernel the GEMM is
+    // ahead with 256 and more output channels on many tiles only (32x28x28 256->256 9.8 us against 13.4, but 128x28x28 64->64
+    // 27 against 8: its 128-wide tiles); else it is ahead of the staged convolution unless that has narrow outputs on many
+    // pixels (401408 pixels bf16 16->256 60 us against 125, 16->32 42 against 37).
+    const int64_t px = N * P * Q, tiles128 = ((px + 127) / 128) * ((K + 127) / 128);
+    const bool one_tap = R == 1 && S == 1 && stride_h == 1 && stride_w == 1 && pad_h == 0 && pad_w == 0 && K >= 16 && C >= 8;
+    const bool staged_ok = (K >= 32 && (xw_dt == PERF_F32 || (C >= 8 && R * S * C >= 16))) ||
+                           (one_tap && (xw_dt == PERF_F32 || K >= 32 || !smallc_ok || C >= 32));
+    // little work in short reductions: a thread per output is done before a tile is staged (14x14 8->64 3.6 us against 4.5 as a
+    // GEMM, 14x14 20->32 at stride 2 4.3 against 7.0; but 14x14 32->64 6.6 against 5.1)
+    const bool few_macs = !mfma_ok && R * S * C <= 20 && px * K * R * S * C <= (1 << 20);
+    if (variant == kConvAuto && one_tap && !few_macs && K <= 64 * kMaxGridYZ && !(xw_dt == PERF_F32 && y_dt == PERF_BF16) &&
+        (mfma_ok ? K >= 256 && tiles128 >= 192 : K > 64 || px < (xw_dt == PERF_F32 ? 65536 : 16384)))
         return perf_gemm(x, w, y, N * P * Q, K, C, PERF_ROW_MAJOR, C, PERF_COL_MAJOR, C, K, 1, 0, 0, 0, 1.0f, xw_dt, y_dt, stream);
     // few tiles with a long reduction: the staged kernel's wave groups share it (8x28x28 256->128 12.8 us against 16.5 on the
     // shared main loop, 20x20 256->256 12.2 against 16.1, 14x14 128->64 with 5x5 taps about even at 1600)
@@ -1719,7 +1726,7 @@ static perf_status conv2d_impl(const void *x, const void *w, void *y, int64_t N,
                   : (wres_ok && wres_rounds <= 2) ? kConvWres
                   : wreg_ok                     ? kConvWreg
                   : (mfma_ok && !few_long)      ? kConvMfma
-                  : staged_ok ? kConvStaged
+                  : (staged_ok && !few_macs) ? kConvStaged
                   : (rowmfma_ok && N * P * Q >= 16384)          ? kConvRowMfma
                   : (C < 32 && smallc_ok && N * P * Q >= 16384) ? kConvSmallC
                                                                 : kConvDirect;

@@ -274,6 +274,11 @@ def test_deterministic():
     dict(N=3, H=7, W=5, C=24, K=17, R=1, S=1, pad=0),          # one tap on every pixel: the GEMM
     dict(N=2, H=9, W=9, C=96, K=64, R=1, S=1, pad=0),
     dict(N=2, H=9, W=9, C=40, K=64, R=1, S=1, pad=0, stride=2),   # one tap, strided: no plain GEMM
+    dict(N=1, H=14, W=14, C=8, K=64, R=1, S=1, pad=0),         # little work: a thread per output
+    dict(N=3, H=14, W=14, C=20, K=33, R=1, S=1, pad=0, stride=2),
+    dict(N=8, H=46, W=45, C=8, K=24, R=1, S=1, pad=0),         # narrow outputs on many pixels: bf16 channel-blocked
+    dict(N=8, H=46, W=45, C=40, K=24, R=1, S=1, pad=0),        # ... the staged convolution
+    dict(N=8, H=91, W=91, C=9, K=31, R=1, S=1, pad=0),
 ])
 def test_staged_conv_edges(kw):
     """The register-staged implicit GEMM and the one-tap route, bf16 and fp32 operands, by the library's own choice."""
