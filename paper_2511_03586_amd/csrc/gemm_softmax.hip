@@ -483,10 +483,18 @@ extern "C" perf_status perf_gemm_softmax(const void *A, const void *B, void *P, 
         if (N <= 256) PERF_WIDE(2, uint16_t);
         PERF_WIDE(4, uint16_t);
     }
-    // (a few strips of long rows are faster as two launches, which spread the columns over the chip: 100x769x128 8 us
-    // against 13; up to more strips where the GEMM runs its direct kernel on tall tiles: 8 x (499x816x64) 11.3 against 12.0)
-    const int64_t least = K % 32 == 0 && M >= 64 ? 192 : 64;
-    if (loads_ok && lda <= (1 << 20) && ldb <= (1 << 20) && p_dt == PERF_F32 && N <= 1024 && K <= 512 && (N <= 512 || strips >= least)) {
+    // A few strips of long rows or long reductions are faster as two launches, which spread the columns over the chip and
+    // pipeline deeper (in us, strips on this kernel against two launches): 100x769x128 13 against 8, up to more strips where the
+    // GEMM runs its direct kernel on tall tiles (8 x (499x816x64) 12.0 against 11.3); with wider K-ranges from more strips on:
+    // 16x200x256 6.8 against 6.4 but 64 x (64x200x256) 7.8 against 8.8, 32x300x384 13.1 against 7.2, 64 x (100x300x384) 16.1
+    // against 13.4, 64 x (300x300x512) 30.6 against 46.6, 64 x (16x1024x384) 26 against 21, 64 x (300x1024x384) 59 against 71.
+    int64_t least = 0;
+    if (N > 512) least = K % 32 == 0 && M >= 64 ? 192 : 64;
+    if (K > 128 && N > 128) {
+        const int64_t more = N <= 256 ? (K <= 256 ? 96 : 128) : K <= 256 ? 96 : 400;
+        least = least > more ? least : more;
+    }
+    if (loads_ok && lda <= (1 << 20) && ldb <= (1 << 20) && p_dt == PERF_F32 && N <= 1024 && K <= 512 && strips >= least) {
         if (N <= 128) PERF_WIDE(1, float);
         if (N <= 256) PERF_WIDE(2, float);
         if (N <= 512) PERF_WIDE(4, float);
