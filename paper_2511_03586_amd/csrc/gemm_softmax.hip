@@ -4,7 +4,7 @@
 // way the paper's fusion moves join producer and consumer scopes, Sections 2.2 and 3.1: the
 // score matrix never goes to memory, so the traffic is the operands plus one write of P).
 //
-//  * gemm_softmax_kernel: bf16 operands, both K-contiguous, K = 64, N = 128, 256 or 512, fp32 P.  A
+//  * gemm_softmax_kernel: bf16 operands, both K-contiguous, K = 64, N = 128, 256 or 512 (K = 128: N = 128), fp32 P.  A
 //    workgroup of 8 waves takes strips of 128 rows x all N columns of one matrix; each wave 16 rows x N
 //    as up to 32 accumulators of 16x16 (128 registers), computed with B as the MFMA's row
 //    operand, so that a lane holds 4 consecutive columns per accumulator and all of a
@@ -469,9 +469,10 @@ extern "C" perf_status perf_gemm_softmax(const void *A, const void *B, void *P, 
     // the header names.
     const bool loads_ok = ab_dt == PERF_BF16 && K % 8 == 0 && lda % 8 == 0 && ldb % 8 == 0 && strideA % 8 == 0 && strideB % 8 == 0 &&
                           aligned(A, 16) && aligned(B, 16) && M <= (1 << 24);
-    // whole chunks of 128 columns, K = 64, fp32 P with 16-byte aligned rows: B stays in the LDS for several strips, the staged
+    // whole chunks of 128 columns, K = 64 (or what else the LDS holds: 128 x 128, 64 x (512x128x128) 7.0 us against 8.9 with the
+    // strip kernel, but 300 x (16x128x128) 7.3 against 5.7), fp32 P with 16-byte aligned rows: B stays in the LDS for several strips, the staged
     // write-out (512 x (512x512x64) 104 us against 116 with the strip kernel, 300 x (256x128x64) 13.2 against 14.5)
-    const bool staged = loads_ok && K == 64 && p_dt == PERF_F32 && lda <= (1 << 21) && ldb <= (1 << 21) && ldp % 4 == 0 &&
+    const bool staged = loads_ok && (K == 64 || (K == 128 && N == 128 && M >= 128)) && p_dt == PERF_F32 && lda <= (1 << 21) && ldb <= (1 << 21) && ldp % 4 == 0 &&
                         strideP % 4 == 0 && aligned(P, 16);
     if (staged && N == 512) return launch_fused_staged<32>(A, B, P, M, N, K, lda, ldb, ldp, batch, strideA, strideB, strideP, alpha, st);
     if (staged && N == 256) return launch_fused_staged<16>(A, B, P, M, N, K, lda, ldb, ldp, batch, strideA, strideB, strideP, alpha, st);
