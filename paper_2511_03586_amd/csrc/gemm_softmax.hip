@@ -214,7 +214,7 @@ template <int NT, typename PT>
 __global__ __launch_bounds__(256, 2) void gemm_softmax_wide_kernel(const uint16_t *__restrict__ A, const uint16_t *__restrict__ B,
                                                                    PT *__restrict__ P, int M, int N, int K, int64_t lda,
                                                                    int64_t ldb, int64_t ldp, int64_t strideA, int64_t strideB,
-                                                                   int64_t strideP, ExpConst ek, float t_min, int strips, int xcd_remap,
+                                                                   int64_t strideP, ExpConst ek, float t_min, int strips, int eights,
                                                                    int whole_lines)
 {
     constexpr int kStageB = 128 * NT * kRowBytes, kStageA = 32 * kRowBytes, kStage = kStageB + kStageA;
@@ -224,9 +224,9 @@ __global__ __launch_bounds__(256, 2) void gemm_softmax_wide_kernel(const uint16_
     __shared__ float red[2][4][32];
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    // (all strips of a matrix on one XCD where the batch allows it: B comes over the fabric once)
+    // (all strips of a matrix on one XCD, but for the last matrices of a batch that 8 does not divide: B comes over the fabric once)
     int si, bz;
-    if (xcd_remap) {
+    if ((int)blockIdx.x < eights * 8 * strips) {
         const int xcd = blockIdx.x & 7, j = blockIdx.x >> 3;
         si = j % strips;
         bz = (j / strips) * 8 + xcd;
@@ -402,7 +402,7 @@ static perf_status launch_wide(const void *A, const void *B, void *P, int64_t M,
         const int64_t nb = batch - b0 < per_launch ? batch - b0 : per_launch;
         hipLaunchKernelGGL(kern, dim3((unsigned)(strips * nb)), dim3(256), kLds, st, (const uint16_t *)A + b0 * strideA,
                            (const uint16_t *)B + b0 * strideB, (PT *)P + b0 * strideP, (int)M, (int)N, (int)K, lda, ldb, ldp,
-                           strideA, strideB, strideP, ek, t_min, (int)strips, nb % 8 == 0 ? 1 : 0, whole_lines);
+                           strideA, strideB, strideP, ek, t_min, (int)strips, (int)(nb / 8), whole_lines);
     }
     return launch_status();
 }
