@@ -196,7 +196,8 @@ __global__ __launch_bounds__(64 * kFusedWaves, 1) void gemm_softmax_kernel(const
     }
 }
 
-// Longer and ragged rows: N <= 1024, K any multiple of 8, P of any alignment.  A workgroup of 4 waves owns 32 rows x all
+// Longer and ragged rows: N <= 1024, K any multiple of 8, P of any alignment.  A workgroup of 4 waves (2 up to 64 columns:
+// 64 x (300x64x128) 5.3 us against 6.3) owns 32 rows x all
 // N columns; wave w the NT tiles of 32 columns from 32 NT w on, as 32x32 accumulators (128 registers at NT = 8) with B as
 // the MFMA's row operand, so that a lane's values belong to ONE row: row maxima and sums are in-lane plus one lane
 // exchange, and one LDS exchange between the waves.  B does not fit the LDS (1024 x 128 bf16 are 256 KiB): both
@@ -210,18 +211,18 @@ __global__ __launch_bounds__(64 * kFusedWaves, 1) void gemm_softmax_kernel(const
 // against 17.9; 32 x (600x301x64) 17.0 against 13.7 at NT = 4)
 constexpr int wide_stages(int nt) { return nt <= 2 ? 2 : 1; }
 constexpr int wide_chunk(int nt) { return nt < 2 ? nt : 2; }  // tiles of a wave that are staged at a time
-template <int NT, typename PT>
-__global__ __launch_bounds__(256, 2) void gemm_softmax_wide_kernel(const uint16_t *__restrict__ A, const uint16_t *__restrict__ B,
+template <int NT, typename PT, int NW>
+__global__ __launch_bounds__(64 * NW, 2) void gemm_softmax_wide_kernel(const uint16_t *__restrict__ A, const uint16_t *__restrict__ B,
                                                                    PT *__restrict__ P, int M, int N, int K, int64_t lda,
                                                                    int64_t ldb, int64_t ldp, int64_t strideA, int64_t strideB,
                                                                    int64_t strideP, ExpConst ek, float t_min, int strips, int eights,
                                                                    int whole_lines)
 {
-    constexpr int kStageB = 128 * NT * kRowBytes, kStageA = 32 * kRowBytes, kStage = kStageB + kStageA;
+    constexpr int kStageB = 32 * NW * NT * kRowBytes, kStageA = 32 * kRowBytes, kStage = kStageB + kStageA;
     constexpr int NST = wide_stages(NT);
     constexpr int LB = 2 * NT, kLoads = LB + 1;
     extern __shared__ __attribute__((aligned(1024))) char smem[];
-    __shared__ float red[2][4][32];
+    __shared__ float red[2][NW][32];
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     // (all strips of a matrix on one XCD, but for the last matrices of a batch that 8 does not divide: B comes over the fabric once)
@@ -240,7 +241,7 @@ __global__ __launch_bounds__(256, 2) void gemm_softmax_wide_kernel(const uint16_
     const rsrc_t ra = make_rsrc(Ab, (uint32_t)(((int64_t)(rows - 1) * lda + K) * 2));
     const rsrc_t rb = make_rsrc(Bb, (uint32_t)(((int64_t)(N - 1) * ldb + K) * 2));
 
-    // load i of wave w: tile rows (4 i + w) * 16 .. +15; lane l row l / 4, the chunk stored at position l % 4
+    // load i of wave w: tile rows (NW i + w) * 16 .. +15; lane l row l / 4, the chunk stored at position l % 4
     const int lrow = lane >> 2;
     uint32_t vb[LB];
     int kb;  // first K of this lane's chunk in a step (the swizzle of a row depends on its low four bits only)
@@ -248,7 +249,7 @@ __global__ __launch_bounds__(256, 2) void gemm_softmax_wide_kernel(const uint16_
         const int ch = load_chunk(lrow, lane);
         kb = ch * 8;
 #pragma unroll
-        for (int i = 0; i < LB; ++i) vb[i] = (uint32_t)(min((i * 4 + wave) * 16 + lrow, N - 1) * ldb * 2) + ch * 16;
+        for (int i = 0; i < LB; ++i) vb[i] = (uint32_t)(min((i * NW + wave) * 16 + lrow, N - 1) * ldb * 2) + ch * 16;
     }
     const uint32_t va = (uint32_t)(min((wave & 1) * 16 + lrow, rows - 1) * lda * 2) + kb * 2;
     auto issue = [&](int ks) {
@@ -256,7 +257,7 @@ __global__ __launch_bounds__(256, 2) void gemm_softmax_wide_kernel(const uint16_
         const bool in = ks * 32 + kb < K;
         const uint32_t so = (uint32_t)ks * kRowBytes;
 #pragma unroll
-        for (int i = 0; i < LB; ++i) issue_load_to(rb, in ? vb[i] : kOutOfRange, so, st + (i * 4 + wave) * 16 * kRowBytes);
+        for (int i = 0; i < LB; ++i) issue_load_to(rb, in ? vb[i] : kOutOfRange, so, st + (i * NW + wave) * 16 * kRowBytes);
         issue_load_to(ra, in ? va : kOutOfRange, so, st + kStageB + (wave & 1) * 16 * kRowBytes);  // (waves 2, 3: the same again)
     };
     float16_t acc[NT];
@@ -311,7 +312,8 @@ __global__ __launch_bounds__(256, 2) void gemm_softmax_wide_kernel(const uint16_
     swap32(m, x, y);
     red[0][wave][row] = __builtin_fmaxf(x, y);  // (both halves write the same)
     __syncthreads();
-    m = __builtin_fmaxf(__builtin_fmaxf(red[0][0][row], red[0][1][row]), __builtin_fmaxf(red[0][2][row], red[0][3][row]));
+    m = __builtin_fmaxf(red[0][0][row], red[0][1][row]);
+    if constexpr (NW == 4) m = __builtin_fmaxf(m, __builtin_fmaxf(red[0][2][row], red[0][3][row]));
 #pragma unroll
     for (int j = 0; j < NT; ++j)
 #pragma unroll
@@ -330,7 +332,9 @@ __global__ __launch_bounds__(256, 2) void gemm_softmax_wide_kernel(const uint16_
     swap32(z, x, y);
     red[1][wave][row] = x + y;
     __syncthreads();  // (the operand stages are free since the last step's barrier)
-    const float inv = 1.0f / ((red[1][0][row] + red[1][1][row]) + (red[1][2][row] + red[1][3][row]));
+    float sum = red[1][0][row] + red[1][1][row];
+    if constexpr (NW == 4) sum += red[1][2][row] + red[1][3][row];
+    const float inv = 1.0f / sum;
 
     // write-out, 4 tiles = 128 columns at a time: 32 pieces of 16 bytes per row, piece s at position s ^ row
     constexpr int NC = wide_chunk(NT), kPieces = 8 * NC, kRowsPer = 64 / kPieces;
@@ -378,14 +382,14 @@ __global__ __launch_bounds__(256, 2) void gemm_softmax_wide_kernel(const uint16_
     }
 }
 
-template <int NT, typename PT>
+template <int NT, typename PT, int NW = 4>
 static perf_status launch_wide(const void *A, const void *B, void *P, int64_t M, int64_t N, int64_t K, int64_t lda, int64_t ldb,
                                int64_t ldp, int64_t batch, int64_t strideA, int64_t strideB, int64_t strideP, float alpha,
                                hipStream_t st)
 {
-    constexpr int kStages = wide_stages(NT) * (128 * NT + 32) * kRowBytes, kOut = 4 * 32 * 128 * wide_chunk(NT);
+    constexpr int kStages = wide_stages(NT) * (32 * NW * NT + 32) * kRowBytes, kOut = NW * 32 * 128 * wide_chunk(NT);
     constexpr int kLds = kStages > kOut ? kStages : kOut;
-    auto kern = gemm_softmax_wide_kernel<NT, PT>;
+    auto kern = gemm_softmax_wide_kernel<NT, PT, NW>;
     static std::atomic<bool> attr_done{false};  // (idempotent per-function setting)
     if (!attr_done) {
         if (hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, kLds) != hipSuccess)
@@ -396,11 +400,11 @@ static perf_status launch_wide(const void *A, const void *B, void *P, int64_t M,
     const float t_min = ek.c_hi > 0.f ? std::fmax(-200.0f / ek.c_hi, -FLT_MAX) : -FLT_MAX;
     const int64_t line = 128 / sizeof(PT);
     const int whole_lines = N % line == 0 && ldp % line == 0 && strideP % line == 0 && aligned(P, 128);
-    const int64_t strips = (M + 31) / 32, per_launch = (max_blocks(256) / strips) / 8 * 8;
+    const int64_t strips = (M + 31) / 32, per_launch = (max_blocks(64 * NW) / strips) / 8 * 8;
     if (per_launch < 8) return PERF_ERR_UNSUPPORTED;
     for (int64_t b0 = 0; b0 < batch; b0 += per_launch) {
         const int64_t nb = batch - b0 < per_launch ? batch - b0 : per_launch;
-        hipLaunchKernelGGL(kern, dim3((unsigned)(strips * nb)), dim3(256), kLds, st, (const uint16_t *)A + b0 * strideA,
+        hipLaunchKernelGGL(kern, dim3((unsigned)(strips * nb)), dim3(64 * NW), kLds, st, (const uint16_t *)A + b0 * strideA,
                            (const uint16_t *)B + b0 * strideB, (PT *)P + b0 * strideP, (int)M, (int)N, (int)K, lda, ldb, ldp,
                            strideA, strideB, strideP, ek, t_min, (int)strips, (int)(nb / 8), whole_lines);
     }
@@ -496,6 +500,7 @@ extern "C" perf_status perf_gemm_softmax(const void *A, const void *B, void *P, 
         least = least > more ? least : more;
     }
     if (loads_ok && lda <= (1 << 20) && ldb <= (1 << 20) && p_dt == PERF_F32 && N <= 1024 && K <= 512 && strips >= least) {
+        if (N <= 64) return launch_wide<1, float, 2>(A, B, P, M, N, K, lda, ldb, ldp, batch, strideA, strideB, strideP, alpha, st);
         if (N <= 128) PERF_WIDE(1, float);
         if (N <= 256) PERF_WIDE(2, float);
         if (N <= 512) PERF_WIDE(4, float);

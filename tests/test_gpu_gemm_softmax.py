@@ -95,6 +95,7 @@ def test_staged_write_out_widths_ragged_strips_and_leading_dimensions():
     (33, 257, 136, 1, 257), (64, 512, 128, 2, 512), (17, 511, 200, 1, 511), (33, 513, 40, 32, 513), (1, 640, 64, 64, 640),
     (33, 641, 96, 32, 641), (20, 768, 80, 64, 768), (1, 769, 512, 64, 771), (33, 896, 64, 32, 896), (1, 897, 8, 65, 897),
     (33, 1023, 80, 32, 1023), (32, 1024, 64, 64, 1024), (70, 1020, 64, 64, 1021), (2, 1025, 64, 3, 1025),
+    (33, 31, 40, 12, 31), (40, 63, 24, 9, 70), (32, 64, 128, 3, 64), (33, 65, 64, 10, 65),   # (2 waves up to 64 columns)
     (127, 128, 128, 2, 128), (128, 128, 128, 3, 128), (300, 128, 128, 9, 132),   # (127 rows here, 128 and more with B in the LDS)
 ])
 def test_strip_kernel_edges(M, N, K, batch, ldp):
