@@ -336,7 +336,7 @@ __global__ __launch_bounds__(64 * NW, 2) void gemm_softmax_wide_kernel(const uin
     if constexpr (NW == 4) sum += red[1][2][row] + red[1][3][row];
     const float inv = 1.0f / sum;
 
-    // write-out, 4 tiles = 128 columns at a time: 32 pieces of 16 bytes per row, piece s at position s ^ row
+    // write-out, NC tiles = up to 64 columns at a time: kPieces pieces of 16 bytes per row, piece s at position s ^ row
     constexpr int NC = wide_chunk(NT), kPieces = 8 * NC, kRowsPer = 64 / kPieces;
     char *const stage = smem + wave * (32 * 16 * kPieces);
     const int piece = lane % kPieces;

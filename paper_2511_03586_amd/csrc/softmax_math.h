@@ -23,10 +23,10 @@ __device__ __forceinline__ float exp_scaled(float t, float c_hi, float c_lo)
 }
 
 // The same with the clamp where the result has become 0 (t_min = -200 / c_hi, or -FLT_MAX): nothing overflows, so no
-// result needs to be discarded.
+// result needs to be discarded.  A NaN stays one (v_maximum3_f32).
 __device__ __forceinline__ float exp_scaled_above(float t, float c_hi, float c_lo, float t_min)
 {
-    t = __builtin_fmaxf(t, t_min);
+    t = __builtin_elementwise_maximum(t, t_min);
     const float p = t * c_hi;
     const float r = __builtin_fmaf(t, c_lo, __builtin_fmaf(t, c_hi, -p));
     const float e = __builtin_amdgcn_exp2f(p);

@@ -218,3 +218,15 @@ def test_more_strips_than_a_launch_holds():
                            G.stream())
     want = torch.softmax(torch.tensor([0.0, 0, 0, 2, 0, 0, 0, 0], dtype=torch.float64), 0).to("cuda")
     assert bool(((p - want).abs() <= 1e-6).all())
+
+
+@pytest.mark.parametrize("M,N,K", [(40, 60, 64), (40, 300, 128), (70, 500, 64), (200, 777, 80), (128, 512, 64)])
+def test_nan_scores_are_not_probabilities(M, N, K):
+    """A NaN among the operands makes NaN of the rows that it meets, whichever kernel runs (never a probability of 0)."""
+    a, b = _inputs(M, N, K, 8)
+    a[1, 5, 3] = 0x7FC0
+    b[2, N - 1, 0] = 0xFFC1
+    p = G.run_gemm_softmax(a, b, M, N, K, alpha=0.125, batch=8)
+    assert np.all(np.isnan(p[1, 5])) and np.all(np.isnan(p[2]))
+    p[1, 5], p[2] = 0, 0
+    assert np.all(np.isfinite(p))
