@@ -179,6 +179,7 @@ __global__ __launch_bounds__(256) void bn_finalize_kernel(const float *__restric
     }
 }
 
+template <int THREADS = 256>
 __device__ __forceinline__ double bn_block_sum_f64(double v, double *red)
 {
 #pragma unroll
@@ -186,7 +187,10 @@ __device__ __forceinline__ double bn_block_sum_f64(double v, double *red)
     __syncthreads();  // red may still be read from the previous use
     if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
     __syncthreads();
-    return (red[0] + red[1]) + (red[2] + red[3]);
+    double sum = (red[0] + red[1]) + (red[2] + red[3]);
+#pragma unroll
+    for (int w = 4; w < THREADS / 64; w += 4) sum += (red[w] + red[w + 1]) + (red[w + 2] + red[w + 3]);
+    return sum;
 }
 
 // Statistics of channel c from its segments' (mean, M2), at most kBnFuseSegs = one per thread:
@@ -272,29 +276,32 @@ __global__ __launch_bounds__(256) void bn_apply_kernel(const XT *__restrict__ x,
 }
 
 // Planes of fewer elements than a chunk of 16 bytes: a workgroup per channel, an element at a time, sums in double.
-template <typename XT, typename PT, typename YT>
-__global__ __launch_bounds__(256) void bn_small_kernel(const XT *__restrict__ x, const PT *__restrict__ gamma,
+template <typename XT, typename PT, typename YT, int THREADS>
+__global__ __launch_bounds__(THREADS) void bn_small_kernel(const XT *__restrict__ x, const PT *__restrict__ gamma,
                                                        const PT *__restrict__ beta, YT *__restrict__ y,
                                                        float *__restrict__ mean_out, float *__restrict__ rstd_out, int HW, int C,
                                                        int N, float eps)
 {
-    __shared__ double red[4];
+    __shared__ double red[THREADS / 64];
     const int c = blockIdx.x, total = N * HW;
     auto at = [&](int i) { return ((int64_t)(i / HW) * C + c) * HW + i % HW; };
     double sum = 0.0, sq = 0.0;
-    for (int i = threadIdx.x; i < total; i += 256) sum += (double)Elem<XT>::load1(x + at(i));
-    const double mean = bn_block_sum_f64(sum, red) / total;
-    for (int i = threadIdx.x; i < total; i += 256) {
+#pragma unroll(THREADS == 1024 ? 4 : 1)
+    for (int i = threadIdx.x; i < total; i += THREADS) sum += (double)Elem<XT>::load1(x + at(i));
+    const double mean = bn_block_sum_f64<THREADS>(sum, red) / total;
+#pragma unroll(THREADS == 1024 ? 4 : 1)
+    for (int i = threadIdx.x; i < total; i += THREADS) {
         const double d = (double)Elem<XT>::load1(x + at(i)) - mean;
         sq += d * d;
     }
-    const float mu = (float)mean, rstd = (float)(1.0 / sqrt(bn_block_sum_f64(sq, red) / total + (double)eps));
+    const float mu = (float)mean, rstd = (float)(1.0 / sqrt(bn_block_sum_f64<THREADS>(sq, red) / total + (double)eps));
     const float scale = rstd * Elem<PT>::load1(gamma + c), b = Elem<PT>::load1(beta + c);
     if (threadIdx.x == 0) {
         if (mean_out) mean_out[c] = mu;
         if (rstd_out) rstd_out[c] = rstd;
     }
-    for (int i = threadIdx.x; i < total; i += 256)
+#pragma unroll(THREADS == 1024 ? 4 : 1)
+    for (int i = threadIdx.x; i < total; i += THREADS)
         Elem<YT>::store1(y + at(i), __builtin_fmaf(Elem<XT>::load1(x + at(i)) - mu, scale, b));
 }
 
@@ -346,7 +353,12 @@ static void launch_bn(const BnArgs &a, bool vec)
 {
     constexpr int E = Elem<XT>::kPerChunk;
     if (a.HW < E) {
-        hipLaunchKernelGGL((bn_small_kernel<XT, PT, YT>), dim3((unsigned)a.C), dim3(256), 0, a.st, (const XT *)a.x,
+        // (a few channels with many elements: 1 x (60000 planes of 7) bf16 287 us with 1024 threads, 758 with 256; a workgroup per
+        // plane and a merge took 295)
+        const bool many = a.N * a.HW > 8192;
+        const int threads = many ? 1024 : 256;
+        auto kern = many ? bn_small_kernel<XT, PT, YT, 1024> : bn_small_kernel<XT, PT, YT, 256>;
+        hipLaunchKernelGGL(kern, dim3((unsigned)a.C), dim3(threads), 0, a.st, (const XT *)a.x,
                            (const PT *)a.gamma, (const PT *)a.beta, (YT *)a.y, a.mean_out, a.rstd_out, (int)a.HW, (int)a.C,
                            (int)a.N, a.eps);
         return;

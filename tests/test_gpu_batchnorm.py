@@ -96,6 +96,7 @@ def test_deterministic():
     (7, 700, 5, 7), (40, 30, 13, 13),        # planes grouped to a segment, a shorter last group, odd planes
     (6, 512, 16, 16), (3, 4, 90, 91),        # ... whole aligned chunks; one plane to a segment
     (3, 4, 1, 8193), (2, 3, 1, 16387), (2, 2, 1, 49152),   # split planes: a ragged last segment, one of 3 elements, whole ones
+    (4096, 1, 2, 1), (2731, 3, 1, 3),        # many short planes: 256 and 1024 threads
     (1, 2, 2100, 2000),                      # more than 256 segments per channel: merged by a kernel of their own
 ])
 def test_segment_edges(N, C, H, W):
