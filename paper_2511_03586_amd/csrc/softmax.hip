@@ -387,17 +387,21 @@ static perf_status softmax_impl(const void *x, void *y, int64_t rows, int64_t co
     // Rows that are not whole aligned vectors: the same two kernels with ragged vectors, as many registers as the row
     // needs (slots without an element cost occupancy: 4099 x 10007 takes 58.5 us with 5 or 6 vectors per thread of
     // 512, 86 with 8, 83 with 4 of 1024; element accesses through LDS took 103).  Up to 2048 columns, against that
-    // kernel: 57600 x 777 62 us (126), 131072 x 101 31 us (100); one pass (a persistent grid: 68 on 57600 x 777).
+    // kernel: 57600 x 777 62 us (126), 131072 x 101 31 us (100); one pass (a persistent grid: 68 on 57600 x 777).  Short
+    // rows go four to a wave where that leaves waves enough (1000 x 63 3.5 us one by one, 4.2 by four; 20000 x 255 9.4, 8.5).
+    // 256 threads up to 4096 columns: 8000 x 2049 25 us against 37 with 512, half of whose slots were empty.
     if (!vec && cols >= 4 && cols <= 32768) {
         const int c = (int)cols;
         if (c > 24576) return launch_wgrow<1024, 8, true>(xp, yp, rows, c, ldx, ldy, k, st);
         if (c > 16384) return launch_wgrow<1024, 6, true>(xp, yp, rows, c, ldx, ldy, k, st);
         if (c > 12288) return launch_wgrow<512, 8, true>(xp, yp, rows, c, ldx, ldy, k, st);
         if (c > 8192) return launch_wgrow<512, 6, true>(xp, yp, rows, c, ldx, ldy, k, st);
-        if (c > 2048) return launch_wgrow<512, 4, true>(xp, yp, rows, c, ldx, ldy, k, st);
+        if (c > 4096) return launch_wgrow<512, 4, true>(xp, yp, rows, c, ldx, ldy, k, st);
+        if (c > 2048) return launch_wgrow<256, 4, true>(xp, yp, rows, c, ldx, ldy, k, st);
         if (c > 1024) launch_rows<8, 1, true>(xp, yp, rows, c, ldx, ldy, k, st);
         else if (c > 512) launch_rows<4, 1, true>(xp, yp, rows, c, ldx, ldy, k, st);
         else if (c > 256) launch_rows<2, 1, true>(xp, yp, rows, c, ldx, ldy, k, st);
+        else if (rows * c < (1 << 21)) launch_rows<1, 1, true>(xp, yp, rows, c, ldx, ldy, k, st);
         else launch_rows<1, 4, true>(xp, yp, rows, c, ldx, ldy, k, st);
         return launch_status();
     }

@@ -67,7 +67,7 @@ def test_padded_rows_unaligned_base_and_inplace():
     _check(x, ldx=203, inplace=True)
 
 
-@pytest.mark.parametrize("cols", [4, 5, 7, 255, 257, 511, 515, 1023, 1025, 2047, 2049, 2051, 8191, 8193, 12289, 16385, 24578,
+@pytest.mark.parametrize("cols", [4, 5, 7, 255, 257, 511, 515, 1023, 1025, 2047, 2049, 2051, 4095, 4097, 8191, 8193, 12289, 16385, 24578,
                                   32767, 32769])
 def test_ragged_rows(cols):
     # rows that are no whole aligned vectors, at the edges of each register shape; odd strides, shifted bases, in place
@@ -75,6 +75,12 @@ def test_ragged_rows(cols):
     _check(x, offset=1)
     _check(x, ldx=cols + 1, ldy=cols + 3, scale=-0.5)
     _check(x, ldx=cols + 1, inplace=True)
+
+
+@pytest.mark.parametrize("rows,cols", [(8224, 255), (8225, 255), (300000, 7), (299593, 7)])
+def test_short_ragged_rows_one_and_four_to_a_wave(rows, cols):
+    x = configs.SoftmaxWorkload(rows=rows, cols=cols).make()["x"]
+    _check(x, ldx=cols + 2)
 
 
 def test_wide_dynamic_range():
