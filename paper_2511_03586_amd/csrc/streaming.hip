@@ -361,8 +361,9 @@ static void launch_mean(const void *x, void *y, int64_t rows, int64_t cols, int6
         else
             hipLaunchKernelGGL((colmean_kernel<XT, YT, 4, 256>), dim3((unsigned)((cols + 4 * E - 1) / (4 * E))), dim3(256),
                                0, st, (const XT *)x, (YT *)y, rows, cols, ldx);
-    } else if (cols >= E) {
-        // (a thread per column, all rows in turn, took 12.4 ms on 51480 x 777 fp32: 168 us; narrower groups where there are few:
+    } else if (cols >= E && rows >= 16) {
+        // (a few rows stay with a thread per column: 3 x 1001 2.8 us against 3.1, 15 x 100001 3.9 against 6.5;
+        // a thread per column, all rows in turn, took 12.4 ms on 51480 x 777 fp32: 168 us; narrower groups where there are few:
         // 9000 x 2222 bf16 36 us against 40, but 5000 x 4001 fp32 55 against 37)
         auto go = [&](auto cw) {
             constexpr int CW = decltype(cw)::value;

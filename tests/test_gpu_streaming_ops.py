@@ -312,7 +312,7 @@ def test_copy_any_alignment_and_size():
 
 
 @pytest.mark.parametrize("rows,cols,ldx", [(513, 7, 7), (1000, 777, 777), (70, 129, 131), (9000, 9, 9), (40, 12345, 12345),
-                                           (300, 64, 67), (3, 2, 2), (2500, 255, 256)])
+                                           (300, 64, 67), (3, 2, 2), (2500, 255, 256), (15, 257, 259), (16, 257, 259)])
 @pytest.mark.parametrize("x_bf16", [False, True])
 @pytest.mark.parametrize("axis", [0, 1])
 def test_reduce_mean_ragged(rows, cols, ldx, x_bf16, axis):
