@@ -673,13 +673,14 @@ __global__ __launch_bounds__(64 * WM * WN * KG, (StagedShape<T, TM, TN, WM, WN, 
         constexpr bool kEdge = decltype(edge)::value, kTimes = decltype(times)::value;
         char *la = mine + (buf ^ 1) * Shape::kStage, *lb = la + Shape::kStageA;
         const int64_t kp = step_k(it + 1), kn = kEdge ? step_k(it + 1 + kD) : min(step_k(it + 1 + kD), K - BK);
+        const bool more = !kEdge || kD > 1 || it + 1 + kD < rounds;  // (one register set: no other loads to wait for)
         multiply(buf, [&](auto ks) {
             if constexpr (ks == 0) {
                 sa.template park<kEdge, kTimes>(la, kp, slot);
-                sa.template fetch<kEdge>(kn, slot);
+                if (more) sa.template fetch<kEdge>(kn, slot);
             } else if constexpr (ks == 1) {
                 sb.template park<kEdge, kTimes>(lb, kp, slot);
-                sb.template fetch<kEdge>(kn, slot);
+                if (more) sb.template fetch<kEdge>(kn, slot);
             }
         });
         __syncthreads();
@@ -691,10 +692,11 @@ __global__ __launch_bounds__(64 * WM * WN * KG, (StagedShape<T, TM, TN, WM, WN, 
             sa.template fetch<true>(step_k(it + d), d);
             sb.template fetch<true>(step_k(it + d), d);
         });
+        const bool more = kD > 1 || rounds > 1;
         sa.template park<true, kTimes>(mine, step_k(it), 0);
-        sa.template fetch<true>(step_k(it + kD), 0);
+        if (more) sa.template fetch<true>(step_k(it + kD), 0);
         sb.template park<true, kTimes>(mine + Shape::kStageA, step_k(it), 0);
-        sb.template fetch<true>(step_k(it + kD), 0);
+        if (more) sb.template fetch<true>(step_k(it + kD), 0);
         __syncthreads();
     };
     auto edge_rounds = [&](auto &sa, auto &sb, auto times, int64_t it) {

@@ -63,23 +63,27 @@ static int64_t tiles_of(const GemmArgs &g, int64_t bm, int64_t bn) { return ((g.
 //   * 128 x 128 (4 waves, two workgroups per CU) from 192 such tiles on: 952x3562x489 13.6 against 17.4 with 64 x 64.
 //   * 64 x 64, four register sets of loads in flight; with few tiles and a long reduction instead two groups of waves
 //     that share the K-steps: 336x640x1000 7.8 against 9.2 (8.7 with four groups), 256x256x4096 16.2 against 20.4 (16.3),
-//     512x512x512 even.
+//     512x512x512 even; one register set up to K = 64, where the loads for steps that do not exist cost more than the
+//     latency they hide (1000x1000x20 6.2 against 5.6, 100x100x36 5.5 against 4.9).
 template <typename CT>
 static perf_status launch_bf16(const GemmArgs &g, bool big_ok)
 {
     if (big_ok && g.K >= 512 && tiles_of(g, 256, 256) >= 192) return launch_layouts<uint16_t, CT, 4, 2, 2, 4, 1, 1>(g);
     if (big_ok && tiles_of(g, 128, 128) >= 192) return launch_layouts<uint16_t, CT, 2, 2, 2, 2, 1, 2>(g);
     if (g.K >= 512 && tiles_of(g, 64, 64) <= 256) return launch_layouts<uint16_t, CT, 1, 1, 2, 2, 2, 2>(g);
+    if (g.K <= 64) return launch_layouts<uint16_t, CT, 1, 1, 2, 2, 1, 1>(g);
     return launch_layouts<uint16_t, CT, 1, 1, 2, 2, 1, 4>(g);
 }
 
 // fp32: the 256 x 128 tile (8 waves of 64 x 64, 144 KiB of LDS for two stages of three planes) from 128 of them on
 // (2696x1608x2139 128 us against 141 with 64 x 64), else 64 x 64; two groups of waves where that leaves CUs idle
-// (1440x544x2216 34 against 41; with more than 256 tiles 592x1688x536 25 against 20).  128 x 64 was never ahead.
+// (1440x544x2216 34 against 41; with more than 256 tiles 592x1688x536 25 against 20).  128 x 64 was never ahead.  One
+// register set up to K = 96 (1000x1000x20 7.1 against 6.3, 512x512x96 6.5 against 5.9).
 static perf_status launch_f32(const GemmArgs &g, bool big_ok)
 {
     if (big_ok && tiles_of(g, 256, 128) >= 128) return launch_layouts<float, float, 2, 2, 4, 2, 1, 1>(g);
     if (g.K >= 256 && tiles_of(g, 64, 64) <= 256) return launch_layouts<float, float, 1, 1, 2, 2, 2, 4>(g);
+    if (g.K <= 96) return launch_layouts<float, float, 1, 1, 2, 2, 1, 1>(g);
     return launch_layouts<float, float, 1, 1, 2, 2, 1, 4>(g);
 }
 

@@ -132,6 +132,8 @@ def test_general_kernel_layouts_exact_integers(a_col, b_col, M, N, K):
     (64, 72, 704, 1, 0), (72, 64, 288, 1, 0), (64, 64, 1216, 1, 0),    # ... whole K-steps that the groups do not divide
     (257, 131, 97, 64, 0), (130, 250, 64, 96, 5),                # 128 x 128 (bf16), 256 x 128 (fp32)
     (40, 33, 521, 200, 1), (300, 261, 512, 100, 0),              # 256 x 256 (bf16): ragged first and second tiles
+    (500, 250, 70, 40, 1), (128, 120, 65, 130, 0), (33, 65, 20, 128, 0),   # 256 x 128 (fp32), full and half full; 64 x 64 instead
+    (70, 130, 64, 1, 1), (70, 130, 65, 1, 0), (70, 130, 97, 1, 0),   # one register set for short reductions
 ])
 def test_staged_kernel_edges(M, N, K, batch, pad, a_col, b_col, ab_bf16, c_bf16):
     """Every layout and type of the register-staged contraction at the edges of its tiles, K-steps and loads."""
