@@ -182,6 +182,7 @@ template <typename T, int ROWS, int THREADS, int D>
 struct KRows {
     using S = Split<T>;
     using Shallow = KRows<T, ROWS, THREADS, 1>;  // one register set
+    static constexpr bool kElements = false;  // loads element by element
     static constexpr int kDepth = D;
     static constexpr int BK = S::kBK, CH = BK / 8, ITEMS = ROWS * CH, PER = ITEMS / THREADS, V = 8 / S::kVec;
     static constexpr int kRowStep = THREADS / CH, kBlock = 1;
@@ -248,6 +249,7 @@ template <typename T, int ROWS, int THREADS, int D>
 struct RRows {
     using S = Split<T>;
     using Shallow = RRows<T, ROWS, THREADS, 1>;  // one register set
+    static constexpr bool kElements = false;  // loads element by element
     static constexpr int kDepth = D;
     static constexpr int BK = S::kBK, V = S::kVec, RB = ROWS / V, KB = RB * BK / THREADS;
     static constexpr int kBlock = V;
@@ -342,6 +344,7 @@ template <typename T, int ROWS, int THREADS, int D>
 struct AnyRows {
     using S = Split<T>;
     using Shallow = AnyRows<T, ROWS, THREADS, 1>;  // one register set
+    static constexpr bool kElements = true;  // loads element by element
     static constexpr int kDepth = D;
     static constexpr int BK = S::kBK, CH = BK / 8, PER = ROWS * CH / THREADS, V = 8 / S::kVec, kRowStep = THREADS / CH, kBlock = 1;
     struct Args {
@@ -406,6 +409,7 @@ template <typename T, int ROWS, int THREADS, int D, bool WHOLE>
 struct ConvRows {
     using S = Split<T>;
     using Shallow = ConvRows<T, ROWS, THREADS, 1, WHOLE>;  // one register set
+    static constexpr bool kElements = !WHOLE;  // loads element by element
     static constexpr int kDepth = D;
     static constexpr int BK = S::kBK, CH = BK / 8, ITEMS = ROWS * CH, PER = ITEMS / THREADS, V = 8 / S::kVec;
     static constexpr int kRowStep = THREADS / CH, kBlock = 1;
@@ -668,19 +672,27 @@ __global__ __launch_bounds__(64 * WM * WN * KG, (StagedShape<T, TM, TN, WM, WN, 
     const bool clean = a_src.whole() && b_src.whole(), even = K % (BK * KG) == 0;
     const int64_t fast_rounds = !clean ? 0 : even ? rounds : K / BK / KG - D - 1;
     auto step_k = [&](int64_t it) { return (it * KG + group) * BK; };
+    // With one register set the start and the EDGE rounds skip fetches of steps that do not exist.  (Behind such a test all
+    // loads are waited for, so it stands behind both parks.)
+    constexpr bool kSkip = D == 1 && !ASrc::kElements && !BSrc::kElements;
     auto round = [&](auto &sa, auto &sb, auto u, auto edge, auto times, int64_t it) {
         constexpr int kD = std::remove_reference_t<decltype(sa)>::kDepth, slot = (u + 1) % kD, buf = u & 1;
         constexpr bool kEdge = decltype(edge)::value, kTimes = decltype(times)::value;
         char *la = mine + (buf ^ 1) * Shape::kStage, *lb = la + Shape::kStageA;
         const int64_t kp = step_k(it + 1), kn = kEdge ? step_k(it + 1 + kD) : min(step_k(it + 1 + kD), K - BK);
-        const bool more = !kEdge || kD > 1 || it + 1 + kD < rounds;  // (one register set: no other loads to wait for)
+        constexpr bool kTest = kSkip && kEdge;
         multiply(buf, [&](auto ks) {
             if constexpr (ks == 0) {
                 sa.template park<kEdge, kTimes>(la, kp, slot);
-                if (more) sa.template fetch<kEdge>(kn, slot);
+                if constexpr (!kTest) sa.template fetch<kEdge>(kn, slot);
             } else if constexpr (ks == 1) {
                 sb.template park<kEdge, kTimes>(lb, kp, slot);
-                if (more) sb.template fetch<kEdge>(kn, slot);
+                if constexpr (!kTest) {
+                    sb.template fetch<kEdge>(kn, slot);
+                } else if (it + 1 + kD < rounds) {
+                    sa.template fetch<kEdge>(kn, slot);
+                    sb.template fetch<kEdge>(kn, slot);
+                }
             }
         });
         __syncthreads();
@@ -692,11 +704,13 @@ __global__ __launch_bounds__(64 * WM * WN * KG, (StagedShape<T, TM, TN, WM, WN, 
             sa.template fetch<true>(step_k(it + d), d);
             sb.template fetch<true>(step_k(it + d), d);
         });
-        const bool more = kD > 1 || rounds > 1;
         sa.template park<true, kTimes>(mine, step_k(it), 0);
-        if (more) sa.template fetch<true>(step_k(it + kD), 0);
+        if constexpr (!kSkip) sa.template fetch<true>(step_k(it + kD), 0);
         sb.template park<true, kTimes>(mine + Shape::kStageA, step_k(it), 0);
-        if (more) sb.template fetch<true>(step_k(it + kD), 0);
+        if (!kSkip || rounds > 1) {
+            if constexpr (kSkip) sa.template fetch<true>(step_k(it + kD), 0);
+            sb.template fetch<true>(step_k(it + kD), 0);
+        }
         __syncthreads();
     };
     auto edge_rounds = [&](auto &sa, auto &sb, auto times, int64_t it) {
