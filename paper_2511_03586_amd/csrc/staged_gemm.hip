@@ -45,12 +45,18 @@ static perf_status launch_layouts(const GemmArgs &g)
                                   : launch<AR, BR, T, CT, TM, TN, WM, WN, KG, D>(g, aa, ba);
 }
 
-// An operand's contiguous extent is shorter than its 16-byte loads: element loads for both.
+// An operand's contiguous extent is shorter than its 16-byte loads: element loads for it, and for the other unless that
+// has rows along K (2x4096x4096 with both operands column-major, fp32 179 us against 239).
 template <typename T, typename CT>
 static perf_status launch_any(const GemmArgs &g)
 {
     using R = AnyRows<T, 64, 256, 1>;
+    using Rows = KRows<T, 64, 256, 1>;
     const bool ar = g.la == PERF_ROW_MAJOR, br = g.lb == PERF_ROW_MAJOR;
+    if (!ar && !br && g.K >= 8)
+        return launch<R, Rows, T, CT, 1, 1, 2, 2, 1, 1>(g, typename R::Args{nullptr, 1, g.lda, g.strideA}, {nullptr, g.ldb, g.strideB});
+    if (ar && br && g.K >= 8)
+        return launch<Rows, R, T, CT, 1, 1, 2, 2, 1, 1>(g, {nullptr, g.lda, g.strideA}, typename R::Args{nullptr, 1, g.ldb, g.strideB});
     return launch<R, R, T, CT, 1, 1, 2, 2, 1, 1>(g, typename R::Args{nullptr, ar ? g.lda : 1, ar ? 1 : g.lda, g.strideA},
                                                  typename R::Args{nullptr, br ? 1 : g.ldb, br ? g.ldb : 1, g.strideB});
 }

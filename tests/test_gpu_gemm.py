@@ -133,6 +133,7 @@ def test_general_kernel_layouts_exact_integers(a_col, b_col, M, N, K):
     (257, 131, 97, 64, 0), (130, 250, 64, 96, 5),                # 128 x 128 (bf16), 256 x 128 (fp32)
     (40, 33, 521, 200, 1), (300, 261, 512, 100, 0),              # 256 x 256 (bf16): ragged first and second tiles
     (500, 250, 70, 40, 1), (128, 120, 65, 130, 0), (33, 65, 20, 128, 0),   # 256 x 128 (fp32), full and half full; 64 x 64 instead
+    (3, 70, 130, 2, 1), (70, 2, 77, 3, 0), (1, 9, 8, 1, 0),      # element loads for the short operand only
     (70, 130, 64, 1, 1), (70, 130, 65, 1, 0), (70, 130, 97, 1, 0),   # one register set for short reductions
 ])
 def test_staged_kernel_edges(M, N, K, batch, pad, a_col, b_col, ab_bf16, c_bf16):
