@@ -68,15 +68,10 @@ struct BnItems {  // this thread's items of a segment
     __device__ __forceinline__ int64_t at(int j, int &dup) const
     {
         const int i = min(j * 256 + (int)threadIdx.x, total - 1);
-        const int p = g.G ? fast_quot(i, (int)g.cpp, g.m_cpp) : 0;
+        const int p = g.G ? div_by(i, (int)g.cpp, g.m_cpp) : 0;
         const int64_t first = (g.G ? i - p * (int)g.cpp : c0 + i) * E, start = RAG ? min(first, g.HW - E) : first;
         dup = (int)(first - start);
         return (int64_t)p * g.C * g.HW + start;
-    }
-    __device__ static __forceinline__ int fast_quot(int n, int d, uint32_t m)
-    {
-        const uint32_t q = __umulhi((uint32_t)n, m);
-        return (int)((uint32_t)n - q * (uint32_t)d >= (uint32_t)d ? q + 1 : q);
     }
 };
 
@@ -328,7 +323,7 @@ static BnGeom bn_geom(const BnArgs &a, int E)
         if (want > a.N) want = a.N;
         g.G = want < 1 ? 1 : (int)want;
         g.segs = (g.N + g.G - 1) / g.G;
-        g.m_cpp = g.cpp <= 1 ? 0xFFFFFFFFu : (uint32_t)((1ull << 32) / (uint64_t)g.cpp);
+        g.m_cpp = div_magic(g.cpp);
     }
     return g;
 }

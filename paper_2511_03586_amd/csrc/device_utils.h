@@ -14,6 +14,18 @@ typedef float float16_t __attribute__((ext_vector_type(16)));
 typedef uint32_t uint4_t __attribute__((ext_vector_type(4)));
 typedef uint32_t uint2_t __attribute__((ext_vector_type(2)));
 typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
+// ... at the alignment of an element (global accesses take any)
+typedef float float4_at4 __attribute__((ext_vector_type(4), aligned(4)));
+typedef uint32_t uint4_at2 __attribute__((ext_vector_type(4), aligned(2)));
+typedef uint32_t uint2_at2 __attribute__((ext_vector_type(2), aligned(2)));
+
+// Exact n / d for 0 <= n < 2^31 with a host-made multiplier floor(2^32 / d).
+static inline uint32_t div_magic(int64_t d) { return d <= 1 ? 0xFFFFFFFFu : (uint32_t)((1ull << 32) / (uint64_t)d); }
+__device__ __forceinline__ int div_by(int n, int d, uint32_t m)
+{
+    const uint32_t q = __umulhi((uint32_t)n, m);
+    return (int)((uint32_t)n - q * (uint32_t)d >= (uint32_t)d ? q + 1 : q);
+}
 
 // ---- bf16 <-> fp32 -------------------------------------------------------------
 // A bf16 is the top half of an fp32: widening is a shift, exact.

@@ -363,11 +363,9 @@ __global__ __launch_bounds__(64 * NW, 2) void gemm_softmax_wide_kernel(const uin
             PT *dst = Pb + (int64_t)r * ldp + col;
             if (r < rows && left >= 4) {
                 if constexpr (sizeof(PT) == 4) {
-                    typedef float float4_at4 __attribute__((ext_vector_type(4), aligned(4)));
                     if (whole_lines) __builtin_nontemporal_store(v, reinterpret_cast<float4_at4 *>(dst));
                     else *reinterpret_cast<float4_at4 *>(dst) = v;
                 } else {
-                    typedef uint32_t uint2_at2 __attribute__((ext_vector_type(2), aligned(2)));
                     const uint2_t o = {pack_bf16(v[0], v[1]), pack_bf16(v[2], v[3])};
                     if (whole_lines) __builtin_nontemporal_store(o, reinterpret_cast<uint2_at2 *>(dst));
                     else *reinterpret_cast<uint2_at2 *>(dst) = o;

@@ -74,7 +74,6 @@ template <bool RAG>
 __device__ __forceinline__ uint4_t load_chunk_nt(const void *p)
 {
     if constexpr (RAG) {
-        typedef uint32_t uint4_at2 __attribute__((ext_vector_type(4), aligned(2)));
         return __builtin_nontemporal_load(reinterpret_cast<const uint4_at2 *>(p));
     } else {
         return __builtin_nontemporal_load(reinterpret_cast<const uint4_t *>(p));
@@ -86,17 +85,14 @@ __device__ __forceinline__ void store_row_chunk(YT *y, const float *v)
     if constexpr (!RAG) {
         store_chunk<YT, E>(y, v);
     } else if constexpr (sizeof(YT) == 4) {
-        typedef float float4_at4 __attribute__((ext_vector_type(4), aligned(4)));
 #pragma unroll
         for (int q = 0; q < E / 4; ++q)
             __builtin_nontemporal_store(float4_t{v[4 * q], v[4 * q + 1], v[4 * q + 2], v[4 * q + 3]},
                                         reinterpret_cast<float4_at4 *>(y) + q);
     } else if constexpr (E == 8) {
-        typedef uint32_t uint4_at2 __attribute__((ext_vector_type(4), aligned(2)));
         const uint4_t o = {pack_bf16(v[0], v[1]), pack_bf16(v[2], v[3]), pack_bf16(v[4], v[5]), pack_bf16(v[6], v[7])};
         __builtin_nontemporal_store(o, reinterpret_cast<uint4_at2 *>(y));
     } else {
-        typedef uint32_t uint2_at2 __attribute__((ext_vector_type(2), aligned(2)));
         const uint2_t o = {pack_bf16(v[0], v[1]), pack_bf16(v[2], v[3])};
         __builtin_nontemporal_store(o, reinterpret_cast<uint2_at2 *>(y));
     }

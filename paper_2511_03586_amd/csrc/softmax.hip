@@ -20,7 +20,6 @@
 
 namespace perf {
 
-typedef float float4_at4 __attribute__((ext_vector_type(4), aligned(4)));
 template <bool RAG>
 __device__ __forceinline__ float4_t load_vec(const float *p)
 {

@@ -29,24 +29,9 @@
 #include <utility>
 #include "host_utils.h"
 #include "mfma_tile.h"
+#include "row_io.h"
 
 namespace perf {
-
-// Exact n / d for 0 <= n < 2^31 with a host-made multiplier floor(2^32 / d).
-static inline uint32_t div_magic(int64_t d) { return d <= 1 ? 0xFFFFFFFFu : (uint32_t)((1ull << 32) / (uint64_t)d); }
-__device__ __forceinline__ int div_by(int n, int d, uint32_t m)
-{
-    const uint32_t q = __umulhi((uint32_t)n, m);
-    return (int)((uint32_t)n - q * (uint32_t)d >= (uint32_t)d ? q + 1 : q);
-}
-
-// 16 bytes at the alignment of an element (global loads take any).
-__device__ __forceinline__ uint4_t load16(const void *p)
-{
-    uint4_t v;
-    __builtin_memcpy(&v, p, 16);
-    return v;
-}
 
 __device__ __forceinline__ float to_f32(float v) { return v; }
 __device__ __forceinline__ float to_f32(uint16_t v) { return bf16_to_f32(v); }
@@ -223,7 +208,7 @@ struct KRows {
 #pragma unroll
         for (int i = 0; i < PER; ++i)
 #pragma unroll
-            for (int v = 0; v < V; ++v) raw[slot][i][v] = load16(b + (Off)(off[i] + d) + v * S::kVec);
+            for (int v = 0; v < V; ++v) raw[slot][i][v] = load_chunk<true>(b + (Off)(off[i] + d) + v * S::kVec);
     }
     template <bool EDGE, bool TIMES>
     __device__ __forceinline__ void park(char *lds, int64_t k0, int slot)
@@ -244,7 +229,8 @@ struct KRows {
 
 // K-strided operand: element (row, k) at p[k * ld + row].  An item is a block of V rows x KB k (V = 8 bf16 or
 // 4 fp32 = 16 bytes; KB = 4, or 2 where 4 would leave half the threads idle), transposed on the way to LDS.  A block that would overhang the last row is loaded from V
-// rows before the end and moved down, so every load stays inside the operand, which has at least V rows.
+// rows before the end and moved down, so every load stays inside the tile, which has at least V rows (the operand has
+// that many, and a later tile starts early enough to end on a whole block).
 template <typename T, int ROWS, int THREADS, int D>
 struct RRows {
     using S = Split<T>;
@@ -259,7 +245,7 @@ struct RRows {
     const T *base;
     int64_t ld, K;
     Off off;
-    int kq, sh, o0, last, back;
+    int kq, sh, o0, last;
     bool all;
     uint4_t raw[D][KB];
     Lost lost;
@@ -276,17 +262,15 @@ struct RRows {
         const int valid = (int)min((int64_t)ROWS, rows - r0), start = min(rb * V, valid - V);
         sh = rb * V < valid ? rb * V - start : 0;  // (a block of rows that are never stored may hold anything)
         all = valid % V == 0;
-        // (start is negative only in a tile of fewer than V rows: the operand then goes on before the tile)
-        back = min(valid - V, 0);
         last = valid - 1;
-        base = a.p + b * a.stride + r0 + back;
-        off = (Off)((int64_t)kq * a.ld + start - back);
+        base = a.p + b * a.stride + r0;
+        off = (Off)((int64_t)kq * a.ld + start);
         o0 = stage_offset<BK>(rb * V, kq >> 3) + (kq & 7) * 2;
     }
     __device__ __forceinline__ bool whole() const { return all; }
     __device__ __forceinline__ float at(const Args &, int row, int64_t k) const
     {
-        const float v = to_f32(base[min(k, K - 1) * ld + min(row, last) - back]);
+        const float v = to_f32(base[min(k, K - 1) * ld + min(row, last)]);
         return row <= last && k < K ? v : 0.f;
     }
     template <bool EDGE>
@@ -295,11 +279,11 @@ struct RRows {
         if constexpr (EDGE) {
             const Off start = off - (Off)((int64_t)kq * ld);
 #pragma unroll
-            for (int u = 0; u < KB; ++u) raw[slot][u] = load16(base + min(k0 + kq + u, K - 1) * ld + start);
+            for (int u = 0; u < KB; ++u) raw[slot][u] = load_chunk<true>(base + min(k0 + kq + u, K - 1) * ld + start);
         } else {
             const T *b = base + k0 * ld;
 #pragma unroll
-            for (int u = 0; u < KB; ++u) raw[slot][u] = load16(b + u * ld + off);
+            for (int u = 0; u < KB; ++u) raw[slot][u] = load_chunk<true>(b + u * ld + off);
         }
     }
     template <bool EDGE, bool TIMES>
@@ -485,7 +469,7 @@ struct ConvRows {
                 good |= in ? 1u << i : 0u;
                 const T *p = g.x + (in ? off[i] + d : 0);
 #pragma unroll
-                for (int v = 0; v < V; ++v) raw[slot][i][v] = load16(p + v * S::kVec);
+                for (int v = 0; v < V; ++v) raw[slot][i][v] = load_chunk<true>(p + v * S::kVec);
             }
         } else {
 #pragma unroll
