@@ -111,8 +111,9 @@ perf_status perf_gemm(const void *A, const void *B, void *C, int64_t M, int64_t 
  *   x  device, NHWC dense;  w  device, KRSC dense;  y  device, NPQK dense
  *   xw_dt  dtype of x and w (bf16 or f32);  y_dt  f32 or bf16;  fp32 accumulation.
  * The bf16 MFMA path is taken for bf16 x/w with C a multiple of 32 and 16-byte aligned
- * pointers; fp32 x/w (and bf16 with other channel counts from 8 on) with at least 32 output channels run
- * an implicit GEMM that treats its operands as perf_gemm does; the remaining cases run direct kernels.
+ * pointers; fp32 x/w (and bf16 with other channel counts from 8 on) with at least 32 output channels (16 for 1x1
+ * filters at stride 1) run an implicit GEMM that treats its operands as perf_gemm does; the remaining cases, and
+ * those of little work, run direct kernels.
  * Errors: NULL, SHAPE (any dim < 1, stride < 1, pad < 0, filter larger than the padded
  * image, more than 2^31-1 output pixels), DTYPE, ALIGN, LAUNCH. */
 perf_status perf_conv2d(const void *x, const void *w, void *y, int64_t N, int64_t H, int64_t W,
@@ -129,9 +130,9 @@ perf_status perf_conv2d(const void *x, const void *w, void *y, int64_t N, int64_
  * arithmetic (fp32 accumulation, fp32 softmax) and the same max convention.
  *   A, B     device, bf16 or f32 (ab_dt);  P  device, M x N, row stride ldp, f32 or bf16
  * For bf16 operands with K a multiple of 8 up to 512, N <= 1024 and 16-byte aligned rows the scores never
- * reach memory (one kernel; for K = 64 and N = 128, 256 or 512 its exponential is exp2 of a plain fp32
- * product, relative error about 2^-24 times the exponent); other legal cases, and few rows of more than
- * 512 columns, run the two operators one after the other through P.  bf16 P takes K = 64 or 128 and
+ * reach memory (one kernel; for K = 64 and N = 128, 256 or 512, and K = N = 128, its exponential is exp2 of a
+ * plain fp32 product, relative error about 2^-24 times the exponent); other legal cases, and few rows of more than
+ * 512 columns, or of more than 128 with K above 128, run the two operators one after the other through P.  bf16 P takes K = 64 or 128 and
  * N <= 512 in one kernel (UNSUPPORTED otherwise).
  * Errors: NULL, SHAPE (dimension < 1, ld too small, negative stride, batches overlapping in
  * P, alpha not finite), DTYPE, ALIGN, UNSUPPORTED, LAUNCH. */

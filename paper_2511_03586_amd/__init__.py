@@ -149,6 +149,7 @@ def perf_layernorm_variant(x, gamma, beta, y, mean_out, rstd_out, rows, cols, ld
                                                x_dt, param_dt, y_dt, waves_per_row, grid, stream), check)
 
 
+# (CONV_F32MFMA keeps its name: variant 7, the implicit GEMM through registers, on the bf16 matrix instruction)
 CONV_WREG, CONV_MFMA, CONV_SMALLC, CONV_DIRECT, CONV_ROWMFMA, CONV_WRES, CONV_F32MFMA, CONV_WSPLIT = 1, 2, 3, 4, 5, 6, 7, 8
 
 

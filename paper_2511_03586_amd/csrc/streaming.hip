@@ -557,7 +557,7 @@ static perf_status launch_eltwise(const void *a, const void *b, void *y, int64_t
 {
     constexpr int E = Elem<T>::kPerChunk;
     const bool vec = aligned(a, 16) && aligned(y, 16) && (OP == PERF_RELU || aligned(b, 16));
-    if (!vec && n > (int64_t(1) << 20) * 64) return PERF_ERR_UNSUPPORTED;  // unaligned bulk: not a streaming case
+    if (!vec && n > (int64_t(1) << 20) * 64) return PERF_ERR_UNSUPPORTED;  // (documented limit of misaligned calls)
     const int64_t nvec = n / E;
     if (nvec == 0) {
         hipLaunchKernelGGL((eltwise_tail_kernel<OP, T>), dim3(1), dim3(64), 0, st, (const T *)a,
