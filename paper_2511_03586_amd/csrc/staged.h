@@ -709,7 +709,7 @@ __global__ __launch_bounds__(64 * WM * WN * KG, (StagedShape<T, TM, TN, WM, WN, 
             });
         }
     };
-    start(a_src, b_src, std::false_type{}, 0);
+    if (D > 1 || !few_k) start(a_src, b_src, std::false_type{}, 0);  // (few k come to kernels with one register set)
     int64_t it = 0;
     for (; it + U <= fast_rounds; it += U)
         unrolled<U>([&](auto u) { round(a_src, b_src, u, std::false_type{}, std::false_type{}, it + u); });
