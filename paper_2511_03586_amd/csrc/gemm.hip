@@ -4,6 +4,7 @@
 //  * gemm_mfma_kernel: bf16 operands, A row-major and B column-major (both K-contiguous),
 //    K a multiple of 32.  256x256, 128x128 or 64x64 workgroup tile; the K-step-64 loop of
 //    mfma_tile.h when K is a multiple of 64, else its K-step-32 loop.
+//  * waves_kernel (kwaves.h, launched by waves_gemm.hip): any layout / dtype / alignment where the output has few tiles.
 //  * staged_kernel (staged.h, launched by staged_gemm.hip): any layout / dtype / size / alignment (fp32 operands,
 //    other layouts, odd K), on the bf16 matrix instruction as well.
 #include <atomic>
@@ -183,6 +184,8 @@ static perf_status gemm_impl(const void *A, const void *B, void *C, int64_t M, i
             (kstep == kK64Mi32 && tile != 256))
             return PERF_ERR_UNSUPPORTED;
     }
+    perf_status waves_status;
+    if (tile == 0 && launch_waves_gemm(g, ab_dt, c_dt, mfma_ok, &waves_status)) return waves_status;
     if (mfma_ok) {
         if (tile == 0) {
             // the 256x256 tile needs enough tiles to occupy the 256 CUs; otherwise 128x128, or 64x64

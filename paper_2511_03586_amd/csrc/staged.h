@@ -864,4 +864,8 @@ perf_status launch_staged_conv(const StagedConv &c, int xw_dt, int y_dt);
 // Any layout, type (ab: bf16 or fp32 operands), size and alignment (staged_gemm.hip).
 perf_status launch_staged_gemm(const GemmArgs &g, int ab_dt, int c_dt);
 
+// The kernels whose waves divide K (waves_gemm.hip): false if they do not suit the call.  direct: the direct kernels of
+// gemm.hip take it as well.
+bool launch_waves_gemm(const GemmArgs &g, int ab_dt, int c_dt, bool direct, perf_status *status);
+
 }  // namespace perf

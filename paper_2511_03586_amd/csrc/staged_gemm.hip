@@ -1,5 +1,5 @@
 // perf_gemm beyond the direct global->LDS kernels: other layouts, fp32 operands, any extent, leading
-// dimension and alignment, on the staged contraction of staged.h.
+// dimension and alignment, on the staged contraction of staged.h.  (Calls with few tiles mostly run waves_gemm.hip.)
 #include <atomic>
 #include "staged.h"
 
@@ -84,16 +84,14 @@ static perf_status launch_bf16(const GemmArgs &g, bool big_ok)
 // fp32: the 256 x 128 tile (8 waves of 64 x 64, 144 KiB of LDS for two stages of three planes) from 128 of them on
 // (2696x1608x2139 128 us against 141 with 64 x 64), if they are full (128 x (33x65x36) 11.9 against 6.9 with 64 x 64) or half
 // full and the reduction is not short (256 x (128x128x160) 19.4 against 27.8, but x8 9.8 against 9.5), and of 256 on for
-// less than a K-step (32 x (512x512x8) 12.6 against 15.0, 2000x2000x16 10.7 against 10.2); else 64 x 64; two groups of waves where that leaves CUs idle
-// (1440x544x2216 34 against 41; with more than 256 tiles 592x1688x536 25 against 20).  128 x 64 was never ahead.  One
-// register set up to K = 96 (1000x1000x20 7.1 against 6.3, 512x512x96 6.5 against 5.9).
+// less than a K-step (32 x (512x512x8) 12.6 against 15.0, 2000x2000x16 10.7 against 10.2); else 64 x 64.  128 x 64 was
+// never ahead.  One register set up to K = 96 (1000x1000x20 7.1 against 6.3, 512x512x96 6.5 against 5.9).
 static perf_status launch_f32(const GemmArgs &g, bool big_ok)
 {
     const int64_t big = tiles_of(g, 256, 128), small = tiles_of(g, 64, 64);
     const bool full = 8 * big <= small * 3 / 2, half = 8 * big <= small * 2;
     if (big_ok && big >= 128 && ((full && (big >= 256 || g.K >= 32)) || (half && g.K >= 64)))
         return launch_layouts<float, float, 2, 2, 4, 2, 1, 1>(g);
-    if (g.K >= 256 && small <= 256) return launch_layouts<float, float, 1, 1, 2, 2, 2, 4>(g);
     if (g.K <= 96) return launch_layouts<float, float, 1, 1, 2, 2, 1, 1>(g);
     return launch_layouts<float, float, 1, 1, 2, 2, 1, 4>(g);
 }

@@ -156,6 +156,21 @@ def test_staged_kernel_edges(M, N, K, batch, pad, a_col, b_col, ab_bf16, c_bf16)
         P.assert_contraction_close(P.bf16_to_f64(c[i]) if c_bf16 else c[i], ref, absdot, K + 1, out_bf16=c_bf16)
 
 
+@pytest.mark.parametrize("ab_bf16,c_bf16", [(True, False), (True, True), (False, False)])
+@pytest.mark.parametrize("a_col,b_col", [(False, False), (True, False), (True, True), (False, True)])
+@pytest.mark.parametrize("M,N,K,batch,pad", [
+    (1, 1, 64, 1, 0), (33, 65, 65, 2, 1), (5, 7, 1031, 1, 0),    # 32 x 32: one K-step, the last one overlapping, more than waves
+    (64, 64, 512, 1, 0), (31, 97, 8 * 64 + 1, 3, 3),             # ... the last step alone in its round; the direct kernels' shapes
+    (700, 600, 40, 1, 1), (577, 450, 66, 1, 0),                  # pairs of tiles; an odd row alone in the last pair
+    (450, 577, 127, 1, 1), (705, 641, 1030, 1, 0),               # ... and column; 64 x 64 in one round
+    (1030, 1090, 130, 1, 1), (1025, 1089, 515, 1, 0),            # 64 x 64 in several, ragged by one
+])
+def test_waves_kernel_edges(M, N, K, batch, pad, a_col, b_col, ab_bf16, c_bf16):
+    """Every layout and type of the contraction whose waves divide K, at the edges of its tiles, K-steps and row pairs (the
+    smallest K of each type included); padding of C stays as it was."""
+    test_staged_kernel_edges(M, N, K, batch, pad, a_col, b_col, ab_bf16, c_bf16)
+
+
 @pytest.mark.parametrize("a_col,b_col", [(False, False), (True, True)])
 @pytest.mark.parametrize("M,N,K,batch", [(70, 65, 33, 1), (96, 64, 300, 1), (130, 250, 64, 96), (7, 3, 5, 1)])
 def test_fp32_range_ends(M, N, K, batch, a_col, b_col):
