@@ -1715,6 +1715,11 @@ static perf_status conv2d_impl(const void *x, const void *w, void *y, int64_t N,
     // few tiles with a long reduction: the staged kernel's wave groups share it (8x28x28 256->128 12.8 us against 16.5 on the
     // shared main loop, 20x20 256->256 12.2 against 16.1, 14x14 128->64 with 5x5 taps about even at 1600)
     const bool few_long = mfma_ok && staged_ok && R * S * C >= 1600 && ((N * P * Q + 63) / 64) * ((K + 63) / 64) <= 256;
+    const StagedConv staged{x, w, y, g.N, g.H, g.W, g.C, g.K, g.R, g.S, g.sh, g.sw, g.ph, g.pw, g.P, g.Q, st};
+    perf_status waves_status;
+    if (variant == kConvAuto && !wsplit_ok && !wreg_ok && staged_ok && !few_macs &&
+        launch_waves_conv(staged, xw_dt, y_dt, mfma_ok, &waves_status))
+        return waves_status;
     if (variant == kConvAuto)
         // (the channel-blocked kernel has one thread per pixel: below ~64 workgroups of pixels the
         // thread-per-output kernel has more parallelism and measured faster)
@@ -1738,9 +1743,7 @@ static perf_status conv2d_impl(const void *x, const void *w, void *y, int64_t N,
     if (variant == kConvWsplit)
         return y_dt == PERF_F32 ? launch_conv_wsplit<3, 3, 64, float>(x, w, y, g, wsplit, st)
                                 : launch_conv_wsplit<3, 3, 64, uint16_t>(x, w, y, g, wsplit, st);
-    if (variant == kConvStaged)
-        return launch_staged_conv(StagedConv{x, w, y, g.N, g.H, g.W, g.C, g.K, g.R, g.S, g.sh, g.sw, g.ph, g.pw, g.P, g.Q, st}, xw_dt,
-                                  y_dt);
+    if (variant == kConvStaged) return launch_staged_conv(staged, xw_dt, y_dt);
     if (variant == kConvWres)
         return y_dt == PERF_F32 ? launch_conv_wres<3, 3, 64, float>(x, w, y, g, wres_px, wres_rows, wres_lds, st)
                                 : launch_conv_wres<3, 3, 64, uint16_t>(x, w, y, g, wres_px, wres_rows, wres_lds, st);

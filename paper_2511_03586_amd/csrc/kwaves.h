@@ -25,6 +25,23 @@ namespace perf {
 // 8 (lane / 32) .. + 7 of the step, as they lie in memory.  kPairs: rows 2 l and 2 l + 1 of 64 are row l of fragments 2 p
 // and 2 p + 1 (else row l of fragment i is row 32 i + l).
 
+// Lane l's chunk l % 8 of rows lds_row(8 i + l / 8) to LDS; wr: the offset for i = 0.
+template <int N>
+__device__ __forceinline__ void park_rows(char *lds, int wr, const uint4_t (&raw)[N])
+{
+#pragma unroll
+    for (int i = 0; i < N; ++i)  // (8 i rows of LDS on, the swizzle changes in constant bits)
+        *reinterpret_cast<uint4_t *>(lds + (wr ^ (((i & 1) ^ (i >> 1)) << 4)) + i * 1024) = raw[i];
+}
+// The lane's 8 elements of a substep in fragment i; rd: the offset of the first 16 bytes in fragment 0.
+template <typename T>
+__device__ __forceinline__ void frag_rows(const char *lds, int rd, int i, uint4_t (&out)[sizeof(T) / 2])
+{
+    const int o = (rd ^ ((2 * i & 7) << 4)) + i * 32 * 128;  // (32 i rows on, the swizzle's bits of chunk XOR 2 i)
+    out[0] = *reinterpret_cast<const uint4_t *>(lds + o);
+    if constexpr (sizeof(T) == 4) out[1] = *reinterpret_cast<const uint4_t *>(lds + (o ^ 16));
+}
+
 // Rows of K-contiguous elements, at least one K-step of them.
 template <typename T, int TR>
 struct WaveRows {
@@ -58,19 +75,74 @@ struct WaveRows {
         for (int i = 0; i < kLoads; ++i) raw[i] = load_chunk<true>(reinterpret_cast<const T *>(b + off[i]));
     }
     __device__ __forceinline__ void cols(int64_t, int) {}
-    __device__ __forceinline__ void park()
-    {
-#pragma unroll
-        for (int i = 0; i < kLoads; ++i)  // (8 i rows of LDS on, the swizzle changes in constant bits)
-            *reinterpret_cast<uint4_t *>(lds + (wr ^ (((i & 1) ^ (i >> 1)) << 4)) + i * 1024) = raw[i];
-    }
+    __device__ __forceinline__ void park() { park_rows(lds, wr, raw); }
     template <typename S>
     __device__ __forceinline__ void frag(S s, int i, uint4_t (&out)[sizeof(T) / 2]) const
     {
-        // rows 32 i + l: 32 i rows on, the swizzle's bits of chunk XOR 2 i
-        const int o = (rd[s] ^ ((2 * i & 7) << 4)) + i * 32 * 128;
-        out[0] = *reinterpret_cast<const uint4_t *>(lds + o);
-        if constexpr (sizeof(T) == 4) out[1] = *reinterpret_cast<const uint4_t *>(lds + (o ^ 16));
+        frag_rows<T>(lds, rd[s], i, out);
+    }
+};
+
+// The implicit im2col matrix of a convolution over NHWC x of less than 2^31 bytes, whose 16-byte chunks lie in one of at most
+// 31 filter taps each: row = output pixel (n, p, q), k = (r, s, c) with c fastest.  Chunks in the zero padding are read past
+// the end of the buffer, which gives zeros.
+template <typename T, int TR>
+struct WaveConv {
+    static constexpr int R = 32 * TR, kLoads = R / 8, V = 16 / sizeof(T), KS = 128 / sizeof(T) / 16, kLds = R * 128;
+    static constexpr bool kPairs = false;
+    struct Args {
+        ConvArgs<T> g;
+        uint32_t bytes;     // of x
+        uint32_t tap_rows;  // bit r S for every filter row r
+        int R;
+    };
+    ConvArgs<T> g;
+    rsrc_t rsrc;
+    int off[kLoads];        // under tap (0, 0), channel 0: byte offset (may lie outside x)
+    uint32_t taps[kLoads];  // bit r S + s: tap (r, s) lies in the image
+    int ch;
+    uint4_t raw[kLoads];
+    char *lds;
+    int wr, rd[KS];
+
+    __device__ __forceinline__ void init(const Args &a, int64_t, int64_t r0, int64_t rows, int lane, char *mine)
+    {
+        g = a.g;
+        rsrc = make_rsrc(g.x, a.bytes);
+        lds = mine;
+        ch = lane % 8;
+#pragma unroll
+        for (int i = 0; i < kLoads; ++i) {
+            const int row = lds_row<64>(8 * i + lane / 8);  // (a wave writes whole bank lines)
+            if (i == 0) wr = stage_offset<64>(row, ch);
+            const int m = (int)min(r0 + row, rows - 1);
+            const int n = div_by(m, g.P * g.Q, g.mPQ), pq = m - n * (g.P * g.Q);
+            const int p = div_by(pq, g.Q, g.mQ), q = pq - p * g.Q;
+            const int ih = p * g.sh - g.ph, iw = q * g.sw - g.pw;
+            off[i] = (int)((((int64_t)n * g.H + ih) * g.W + iw) * g.C * (int)sizeof(T));
+            const int r_lo = min(max(-ih, 0), a.R), r_hi = max(min(a.R, g.H - ih), 0), s_lo = min(max(-iw, 0), g.S), s_hi = max(min(g.S, g.W - iw), 0);
+            auto low = [](int bits) { return (1u << bits) - 1; };
+            taps[i] = (a.tap_rows & low(r_hi * g.S) & ~low(r_lo * g.S)) * (low(s_hi) & ~low(s_lo));
+        }
+#pragma unroll
+        for (int s = 0; s < KS; ++s) rd[s] = stage_offset<64>(lane & 31, sizeof(T) == 2 ? 2 * s + (lane >> 5) : 4 * s + 2 * (lane >> 5));
+    }
+    __device__ __forceinline__ void rows(int64_t k0)
+    {
+        const int k = (int)k0 + ch * V, t = div_by(k, g.C, g.mC), c = k - t * g.C, r = div_by(t, g.S, g.mS), s = t - r * g.S;
+        const int d = ((r * g.W + s) * g.C + c) * (int)sizeof(T);
+#pragma unroll
+        for (int i = 0; i < kLoads; ++i) {
+            const uint32_t from = taps[i] >> t & 1 ? (uint32_t)(off[i] + d) : kOutOfRange;
+            raw[i] = __builtin_bit_cast(uint4_t, __builtin_amdgcn_raw_buffer_load_b128(rsrc, from, 0, 0));
+        }
+    }
+    __device__ __forceinline__ void cols(int64_t, int) {}
+    __device__ __forceinline__ void park() { park_rows(lds, wr, raw); }
+    template <typename S>
+    __device__ __forceinline__ void frag(S s, int i, uint4_t (&out)[sizeof(T) / 2]) const
+    {
+        frag_rows<T>(lds, rd[s], i, out);
     }
 };
 
@@ -173,8 +245,8 @@ struct WavesShape {
     static constexpr int kWave = ASrc::kLds + BSrc::kLds > kSum ? ASrc::kLds + BSrc::kLds : kSum;
     static constexpr int kLds = kWave * W + 4 * W;
     static_assert(kLds <= 160 * 1024, "LDS of one CU");
-    // registers: 256 for 64 x 64, 168 and 128 for the smaller tiles
-    static constexpr int kWavesPerSimd = TM * TN == 4 ? 2 : TM * TN == 2 ? 3 : 4;
+    // registers: 256 for 64 x 64 (and all but the smallest fp32 tile), 168 and 128 for the smaller ones
+    static constexpr int kWavesPerSimd = TM * TN == 1 ? 4 : TM * TN == 2 && sizeof(T) == 2 ? 3 : 2;
 };
 
 template <typename ASrc, typename BSrc, typename T, typename CT, int TM, int TN, int W>

@@ -861,6 +861,10 @@ struct StagedConv {
 // Any stride, padding, channel count and type (staged_conv.hip).
 perf_status launch_staged_conv(const StagedConv &c, int xw_dt, int y_dt);
 
+// The kernels whose waves divide the reduction (waves_conv.hip): false if they do not suit the call.  direct: the
+// convolution's own main loop takes it as well.
+bool launch_waves_conv(const StagedConv &c, int xw_dt, int y_dt, bool direct, perf_status *status);
+
 // Any layout, type (ab: bf16 or fp32 operands), size and alignment (staged_gemm.hip).
 perf_status launch_staged_gemm(const GemmArgs &g, int ab_dt, int c_dt);
 

@@ -298,6 +298,21 @@ def test_staged_conv_edges(kw):
             P.assert_contraction_close(yg, ref, ad + 2.0 ** -126, wl.R * wl.S * wl.C + 1, out_bf16=y_bf16)
 
 
+@pytest.mark.parametrize("kw", [
+    dict(N=1, H=9, W=9, C=64, K=33, R=3, S=3, pad=1),           # 32 x 32, fewer pixels than its last tile
+    dict(N=1, H=3, W=3, C=16, K=32, R=5, S=5, pad=4),           # most taps in the padding; the last K-step overlaps
+    dict(N=2, H=15, W=11, C=20, K=40, R=2, S=5, pad=1, stride=3),   # chunks of 4 channels (fp32) of several taps
+    dict(N=1, H=61, W=70, C=48, K=96, R=3, S=3, pad=1),         # 64 x 32 with 8 waves (fp32)
+    dict(N=3, H=61, W=71, C=64, K=70, R=3, S=3, pad=0),         # ... with 4, the last 64 channels not half used
+    dict(N=2, H=67, W=67, C=88, K=64, R=5, S=5, pad=2),         # 64 x 64 in one round
+    dict(N=2, H=92, W=91, C=80, K=64, R=5, S=5, pad=2),         # ... in several
+    dict(N=4, H=60, W=61, C=24, K=32, R=5, S=5, pad=0),         # bf16 channels that the main loop cannot take, 32 outputs
+])
+def test_waves_conv_edges(kw):
+    """The convolution whose waves divide the reduction, at the edges of its tiles, K-steps and taps."""
+    test_staged_conv_edges(kw)
+
+
 @pytest.mark.parametrize("C,R,stride", [(1, 1, 2), (2, 1, 2), (7, 1, 2), (1, 3, 1), (8, 1, 2), (40, 3, 1), (64, 5, 1)])
 def test_fp32_operands_that_split_badly(C, R, stride):
     """As for the GEMM: all operands 1 + 2^-7 - 2^-23, whose lower parts are the largest that truncation leaves."""
