@@ -4,6 +4,7 @@
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
+#include <utility>
 
 namespace perf {
 
@@ -111,6 +112,18 @@ __device__ __forceinline__ float half_allreduce(float v, Op op)
     float a, b;
     swap16(v, a, b);
     return op(a, b);
+}
+
+// f(integral_constant<int, 0>) ... f(integral_constant<int, N-1>): the index is a constant in the body.
+template <typename F, int... I>
+__device__ __forceinline__ void unrolled_impl(F &&f, std::integer_sequence<int, I...>)
+{
+    (f(std::integral_constant<int, I>{}), ...);
+}
+template <int N, typename F>
+__device__ __forceinline__ void unrolled(F &&f)
+{
+    unrolled_impl(f, std::make_integer_sequence<int, N>{});
 }
 
 }  // namespace perf

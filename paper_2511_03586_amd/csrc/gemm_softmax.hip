@@ -196,31 +196,33 @@ __global__ __launch_bounds__(64 * kFusedWaves, 1) void gemm_softmax_kernel(const
     }
 }
 
-// Longer and ragged rows: N <= 1024, K any multiple of 8, P of any alignment.  A workgroup of 4 waves (2 up to 64 columns:
-// 64 x (300x64x128) 5.3 us against 6.3) owns 32 rows x all
-// N columns; wave w the NT tiles of 32 columns from 32 NT w on, as 32x32 accumulators (128 registers at NT = 8) with B as
-// the MFMA's row operand, so that a lane's values belong to ONE row: row maxima and sums are in-lane plus one lane
-// exchange, and one LDS exchange between the waves.  B does not fit the LDS (1024 x 128 bf16 are 256 KiB): both
-// operands pass through it 32 K at a time (global->LDS loads, chunks past K read as zeros), B once per strip from the
-// L2.  At most 80 KiB of LDS, so that two workgroups share a CU and one's loads and exponentials overlap the other's
-// stores; those leave through staging of 8 KiB per wave as 4 rows x 256 bytes per instruction, past the caches
-// only where rows are whole 128-byte lines (a line that two waves or two instructions write is put together in the L2:
-// 96 x (600x777x80) 72 us so, 105 us past the caches).  That shape took 135 us as two launches; its P alone is 28 us
-// of writes at the copy rate, its exponentials about 20 us of vector work.
-// K-steps of operands in the LDS: a second one pays while it costs no workgroup per CU (400 x (200x100x80) 13.9 us
-// against 17.9; 32 x (600x301x64) 17.0 against 13.7 at NT = 4)
-constexpr int wide_stages(int nt) { return nt <= 2 ? 2 : 1; }
-constexpr int wide_chunk(int nt) { return nt < 2 ? nt : 2; }  // tiles of a wave that are staged at a time
+// Longer and ragged rows: N <= 1024, K any multiple of 8, P of any alignment.  A workgroup of NW waves owns 32 rows x all N
+// columns; wave w the NT tiles of 32 columns from 32 NT w on, as 32x32 accumulators with B as the MFMA's row operand, so
+// that a lane's values belong to ONE row: row maxima and sums are in-lane plus one lane exchange, and one LDS exchange
+// between the waves.  Both operands come 32 K at a time (chunks past K read as zeros), B once per strip from the L2:
+//   * NT <= 2: through two stages of the LDS that all waves fill (400 x (200x100x80) 13.2 us against 15.7 with the other form).
+//   * above: a wave loads the rows of B that it multiplies itself, reads a step's operands into registers and refills the
+//     stage behind its matrix instructions, without a barrier (80 x (512x384x64) 17.8 against 19.6).
+// At most 80 KiB of LDS, so that two workgroups or more share a CU and one's loads and exponentials overlap the other's
+// stores; from 385 columns on eight waves (the fp32 instructions of an exponential issue twice as fast from two waves
+// of a SIMD as from one): 96 x (600x800x80) 60 us against 63, 60 x (100x450x128) 9.6 against 11.3, but five tiles for 513 to 640
+// columns: 64 x (300x600x96) 19 against 23 with eight.
+// Write-out: 16 or 32 rows at a time through the LDS, so that a wave stores whole rows, 1 KiB of consecutive bytes per instruction,
+// past the caches.  With 256 bytes of four rows per instruction the lines that two of them share had to be put together in
+// the L2: 96 x (600x777x80) 82 us against 65 now, 80 x (512x384x64), whose rows are whole lines, 24.5 against 17.8,
+// 64 x (1000x1024x128) 106 against 74, 400 x (200x100x80) 18.7 against 13.2.  (Two store instructions that differ in the cache
+// policy alone, on the two sides of a test, are merged by the compiler into one of the plain kind.)
+// The first shape's P is 28 us of writes at the copy rate, its exponentials about 15 us of vector work.
+constexpr bool wide_own(int nt) { return nt > 2; }
+constexpr int wide_rows_out(int nt) { return nt > 2 ? 16 : 32; }  // as the LDS of the operands holds them
 template <int NT, typename PT, int NW>
-__global__ __launch_bounds__(64 * NW, 2) void gemm_softmax_wide_kernel(const uint16_t *__restrict__ A, const uint16_t *__restrict__ B,
+__global__ __launch_bounds__(64 * NW, NW == 8 ? 4 : 2) void gemm_softmax_wide_kernel(const uint16_t *__restrict__ A, const uint16_t *__restrict__ B,
                                                                    PT *__restrict__ P, int M, int N, int K, int64_t lda,
                                                                    int64_t ldb, int64_t ldp, int64_t strideA, int64_t strideB,
-                                                                   int64_t strideP, ExpConst ek, float t_min, int strips, int eights,
-                                                                   int whole_lines)
+                                                                   int64_t strideP, ExpConst ek, float t_min, int strips, int eights)
 {
-    constexpr int kStageB = 32 * NW * NT * kRowBytes, kStageA = 32 * kRowBytes, kStage = kStageB + kStageA;
-    constexpr int NST = wide_stages(NT);
-    constexpr int LB = 2 * NT, kLoads = LB + 1;
+    constexpr bool kOwn = wide_own(NT);
+    constexpr int kStage = (kOwn ? 32 * NT : 32 * NW * NT + 32) * kRowBytes, LB = 2 * NT;
     extern __shared__ __attribute__((aligned(1024))) char smem[];
     __shared__ float red[2][NW][32];
     const int tid = threadIdx.x, lane = tid & 63;
@@ -241,50 +243,85 @@ __global__ __launch_bounds__(64 * NW, 2) void gemm_softmax_wide_kernel(const uin
     const rsrc_t ra = make_rsrc(Ab, (uint32_t)(((int64_t)(rows - 1) * lda + K) * 2));
     const rsrc_t rb = make_rsrc(Bb, (uint32_t)(((int64_t)(N - 1) * ldb + K) * 2));
 
-    // load i of wave w: tile rows (NW i + w) * 16 .. +15; lane l row l / 4, the chunk stored at position l % 4
-    const int lrow = lane >> 2;
-    uint32_t vb[LB];
-    int kb;  // first K of this lane's chunk in a step (the swizzle of a row depends on its low four bits only)
-    {
-        const int ch = load_chunk(lrow, lane);
-        kb = ch * 8;
-#pragma unroll
-        for (int i = 0; i < LB; ++i) vb[i] = (uint32_t)(min((i * NW + wave) * 16 + lrow, N - 1) * ldb * 2) + ch * 16;
-    }
-    const uint32_t va = (uint32_t)(min((wave & 1) * 16 + lrow, rows - 1) * lda * 2) + kb * 2;
-    auto issue = [&](int ks) {
-        char *st = smem + (NST == 2 ? (ks & 1) * kStage : 0);
-        const bool in = ks * 32 + kb < K;
-        const uint32_t so = (uint32_t)ks * kRowBytes;
-#pragma unroll
-        for (int i = 0; i < LB; ++i) issue_load_to(rb, in ? vb[i] : kOutOfRange, so, st + (i * NW + wave) * 16 * kRowBytes);
-        issue_load_to(ra, in ? va : kOutOfRange, so, st + kStageB + (wave & 1) * 16 * kRowBytes);  // (waves 2, 3: the same again)
-    };
+    const int lrow = lane >> 2, kb = load_chunk(lrow, lane) * 8;  // a load: 16 rows, lane l row l / 4, the chunk stored at position l % 4
     float16_t acc[NT];
 #pragma unroll
     for (int j = 0; j < NT; ++j)
 #pragma unroll
         for (int e = 0; e < 16; ++e) acc[j][e] = 0.f;
-    issue(0);
-    if (NST == 2 && ksteps > 1) issue(1);
-    for (int ks = 0; ks < ksteps; ++ks) {
-        if (NST == 2 && ks + 1 < ksteps) wait_vmem<kLoads>();
-        else wait_vmem<0>();
-        wg_barrier();
-        const char *st = smem + (NST == 2 ? (ks & 1) * kStage : 0);
+    if constexpr (!kOwn) {
+        // load i of wave w: rows (NW i + w) * 16 .. + 15 of B
+        uint32_t vb[LB];
 #pragma unroll
-        for (int h = 0; h < 2; ++h) {
-            const int chunk = 2 * h + (lane >> 5);
-            const bf16x8_t a = *reinterpret_cast<const bf16x8_t *>(st + kStageB + frag_offset(lane & 31, chunk));
+        for (int i = 0; i < LB; ++i) vb[i] = (uint32_t)(min((i * NW + wave) * 16 + lrow, N - 1) * ldb * 2) + kb * 2;
+        const uint32_t va = (uint32_t)(min((wave & 1) * 16 + lrow, rows - 1) * lda * 2) + kb * 2;
+        auto issue = [&](int ks) {
+            char *st = smem + (ks & 1) * kStage;
+            const bool in = ks * 32 + kb < K;
+            const uint32_t so = (uint32_t)ks * kRowBytes;
 #pragma unroll
-            for (int j = 0; j < NT; ++j) {
-                const bf16x8_t b = *reinterpret_cast<const bf16x8_t *>(st + frag_offset((wave * NT + j) * 32 + (lane & 31), chunk));
-                acc[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(b, a, acc[j], 0, 0, 0);
+            for (int i = 0; i < LB; ++i) issue_load_to(rb, in ? vb[i] : kOutOfRange, so, st + (i * NW + wave) * 16 * kRowBytes);
+            issue_load_to(ra, in ? va : kOutOfRange, so, st + (32 * NW * NT + (wave & 1) * 16) * kRowBytes);  // (waves 2 on: the same again)
+        };
+        issue(0);
+        if (ksteps > 1) issue(1);
+        for (int ks = 0; ks < ksteps; ++ks) {
+            if (ks + 1 < ksteps) wait_vmem<LB + 1>();
+            else wait_vmem<0>();
+            wg_barrier();
+            const char *st = smem + (ks & 1) * kStage;
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                const int chunk = 2 * h + (lane >> 5);
+                const bf16x8_t a = *reinterpret_cast<const bf16x8_t *>(st + frag_offset(32 * NW * NT + (lane & 31), chunk));
+#pragma unroll
+                for (int j = 0; j < NT; ++j) {
+                    const bf16x8_t b = *reinterpret_cast<const bf16x8_t *>(st + frag_offset((wave * NT + j) * 32 + (lane & 31), chunk));
+                    acc[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(b, a, acc[j], 0, 0, 0);
+                }
             }
+            __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0): this wave is done with the stage
+            wg_barrier();
+            if (ks + 2 < ksteps) issue(ks + 2);
         }
-        __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0): this wave is done with the stage
-        wg_barrier();
-        if (ks + NST < ksteps) issue(ks + NST);
+    } else {
+        // load i: rows 16 i .. + 15 of the wave's own columns; the rows of A come straight into the matrix instruction's layout
+        char *const st = smem + wave * kStage;
+        const int tiles = min(max((N - 32 * wave * NT + 31) / 32, 0), NT);  // those that have columns
+        uint32_t vb[LB];
+#pragma unroll
+        for (int i = 0; i < LB; ++i) vb[i] = (uint32_t)(min(32 * wave * NT + 16 * i + lrow, N - 1) * ldb * 2) + kb * 2;
+        const uint32_t va = (uint32_t)(min(lane & 31, rows - 1) * lda * 2) + (lane >> 5) * 16;
+        bf16x8_t a[2], b[2][NT], next[2];
+        auto issue = [&](int ks) {
+            const bool in = ks * 32 + kb < K;
+            const uint32_t so = (uint32_t)ks * kRowBytes;
+#pragma unroll
+            for (int i = 0; i < LB; ++i)
+                if (i / 2 < tiles) issue_load_to(rb, in ? vb[i] : kOutOfRange, so, st + i * 16 * kRowBytes);
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                const uint32_t from = ks * 32 + 16 * h + 8 * (lane >> 5) < K ? va + 32 * h : kOutOfRange;
+                next[h] = __builtin_bit_cast(bf16x8_t, __builtin_amdgcn_raw_buffer_load_b128(ra, from, so, 0));
+            }
+        };
+        issue(0);
+        for (int ks = 0; ks < ksteps; ++ks) {
+            wait_vmem<0>();
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                a[h] = next[h];
+#pragma unroll
+                for (int j = 0; j < NT; ++j)
+                    b[h][j] = *reinterpret_cast<const bf16x8_t *>(st + frag_offset(j * 32 + (lane & 31), 2 * h + (lane >> 5)));
+            }
+            __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0): this wave is done with the stage
+            if (ks + 1 < ksteps) issue(ks + 1);
+#pragma unroll
+            for (int h = 0; h < 2; ++h)
+#pragma unroll
+                for (int j = 0; j < NT; ++j) acc[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(b[h][j], a[h], acc[j], 0, 0, 0);
+        }
     }
 
     // acc[j] element e: row m0 + lane % 32, column 32 (wave NT + j) + 8 (e / 4) + 4 (lane / 32) + e % 4
@@ -312,8 +349,9 @@ __global__ __launch_bounds__(64 * NW, 2) void gemm_softmax_wide_kernel(const uin
     swap32(m, x, y);
     red[0][wave][row] = __builtin_fmaxf(x, y);  // (both halves write the same)
     __syncthreads();
-    m = __builtin_fmaxf(red[0][0][row], red[0][1][row]);
-    if constexpr (NW == 4) m = __builtin_fmaxf(m, __builtin_fmaxf(red[0][2][row], red[0][3][row]));
+    m = red[0][0][row];
+#pragma unroll
+    for (int w = 1; w < NW; ++w) m = __builtin_fmaxf(m, red[0][w][row]);
 #pragma unroll
     for (int j = 0; j < NT; ++j)
 #pragma unroll
@@ -331,52 +369,62 @@ __global__ __launch_bounds__(64 * NW, 2) void gemm_softmax_wide_kernel(const uin
         for (int e = 0; e < 16; ++e) z += acc[j][e];
     swap32(z, x, y);
     red[1][wave][row] = x + y;
-    __syncthreads();  // (the operand stages are free since the last step's barrier)
-    float sum = red[1][0][row] + red[1][1][row];
-    if constexpr (NW == 4) sum += red[1][2][row] + red[1][3][row];
+    __syncthreads();  // (behind it the operand stages are free)
+    float part[NW];
+#pragma unroll
+    for (int w = 0; w < NW; ++w) part[w] = red[1][w][row];
+#pragma unroll
+    for (int d = 1; d < NW; d *= 2)
+#pragma unroll
+        for (int w = 0; w + d < NW; w += 2 * d) part[w] += part[w + d];
+    const float sum = part[0];
     const float inv = 1.0f / sum;
 
-    // write-out, NC tiles = up to 64 columns at a time: kPieces pieces of 16 bytes per row, piece s at position s ^ row
-    constexpr int NC = wide_chunk(NT), kPieces = 8 * NC, kRowsPer = 64 / kPieces;
-    char *const stage = smem + wave * (32 * 16 * kPieces);
-    const int piece = lane % kPieces;
+    // Write-out, kOut rows at a time through the LDS of the operands.  kPieces pieces of 16 bytes per row, piece s at
+    // position s ^ row.
+    constexpr int kOut = wide_rows_out(NT), kPieces = 8 * NT * NW, kPitch = 16 * kPieces;
+    constexpr int kRowsPer = kPieces < 64 ? 64 / kPieces : 1;  // rows per store instruction
     PT *Pb = P + (int64_t)bz * strideP + (int64_t)m0 * ldp;
 #pragma unroll
-    for (int j0 = 0; j0 < NT; j0 += NC) {
+    for (int pass = 0; pass < 32 / kOut; ++pass) {
+        if (pass > 0) __syncthreads();  // the rows before have been read
+        if (row / kOut == pass) {
 #pragma unroll
-        for (int j = 0; j < NC; ++j)
-            if (j0 + j < NT) {
+            for (int j = 0; j < NT; ++j)
 #pragma unroll
                 for (int q = 0; q < 4; ++q) {
-                    const float16_t &c = acc[j0 + j < NT ? j0 + j : 0];
-                    const float4_t v = {c[4 * q] * inv, c[4 * q + 1] * inv, c[4 * q + 2] * inv, c[4 * q + 3] * inv};
-                    *reinterpret_cast<float4_t *>(stage + row * (16 * kPieces) + (((8 * j + 2 * q + half) ^ (row & (kPieces - 1))) << 4)) = v;
+                    const float4_t v = {acc[j][4 * q] * inv, acc[j][4 * q + 1] * inv, acc[j][4 * q + 2] * inv, acc[j][4 * q + 3] * inv};
+                    const int piece = 8 * (wave * NT + j) + 2 * q + half;
+                    *reinterpret_cast<float4_t *>(smem + row % kOut * kPitch + ((piece ^ (row & 15)) << 4)) = v;
                 }
-            }
-        __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0): own writes are in LDS (the region is this wave's alone)
-        const int col = col0 + 32 * j0 + 4 * piece;
-        const int left = piece < 8 * (NT - j0) ? N - col : 0;  // columns of this lane's piece that exist
+        }
+        __syncthreads();
 #pragma unroll
-        for (int i = 0; i < 32 / kRowsPer; ++i) {
-            const int r = kRowsPer * i + lane / kPieces;
-            const float4_t v = *reinterpret_cast<const float4_t *>(stage + r * (16 * kPieces) + ((piece ^ (r & (kPieces - 1))) << 4));
-            PT *dst = Pb + (int64_t)r * ldp + col;
-            if (r < rows && left >= 4) {
-                if constexpr (sizeof(PT) == 4) {
-                    if (whole_lines) __builtin_nontemporal_store(v, reinterpret_cast<float4_at4 *>(dst));
-                    else *reinterpret_cast<float4_at4 *>(dst) = v;
-                } else {
-                    const uint2_t o = {pack_bf16(v[0], v[1]), pack_bf16(v[2], v[3])};
-                    if (whole_lines) __builtin_nontemporal_store(o, reinterpret_cast<uint2_at2 *>(dst));
-                    else *reinterpret_cast<uint2_at2 *>(dst) = o;
+        for (int i = 0; i < kOut / NW / kRowsPer; ++i) {
+            const int r = wave * (kOut / NW) + i * kRowsPer + (kRowsPer > 1 ? lane / kPieces : 0);
+            if (pass * kOut + r < rows) {
+                PT *to = Pb + (int64_t)(pass * kOut + r) * ldp;
+#pragma unroll
+                for (int p0 = 0; p0 < kPieces; p0 += 64) {
+                    const int piece = kRowsPer > 1 ? lane % kPieces : p0 + lane, left = N - 4 * piece;  // columns from here on
+                    if (left <= 0) continue;
+                    const float4_t v = *reinterpret_cast<const float4_t *>(smem + r * kPitch + ((piece ^ (r & 15)) << 4));
+                    PT *dst = to + 4 * piece;
+                    if (left >= 4) {
+                        if constexpr (sizeof(PT) == 4) {
+                            __builtin_nontemporal_store(v, reinterpret_cast<float4_at4 *>(dst));
+                        } else {
+                            const uint2_t o = {pack_bf16(v[0], v[1]), pack_bf16(v[2], v[3])};
+                            __builtin_nontemporal_store(o, reinterpret_cast<uint2_at2 *>(dst));
+                        }
+                    } else {
+#pragma unroll
+                        for (int e = 0; e < 3; ++e)
+                            if (e < left) Elem<PT>::store1(dst + e, v[e]);
+                    }
                 }
-            } else if (r < rows) {
-#pragma unroll
-                for (int e = 0; e < 3; ++e)
-                    if (e < left) Elem<PT>::store1(dst + e, v[e]);
             }
         }
-        __builtin_amdgcn_wave_barrier();  // (the wave's LDS operations execute in order)
     }
 }
 
@@ -385,7 +433,7 @@ static perf_status launch_wide(const void *A, const void *B, void *P, int64_t M,
                                int64_t ldp, int64_t batch, int64_t strideA, int64_t strideB, int64_t strideP, float alpha,
                                hipStream_t st)
 {
-    constexpr int kStages = wide_stages(NT) * (32 * NW * NT + 32) * kRowBytes, kOut = NW * 32 * 128 * wide_chunk(NT);
+    constexpr int kStages = wide_own(NT) ? 32 * NW * NT * kRowBytes : 2 * (32 * NW * NT + 32) * kRowBytes, kOut = wide_rows_out(NT) * 128 * NT * NW;
     constexpr int kLds = kStages > kOut ? kStages : kOut;
     auto kern = gemm_softmax_wide_kernel<NT, PT, NW>;
     static std::atomic<bool> attr_done{false};  // (idempotent per-function setting)
@@ -396,15 +444,13 @@ static perf_status launch_wide(const void *A, const void *B, void *P, int64_t M,
     }
     const ExpConst ek = make_exp_const(alpha);
     const float t_min = ek.c_hi > 0.f ? std::fmax(-200.0f / ek.c_hi, -FLT_MAX) : -FLT_MAX;
-    const int64_t line = 128 / sizeof(PT);
-    const int whole_lines = N % line == 0 && ldp % line == 0 && strideP % line == 0 && aligned(P, 128);
     const int64_t strips = (M + 31) / 32, per_launch = (max_blocks(64 * NW) / strips) / 8 * 8;
     if (per_launch < 8) return PERF_ERR_UNSUPPORTED;
     for (int64_t b0 = 0; b0 < batch; b0 += per_launch) {
         const int64_t nb = batch - b0 < per_launch ? batch - b0 : per_launch;
         hipLaunchKernelGGL(kern, dim3((unsigned)(strips * nb)), dim3(64 * NW), kLds, st, (const uint16_t *)A + b0 * strideA,
                            (const uint16_t *)B + b0 * strideB, (PT *)P + b0 * strideP, (int)M, (int)N, (int)K, lda, ldb, ldp,
-                           strideA, strideB, strideP, ek, t_min, (int)strips, (int)(nb / 8), whole_lines);
+                           strideA, strideB, strideP, ek, t_min, (int)strips, (int)(nb / 8));
     }
     return launch_status();
 }
@@ -481,6 +527,7 @@ extern "C" perf_status perf_gemm_softmax(const void *A, const void *B, void *P, 
     if (staged && N == 128) return launch_fused_staged<8>(A, B, P, M, N, K, lda, ldb, ldp, batch, strideA, strideB, strideP, alpha, st);
     const int64_t strips = (M + 31) / 32 * batch;
 #define PERF_WIDE(T, PT) return launch_wide<T, PT>(A, B, P, M, N, K, lda, ldb, ldp, batch, strideA, strideB, strideP, alpha, st)
+#define PERF_WIDE8(T) return launch_wide<T, float, 8>(A, B, P, M, N, K, lda, ldb, ldp, batch, strideA, strideB, strideP, alpha, st)
     if (loads_ok && lda <= (1 << 21) && ldb <= (1 << 21) && p_dt == PERF_BF16 && N <= 512 && (K == 64 || K == 128)) {
         if (N <= 128) PERF_WIDE(1, uint16_t);
         if (N <= 256) PERF_WIDE(2, uint16_t);
@@ -501,13 +548,14 @@ extern "C" perf_status perf_gemm_softmax(const void *A, const void *B, void *P, 
         if (N <= 64) return launch_wide<1, float, 2>(A, B, P, M, N, K, lda, ldb, ldp, batch, strideA, strideB, strideP, alpha, st);
         if (N <= 128) PERF_WIDE(1, float);
         if (N <= 256) PERF_WIDE(2, float);
-        if (N <= 512) PERF_WIDE(4, float);
+        if (N <= 384) PERF_WIDE(3, float);
+        if (N <= 512) PERF_WIDE8(2);
         if (N <= 640) PERF_WIDE(5, float);
-        if (N <= 768) PERF_WIDE(6, float);
-        if (N <= 896) PERF_WIDE(7, float);
-        PERF_WIDE(8, float);
+        if (N <= 768) PERF_WIDE8(3);
+        PERF_WIDE8(4);
     }
 #undef PERF_WIDE
+#undef PERF_WIDE8
     // Unfused: scores into P, then the row softmax in place (fp32 P only).
     if (p_dt != PERF_F32) return PERF_ERR_UNSUPPORTED;
     perf_status s = perf_gemm(A, B, P, M, N, K, PERF_ROW_MAJOR, lda, PERF_COL_MAJOR, ldb, ldp, batch, strideA, strideB,

@@ -26,7 +26,6 @@
 // groups of waves of the workgroup, whose sums are added through LDS in a fixed order.
 #pragma once
 #include <type_traits>
-#include <utility>
 #include "host_utils.h"
 #include "mfma_tile.h"
 #include "row_io.h"
@@ -516,18 +515,6 @@ struct ConvRows {
         }
     }
 };
-
-// f(integral_constant<int, 0>) ... f(integral_constant<int, N-1>): the index is a constant in the body.
-template <typename F, int... I>
-__device__ __forceinline__ void unrolled_impl(F &&f, std::integer_sequence<int, I...>)
-{
-    (f(std::integral_constant<int, I>{}), ...);
-}
-template <int N, typename F>
-__device__ __forceinline__ void unrolled(F &&f)
-{
-    unrolled_impl(f, std::make_integer_sequence<int, N>{});
-}
 
 // Workgroup id -> output tile: each XCD (ids are dealt round-robin to the 8 of them) gets a contiguous run of
 // tiles, and runs walk the grid in column-major bands of 4 tile-rows (a compact patch shares operand panels).

@@ -108,6 +108,15 @@ def test_strip_kernel_edges(M, N, K, batch, ldp):
     _check(M, N, K, alpha=0.0, batch=batch, ldp=ldp)
 
 
+@pytest.mark.parametrize("M,N,K,batch,ldp", [
+    (33, 384, 72, 9, 384), (31, 385, 80, 9, 385), (17, 449, 128, 16, 452),      # three tiles per wave, then two with eight waves
+    (33, 545, 96, 32, 545), (16, 673, 64, 64, 675), (32, 800, 136, 64, 800),    # five; three and four, whose last waves have none
+])
+def test_strip_kernel_waves_and_tiles(M, N, K, batch, ldp):
+    # both forms of the K-loop and of the write-out at the counts where they change, rows of 4 and 16 bytes' alignment
+    test_strip_kernel_edges(M, N, K, batch, ldp)
+
+
 @pytest.mark.parametrize("M,N,K", [(33, 5, 64), (40, 130, 128), (64, 512, 64), (1, 301, 128)])
 def test_strip_kernel_bf16_output(M, N, K):
     _check(M, N, K, batch=3, p_bf16=True)
