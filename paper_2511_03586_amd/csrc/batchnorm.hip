@@ -7,6 +7,7 @@
 //    part of a plane, or several whole planes where they are small; provisional mean, then first and second
 //    moments of the shifted data (the corrected two-pass form of the LayerNorm kernel), written as
 //    (mean_hi, mean_lo, M2).
+//  * bn_channel_kernel: channels that a workgroup holds in registers, in one launch.
 //  * bn_apply_kernel: streaming y = (x - mean) * scale + beta, 16-byte accesses, on the same segments.  The channel's
 //    segments are merged in double precision, by every workgroup while its loads fly if there are at most
 //    256 of them, else by bn_finalize_kernel (one workgroup per channel).
@@ -49,7 +50,7 @@ struct BnGeom {
     }
 };
 
-template <typename T, int NJ, bool RAG>
+template <typename T, int NJ, bool RAG, int THREADS = 256>
 struct BnItems {  // this thread's items of a segment
     static constexpr int E = Elem<T>::kPerChunk;
     const BnGeom &g;
@@ -62,12 +63,12 @@ struct BnItems {  // this thread's items of a segment
         c0 = (int64_t)part * (kBnSeg / E);
         total = g.G ? min(g.G, g.N - n0) * (int)g.cpp : (int)min((int64_t)(kBnSeg / E), g.cpp - c0);
     }
-    __device__ __forceinline__ bool all() const { return total == NJ * 256; }
-    __device__ __forceinline__ bool valid(int j) const { return j * 256 + (int)threadIdx.x < total; }
+    __device__ __forceinline__ bool all() const { return total == NJ * THREADS; }
+    __device__ __forceinline__ bool valid(int j) const { return j * THREADS + (int)threadIdx.x < total; }
     // element offset of item j from `base`; `dup`: its first elements that the chunk before holds as well
     __device__ __forceinline__ int64_t at(int j, int &dup) const
     {
-        const int i = min(j * 256 + (int)threadIdx.x, total - 1);
+        const int i = min(j * THREADS + (int)threadIdx.x, total - 1);
         const int p = g.G ? div_by(i, (int)g.cpp, g.m_cpp) : 0;
         const int64_t first = (g.G ? i - p * (int)g.cpp : c0 + i) * E, start = RAG ? min(first, g.HW - E) : first;
         dup = (int)(first - start);
@@ -270,6 +271,101 @@ __global__ __launch_bounds__(256) void bn_apply_kernel(const XT *__restrict__ x,
     else write(std::true_type{});
 }
 
+// Channels of up to 4096 chunks, which a workgroup holds in registers: a workgroup per channel, one launch, x is read once.
+// Bound by latency (launch, loads, block sums, stores) and the vector work of one CU per channel; two launches took (us, now):
+// 8x232x128x8 bf16 9.5 (4.3), 32x256x7x7 fp32 8.1 (4.2), 8x224x76x16 fp32 10.2 (6.4), 1x40x104x286 bf16 8.6 (6.5).  Larger channels
+// use more CUs in two launches (16x39x65x42 bf16, 5472 chunks, 8.1 against 11.0; 10x16x12x194 fp32, 5820, 6.9 against 7.4).
+// Sums as in bn_partial_kernel, the waves' in double.
+template <typename XT, typename PT, typename YT, int NJ, bool RAG, int THREADS>
+__global__ __launch_bounds__(THREADS) void bn_channel_kernel(const XT *__restrict__ x, const PT *__restrict__ gamma,
+                                                             const PT *__restrict__ beta, YT *__restrict__ y,
+                                                             float *__restrict__ mean_out, float *__restrict__ rstd_out, BnGeom g,
+                                                             float eps)
+{
+    constexpr int E = Elem<XT>::kPerChunk, W = THREADS / 64;
+    __shared__ double red[3][W];
+    const int c = blockIdx.x;
+    const BnItems<XT, NJ, RAG, THREADS> items(g, c, 0);
+    const XT *xp = x + items.base;
+    uint4_t raw[NJ];
+    int dup[RAG ? NJ : 1];
+#pragma unroll
+    for (int j = 0; j < NJ; ++j) raw[j] = load_chunk_nt<RAG>(xp + items.at(j, dup[RAG ? j : 0]));
+    const float b = Elem<PT>::load1(beta + c), w = Elem<PT>::load1(gamma + c);
+    const double n = (double)g.N * (double)g.HW;
+    float mu, scale, rstd;
+    auto block_sum = [&](float v, double *to) {
+        v = wave_allreduce(v, OpSum{});
+        if ((threadIdx.x & 63) == 0) to[threadIdx.x >> 6] = (double)v;
+    };
+    auto total = [&](const double *from) {
+        double sum = from[0];
+#pragma unroll
+        for (int i = 1; i < W; ++i) sum += from[i];
+        return sum;
+    };
+    auto reduce = [&](auto masked) {
+        constexpr bool kMasked = decltype(masked)::value;
+        auto counts = [&](int j, int e) { return !kMasked || (items.valid(j) && (!RAG || e >= dup[RAG ? j : 0])); };
+        float sum = 0.f;
+#pragma unroll
+        for (int j = 0; j < NJ; ++j) {
+            float v[E];
+            Elem<XT>::unpack(raw[j], v);
+#pragma unroll
+            for (int e = 0; e < E; ++e) sum += counts(j, e) ? v[e] : 0.f;
+        }
+        block_sum(sum, red[0]);
+        __syncthreads();
+        // (16 bits of it: the differences of bf16 elements are exact then, and those of fp32 ones lose nothing to speak of;
+        // one rounding pattern for a whole channel would not average out)
+        const float mean0 = __builtin_bit_cast(float, __builtin_bit_cast(uint32_t, (float)(total(red[0]) / n)) & 0xffffff00u);
+        float s1 = 0.f, s2 = 0.f;
+#pragma unroll
+        for (int j = 0; j < NJ; ++j) {
+            float v[E], q1 = 0.f, q2 = 0.f;  // (chunk by chunk: short chains of roundings)
+            Elem<XT>::unpack(raw[j], v);
+#pragma unroll
+            for (int e = 0; e < E; ++e) {
+                const float d = counts(j, e) ? v[e] - mean0 : 0.f;
+                q1 += d;
+                q2 = __builtin_fmaf(d, d, q2);
+            }
+            s1 += q1;
+            s2 += q2;
+        }
+        block_sum(s1, red[1]);
+        block_sum(s2, red[2]);
+        __syncthreads();
+        const double dm = total(red[1]) / n, m2 = total(red[2]) - dm * dm * n, var = m2 > 0.0 ? m2 / n : m2 * 0.0;  // (NaN stays)
+        mu = (float)((double)mean0 + dm);
+        rstd = (float)(1.0 / sqrt(var + (double)eps));
+    };
+    if (!RAG && items.all()) reduce(std::false_type{});
+    else reduce(std::true_type{});
+    scale = rstd * w;
+    if (threadIdx.x == 0) {
+        if (mean_out) mean_out[c] = mu;
+        if (rstd_out) rstd_out[c] = rstd;
+    }
+    // (y may be x: everything has been read.  Elements that two chunks of a ragged plane share are written twice, the same.)
+    YT *yp = y + items.base;
+    auto write = [&](auto masked) {
+#pragma unroll
+        for (int j = 0; j < NJ; ++j) {
+            int skip;
+            const int64_t o = items.at(j, skip);
+            float v[E], r[E];
+            Elem<XT>::unpack(raw[j], v);
+#pragma unroll
+            for (int e = 0; e < E; ++e) r[e] = __builtin_fmaf(v[e] - mu, scale, b);
+            if (!decltype(masked)::value || items.valid(j)) store_row_chunk<RAG, YT, E>(yp + o, r);
+        }
+    };
+    if (!RAG && items.all()) write(std::false_type{});
+    else write(std::true_type{});
+}
+
 // Planes of fewer elements than a chunk of 16 bytes: a workgroup per channel, an element at a time, sums in double.
 template <typename XT, typename PT, typename YT, int THREADS>
 __global__ __launch_bounds__(THREADS) void bn_small_kernel(const XT *__restrict__ x, const PT *__restrict__ gamma,
@@ -356,6 +452,22 @@ static void launch_bn(const BnArgs &a, bool vec)
         hipLaunchKernelGGL(kern, dim3((unsigned)a.C), dim3(threads), 0, a.st, (const XT *)a.x,
                            (const PT *)a.gamma, (const PT *)a.beta, (YT *)a.y, a.mean_out, a.rstd_out, (int)a.HW, (int)a.C,
                            (int)a.N, a.eps);
+        return;
+    }
+    const int64_t cpp = (a.HW + E - 1) / E;
+    if (a.N * cpp <= 4096) {
+        const BnGeom g{a.HW, (int)a.C, (int)a.N, cpp, (int)a.N, 0, 1, div_magic(cpp)};
+        auto go = [&](auto nj, auto threads) {
+            constexpr int NJ = decltype(nj)::value, THREADS = decltype(threads)::value;
+            auto kern = vec ? bn_channel_kernel<XT, PT, YT, NJ, false, THREADS> : bn_channel_kernel<XT, PT, YT, NJ, true, THREADS>;
+            hipLaunchKernelGGL(kern, dim3((unsigned)a.C), dim3(THREADS), 0, a.st, (const XT *)a.x, (const PT *)a.gamma, (const PT *)a.beta,
+                               (YT *)a.y, a.mean_out, a.rstd_out, g, a.eps);
+        };
+        const int64_t items = a.N * cpp;
+        if (items <= 256) go(std::integral_constant<int, 1>{}, std::integral_constant<int, 256>{});
+        else if (items <= 1024) go(std::integral_constant<int, 4>{}, std::integral_constant<int, 256>{});
+        else if (items <= 2048) go(std::integral_constant<int, 2>{}, std::integral_constant<int, 1024>{});
+        else go(std::integral_constant<int, 4>{}, std::integral_constant<int, 1024>{});
         return;
     }
     const BnGeom g = bn_geom(a, E);

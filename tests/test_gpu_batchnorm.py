@@ -104,3 +104,23 @@ def test_segment_edges(N, C, H, W):
     _check(N, C, H, W, x_bf16=True, y_bf16=True, inplace=True)
     _check(N, C, H, W, x_bf16=True, p_bf16=True)
     _check(N, C, H, W, y_bf16=True)
+
+
+@pytest.mark.parametrize("x_bf16,y_bf16", [(False, False), (True, True), (True, False)])
+@pytest.mark.parametrize("N,C,H,W", [
+    (1, 3, 2, 4), (2, 2, 16, 32), (3, 2, 3, 3), (4, 3, 11, 23),      # 256 threads: one chunk in all, every thread's full, ragged planes
+    (8, 2, 8, 64), (5, 2, 25, 33), (16, 2, 32, 32), (4, 2, 65, 63),  # 1024 threads, full and ragged; as many chunks as are held
+    (1, 1, 129, 128), (1, 1, 127, 257),                              # one row more than that (fp32): two launches
+])
+def test_channels_in_one_workgroup(N, C, H, W, x_bf16, y_bf16):
+    _check(N, C, H, W, x_bf16=x_bf16, y_bf16=y_bf16, seed=N + W)
+    # (the mean is an fp32 number: half a unit in its last place, 2^-20 at 30, over a deviation of 0.2 and more is under 1e-5)
+    _check(N, C, H, W, x_bf16=x_bf16, y_bf16=y_bf16, seed=N + W, offsets=[30.0] * C, inplace=x_bf16 == y_bf16, want_stats=False)
+
+
+def test_one_workgroup_nan_stays_in_its_channel():
+    x = np.random.default_rng(0).standard_normal((2, 3, 8, 9)).astype(np.float32)
+    x[1, 1, 3, 3] = np.nan
+    y, m, r = _run(x, np.ones(3, np.float32), np.zeros(3, np.float32), 1e-5, False, False, False)
+    assert np.isnan(y[:, 1]).all() and np.isnan(m[1]) and np.isnan(r[1])
+    assert np.isfinite(y[:, [0, 2]]).all() and np.isfinite(m[[0, 2]]).all()
