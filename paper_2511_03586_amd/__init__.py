@@ -1,13 +1,16 @@
-"""MI355X (gfx950) operator library: thin ctypes binding over ``libperf.so``.
+"""MI355X (gfx950) operator library: thin binding over ``libperf.so``.
 
 The functions here have the names and arguments of the C ABI in ``include/perf.h`` and do
 argument marshalling only; every step of every operator runs in the HIP kernels. torch is
 used by callers for device memory and streams. The library is loaded lazily and loading
-fails loudly: there is no fallback path of any kind.
+fails loudly: there is no fallback path of any kind. The operators are called through the
+CPython module ``_binding`` (csrc/binding.cpp), everything else through ctypes.
 """
 from __future__ import annotations
 
 import ctypes
+import importlib.machinery
+import importlib.util
 import os
 
 PERF_OK = 0
@@ -80,6 +83,27 @@ def lib() -> ctypes.CDLL:
     return _lib
 
 
+class _Native:
+    """The operators of ``_binding``; the module is loaded with the first of them."""
+
+    def __getattr__(self, name):
+        lib()
+        path = os.path.join(_HERE, "_binding.so")
+        if not os.path.exists(path):
+            raise RuntimeError(f"{path} not found: build it with `python -m paper_2511_03586_amd.build`")
+        loader = importlib.machinery.ExtensionFileLoader("_binding", path)
+        module = importlib.util.module_from_spec(importlib.util.spec_from_loader("_binding", loader))
+        loader.exec_module(module)
+        module.set_fallback(lambda fn: getattr(lib(), fn))
+        for fn in SIGNATURES:
+            if hasattr(module, fn):
+                self.__dict__[fn] = getattr(module, fn)
+        return self.__dict__[name]
+
+
+_native = _Native()
+
+
 def status_string(status: int) -> str:
     return lib().perf_status_string(int(status)).decode()
 
@@ -97,35 +121,45 @@ def _check(fn: str, status: int, check: bool) -> int:
 def perf_softmax(x, y, rows, cols, ldx, ldy, x_dt=PERF_F32, y_dt=PERF_F32, scale=1.0, stream=None,
                  check=True) -> int:
     """x, y: device addresses (ints). See ``perf_softmax`` in include/perf.h."""
-    return _check("perf_softmax", lib().perf_softmax(x, y, rows, cols, ldx, ldy, x_dt, y_dt, scale, stream), check)
+    status = _native.perf_softmax(x, y, rows, cols, ldx, ldy, x_dt, y_dt, scale, stream)
+    if status and check:
+        raise PerfError("perf_softmax", status)
+    return status
 
 
 def perf_layernorm(x, gamma, beta, y, mean_out, rstd_out, rows, cols, ldx, ldy, eps, x_dt, param_dt, y_dt,
                    stream=None, check=True) -> int:
-    return _check("perf_layernorm",
-                  lib().perf_layernorm(x, gamma, beta, y, mean_out, rstd_out, rows, cols, ldx, ldy, eps,
-                                       x_dt, param_dt, y_dt, stream), check)
+    status = _native.perf_layernorm(
+        x, gamma, beta, y, mean_out, rstd_out, rows, cols, ldx, ldy, eps, x_dt, param_dt, y_dt, stream)
+    if status and check:
+        raise PerfError("perf_layernorm", status)
+    return status
 
 
 def perf_gemm(A, B, C, M, N, K, la, lda, lb, ldb, ldc, batch=1, strideA=0, strideB=0, strideC=0, alpha=1.0,
               ab_dt=PERF_BF16, c_dt=PERF_F32, stream=None, check=True) -> int:
-    return _check("perf_gemm",
-                  lib().perf_gemm(A, B, C, M, N, K, la, lda, lb, ldb, ldc, batch, strideA, strideB, strideC,
-                                  alpha, ab_dt, c_dt, stream), check)
+    status = _native.perf_gemm(
+        A, B, C, M, N, K, la, lda, lb, ldb, ldc, batch, strideA, strideB, strideC, alpha, ab_dt, c_dt, stream)
+    if status and check:
+        raise PerfError("perf_gemm", status)
+    return status
 
 
 def perf_gemm_softmax(A, B, P, M, N, K, lda, ldb, ldp, batch=1, strideA=0, strideB=0, strideP=0, alpha=1.0,
                       ab_dt=PERF_BF16, p_dt=PERF_F32, stream=None, check=True) -> int:
-    return _check("perf_gemm_softmax",
-                  lib().perf_gemm_softmax(A, B, P, M, N, K, lda, ldb, ldp, batch, strideA, strideB, strideP,
-                                          alpha, ab_dt, p_dt, stream), check)
+    status = _native.perf_gemm_softmax(
+        A, B, P, M, N, K, lda, ldb, ldp, batch, strideA, strideB, strideP, alpha, ab_dt, p_dt, stream)
+    if status and check:
+        raise PerfError("perf_gemm_softmax", status)
+    return status
 
 
 def perf_conv2d(x, w, y, N, H, W, C, K, R, S, stride_h, stride_w, pad_h, pad_w, xw_dt=PERF_BF16,
                 y_dt=PERF_BF16, stream=None, check=True) -> int:
-    return _check("perf_conv2d",
-                  lib().perf_conv2d(x, w, y, N, H, W, C, K, R, S, stride_h, stride_w, pad_h, pad_w,
-                                    xw_dt, y_dt, stream), check)
+    status = _native.perf_conv2d(x, w, y, N, H, W, C, K, R, S, stride_h, stride_w, pad_h, pad_w, xw_dt, y_dt, stream)
+    if status and check:
+        raise PerfError("perf_conv2d", status)
+    return status
 
 
 def perf_gemm_variant(A, B, C, M, N, K, la, lda, lb, ldb, ldc, batch, strideA, strideB, strideC, alpha, ab_dt, c_dt,
@@ -165,13 +199,17 @@ PERF_ADD, PERF_MUL, PERF_RELU = 0, 1, 2
 
 def perf_rmsnorm(x, gamma, y, rrms_out, rows, cols, ldx, ldy, eps, x_dt=PERF_BF16, param_dt=PERF_F32,
                  y_dt=PERF_BF16, stream=None, check=True) -> int:
-    return _check("perf_rmsnorm",
-                  lib().perf_rmsnorm(x, gamma, y, rrms_out, rows, cols, ldx, ldy, eps, x_dt, param_dt, y_dt, stream),
-                  check)
+    status = _native.perf_rmsnorm(x, gamma, y, rrms_out, rows, cols, ldx, ldy, eps, x_dt, param_dt, y_dt, stream)
+    if status and check:
+        raise PerfError("perf_rmsnorm", status)
+    return status
 
 
 def perf_reduce_mean(x, y, rows, cols, ldx, axis, x_dt=PERF_F32, y_dt=PERF_F32, stream=None, check=True) -> int:
-    return _check("perf_reduce_mean", lib().perf_reduce_mean(x, y, rows, cols, ldx, axis, x_dt, y_dt, stream), check)
+    status = _native.perf_reduce_mean(x, y, rows, cols, ldx, axis, x_dt, y_dt, stream)
+    if status and check:
+        raise PerfError("perf_reduce_mean", status)
+    return status
 
 
 def perf_reduce_mean_workspace_bytes(rows, cols, axis, x_dt=PERF_F32) -> int:
@@ -180,12 +218,17 @@ def perf_reduce_mean_workspace_bytes(rows, cols, axis, x_dt=PERF_F32) -> int:
 
 def perf_reduce_mean_ws(x, y, workspace, rows, cols, ldx, axis, x_dt=PERF_F32, y_dt=PERF_F32, stream=None,
                         check=True) -> int:
-    return _check("perf_reduce_mean_ws",
-                  lib().perf_reduce_mean_ws(x, y, workspace, rows, cols, ldx, axis, x_dt, y_dt, stream), check)
+    status = _native.perf_reduce_mean_ws(x, y, workspace, rows, cols, ldx, axis, x_dt, y_dt, stream)
+    if status and check:
+        raise PerfError("perf_reduce_mean_ws", status)
+    return status
 
 
 def perf_eltwise(op, a, b, y, n, dt=PERF_F32, stream=None, check=True) -> int:
-    return _check("perf_eltwise", lib().perf_eltwise(op, a, b, y, n, dt, stream), check)
+    status = _native.perf_eltwise(op, a, b, y, n, dt, stream)
+    if status and check:
+        raise PerfError("perf_eltwise", status)
+    return status
 
 
 def perf_batchnorm_workspace_bytes(N, C, H, W) -> int:
@@ -194,9 +237,11 @@ def perf_batchnorm_workspace_bytes(N, C, H, W) -> int:
 
 def perf_batchnorm(x, gamma, beta, y, mean_out, rstd_out, workspace, N, C, H, W, eps, x_dt=PERF_F32,
                    param_dt=PERF_F32, y_dt=PERF_F32, stream=None, check=True) -> int:
-    return _check("perf_batchnorm",
-                  lib().perf_batchnorm(x, gamma, beta, y, mean_out, rstd_out, workspace, N, C, H, W, eps, x_dt,
-                                       param_dt, y_dt, stream), check)
+    status = _native.perf_batchnorm(
+        x, gamma, beta, y, mean_out, rstd_out, workspace, N, C, H, W, eps, x_dt, param_dt, y_dt, stream)
+    if status and check:
+        raise PerfError("perf_batchnorm", status)
+    return status
 
 
 def perf_batchnorm_static_max_bytes() -> int:
@@ -205,13 +250,18 @@ def perf_batchnorm_static_max_bytes() -> int:
 
 def perf_batchnorm_static(x, gamma, beta, y, mean_out, rstd_out, N, C, H, W, eps, x_dt=PERF_F32,
                           param_dt=PERF_F32, y_dt=PERF_F32, stream=None, check=True) -> int:
-    return _check("perf_batchnorm_static",
-                  lib().perf_batchnorm_static(x, gamma, beta, y, mean_out, rstd_out, N, C, H, W, eps, x_dt,
-                                              param_dt, y_dt, stream), check)
+    status = _native.perf_batchnorm_static(
+        x, gamma, beta, y, mean_out, rstd_out, N, C, H, W, eps, x_dt, param_dt, y_dt, stream)
+    if status and check:
+        raise PerfError("perf_batchnorm_static", status)
+    return status
 
 
 def perf_copy(src, dst, nbytes, stream=None, check=True) -> int:
-    return _check("perf_copy", lib().perf_copy(src, dst, nbytes, stream), check)
+    status = _native.perf_copy(src, dst, nbytes, stream)
+    if status and check:
+        raise PerfError("perf_copy", status)
+    return status
 
 
 def perf_stream_probe(src, dst, nbytes, mode, unroll, threads, grid, policy, stream=None, check=True) -> int:

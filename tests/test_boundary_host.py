@@ -53,6 +53,23 @@ def test_softmax_argument_errors():
         perf.perf_softmax(None, FAKE, 1, 1, 1, 1)
 
 
+def test_argument_types_that_ctypes_takes():
+    # plain ints, floats and None are converted by the native module, everything else as ctypes does
+    import numpy as np
+    f = lambda **kw: perf.perf_softmax(**{**dict(x=FAKE, y=FAKE + 4096, rows=4, cols=8, ldx=8, ldy=7, check=False), **kw})
+    assert f() == perf.PERF_ERR_SHAPE  # (ldy < cols: every call below stops at the same check or an earlier one)
+    assert f(rows=np.int64(4), cols=np.int32(8)) == perf.PERF_ERR_SHAPE
+    assert f(x=ctypes.c_void_p(FAKE), y=ctypes.c_void_p(None)) == perf.PERF_ERR_NULL
+    assert f(scale=1, rows=True) == perf.PERF_ERR_SHAPE and f(scale=np.float32(2)) == perf.PERF_ERR_SHAPE
+    assert f(rows=2 ** 64 + 4) == perf.PERF_ERR_SHAPE and f(x_dt=2 ** 32 + 7) == perf.PERF_ERR_DTYPE  # (integers wrap)
+    assert f(x=2 ** 64 + FAKE, stream=0) == perf.PERF_ERR_SHAPE
+    for bad in (dict(rows=4.0), dict(x="x" * 3, rows="4"), dict(scale="1")):
+        with pytest.raises(ctypes.ArgumentError):
+            f(**bad)
+    with pytest.raises(TypeError):
+        perf.perf_softmax(FAKE)
+
+
 def test_layernorm_argument_errors():
     base = dict(x=FAKE, gamma=FAKE + 4096, beta=FAKE + 8192, y=FAKE + 12288, mean_out=None, rstd_out=None,
                 rows=4, cols=8, ldx=8, ldy=8, eps=1e-5, x_dt=perf.PERF_BF16, param_dt=perf.PERF_F32,
