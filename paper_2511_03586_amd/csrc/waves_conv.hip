@@ -50,7 +50,10 @@ static int64_t tiles_of(const StagedConv &c, int64_t bm, int64_t bn)
 //     (6x37x112x128 -> 64 5x5 22.5 against 26.4).  The main loop is ahead or level below 800 (1x16x96x64 -> 128 4.2 against
 //     4.3, 8x96x22x64 -> 64 6.2 against 7.0), with 257 to 700 tiles of 32 x 32 below 432 (5x83x32x128 -> 64 1x1 3.6 against 4.6,
 //     but 8x64x16x64 -> 64 5.9 against 5.1); the staged kernel below 400.
-//     Channels that it cannot take, 32 outputs: 7x64x120x48 -> 32 9.7 against 14.2.
+//     Where 64 channels would waste half a tile: 32 outputs from 576 on 32 x 32 up to 768 tiles (4x64x80x128 -> 32 8.5 against
+//     11.4), 64 x 32 up to 4096 (12x21x80x256 -> 32 5x5 26.7 against 47.4, 16x50x60x96 -> 32 11.1 against 12.9, 32x64x64x64 ->
+//     32 18.8 against 19.9); more outputs from 2000 on (6x64x192x256 -> 96 at stride 2 23.6 against 27.5, but 8x50x60x128 -> 96
+//     17.5 against 15.5).  Channels that the main loop cannot take, 32 outputs: 7x64x120x48 -> 32 9.7 against 14.2.
 struct WavesChoice {
     int tm, tn, waves;
 };
@@ -70,7 +73,9 @@ static WavesChoice choose(const StagedConv &c, int xw_dt, bool direct)
     }
     if (k < (!direct ? 400 : t32 > 256 && t32 <= 700 ? 432 : 800)) return {0, 0, 0};
     if (t32 <= 256) return {1, 1, k >= 1024 ? 8 : 4};
+    if (c.K <= 32 && k >= 576 && t32 <= 4096) return t32 <= 768 ? WavesChoice{1, 1, 4} : WavesChoice{2, 1, 4};
     if (t64 <= 256) return t64 > 128 && k >= 2000 ? WavesChoice{2, 2, 8} : WavesChoice{1, 1, 4};
+    if (narrow && t64 <= 640 && k >= 2000) return {2, 1, 4};
     if (t64 <= 400 && k >= 2000) return {2, 2, 4};
     if (!direct && c.K <= 32 && t32 <= 2048) return {1, 1, 4};
     return {0, 0, 0};
@@ -81,7 +86,8 @@ static perf_status launch_typed(const StagedConv &c, WavesChoice w)
 {
     if (w.tm == 2 && w.tn == 2) return w.waves == 8 ? launch<T, CT, 2, 2, 8>(c) : launch<T, CT, 2, 2, 4>(c);
     if constexpr (sizeof(T) == 4)
-        if (w.tm == 2) return w.waves == 8 ? launch<T, CT, 2, 1, 8>(c) : launch<T, CT, 2, 1, 4>(c);
+        if (w.tm == 2 && w.waves == 8) return launch<T, CT, 2, 1, 8>(c);
+    if (w.tm == 2) return launch<T, CT, 2, 1, 4>(c);
     return w.waves == 8 ? launch<T, CT, 1, 1, 8>(c) : launch<T, CT, 1, 1, 4>(c);
 }
 

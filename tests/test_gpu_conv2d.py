@@ -307,6 +307,7 @@ def test_staged_conv_edges(kw):
     dict(N=2, H=67, W=67, C=88, K=64, R=5, S=5, pad=2),         # 64 x 64 in one round
     dict(N=2, H=92, W=91, C=80, K=64, R=5, S=5, pad=2),         # ... in several
     dict(N=4, H=60, W=61, C=24, K=32, R=5, S=5, pad=0),         # bf16 channels that the main loop cannot take, 32 outputs
+    dict(N=7, H=60, W=61, C=64, K=32, R=3, S=3, pad=1),         # 64 x 32, one tile of channels
 ])
 def test_waves_conv_edges(kw):
     """The convolution whose waves divide the reduction, at the edges of its tiles, K-steps and taps."""
