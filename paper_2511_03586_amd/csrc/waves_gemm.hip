@@ -46,16 +46,18 @@ static int64_t tiles_of(const GemmArgs &g, int64_t bm, int64_t bn) { return ((g.
 //   * 32 x 32 while one round of them leaves CUs idle: fp32 with 8 waves (640x24x1920 11.0 against 28, 896x235x3200 19.8 against
 //     42 [64 x 64 41], 80x384x208 x4 4.3 against 9.3); bf16 with 8 from K = 1024 on, else 4 (63x208x3673 13.0 against 21.4,
 //     256x64x448 x5 4.0 against 5.8).  The direct kernel is ahead for K under 512 (512x512x384 3.4 against 3.8).
-//   * bf16 up to 512 such tiles: two of them per wave, along an operand with K strided, whose rows are loaded in pairs
-//     (160x2325x968 6.4 against 9.1 [32 x 32 7.9]).
+//   * bf16 up to 512 such tiles: two of them per wave, along an operand with K strided, whose rows are loaded in pairs, along A if
+//     both have (160x2325x968 6.4 against 9.1 [32 x 32 7.9], 696x720x2232 11.7 against 14.8 [along B 19.2]).
 //   * in one round of 64 x 64: these with 8 waves if they fill half of the chip and K is long (768x1024x1024 fp32 row-major
-//     16.8 against 19.4, 320x2998x2208 bf16 13.7 against 15.6, 1024x1024x4096 bf16, direct 16.8 against 19.1 but K = 2048 even),
-//     else 32 x 32 with 4 (736x728x144 fp32 5.9 against 9.1, 544x1131x222 bf16 5.2 against 6.5), but not bf16 of middling
-//     K (1408x384x528 7.2 against 6.7; row-major 960x1000x384 7.4 against 7.0; K contiguous 80x122x481 x46 8.6 against 8.2).
+//     16.8 against 19.4, 320x2998x2208 bf16 13.7 against 15.6, 1024x1024x4096 bf16, direct 16.8 against 19.1 but K = 2048 even;
+//     bf16 with K contiguous in both from 2048 on: 2488x256x1368 10.7 against 10.2), else 32 x 32 with 4 (736x728x144 fp32 5.9
+//     against 9.1, 544x1131x222 bf16 5.2 against 6.5), but not bf16 of middling K (1408x384x528 7.2 against 6.7; row-major
+//     960x1000x384 7.4 against 7.0; K contiguous in both 1538x640x349 8.0 against 6.8).
 //   * beyond that, to about two and a half rounds, tiles with 4 waves, two workgroups per CU (3480x376x568 fp32 19.0 against 23.5,
-//     3904x496x911 bf16 12.2 against 14.9, K under 512 448x2653x224 6.0 against 8.1), not for short K (1500x1200x80 fp32 8.3
-//     against 7.8), fp32 with K contiguous in both, or bf16 with K over 128 in row-major operands (1500x1200x256 8.7 against 6.9) or, up
-//     to 384, contiguous in both (487x3201x176 6.8 against 6.5).
+//     3904x496x911 bf16 12.2 against 14.9, K under 512 448x2653x224 6.0 against 8.1); fp32 of more than 512 of them 32 x 32 for
+//     K under 256 (2300x1000x160 12.5 against 14.0 [14.5]); not for short K (1024x2512x96 fp32 11.2 against 9.5), fp32 with
+//     K contiguous in both, row-major bf16 (832x2320x512 10.5 against 9.0) or bf16 with K contiguous in both from 81 to 383
+//     (1300x1300x100 6.8 against 6.3) and from 1500 on (3936x336x2080 21.6 against 20.5).
 struct WavesChoice {
     int tm, tn, waves;
 };
@@ -71,17 +73,16 @@ static WavesChoice choose(const GemmArgs &g, int ab_dt, bool direct)
     if (bf16) {
         const bool a_rows = g.la == PERF_ROW_MAJOR;
         if (t32 <= 256) return {1, 1, g.K >= 1024 ? 8 : 4};
-        if (t32 <= 512) return b_rows ? WavesChoice{1, 2, 4} : WavesChoice{2, 1, 4};
-        if (t64 <= 256 && g.K >= 1024) return {2, 2, 8};
-        if (t64 <= 256 && g.K <= (a_rows && b_rows ? 256 : both_k ? 400 : 511)) return {1, 1, 4};
-        if (t64 <= 256 || t64 > 512 || (both_k && g.K > 128 && g.K < 384)) return {0, 0, 0};
-        if (g.K >= 512) return {2, 2, 4};
-        if (a_rows && b_rows) return g.K <= 128 ? WavesChoice{1, 2, 4} : WavesChoice{0, 0, 0};
-        return {2, 1, 4};
+        if (t32 <= 512) return a_rows && b_rows ? WavesChoice{1, 2, 4} : WavesChoice{2, 1, 4};
+        const bool rows = a_rows && b_rows;
+        if (t64 <= 256 && g.K >= 1024) return g.K < (both_k ? 2048 : b_rows ? 1024 : 1280) ? WavesChoice{0, 0, 0} : WavesChoice{2, 2, 8};
+        if (t64 <= 256 && g.K <= (rows ? 256 : both_k ? 264 : 511)) return {1, 1, 4};
+        if (t64 <= 256 || t64 > 512 || rows || (both_k && ((g.K > 80 && g.K < 384) || g.K >= 1500))) return {0, 0, 0};
+        return g.K >= 512 || (!a_rows && !b_rows && g.K >= 256) ? WavesChoice{2, 2, 4} : WavesChoice{2, 1, 4};
     }
     if (t32 <= 256) return {1, 1, 8};
     if (t64 <= 256) return t64 > 128 && g.K >= 512 ? WavesChoice{2, 2, 8} : WavesChoice{1, 1, 4};
-    if (t64 <= 640 && !both_k && g.K >= 96) return g.K <= 128 ? WavesChoice{1, 1, 4} : WavesChoice{2, 2, 4};
+    if (t64 <= 640 && !both_k && g.K > 96) return t64 > 512 && g.K < 256 ? WavesChoice{1, 1, 4} : WavesChoice{2, 2, 4};
     return {0, 0, 0};
 }
 
