@@ -275,7 +275,7 @@ def build_paper_workloads(torch, perf):
     # the same two shapes with fp32 operands (the table states no dtype): split into bf16, a sixth of its peak
     amf = sets(G.dev(rng.uniform(rng.tensor_seed(pm.config, 0), (pm.M, pm.K), -1.0, 1.0)), 16)
     bmf = sets(G.dev(rng.uniform(rng.tensor_seed(pm.config, 1), (pm.N, pm.K), -1.0, 1.0)), 16)
-    wls.append(Workload("paper_matmul_768x1024x1024_f32", "staged_kernel<KRows,KRows,f32,64x64,2 groups>", "mfma_f32", pm.flops(),
+    wls.append(Workload("paper_matmul_768x1024x1024_f32", "waves_kernel<WaveRows,WaveRows,f32,64x64>", "mfma_f32", pm.flops(),
                         lambda i: perf.perf_gemm(amf[i % 16].data_ptr(), bmf[i % 16].data_ptr(), cm[i % 16].data_ptr(),
                                                  pm.M, pm.N, pm.K, ROW, pm.K, COL, pm.K, pm.N, 1, 0, 0, 0, 1.0, F32,
                                                  F32, st()), 16, "fp32 operands: 192 tiles of 64x64"))
