@@ -3,7 +3,7 @@
 The functions here have the names and arguments of the C ABI in ``include/perf.h`` and do
 argument marshalling only; every step of every operator runs in the HIP kernels. torch is
 used by callers for device memory and streams. The library is loaded lazily and loading
-fails loudly: there is no fallback path of any kind. The operators are called through the
+fails loudly: every call runs that library. The operators are called through the
 CPython module ``_binding`` (csrc/binding.cpp), everything else through ctypes.
 """
 from __future__ import annotations
@@ -83,21 +83,28 @@ def lib() -> ctypes.CDLL:
     return _lib
 
 
+_OPERATORS = ("perf_softmax", "perf_layernorm", "perf_gemm", "perf_gemm_softmax", "perf_conv2d", "perf_rmsnorm", "perf_reduce_mean",
+              "perf_reduce_mean_ws", "perf_eltwise", "perf_batchnorm", "perf_batchnorm_static", "perf_copy")
+
+
 class _Native:
-    """The operators of ``_binding``; the module is loaded with the first of them."""
+    """The operators: functions of ``_binding`` bound to the library that ``lib()`` has loaded, set with the first of them; under
+    a Python that ``_binding`` was not built for, the library's ctypes functions."""
 
     def __getattr__(self, name):
-        lib()
-        path = os.path.join(_HERE, "_binding.so")
-        if not os.path.exists(path):
-            raise RuntimeError(f"{path} not found: build it with `python -m paper_2511_03586_amd.build`")
-        loader = importlib.machinery.ExtensionFileLoader("_binding", path)
-        module = importlib.util.module_from_spec(importlib.util.spec_from_loader("_binding", loader))
-        loader.exec_module(module)
-        module.set_fallback(lambda fn: getattr(lib(), fn))
-        for fn in SIGNATURES:
-            if hasattr(module, fn):
-                self.__dict__[fn] = getattr(module, fn)
+        if name not in _OPERATORS:
+            raise AttributeError(name)
+        handle = lib()
+        path = os.path.join(_HERE, "_binding" + importlib.machinery.EXTENSION_SUFFIXES[0])
+        if os.path.exists(path):
+            loader = importlib.machinery.ExtensionFileLoader("_binding", path)
+            native = importlib.util.module_from_spec(importlib.util.spec_from_loader("_binding", loader))
+            loader.exec_module(native)
+            native.bind(lambda fn: ctypes.cast(getattr(handle, fn), _ptr).value, lambda fn: getattr(handle, fn))
+        else:
+            native = handle
+        for fn in _OPERATORS:
+            self.__dict__[fn] = getattr(native, fn)
         return self.__dict__[name]
 
 

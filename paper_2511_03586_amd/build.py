@@ -2,7 +2,8 @@
 
 Usage: ``python -m paper_2511_03586_amd.build``. hipcc cross-compiles, so this works on a
 machine without a GPU. Objects go to ``_build/`` (ignored); the library is written next to
-this file, where the binding looks for it, and ``_binding.so`` (g++, for the Python that runs this) with it.
+this file, where the binding looks for it, and with it the CPython module ``_binding`` (g++; its file name carries the tag of
+the Python that runs this).
 
 ``python -m paper_2511_03586_amd.build --timeline`` builds, beside it, the two diagnostic
 libraries ``libperf_timeline1.so`` / ``libperf_timeline2.so``: the same sources with the
@@ -11,6 +12,7 @@ main-loop step). ``paper_2511_03586_amd.timeline`` runs them; nothing else loads
 """
 from __future__ import annotations
 
+import importlib.machinery
 import os
 import subprocess
 import sys
@@ -20,7 +22,7 @@ from concurrent.futures import ThreadPoolExecutor
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libperf.so")
-BINDING = os.path.join(HERE, "_binding.so")
+BINDING = os.path.join(HERE, "_binding" + importlib.machinery.EXTENSION_SUFFIXES[0])
 SOURCES = ["misc.hip", "softmax.hip", "layernorm.hip", "gemm.hip", "waves_gemm.hip", "waves_conv.hip", "staged_gemm.hip", "staged_conv.hip", "gemm_softmax.hip", "conv2d.hip", "streaming.hip", "batchnorm.hip"]
 FLAGS = ["--offload-arch=gfx950", "-O3", "-fPIC", "-std=c++17",
          # keep the compiler from forming packed-fp32 VALU ops
@@ -47,9 +49,8 @@ def build(verbose: bool = True) -> str:
     with ThreadPoolExecutor(max_workers=min(len(SOURCES), os.cpu_count() or 1)) as pool:
         objs = list(pool.map(lambda s: _compile(s, objdir), SOURCES))
     subprocess.check_call(["hipcc", "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB, *objs])
-    # the CPython module beside it, which finds the library in its own folder
     subprocess.check_call(["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-I", sysconfig.get_paths()["include"],
-                           os.path.join(CSRC, "binding.cpp"), "-o", BINDING, "-L", HERE, "-l:libperf.so", "-Wl,-rpath,$ORIGIN"])
+                           os.path.join(CSRC, "binding.cpp"), "-o", BINDING])
     if verbose:
         print(f"built {LIB}")
     return LIB

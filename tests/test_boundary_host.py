@@ -4,6 +4,9 @@ machine without a GPU). No compute call is made here."""
 import ctypes
 import os
 import re
+import shutil
+import subprocess
+import sys
 
 import pytest
 
@@ -68,6 +71,34 @@ def test_argument_types_that_ctypes_takes():
             f(**bad)
     with pytest.raises(TypeError):
         perf.perf_softmax(FAKE)
+
+
+def test_operators_follow_the_library_path(tmp_path):
+    # LIB_PATH names the library for every function, wherever the loader would find another file of that name
+    (tmp_path / "found").mkdir()
+    (tmp_path / "found" / "libperf.so").write_bytes(b"not a library")
+    copy = shutil.copy(perf.LIB_PATH, tmp_path / "libother.so")
+    code = f"""
+import paper_2511_03586_amd as perf
+perf.LIB_PATH = {str(copy)!r}
+assert perf.perf_softmax({FAKE}, None, 4, 8, 8, 8, check=False) == perf.PERF_ERR_NULL
+assert type(perf._native.perf_softmax).__name__ == "builtin_function_or_method"
+loaded = [l.split()[-1] for l in open("/proc/self/maps") if "libperf" in l or "libother" in l]
+assert set(loaded) == {{perf.LIB_PATH}}, set(loaded)
+"""
+    subprocess.check_call([sys.executable, "-c", code], cwd=ROOT, env={**os.environ, "LD_LIBRARY_PATH": str(tmp_path / "found")})
+
+
+def test_operators_without_the_native_module():
+    # another Python than the one that built the module calls the same library through ctypes
+    code = f"""
+import importlib.machinery
+importlib.machinery.EXTENSION_SUFFIXES[0] = ".other.so"
+import paper_2511_03586_amd as perf
+assert perf.perf_softmax({FAKE}, None, 4, 8, 8, 8, check=False) == perf.PERF_ERR_NULL
+assert perf._native.perf_softmax is perf.lib().perf_softmax
+"""
+    subprocess.check_call([sys.executable, "-c", code], cwd=ROOT)
 
 
 def test_layernorm_argument_errors():
