@@ -317,27 +317,41 @@ __global__ __launch_bounds__(THREADS) void bn_channel_kernel(const XT *__restric
         }
         block_sum(sum, red[0]);
         __syncthreads();
-        // (16 bits of it: the differences of bf16 elements are exact then, and those of fp32 ones lose nothing to speak of;
-        // one rounding pattern for a whole channel would not average out)
-        const float mean0 = __builtin_bit_cast(float, __builtin_bit_cast(uint32_t, (float)(total(red[0]) / n)) & 0xffffff00u);
-        float s1 = 0.f, s2 = 0.f;
+        float mean0;
+        double dm, var;
+        auto moments = [&]() {
+            float s1 = 0.f, s2 = 0.f;
 #pragma unroll
-        for (int j = 0; j < NJ; ++j) {
-            float v[E], q1 = 0.f, q2 = 0.f;  // (chunk by chunk: short chains of roundings)
-            Elem<XT>::unpack(raw[j], v);
+            for (int j = 0; j < NJ; ++j) {
+                float v[E], q1 = 0.f, q2 = 0.f;  // (chunk by chunk: short chains of roundings)
+                Elem<XT>::unpack(raw[j], v);
 #pragma unroll
-            for (int e = 0; e < E; ++e) {
-                const float d = counts(j, e) ? v[e] - mean0 : 0.f;
-                q1 += d;
-                q2 = __builtin_fmaf(d, d, q2);
+                for (int e = 0; e < E; ++e) {
+                    const float d = counts(j, e) ? v[e] - mean0 : 0.f;
+                    q1 += d;
+                    q2 = __builtin_fmaf(d, d, q2);
+                }
+                s1 += q1;
+                s2 += q2;
             }
-            s1 += q1;
-            s2 += q2;
+            block_sum(s1, red[1]);
+            block_sum(s2, red[2]);
+            __syncthreads();
+            dm = total(red[1]) / n;
+            const double m2 = total(red[2]) - dm * dm * n;
+            var = m2 > 0.0 ? m2 / n : m2 * 0.0;  // (NaN stays)
+        };
+        // 16 bits of the mean: the differences of bf16 elements are exact then (one rounding pattern for a whole channel would
+        // not average out).  Where they miss it by more than half a deviation (fp32, a mean of 3e4 deviations and more) var
+        // would be what cancellation leaves of m2, so again about the mean itself: relative error of var at mean / deviation
+        // 1e6 1.5e-5 without, under 1e-7 with.  (dm and var are the same in all threads.)
+        mean0 = __builtin_bit_cast(float, __builtin_bit_cast(uint32_t, (float)(total(red[0]) / n)) & 0xffffff00u);
+        moments();
+        if (__builtin_amdgcn_readfirstlane(4.0 * dm * dm > var)) {
+            mean0 = (float)((double)mean0 + dm);
+            __syncthreads();  // (the sums have been read)
+            moments();
         }
-        block_sum(s1, red[1]);
-        block_sum(s2, red[2]);
-        __syncthreads();
-        const double dm = total(red[1]) / n, m2 = total(red[2]) - dm * dm * n, var = m2 > 0.0 ? m2 / n : m2 * 0.0;  // (NaN stays)
         mu = (float)((double)mean0 + dm);
         rstd = (float)(1.0 / sqrt(var + (double)eps));
     };

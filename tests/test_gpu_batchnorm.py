@@ -118,6 +118,26 @@ def test_channels_in_one_workgroup(N, C, H, W, x_bf16, y_bf16):
     _check(N, C, H, W, x_bf16=x_bf16, y_bf16=y_bf16, seed=N + W, offsets=[30.0] * C, inplace=x_bf16 == y_bf16, want_stats=False)
 
 
+@pytest.mark.parametrize("ratio", [1e4, 1e5, 1e6, 3e6])
+@pytest.mark.parametrize("N,C,H,W", [(2, 16, 16, 32), (4, 16, 31, 33), (4, 16, 64, 64)])   # 256 and 1024 threads, whole and ragged
+def test_one_workgroup_large_offsets(N, C, H, W, ratio):
+    """Means of up to 3e6 deviations, and a constant channel whose value 16 bits do not hold. An element's square meets at most
+    4 roundings in its chunk, 4 over the thread's chunks and 6 in the wave; the moment about the provisional mean is at
+    most 5/4 of the one about the mean: the variance is within 1.25 * 14 * 2^-24, its root within half of that."""
+    g = np.random.default_rng(int(ratio) + H)
+    x = (g.standard_normal((N, C, H, W)) + ratio * (1 + np.arange(C) / C)[None, :, None, None]).astype(np.float32)
+    x[:, 0] = np.float32(ratio * 1.2345678)
+    gamma, beta, eps = g.uniform(0.5, 1.5, C).astype(np.float32), np.zeros(C, np.float32), float(np.float32(1e-5))
+    y, m, r = _run(x, gamma, beta, eps, False, False, False)
+    x = x.astype(np.float64)
+    mean = x.mean(axis=(0, 2, 3))
+    rstd = 1 / np.sqrt(np.square(x - mean[None, :, None, None]).mean(axis=(0, 2, 3)) + eps)
+    assert np.max(np.abs(m - mean) / mean) <= 2.0 ** -23
+    assert np.max(np.abs(r - rstd) / rstd) <= 0.625 * 14 * 2.0 ** -24 + 2.0 ** -24
+    want = (x - m.astype(np.float64)[None, :, None, None]) * (rstd * gamma)[None, :, None, None]
+    assert np.all(np.abs(y - want) <= 1e-6 * np.abs(want) + 1e-6)
+
+
 def test_one_workgroup_nan_stays_in_its_channel():
     x = np.random.default_rng(0).standard_normal((2, 3, 8, 9)).astype(np.float32)
     x[1, 1, 3, 3] = np.nan
