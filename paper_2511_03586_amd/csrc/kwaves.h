@@ -25,6 +25,10 @@ namespace perf {
 // 8 (lane / 32) .. + 7 of the step, as they lie in memory.  kPairs: rows 2 l and 2 l + 1 of 64 are row l of fragments 2 p
 // and 2 p + 1 (else row l of fragment i is row 32 i + l).
 
+// A wave's LDS accesses execute in program order; this holds the compiler to it where a lane reads what another one wrote, or
+// writes what another one has read.
+__device__ __forceinline__ void wave_lds_fence() { __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront", "local"); }
+
 // Lane l's chunk l % 8 of rows lds_row(8 i + l / 8) to LDS; wr: the offset for i = 0.
 template <int N>
 __device__ __forceinline__ void park_rows(char *lds, int wr, const uint4_t (&raw)[N])
@@ -332,6 +336,12 @@ __global__ __launch_bounds__(64 * W, (WavesShape<T, TM, TN, W, ASrc, BSrc>::kWav
                         t.acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(pa[c][kPa[q]][i], pb[c][kPb[q]][j], t.acc[i][j], 0, 0, 0);
         }
     };
+    auto park = [&]() {
+        wave_lds_fence();  // (the step before has been read)
+        sa.park();
+        sb.park();
+        wave_lds_fence();
+    };
     // A step whose substep 0 is converted: the next substep's fragments are read and converted beside the products of one,
     // and behind the last one's reads the next step (NEXT) takes the LDS and the one after that the registers of its loads.
     auto step = [&](auto next, auto edge, auto next_edge, int i, int skip) {
@@ -345,8 +355,7 @@ __global__ __launch_bounds__(64 * W, (WavesShape<T, TM, TN, W, ASrc, BSrc>::kWav
             if constexpr (!kLast) {
                 read(std::integral_constant<int, s + 1>{});
             } else if constexpr (kNext) {
-                sa.park();
-                sb.park();
+                park();
                 sa.rows(k_of(i + 2));
                 sb.rows(k_of(i + 2));
                 read(std::integral_constant<int, 0>{});
@@ -382,8 +391,7 @@ __global__ __launch_bounds__(64 * W, (WavesShape<T, TM, TN, W, ASrc, BSrc>::kWav
         const bool ends = wave + (count - 1) * W == steps - 1;
         const int cut = ends ? skip : 0;
         start(k_of(0));
-        sa.park();
-        sb.park();
+        park();
         sa.rows(k_of(1));
         sb.rows(k_of(1));
         read(std::integral_constant<int, 0>{});
@@ -398,8 +406,7 @@ __global__ __launch_bounds__(64 * W, (WavesShape<T, TM, TN, W, ASrc, BSrc>::kWav
         t.clear();
         for (int i = first; i < count; ++i) {
             start(k_of(i));
-            sa.park();
-            sb.park();
+            park();
             const int cut = wave + i * W == steps - 1 ? skip : 0;
             unrolled<KS>([&](auto s) {
                 read(s);
@@ -423,6 +430,7 @@ __global__ __launch_bounds__(64 * W, (WavesShape<T, TM, TN, W, ASrc, BSrc>::kWav
     };
     // Sums to LDS in quads of rows; quad u of the tile (TM * TN * 4 of them, 64 lanes each) is added and stored by wave u % W.
     auto leave = [&]() {
+        wave_lds_fence();  // (the last step has been read)
 #pragma unroll
         for (int i = 0; i < TM; ++i)
 #pragma unroll
