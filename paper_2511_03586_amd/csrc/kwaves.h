@@ -12,8 +12,9 @@
 //     (a row per lane, as the matrix instruction wants it, moves 17 bytes per clock and CU from the L2, this form 55);
 //     passed through 128-byte LDS rows of the wave's own.
 //   * K-strided operand (WaveCols): one element (two for bf16) per lane, straight into the matrix instruction's layout.
-//   * fp32 is split into three bf16 after that, in registers (split_pair).  If a value did not split or a sum is not
-//     finite, the tile is computed again on the fp32 matrix instruction, which takes the same registers.
+//   * fp32 is split into three bf16 after that, in registers (split_pair).  If a value did not split and that can show in a
+//     sum, the tile is computed again with scaled operands; if a sum is not finite, on the fp32 matrix instruction, which
+//     takes the same registers.
 // The order of a sum depends on K and W alone, not on the tile.
 #pragma once
 #include "staged.h"
@@ -23,7 +24,7 @@ namespace perf {
 // The sources share an interface: init(); rows(k0): the loads of a K-step that are issued at once; cols(k0, s): those of
 // its k-substep s (16 k); park(): to LDS; frag(s, i, bits): the 8 elements of the lane in fragment i of substep s, k = 16 s +
 // 8 (lane / 32) .. + 7 of the step, as they lie in memory.  kPairs: rows 2 l and 2 l + 1 of 64 are row l of fragments 2 p
-// and 2 p + 1 (else row l of fragment i is row 32 i + l).
+// and 2 p + 1 (else row l of fragment i is row 32 i + l).  kTightRegs: not one more to spare beside this source.
 
 // A wave's LDS accesses execute in program order; this holds the compiler to it where a lane reads what another one wrote, or
 // writes what another one has read.
@@ -50,7 +51,7 @@ __device__ __forceinline__ void frag_rows(const char *lds, int rd, int i, uint4_
 template <typename T, int TR>
 struct WaveRows {
     static constexpr int R = 32 * TR, kLoads = R / 8, KS = 128 / sizeof(T) / 16, kLds = R * 128;
-    static constexpr bool kPairs = false;
+    static constexpr bool kPairs = false, kTightRegs = false;
     using Args = DenseArgs<T>;
     const T *base;
     uint32_t off[kLoads];  // bytes
@@ -93,7 +94,7 @@ struct WaveRows {
 template <typename T, int TR>
 struct WaveConv {
     static constexpr int R = 32 * TR, kLoads = R / 8, V = 16 / sizeof(T), KS = 128 / sizeof(T) / 16, kLds = R * 128;
-    static constexpr bool kPairs = false;
+    static constexpr bool kPairs = false, kTightRegs = true;
     struct Args {
         ConvArgs<T> g;
         uint32_t bytes;     // of x
@@ -156,7 +157,7 @@ struct WaveCols;
 template <int TR>
 struct WaveCols<float, TR> {
     static constexpr int KS = 2, kLds = 0;
-    static constexpr bool kPairs = false;
+    static constexpr bool kPairs = false, kTightRegs = false;
     using Args = DenseArgs<float>;
     const float *base;
     int64_t ld;
@@ -193,7 +194,7 @@ struct WaveCols<float, TR> {
 template <int TR>
 struct WaveCols<uint16_t, TR> {
     static constexpr int KS = 4, kLds = 0;
-    static constexpr bool kPairs = TR > 1;
+    static constexpr bool kPairs = TR > 1, kTightRegs = false;
     static constexpr int P = kPairs ? TR / 2 : 1;
     using Args = DenseArgs<uint16_t>;
     const uint16_t *base;
@@ -242,12 +243,37 @@ struct WaveCols<uint16_t, TR> {
     }
 };
 
+// The largest magnitude among the fp32 values of a step.
+__device__ __forceinline__ float larger(float m, uint32_t bits) { return __builtin_fmaxf(m, __builtin_fabsf(__builtin_bit_cast(float, bits))); }
+template <int N>
+__device__ __forceinline__ float largest_of(const uint4_t (&raw)[N])
+{
+    float m = 0.f;
+#pragma unroll
+    for (int i = 0; i < N; ++i)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) m = larger(m, raw[i][e]);
+    return m;
+}
+template <int KS, int N>
+__device__ __forceinline__ float largest_of(const uint32_t (&raw)[KS][N][8])
+{
+    float m = 0.f;
+#pragma unroll
+    for (int s = 0; s < KS; ++s)
+#pragma unroll
+        for (int i = 0; i < N; ++i)
+#pragma unroll
+            for (int e = 0; e < 8; ++e) m = larger(m, raw[s][i][e]);
+    return m;
+}
+
 template <typename T, int TM, int TN, int W, typename ASrc, typename BSrc>
 struct WavesShape {
     static constexpr int BM = 32 * TM, BN = 32 * TN, kThreads = 64 * W, BK = 128 / sizeof(T);
     static constexpr int kSum = TM * TN * 4096;  // a wave's sum
     static constexpr int kWave = ASrc::kLds + BSrc::kLds > kSum ? ASrc::kLds + BSrc::kLds : kSum;
-    static constexpr int kLds = kWave * W + 4 * W;
+    static constexpr int kLds = kWave * W + 8 * W;  // (and a flag and a value per wave)
     static_assert(kLds <= 160 * 1024, "LDS of one CU");
     // registers: 256 for 64 x 64 (and all but the smallest fp32 tile), 168 and 128 for the smaller ones
     static constexpr int kWavesPerSimd = TM * TN == 1 ? 4 : TM * TN == 2 && sizeof(T) == 2 ? 3 : 2;
@@ -274,7 +300,7 @@ __global__ __launch_bounds__(64 * W, (WavesShape<T, TM, TN, W, ASrc, BSrc>::kWav
     const int steps = (int)((K + BK - 1) / BK), count = steps > wave ? (steps - wave + W - 1) / W : 0;
     auto k_of = [&](int i) { return min((int64_t)(wave + i * W) * BK, K - BK); };  // (past the last: the last)
     WaveTile<TM, TN> t;
-    Lost lost;
+    Lost lost_of[ASrc::kTightRegs ? 1 : 2], &lost_a = lost_of[0], &lost_b = lost_of[ASrc::kTightRegs ? 0 : 1];
     // A k-substep: its fragments as they lie in memory (read), as the matrix instruction takes them (convert; EDGE: the first
     // `skip` k of the step are zeros), its products (multiply).
     uint4_t ra[TM][NV], rb[TN][NV];
@@ -294,7 +320,7 @@ __global__ __launch_bounds__(64 * W, (WavesShape<T, TM, TN, W, ASrc, BSrc>::kWav
     };
     bf16x8_t pa[2][NP][TM], pb[2][NP][TN];
     auto convert = [&](auto s, auto edge, int skip) {
-        auto one = [&](uint4_t (&raw)[NV], auto &planes, int i) {
+        auto one = [&](uint4_t (&raw)[NV], auto &planes, int i, Lost &lost) {
             if constexpr (decltype(edge)::value) mask(s, raw, skip);
             if constexpr (NP == 1) {
                 planes[0][i] = __builtin_bit_cast(bf16x8_t, raw[0]);
@@ -313,9 +339,9 @@ __global__ __launch_bounds__(64 * W, (WavesShape<T, TM, TN, W, ASrc, BSrc>::kWav
             }
         };
 #pragma unroll
-        for (int i = 0; i < TM; ++i) one(ra[i], pa[s & 1], i);
+        for (int i = 0; i < TM; ++i) one(ra[i], pa[s & 1], i, lost_a);
 #pragma unroll
-        for (int j = 0; j < TN; ++j) one(rb[j], pb[s & 1], j);
+        for (int j = 0; j < TN; ++j) one(rb[j], pb[s & 1], j, lost_b);
     };
     auto multiply = [&](auto s) {
         constexpr int c = s & 1;
@@ -336,11 +362,16 @@ __global__ __launch_bounds__(64 * W, (WavesShape<T, TM, TN, W, ASrc, BSrc>::kWav
                         t.acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(pa[c][kPa[q]][i], pb[c][kPb[q]][j], t.acc[i][j], 0, 0, 0);
         }
     };
-    auto park = [&]() {
+    // Parks a step; load(): the loads that take its registers.  (The compiler moves none past a fence: beside the convolution's
+    // source they go between the writes, 4x28x28x64 -> 128 fp32 8.5 us against 8.75, 768x768x1024 with K contiguous 16.0 behind them
+    // against 16.9.)
+    auto park = [&](auto &&load) {
         wave_lds_fence();  // (the step before has been read)
         sa.park();
         sb.park();
+        if constexpr (ASrc::kTightRegs) load();
         wave_lds_fence();
+        if constexpr (!ASrc::kTightRegs) load();
     };
     // A step whose substep 0 is converted: the next substep's fragments are read and converted beside the products of one,
     // and behind the last one's reads the next step (NEXT) takes the LDS and the one after that the registers of its loads.
@@ -355,9 +386,10 @@ __global__ __launch_bounds__(64 * W, (WavesShape<T, TM, TN, W, ASrc, BSrc>::kWav
             if constexpr (!kLast) {
                 read(std::integral_constant<int, s + 1>{});
             } else if constexpr (kNext) {
-                park();
-                sa.rows(k_of(i + 2));
-                sb.rows(k_of(i + 2));
+                park([&]() {
+                    sa.rows(k_of(i + 2));
+                    sb.rows(k_of(i + 2));
+                });
                 read(std::integral_constant<int, 0>{});
             }
             __builtin_amdgcn_sched_barrier(0);
@@ -391,9 +423,10 @@ __global__ __launch_bounds__(64 * W, (WavesShape<T, TM, TN, W, ASrc, BSrc>::kWav
         const bool ends = wave + (count - 1) * W == steps - 1;
         const int cut = ends ? skip : 0;
         start(k_of(0));
-        park();
-        sa.rows(k_of(1));
-        sb.rows(k_of(1));
+        park([&]() {
+            sa.rows(k_of(1));
+            sb.rows(k_of(1));
+        });
         read(std::integral_constant<int, 0>{});
         convert(std::integral_constant<int, 0>{}, yes, count == 1 ? cut : 0);
         int i = 0;
@@ -401,31 +434,59 @@ __global__ __launch_bounds__(64 * W, (WavesShape<T, TM, TN, W, ASrc, BSrc>::kWav
         if (i + 1 < count) step(yes, no, yes, i, cut);
         step(no, yes, no, 0, cut);
     }
-    // The same on the fp32 instruction, without the overlap.
-    auto sum_unit = [&](int first) {
+    // The sum again without the overlap, from step `first` on: split once more, the operands times times_a and times_b (SCALED;
+    // then every fp32 value fits), or on the fp32 instruction, which takes 2.7 times the cycles (all of A of 768x1024x1024 under
+    // 2^-110: 32 us for 36).
+    auto sum_again = [&](auto scaled, int first, float times_a, float times_b) {
+        constexpr bool kScaled = decltype(scaled)::value;
         t.clear();
         for (int i = first; i < count; ++i) {
             start(k_of(i));
-            park();
+            park([]() {});
             const int cut = wave + i * W == steps - 1 ? skip : 0;
             unrolled<KS>([&](auto s) {
                 read(s);
+                if constexpr (kScaled) {
+                    auto scale = [&](uint4_t (&raw)[NV], float times) {
 #pragma unroll
-                for (int m = 0; m < TM; ++m) mask(s, ra[m], cut);
-#pragma unroll
-                for (int n = 0; n < TN; ++n) mask(s, rb[n], cut);
-#pragma unroll
-                for (int e = 0; e < 8; ++e)
-#pragma unroll
-                    for (int m = 0; m < TM; ++m)
-#pragma unroll
-                        for (int n = 0; n < TN; ++n) {
-                            const uint32_t x = ra[m][e >> 2][e & 3], y = rb[n][e >> 2][e & 3];
-                            t.acc[m][n] = __builtin_amdgcn_mfma_f32_32x32x2f32(__builtin_bit_cast(float, x), __builtin_bit_cast(float, y),
-                                                                              t.acc[m][n], 0, 0, 0);
+                        for (int e = 0; e < 8; ++e) {
+                            const uint32_t bits = raw[e >> 2][e & 3];
+                            raw[e >> 2][e & 3] = __builtin_bit_cast(uint32_t, __builtin_bit_cast(float, bits) * times);
                         }
+                    };
+#pragma unroll
+                    for (int m = 0; m < TM; ++m) scale(ra[m], times_a);
+#pragma unroll
+                    for (int n = 0; n < TN; ++n) scale(rb[n], times_b);
+                    convert(s, yes, cut);
+                    multiply(s);
+                } else {
+#pragma unroll
+                    for (int m = 0; m < TM; ++m) mask(s, ra[m], cut);
+#pragma unroll
+                    for (int n = 0; n < TN; ++n) mask(s, rb[n], cut);
+#pragma unroll
+                    for (int e = 0; e < 8; ++e)
+#pragma unroll
+                        for (int m = 0; m < TM; ++m)
+#pragma unroll
+                            for (int n = 0; n < TN; ++n) {
+                                const uint32_t x = ra[m][e >> 2][e & 3], y = rb[n][e >> 2][e & 3];
+                                t.acc[m][n] = __builtin_amdgcn_mfma_f32_32x32x2f32(__builtin_bit_cast(float, x), __builtin_bit_cast(float, y),
+                                                                                  t.acc[m][n], 0, 0, 0);
+                            }
+                }
                 __builtin_amdgcn_sched_barrier(0);
             });
+        }
+        if constexpr (kScaled) {
+            const float back_a = times_a > 1.f ? 0x1p-24f : 1.f, back_b = times_b > 1.f ? 0x1p-24f : 1.f;
+#pragma unroll
+            for (int i = 0; i < TM; ++i)
+#pragma unroll
+                for (int j = 0; j < TN; ++j)
+#pragma unroll
+                    for (int e = 0; e < 16; ++e) t.acc[i][j][e] *= back_a * back_b;
         }
     };
     // Sums to LDS in quads of rows; quad u of the tile (TM * TN * 4 of them, 64 lanes each) is added and stored by wave u % W.
@@ -440,29 +501,84 @@ __global__ __launch_bounds__(64 * W, (WavesShape<T, TM, TN, W, ASrc, BSrc>::kWav
                     *reinterpret_cast<float4_t *>(mine + (((i * TN + j) * 4 + q) * 64 + lane) * 16) =
                         float4_t{t.acc[i][j][4 * q], t.acc[i][j][4 * q + 1], t.acc[i][j][4 * q + 2], t.acc[i][j][4 * q + 3]};
     };
+    // Quad u of the tile's sums.
+    auto total = [&](int u) {
+        const char *from = smem + (u * 64 + lane) * 16;
+        float4_t v = *reinterpret_cast<const float4_t *>(from);
+#pragma unroll
+        for (int w = 1; w < W; ++w) v += *reinterpret_cast<const float4_t *>(from + w * Shape::kWave);
+        return v;
+    };
     leave();
     if constexpr (NP > 1) {
-        float z = 0.f;  // (infinities and NaN make it NaN)
+        auto not_finite = [&]() {
+            float z = 0.f;  // (infinities and NaN make it NaN)
 #pragma unroll
-        for (int i = 0; i < TM; ++i)
+            for (int i = 0; i < TM; ++i)
 #pragma unroll
-            for (int j = 0; j < TN; ++j)
+                for (int j = 0; j < TN; ++j)
 #pragma unroll
-                for (int e = 0; e < 16; ++e) z = __builtin_fmaf(t.acc[i][j][e], 0.f, z);
+                    for (int e = 0; e < 16; ++e) z = __builtin_fmaf(t.acc[i][j][e], 0.f, z);
+            return __any(z != 0.f);
+        };
         int *flags = reinterpret_cast<int *>(smem + Shape::kWave * W);
-        const bool odd = __any(lost.any() || z != 0.f);
-        if (lane == 0) flags[wave] = odd;
-        __syncthreads();
-        int any = 0;
+        float *values = reinterpret_cast<float *>(flags + W);
+        // Any wave's flags, in all of them (a barrier: the sums are complete behind it).
+        auto any_of = [&](int mine) {
+            if (lane == 0) flags[wave] = mine;
+            __syncthreads();
+            int any = 0;
 #pragma unroll
-        for (int w = 0; w < W; ++w) any |= flags[w];
-        if (__builtin_amdgcn_readfirstlane(any)) {
-            __syncthreads();  // (flags and sums have been read before anything is written again)
+            for (int w = 0; w < W; ++w) any |= flags[w];
+            return __builtin_amdgcn_readfirstlane(any);
+        };
+        constexpr int kLostA = 1, kLostB = 2, kNotFinite = 4;
+        const int met = any_of((__any(lost_a.any()) ? kLostA : 0) | (__any(lost_b.any()) ? kLostB : 0) | (not_finite() ? kNotFinite : 0));
+        if (met) {
             int first = 0;
             asm volatile("" : "+s"(first));  // (what the compiler would keep for this costs the loop above registers)
-            sum_unit(first);
-            leave();
-            __syncthreads();
+            bool unit = (met & kNotFinite) != 0, again = unit;
+            if (!unit) {
+                // A value loses less than 2^-133, so a sum less than 2^-133 K max |other operand|: nothing that shows if
+                // every sum is 2^28 times that.  (Probabilities times values: those that underflow stand beside others.
+                // A few of them in A of 1024x2048x512: 19 us for 36 with the repeat, none 16.)
+                auto largest = [&](const auto &src) {
+                    float m = 0.f;
+                    for (int i = first; i < count; i += 4)  // (four steps in flight: the loads' latency counts here)
+                        unrolled<4>([&](auto u) {
+                            auto step_of = src;
+                            step_of.rows(k_of(i + u));
+                            unrolled<KS>([&](auto s) { step_of.cols(k_of(i + u), s); });
+                            m = __builtin_fmaxf(m, largest_of(step_of.raw));
+                        });
+                    return m;
+                };
+                float big = met & kLostA ? largest(sb) : 0.f;
+                if (met & kLostB) big = __builtin_fmaxf(big, largest(sa));
+                big = wave_allreduce(big, OpMax{});
+                if (lane == 0) values[wave] = big;
+                __syncthreads();
+#pragma unroll
+                for (int w = 0; w < W; ++w) big = __builtin_fmaxf(big, values[w]);
+                const float least = 0x1p-104f * (float)K * big;  // (2^29 times: both operands may have lost)
+                bool small = false;
+                for (int u = first + wave; u < TM * TN * 4; u += W) {
+                    const float4_t v = total(u);
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) small |= !(__builtin_fabsf(v[e]) >= least);
+                }
+                again = any_of(__any(small)) != 0;
+            }
+            if (again) {
+                if (!unit) {
+                    sum_again(yes, first, met & kLostA ? 0x1p24f : 1.f, met & kLostB ? 0x1p24f : 1.f);
+                    __syncthreads();  // (the flags have been read)
+                    unit = any_of(not_finite()) != 0;
+                }
+                if (unit) sum_again(no, first, 1.f, 1.f);
+                leave();
+                __syncthreads();
+            }
         }
     } else {
         __syncthreads();
@@ -473,10 +589,7 @@ __global__ __launch_bounds__(64 * W, (WavesShape<T, TM, TN, W, ASrc, BSrc>::kWav
     for (int u0 = 0; u0 < TM * TN * 4; u0 += W) {
         const int u = u0 + wave;
         if (W > 4 * TM * TN && u >= TM * TN * 4) break;
-        const char *from = smem + (u * 64 + lane) * 16;
-        float4_t v = *reinterpret_cast<const float4_t *>(from);
-#pragma unroll
-        for (int w = 1; w < W; ++w) v += *reinterpret_cast<const float4_t *>(from + w * Shape::kWave);
+        const float4_t v = total(u);
         const int q = u % 4, i = u / (4 * TN), j = u / 4 % TN, l = 8 * q + 4 * (lane >> 5);
         const int c = BSrc::kPairs ? 64 * (j / 2) + 2 * (lane & 31) + j % 2 : 32 * j + (lane & 31);
 #pragma unroll
