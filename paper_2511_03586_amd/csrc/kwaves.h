@@ -288,14 +288,18 @@ __global__ __launch_bounds__(64 * W, (WavesShape<T, TM, TN, W, ASrc, BSrc>::kWav
     constexpr int NP = Split<T>::kPlanes, BK = Shape::BK, BM = Shape::BM, BN = Shape::BN, KS = BK / 16, NV = sizeof(T) / 2;
     extern __shared__ __attribute__((aligned(1024))) char smem[];
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    // (an XCD's run goes through the batch: a matrix's panels are read into one L2, not into all of them.  64 x (128x128x384) bf16
+    // both K-strided 10.6 us without, 7.2 with)
+    const unsigned id = xcd_run(blockIdx.x, gridDim.x), tiles = (unsigned)tiles_m * (unsigned)tiles_n;
+    const unsigned batch = gridDim.x == tiles ? 0 : id / tiles;
     int tm, tn;
-    staged_tile(blockIdx.x, tiles_m, tiles_n, tm, tn);
+    band_tile(id - batch * tiles, tiles_m, tiles_n, tm, tn);
     const int64_t m0 = (int64_t)tm * BM, n0 = (int64_t)tn * BN;
     char *const mine = smem + wave * Shape::kWave;
     ASrc sa;
     BSrc sb;
-    sa.init(aa, blockIdx.y, m0, M, lane, mine);
-    sb.init(ba, blockIdx.y, n0, N, lane, mine + ASrc::kLds);
+    sa.init(aa, batch, m0, M, lane, mine);
+    sb.init(ba, batch, n0, N, lane, mine + ASrc::kLds);
     // The last step starts early enough to be whole; the k of the step before it that it holds too count as zeros.
     const int steps = (int)((K + BK - 1) / BK), count = steps > wave ? (steps - wave + W - 1) / W : 0;
     auto k_of = [&](int i) { return min((int64_t)(wave + i * W) * BK, K - BK); };  // (past the last: the last)
@@ -584,7 +588,7 @@ __global__ __launch_bounds__(64 * W, (WavesShape<T, TM, TN, W, ASrc, BSrc>::kWav
         __syncthreads();
     }
     const int rows = (int)min((int64_t)BM, M - m0), cols = (int)min((int64_t)BN, N - n0);
-    CT *Ct = C + (int64_t)blockIdx.y * strideC + m0 * ldc + n0;
+    CT *Ct = C + (int64_t)batch * strideC + m0 * ldc + n0;
 #pragma unroll
     for (int u0 = 0; u0 < TM * TN * 4; u0 += W) {
         const int u = u0 + wave;

@@ -518,11 +518,13 @@ struct ConvRows {
 
 // Workgroup id -> output tile: each XCD (ids are dealt round-robin to the 8 of them) gets a contiguous run of
 // tiles, and runs walk the grid in column-major bands of 4 tile-rows (a compact patch shares operand panels).
-__device__ __forceinline__ void staged_tile(unsigned bid, int tiles_m, int tiles_n, int &tm, int &tn)
+__device__ __forceinline__ unsigned xcd_run(unsigned bid, unsigned total)
 {
-    const unsigned total = (unsigned)tiles_m * (unsigned)tiles_n;
     const unsigned q = total / 8, rem = total % 8, xcd = bid % 8;
-    const unsigned id = xcd * q + min(xcd, rem) + bid / 8;
+    return xcd * q + min(xcd, rem) + bid / 8;
+}
+__device__ __forceinline__ void band_tile(unsigned id, int tiles_m, int tiles_n, int &tm, int &tn)
+{
     constexpr unsigned kBand = 4;
     const unsigned band = id / (kBand * (unsigned)tiles_n);
     const unsigned in_band = min(kBand, (unsigned)tiles_m - band * kBand);
@@ -560,7 +562,7 @@ __global__ __launch_bounds__(64 * WM * WN * KG, (StagedShape<T, TM, TN, WM, WN, 
     const int group = KG > 1 ? wave_all / NW : 0, wave = KG > 1 ? wave_all % NW : wave_all;
     const int wm = wave / WN, wn = wave % WN;
     int tm, tn;
-    staged_tile(blockIdx.x, tiles_m, tiles_n, tm, tn);
+    band_tile(xcd_run(blockIdx.x, (unsigned)tiles_m * (unsigned)tiles_n), tiles_m, tiles_n, tm, tn);
     // A ragged last tile starts a few rows early if that lets it end on a whole block of its source.  The rows it shares
     // with its neighbour are the neighbour's to store: the two need not agree on them (one may have met a value that the
     // split does not hold), and an element has one writer.

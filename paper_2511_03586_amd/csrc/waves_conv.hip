@@ -26,7 +26,7 @@ static perf_status launch(const StagedConv &c)
     const typename ASrc::Args aa{{(const T *)c.x, c.H, c.W, c.C, c.S, c.sh, c.sw, c.ph, c.pw, c.P, c.Q,
                                   div_magic(c.C), div_magic(c.S), div_magic((int64_t)c.P * c.Q), div_magic(c.Q)},
                                  (uint32_t)((int64_t)c.N * c.H * c.W * c.C * sizeof(T)), tap_rows, c.R};
-    hipLaunchKernelGGL(kern, dim3((unsigned)((int64_t)tiles_m * tiles_n), 1), dim3(Shape::kThreads), Shape::kLds, c.st, aa,
+    hipLaunchKernelGGL(kern, dim3((unsigned)((int64_t)tiles_m * tiles_n)), dim3(Shape::kThreads), Shape::kLds, c.st, aa,
                        DenseArgs<T>{(const T *)c.w, K, 0}, (CT *)c.y, M, (int64_t)c.K, K, (int64_t)c.K, (int64_t)0, 1.0f, tiles_m, tiles_n);
     return launch_status();
 }

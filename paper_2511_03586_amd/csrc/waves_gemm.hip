@@ -5,7 +5,7 @@
 namespace perf {
 
 template <typename ASrc, typename BSrc, typename T, typename CT, int TM, int TN, int W>
-static perf_status launch(const GemmArgs &g, typename ASrc::Args aa, typename BSrc::Args ba)
+static perf_status launch(const GemmArgs &g, const typename ASrc::Args &aa, const typename BSrc::Args &ba)
 {
     using Shape = WavesShape<T, TM, TN, W, ASrc, BSrc>;
     const int tiles_m = (int)((g.M + Shape::BM - 1) / Shape::BM), tiles_n = (int)((g.N + Shape::BN - 1) / Shape::BN);
@@ -17,21 +17,15 @@ static perf_status launch(const GemmArgs &g, typename ASrc::Args aa, typename BS
             return PERF_ERR_LAUNCH;
         attr_done = true;
     }
-    // grid.y carries the batch index; batches beyond the grid limit take further launches
-    for (int64_t b0 = 0; b0 < g.batch; b0 += kMaxGridYZ) {
-        const unsigned gy = (unsigned)(g.batch - b0 < kMaxGridYZ ? g.batch - b0 : kMaxGridYZ);
-        aa.p = (const T *)g.A + b0 * g.strideA;
-        ba.p = (const T *)g.B + b0 * g.strideB;
-        hipLaunchKernelGGL(kern, dim3((unsigned)((int64_t)tiles_m * tiles_n), gy), dim3(Shape::kThreads), Shape::kLds, g.st, aa, ba,
-                           (CT *)g.C + b0 * g.strideC, g.M, g.N, g.K, g.ldc, g.strideC, g.alpha, tiles_m, tiles_n);
-    }
+    hipLaunchKernelGGL(kern, dim3((unsigned)((int64_t)tiles_m * tiles_n * g.batch)), dim3(Shape::kThreads), Shape::kLds, g.st, aa, ba, (CT *)g.C, g.M,
+                       g.N, g.K, g.ldc, g.strideC, g.alpha, tiles_m, tiles_n);
     return launch_status();
 }
 
 template <typename T, typename CT, int TM, int TN, int W>
 static perf_status launch_layouts(const GemmArgs &g)
 {
-    const DenseArgs<T> aa{nullptr, g.lda, g.strideA}, ba{nullptr, g.ldb, g.strideB};
+    const DenseArgs<T> aa{(const T *)g.A, g.lda, g.strideA}, ba{(const T *)g.B, g.ldb, g.strideB};
     if (g.la == PERF_ROW_MAJOR)
         return g.lb == PERF_COL_MAJOR ? launch<WaveRows<T, TM>, WaveRows<T, TN>, T, CT, TM, TN, W>(g, aa, ba)
                                       : launch<WaveRows<T, TM>, WaveCols<T, TN>, T, CT, TM, TN, W>(g, aa, ba);
