@@ -161,9 +161,16 @@ def test_staged_kernel_edges(M, N, K, batch, pad, a_col, b_col, ab_bf16, c_bf16)
 @pytest.mark.parametrize("M,N,K,batch,pad", [
     (1, 1, 64, 1, 0), (33, 65, 65, 2, 1), (5, 7, 1031, 1, 0),    # 32 x 32: one K-step, the last one overlapping, more than waves
     (64, 64, 512, 1, 0), (31, 97, 8 * 64 + 1, 3, 3),             # ... the last step alone in its round; the direct kernels' shapes
-    (700, 600, 40, 1, 1), (577, 450, 66, 1, 0),                  # pairs of tiles; an odd row alone in the last pair
-    (450, 577, 127, 1, 1), (705, 641, 1030, 1, 0),               # ... and column; 64 x 64 in one round
-    (1030, 1090, 130, 1, 1), (1025, 1089, 515, 1, 0),            # 64 x 64 in several, ragged by one
+    (33, 65, 32, 1, 0), (33, 65, 63, 3, 1),                      # fp32: one K-step, one and most of another
+    (700, 600, 40, 1, 1), (577, 450, 66, 1, 0),                  # 32 x 32 with four waves (fp32), pairs of tiles (bf16); an odd row alone
+    (450, 577, 127, 1, 1), (450, 577, 513, 1, 1),                # in the last pair, an odd column (row-major)
+    (20, 9000, 130, 1, 1), (9000, 20, 513, 1, 0),                # pairs along the only operand with more than a tile
+    (705, 641, 64, 1, 1), (705, 641, 100, 1, 0), (705, 641, 128, 1, 1),   # two waves: one K-step, the last overlapping, one each
+    (705, 641, 200, 1, 1), (705, 641, 400, 1, 0),                # one round of 64 x 64: 32 x 32 and pairs
+    (705, 641, 1030, 1, 0), (705, 741, 2113, 1, 1), (768, 768, 2080, 1, 0),   # ... 64 x 64 with eight waves; the direct kernels' shapes
+    (1030, 1090, 70, 1, 0), (1030, 1090, 130, 1, 1), (1030, 1090, 300, 1, 1),   # several rounds: two waves; pairs with two and four
+    (1025, 1089, 515, 1, 0), (1025, 1089, 1100, 1, 1),           # ... 64 x 64, ragged by one
+    (100, 70, 130, 37, 3), (65, 33, 200, 11, 0), (64, 64, 520, 300, 0),   # batches that 8 does not divide, tiles that it does not
 ])
 def test_waves_kernel_edges(M, N, K, batch, pad, a_col, b_col, ab_bf16, c_bf16):
     """Every layout and type of the contraction whose waves divide K, at the edges of its tiles, K-steps and row pairs (the
