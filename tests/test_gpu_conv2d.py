@@ -269,7 +269,10 @@ def test_deterministic():
     dict(N=2, H=13, W=9, C=5, K=40, R=3, S=2, pad=1, stride=2),   # element loads, ragged everything
     dict(N=1, H=17, W=16, C=12, K=64, R=5, S=5, pad=0),
     dict(N=8, H=56, W=57, C=8, K=70, R=3, S=3, pad=1),         # 128 x 64 tiles (fp32), ragged; K-step of several taps
-    dict(N=1, H=10, W=11, C=72, K=40, R=3, S=3, pad=2),        # two groups of waves that do not divide the K-steps
+    dict(N=1, H=10, W=11, C=72, K=40, R=3, S=3, pad=2),        # a long reduction on few tiles (the waves' kernel)
+    dict(N=1, H=10, W=11, C=16, K=40, R=7, S=7, pad=2),        # more than 31 taps: two groups of waves that do not divide the K-steps
+    dict(N=1, H=9, W=12, C=40, K=70, R=7, S=7, pad=3),         # ... four (bf16)
+    dict(N=2, H=9, W=9, C=64, K=64, R=7, S=6, pad=3),          # ... on whole 32-channel steps
     dict(N=1, H=8, W=8, C=64, K=64, R=3, S=3, pad=1),
     dict(N=3, H=7, W=5, C=24, K=17, R=1, S=1, pad=0),          # one tap on every pixel: the GEMM
     dict(N=2, H=9, W=9, C=96, K=64, R=1, S=1, pad=0),

@@ -128,8 +128,12 @@ def test_general_kernel_layouts_exact_integers(a_col, b_col, M, N, K):
 @pytest.mark.parametrize("M,N,K,batch,pad", [
     (1, 1, 1, 1, 0), (7, 3, 5, 2, 0), (3, 300, 7, 1, 1),       # extents below a 16-byte load: element loads
     (8, 9, 8, 1, 0), (64, 64, 64, 1, 0), (65, 71, 130, 2, 3),    # 64 x 64 tile: exact, ragged in every extent, odd ld
-    (100, 70, 643, 1, 1), (64, 130, 1024, 1, 0), (9, 10, 257, 3, 1),   # several wave groups
-    (64, 72, 704, 1, 0), (72, 64, 288, 1, 0), (64, 64, 1216, 1, 0),    # ... whole K-steps that the groups do not divide
+    (100, 70, 643, 1, 1), (64, 130, 1024, 1, 0), (9, 10, 257, 3, 1),   # long reductions on few tiles (the waves' kernel)
+    (64, 72, 704, 1, 0), (72, 64, 288, 1, 0), (64, 64, 1216, 1, 0),
+    (705, 641, 577, 1, 1), (704, 648, 704, 1, 0), (704, 648, 1088, 1, 0),   # two groups of waves (bf16, row-major): K-steps that they
+                                                                 # do not divide, with edges and without
+    (70, 65, 96, 65, 1), (100, 66, 67, 100, 0),                  # 64 x 64 (fp32), one register set
+    (64, 61, 300, 641, 0),                                       # ... four
     (257, 131, 97, 64, 0), (130, 250, 64, 96, 5),                # 128 x 128 (bf16), 256 x 128 (fp32)
     (40, 33, 521, 200, 1), (300, 261, 512, 100, 0),              # 256 x 256 (bf16): ragged first and second tiles
     (500, 250, 70, 40, 1), (128, 120, 65, 130, 0), (33, 65, 20, 128, 0),   # 256 x 128 (fp32), full and half full; 64 x 64 instead
@@ -179,7 +183,8 @@ def test_waves_kernel_edges(M, N, K, batch, pad, a_col, b_col, ab_bf16, c_bf16):
 
 
 @pytest.mark.parametrize("a_col,b_col", [(False, False), (True, True)])
-@pytest.mark.parametrize("M,N,K,batch", [(70, 65, 33, 1), (96, 64, 300, 1), (130, 250, 64, 96), (7, 3, 5, 1)])
+@pytest.mark.parametrize("M,N,K,batch", [(70, 65, 33, 1), (96, 64, 300, 1), (130, 250, 64, 96), (7, 3, 5, 1),
+                                         (70, 65, 33, 65), (64, 61, 100, 641)])   # (the staged kernel's 64 x 64)
 def test_fp32_range_ends(M, N, K, batch, a_col, b_col):
     """fp32 operands at both ends of the range: values around 2^-118 (below what the three-way split holds), one of
     them among ordinary ones, and values next to the largest. Bounds as for any fp32 accumulation order."""
@@ -253,7 +258,8 @@ def test_fp32_values_next_to_what_splits(M, N, K, a_col, b_col):
 
 
 @pytest.mark.parametrize("a_col,b_col", [(False, True), (True, False)])
-@pytest.mark.parametrize("M,N,K,batch", [(70, 65, 33, 1), (64, 64, 96, 1), (96, 64, 300, 1), (130, 250, 64, 96), (3, 9, 40, 1)])
+@pytest.mark.parametrize("M,N,K,batch", [(70, 65, 33, 1), (64, 64, 96, 1), (96, 64, 300, 1), (130, 250, 64, 96), (3, 9, 40, 1),
+                                         (70, 65, 33, 65), (64, 61, 100, 641)])   # (the staged kernel's 64 x 64)
 def test_fp32_tiny_values(M, N, K, batch, a_col, b_col):
     """Values under 2^-110 (which need more than the three-way split): beside ordinary ones in sums that they do not
     show in, alone in the sums of some columns, in both operands, and beside values that leave no room to scale."""
@@ -281,9 +287,9 @@ def test_fp32_tiny_values(M, N, K, batch, a_col, b_col):
 @pytest.mark.parametrize("M,N,K,tiny_row,tiny_col", [(70, 70, 300, 5, None), (70, 70, 300, None, 5), (65, 131, 33, 3, 66),
                                                      (257, 129, 40, None, 128), (199, 67, 1024, 130, 65)])
 def test_rows_shared_by_two_tiles_have_one_writer(M, N, K, tiny_row, tiny_col):
-    """K-strided fp32 operands whose ragged last tile reads rows and columns of its neighbour, with a value under 2^-110
-    in some tiles only (those may take another way): every element carries the bits of the 64 x 64 tile that owns it,
-    in every run. A tile's bits alone come from a call on its rows and columns."""
+    """K-strided fp32 operands with ragged last tiles and a value under 2^-110 in some tiles only (those may take another way):
+    every element carries the bits of the 64 x 64 tile that owns it, in every run. A tile's bits alone come from a call on its
+    rows and columns. (These shapes run the contraction whose waves divide K, the staged one's are below.)"""
     g = np.random.default_rng(M + N)
     a, b = g.uniform(-1, 1, (K, M)).astype(np.float32), g.uniform(-1, 1, (K, N)).astype(np.float32)
     if tiny_row is not None:
@@ -299,6 +305,32 @@ def test_rows_shared_by_two_tiles_have_one_writer(M, N, K, tiny_row, tiny_col):
             m, n = m0 - (m0 - m1) % 4, n0 - (n0 - n1) % 4  # (the tile reads whole blocks of 4)
             own = G.run_gemm(a[:, m:m1], b[:, n:n1], m1 - m, n1 - n, K, a_col=True, b_col=False, ab_bf16=False)[0]
             assert np.array_equal(c[m0:m1, n0:n1], own[m0 - m:, n0 - n:])
+
+
+@pytest.mark.parametrize("M,N,K,tiny_row,tiny_col", [(1061, 1030, 40, 1040, None), (1061, 1030, 96, None, 1026), (1633, 1630, 130, 1605, 1626)])
+def test_rows_shared_by_two_tiles_have_one_writer_staged(M, N, K, tiny_row, tiny_col):
+    """As above on shapes that the staged kernel runs, with 64 x 64 tiles: there a ragged last tile starts early and reads rows and columns that its neighbour stores. A tile's bits alone come from a batch of
+    it that the same kernel runs."""
+    g = np.random.default_rng(M + N)
+    a, b = g.uniform(-1, 1, (K, M)).astype(np.float32), g.uniform(-1, 1, (K, N)).astype(np.float32)
+    if tiny_row is not None:
+        a[7, tiny_row] = 1.7 * 2.0 ** -118
+    if tiny_col is not None:
+        b[9, tiny_col] = 1.7 * 2.0 ** -118
+    c = G.run_gemm(a, b, M, N, K, a_col=True, b_col=False, ab_bf16=False)[0]
+    for _ in range(3):
+        assert np.array_equal(c, G.run_gemm(a, b, M, N, K, a_col=True, b_col=False, ab_bf16=False)[0])
+    ref = a.T.astype(np.float64) @ b.astype(np.float64)
+    P.assert_contraction_close(c, ref, np.abs(a).T.astype(np.float64) @ np.abs(b).astype(np.float64), K + 1)
+    last_m, last_n, copies = (M - 1) // 64 * 64, (N - 1) // 64 * 64, 641
+    for m0 in (last_m - 64, last_m):
+        for n0 in (last_n - 64, last_n):
+            m1, n1 = min(M, m0 + 64), min(N, n0 + 64)
+            m, n = m0 - (m0 - m1) % 4, n0 - (n0 - n1) % 4  # (the tile reads whole blocks of 4)
+            own = G.run_gemm(np.tile(a[:, m:m1], (copies, 1)), np.tile(b[:, n:n1], (copies, 1)), m1 - m, n1 - n, K, a_col=True, b_col=False,
+                             batch=copies, ab_bf16=False)
+            for i in (0, copies - 1):
+                assert np.array_equal(c[m0:m1, n0:n1], own[i][m0 - m:, n0 - n:])
 
 
 def test_mfma_exact_integers_identity_permutation_ones():
