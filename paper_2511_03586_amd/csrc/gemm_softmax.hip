@@ -211,11 +211,14 @@ __global__ __launch_bounds__(64 * kFusedWaves, 1) void gemm_softmax_kernel(const
 // past the caches.  With 256 bytes of four rows per instruction the lines that two of them share had to be put together in
 // the L2: 96 x (600x777x80) 82 us against 65 now, 80 x (512x384x64), whose rows are whole lines, 24.5 against 17.8,
 // 64 x (1000x1024x128) 106 against 74, 400 x (200x100x80) 18.7 against 13.2.  (Two store instructions that differ in the cache
-// policy alone, on the two sides of a test, are merged by the compiler into one of the plain kind.)
+// policy alone, on the two sides of a test, are merged by the compiler into one of the plain kind.)  Up to 16 rows of a strip
+// are dealt to the waves one by one: 128 x (6x192x32) 4.56 us with all of them stored by the first wave, 4.32.
+//   * FEW: a P that the caches hold leaves from the registers (plain stores, 16 bytes of a row per lane) without the LDS's latency and
+//     two barriers: 360 x (32x13x80) 4.22 -> 3.96 us, 155 x (22x56x16) 3.35 -> 3.14, bf16 P 43 x (48x35x128) 4.32 -> 3.94.
 // The first shape's P is 28 us of writes at the copy rate, its exponentials about 15 us of vector work.
 constexpr bool wide_own(int nt) { return nt > 2; }
 constexpr int wide_rows_out(int nt) { return nt > 2 ? 16 : 32; }  // as the LDS of the operands holds them
-template <int NT, typename PT, int NW>
+template <int NT, typename PT, int NW, bool FEW>
 __global__ __launch_bounds__(64 * NW, NW == 8 ? 4 : 2) void gemm_softmax_wide_kernel(const uint16_t *__restrict__ A, const uint16_t *__restrict__ B,
                                                                    PT *__restrict__ P, int M, int N, int K, int64_t lda,
                                                                    int64_t ldb, int64_t ldp, int64_t strideA, int64_t strideB,
@@ -380,11 +383,40 @@ __global__ __launch_bounds__(64 * NW, NW == 8 ? 4 : 2) void gemm_softmax_wide_ke
     const float sum = part[0];
     const float inv = 1.0f / sum;
 
+    auto store = [&](PT *dst, float4_t v, int left) {  // `left` columns of the row from here on
+        if (left >= 4) {
+            if constexpr (sizeof(PT) == 4) {
+                if constexpr (FEW) *reinterpret_cast<float4_at4 *>(dst) = v;
+                else __builtin_nontemporal_store(v, reinterpret_cast<float4_at4 *>(dst));
+            } else {
+                const uint2_t o = {pack_bf16(v[0], v[1]), pack_bf16(v[2], v[3])};
+                if constexpr (FEW) *reinterpret_cast<uint2_at2 *>(dst) = o;
+                else __builtin_nontemporal_store(o, reinterpret_cast<uint2_at2 *>(dst));
+            }
+        } else {
+#pragma unroll
+            for (int e = 0; e < 3; ++e)
+                if (e < left) Elem<PT>::store1(dst + e, v[e]);
+        }
+    };
+    PT *Pb = P + (int64_t)bz * strideP + (int64_t)m0 * ldp;
+    if (FEW && rows > 16) {  // straight from the registers
+        if (row < rows) {
+#pragma unroll
+            for (int j = 0; j < NT; ++j)
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    const float4_t v = {acc[j][4 * q] * inv, acc[j][4 * q + 1] * inv, acc[j][4 * q + 2] * inv, acc[j][4 * q + 3] * inv};
+                    const int col = column(j, 4 * q);
+                    store(Pb + (int64_t)row * ldp + col, v, N - col);
+                }
+        }
+        return;
+    }
     // Write-out, kOut rows at a time through the LDS of the operands.  kPieces pieces of 16 bytes per row, piece s at
     // position s ^ row.
     constexpr int kOut = wide_rows_out(NT), kPieces = 8 * NT * NW, kPitch = 16 * kPieces;
     constexpr int kRowsPer = kPieces < 64 ? 64 / kPieces : 1;  // rows per store instruction
-    PT *Pb = P + (int64_t)bz * strideP + (int64_t)m0 * ldp;
 #pragma unroll
     for (int pass = 0; pass < 32 / kOut; ++pass) {
         if (pass > 0) __syncthreads();  // the rows before have been read
@@ -401,41 +433,29 @@ __global__ __launch_bounds__(64 * NW, NW == 8 ? 4 : 2) void gemm_softmax_wide_ke
         __syncthreads();
 #pragma unroll
         for (int i = 0; i < kOut / NW / kRowsPer; ++i) {
-            const int r = wave * (kOut / NW) + i * kRowsPer + (kRowsPer > 1 ? lane / kPieces : 0);
+            // (a wave's rows lie one after the other; few of them are dealt out)
+            const int r = (rows > 16 ? wave * (kOut / NW) + i * kRowsPer : (i * NW + wave) * kRowsPer) + (kRowsPer > 1 ? lane / kPieces : 0);
             if (pass * kOut + r < rows) {
                 PT *to = Pb + (int64_t)(pass * kOut + r) * ldp;
 #pragma unroll
                 for (int p0 = 0; p0 < kPieces; p0 += 64) {
                     const int piece = kRowsPer > 1 ? lane % kPieces : p0 + lane, left = N - 4 * piece;  // columns from here on
-                    if (left <= 0) continue;
-                    const float4_t v = *reinterpret_cast<const float4_t *>(smem + r * kPitch + ((piece ^ (r & 15)) << 4));
-                    PT *dst = to + 4 * piece;
-                    if (left >= 4) {
-                        if constexpr (sizeof(PT) == 4) {
-                            __builtin_nontemporal_store(v, reinterpret_cast<float4_at4 *>(dst));
-                        } else {
-                            const uint2_t o = {pack_bf16(v[0], v[1]), pack_bf16(v[2], v[3])};
-                            __builtin_nontemporal_store(o, reinterpret_cast<uint2_at2 *>(dst));
-                        }
-                    } else {
-#pragma unroll
-                        for (int e = 0; e < 3; ++e)
-                            if (e < left) Elem<PT>::store1(dst + e, v[e]);
-                    }
+                    if (left > 0)
+                        store(to + 4 * piece, *reinterpret_cast<const float4_t *>(smem + r * kPitch + ((piece ^ (r & 15)) << 4)), left);
                 }
             }
         }
     }
 }
 
-template <int NT, typename PT, int NW = 4>
+template <int NT, typename PT, int NW = 4, bool FEW = false>
 static perf_status launch_wide(const void *A, const void *B, void *P, int64_t M, int64_t N, int64_t K, int64_t lda, int64_t ldb,
                                int64_t ldp, int64_t batch, int64_t strideA, int64_t strideB, int64_t strideP, float alpha,
                                hipStream_t st)
 {
     constexpr int kStages = wide_own(NT) ? 32 * NW * NT * kRowBytes : 2 * (32 * NW * NT + 32) * kRowBytes, kOut = wide_rows_out(NT) * 128 * NT * NW;
     constexpr int kLds = kStages > kOut ? kStages : kOut;
-    auto kern = gemm_softmax_wide_kernel<NT, PT, NW>;
+    auto kern = gemm_softmax_wide_kernel<NT, PT, NW, FEW>;
     static std::atomic<bool> attr_done{false};  // (idempotent per-function setting)
     if (!attr_done) {
         if (hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, kLds) != hipSuccess)
@@ -526,11 +546,13 @@ extern "C" perf_status perf_gemm_softmax(const void *A, const void *B, void *P, 
     if (staged && N == 256) return launch_fused_staged<16>(A, B, P, M, N, K, lda, ldb, ldp, batch, strideA, strideB, strideP, alpha, st);
     if (staged && N == 128) return launch_fused_staged<8>(A, B, P, M, N, K, lda, ldb, ldp, batch, strideA, strideB, strideP, alpha, st);
     const int64_t strips = (M + 31) / 32 * batch;
-#define PERF_WIDE(T, PT) return launch_wide<T, PT>(A, B, P, M, N, K, lda, ldb, ldp, batch, strideA, strideB, strideP, alpha, st)
-#define PERF_WIDE8(T) return launch_wide<T, float, 8>(A, B, P, M, N, K, lda, ldb, ldp, batch, strideA, strideB, strideP, alpha, st)
+    // (5 MiB of fp32 P and less, 4 of bf16: 1 to 8 % ahead; even up to 1.6 times that, with single shapes 7 % behind)
+    const bool few = strips * N <= (p_dt == PERF_F32 ? 40960 : 65536);
+#define PERF_WIDE(...) return launch_wide<__VA_ARGS__>(A, B, P, M, N, K, lda, ldb, ldp, batch, strideA, strideB, strideP, alpha, st)
     if (loads_ok && lda <= (1 << 21) && ldb <= (1 << 21) && p_dt == PERF_BF16 && N <= 512 && (K == 64 || K == 128)) {
-        if (N <= 128) PERF_WIDE(1, uint16_t);
-        if (N <= 256) PERF_WIDE(2, uint16_t);
+        if (N <= 128 && few) PERF_WIDE(1, uint16_t, 4, true);
+        if (N <= 128) PERF_WIDE(1, uint16_t, 4);
+        if (N <= 256) PERF_WIDE(2, uint16_t, 4);
         PERF_WIDE(4, uint16_t);
     }
     // A few strips of long rows or long reductions are faster as two launches, which spread the columns over the chip and
@@ -545,17 +567,18 @@ extern "C" perf_status perf_gemm_softmax(const void *A, const void *B, void *P, 
         least = least > more ? least : more;
     }
     if (loads_ok && lda <= (1 << 20) && ldb <= (1 << 20) && p_dt == PERF_F32 && N <= 1024 && K <= 512 && strips >= least) {
-        if (N <= 64) return launch_wide<1, float, 2>(A, B, P, M, N, K, lda, ldb, ldp, batch, strideA, strideB, strideP, alpha, st);
-        if (N <= 128) PERF_WIDE(1, float);
-        if (N <= 256) PERF_WIDE(2, float);
+        if (N <= 64 && few) PERF_WIDE(1, float, 2, true);
+        if (N <= 64) PERF_WIDE(1, float, 2);
+        if (N <= 128 && few) PERF_WIDE(1, float, 4, true);
+        if (N <= 128) PERF_WIDE(1, float, 4);
+        if (N <= 256) PERF_WIDE(2, float, 4);
         if (N <= 384) PERF_WIDE(3, float);
-        if (N <= 512) PERF_WIDE8(2);
+        if (N <= 512) PERF_WIDE(2, float, 8);
         if (N <= 640) PERF_WIDE(5, float);
-        if (N <= 768) PERF_WIDE8(3);
-        PERF_WIDE8(4);
+        if (N <= 768) PERF_WIDE(3, float, 8);
+        PERF_WIDE(4, float, 8);
     }
 #undef PERF_WIDE
-#undef PERF_WIDE8
     // Unfused: scores into P, then the row softmax in place (fp32 P only).
     if (p_dt != PERF_F32) return PERF_ERR_UNSUPPORTED;
     perf_status s = perf_gemm(A, B, P, M, N, K, PERF_ROW_MAJOR, lda, PERF_COL_MAJOR, ldb, ldp, batch, strideA, strideB,

@@ -110,16 +110,29 @@ def test_strip_kernel_edges(M, N, K, batch, ldp):
 
 @pytest.mark.parametrize("M,N,K,batch,ldp", [
     (33, 384, 72, 9, 384), (31, 385, 80, 9, 385), (17, 449, 128, 16, 452),      # three tiles per wave, then two with eight waves
-    (33, 545, 96, 32, 545), (16, 673, 64, 64, 675), (32, 800, 136, 64, 800),    # five; three and four, whose last waves have none
+    (33, 545, 96, 32, 545), (16, 673, 64, 64, 675), (32, 800, 136, 64, 800),    # three and four, whose last waves have none
 ])
 def test_strip_kernel_waves_and_tiles(M, N, K, batch, ldp):
     # both forms of the K-loop and of the write-out at the counts where they change, rows of 4 and 16 bytes' alignment
     test_strip_kernel_edges(M, N, K, batch, ldp)
 
 
+@pytest.mark.parametrize("M,N,K,batch,ldp", [
+    (16, 100, 64, 4, 100), (17, 100, 64, 4, 101), (49, 61, 72, 5, 61),    # stores from the registers from 17 rows of a strip on
+    (33, 64, 64, 520, 64), (65, 127, 40, 200, 128),                       # ... and for no more of P than the caches hold
+])
+def test_strip_kernel_few_and_many(M, N, K, batch, ldp):
+    test_strip_kernel_edges(M, N, K, batch, ldp)
+
+
 @pytest.mark.parametrize("M,N,K", [(33, 5, 64), (40, 130, 128), (64, 512, 64), (1, 301, 128)])
 def test_strip_kernel_bf16_output(M, N, K):
     _check(M, N, K, batch=3, p_bf16=True)
+
+
+@pytest.mark.parametrize("M,N,K,batch", [(16, 100, 64, 4), (17, 103, 128, 4), (65, 127, 64, 200)])
+def test_strip_kernel_bf16_output_few_and_many(M, N, K, batch):
+    _check(M, N, K, batch=batch, p_bf16=True)
 
 
 def test_argmax_matches_scores():
