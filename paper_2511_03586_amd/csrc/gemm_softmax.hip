@@ -200,13 +200,14 @@ __global__ __launch_bounds__(64 * kFusedWaves, 1) void gemm_softmax_kernel(const
 // columns; wave w the NT tiles of 32 columns from 32 NT w on, as 32x32 accumulators with B as the MFMA's row operand, so
 // that a lane's values belong to ONE row: row maxima and sums are in-lane plus one lane exchange, and one LDS exchange
 // between the waves.  Both operands come 32 K at a time (chunks past K read as zeros), B once per strip from the L2:
-//   * NT <= 2: through two stages of the LDS that all waves fill (400 x (200x100x80) 13.2 us against 15.7 with the other form).
-//   * above: a wave loads the rows of B that it multiplies itself, reads a step's operands into registers and refills the
-//     stage behind its matrix instructions, without a barrier (80 x (512x384x64) 17.8 against 19.6).
+//   * OWN: a wave loads the rows of B that it multiplies itself, reads a step's operands into registers and refills the
+//     stage in front of its matrix instructions, without a barrier (80 x (512x384x64) 17.8 against 19.6 on shared stages).  It takes
+//     24 registers and more that the shared stages do not.  <4, float, 8, true> has one too few for its eight addresses of B and
+//     reloads one of them in each step, which waits for the step's other loads.
+//   * else through the LDS that all waves fill, two stages for NT <= 2 (400 x (200x100x80) 13.2 us against 15.7 with OWN), one above.
 // At most 80 KiB of LDS, so that two workgroups or more share a CU and one's loads and exponentials overlap the other's
-// stores; from 385 columns on eight waves (the fp32 instructions of an exponential issue twice as fast from two waves
-// of a SIMD as from one): 96 x (600x800x80) 60 us against 63, 60 x (100x450x128) 9.6 against 11.3, but five tiles for 513 to 640
-// columns: 64 x (300x600x96) 19 against 23 with eight.
+// stores; eight waves where there are registers for them (the fp32 instructions of an exponential issue twice as fast from two
+// waves of a SIMD as from one): 96 x (600x800x80) 60 us against 63, 60 x (100x450x128) 9.6 against 11.3.
 // Write-out: 16 or 32 rows at a time through the LDS, so that a wave stores whole rows, 1 KiB of consecutive bytes per instruction,
 // past the caches.  With 256 bytes of four rows per instruction the lines that two of them share had to be put together in
 // the L2: 96 x (600x777x80) 82 us against 65 now, 80 x (512x384x64), whose rows are whole lines, 24.5 against 17.8,
@@ -216,16 +217,15 @@ __global__ __launch_bounds__(64 * kFusedWaves, 1) void gemm_softmax_kernel(const
 //   * FEW: a P that the caches hold leaves from the registers (plain stores, 16 bytes of a row per lane) without the LDS's latency and
 //     two barriers: 360 x (32x13x80) 4.22 -> 3.96 us, 155 x (22x56x16) 3.35 -> 3.14, bf16 P 43 x (48x35x128) 4.32 -> 3.94.
 // The first shape's P is 28 us of writes at the copy rate, its exponentials about 15 us of vector work.
-constexpr bool wide_own(int nt) { return nt > 2; }
+constexpr int wide_stages(int nt) { return nt <= 2 ? 2 : 1; }      // that all waves fill
 constexpr int wide_rows_out(int nt) { return nt > 2 ? 16 : 32; }  // as the LDS of the operands holds them
-template <int NT, typename PT, int NW, bool FEW>
+template <int NT, typename PT, int NW, bool OWN, bool FEW>
 __global__ __launch_bounds__(64 * NW, NW == 8 ? 4 : 2) void gemm_softmax_wide_kernel(const uint16_t *__restrict__ A, const uint16_t *__restrict__ B,
                                                                    PT *__restrict__ P, int M, int N, int K, int64_t lda,
                                                                    int64_t ldb, int64_t ldp, int64_t strideA, int64_t strideB,
                                                                    int64_t strideP, ExpConst ek, float t_min, int strips, int eights)
 {
-    constexpr bool kOwn = wide_own(NT);
-    constexpr int kStage = (kOwn ? 32 * NT : 32 * NW * NT + 32) * kRowBytes, LB = 2 * NT;
+    constexpr int kStage = (OWN ? 32 * NT : 32 * NW * NT + 32) * kRowBytes, LB = 2 * NT, NST = wide_stages(NT);
     extern __shared__ __attribute__((aligned(1024))) char smem[];
     __shared__ float red[2][NW][32];
     const int tid = threadIdx.x, lane = tid & 63;
@@ -252,14 +252,14 @@ __global__ __launch_bounds__(64 * NW, NW == 8 ? 4 : 2) void gemm_softmax_wide_ke
     for (int j = 0; j < NT; ++j)
 #pragma unroll
         for (int e = 0; e < 16; ++e) acc[j][e] = 0.f;
-    if constexpr (!kOwn) {
+    if constexpr (!OWN) {
         // load i of wave w: rows (NW i + w) * 16 .. + 15 of B
         uint32_t vb[LB];
 #pragma unroll
         for (int i = 0; i < LB; ++i) vb[i] = (uint32_t)(min((i * NW + wave) * 16 + lrow, N - 1) * ldb * 2) + kb * 2;
         const uint32_t va = (uint32_t)(min((wave & 1) * 16 + lrow, rows - 1) * lda * 2) + kb * 2;
         auto issue = [&](int ks) {
-            char *st = smem + (ks & 1) * kStage;
+            char *st = smem + (NST == 2 ? (ks & 1) * kStage : 0);
             const bool in = ks * 32 + kb < K;
             const uint32_t so = (uint32_t)ks * kRowBytes;
 #pragma unroll
@@ -267,12 +267,12 @@ __global__ __launch_bounds__(64 * NW, NW == 8 ? 4 : 2) void gemm_softmax_wide_ke
             issue_load_to(ra, in ? va : kOutOfRange, so, st + (32 * NW * NT + (wave & 1) * 16) * kRowBytes);  // (waves 2 on: the same again)
         };
         issue(0);
-        if (ksteps > 1) issue(1);
+        if (NST == 2 && ksteps > 1) issue(1);
         for (int ks = 0; ks < ksteps; ++ks) {
-            if (ks + 1 < ksteps) wait_vmem<LB + 1>();
+            if (NST == 2 && ks + 1 < ksteps) wait_vmem<LB + 1>();
             else wait_vmem<0>();
             wg_barrier();
-            const char *st = smem + (ks & 1) * kStage;
+            const char *st = smem + (NST == 2 ? (ks & 1) * kStage : 0);
 #pragma unroll
             for (int h = 0; h < 2; ++h) {
                 const int chunk = 2 * h + (lane >> 5);
@@ -285,7 +285,7 @@ __global__ __launch_bounds__(64 * NW, NW == 8 ? 4 : 2) void gemm_softmax_wide_ke
             }
             __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0): this wave is done with the stage
             wg_barrier();
-            if (ks + 2 < ksteps) issue(ks + 2);
+            if (ks + NST < ksteps) issue(ks + NST);
         }
     } else {
         // load i: rows 16 i .. + 15 of the wave's own columns; the rows of A come straight into the matrix instruction's layout
@@ -448,14 +448,14 @@ __global__ __launch_bounds__(64 * NW, NW == 8 ? 4 : 2) void gemm_softmax_wide_ke
     }
 }
 
-template <int NT, typename PT, int NW = 4, bool FEW = false>
+template <int NT, typename PT, int NW = 4, bool OWN = false, bool FEW = false>
 static perf_status launch_wide(const void *A, const void *B, void *P, int64_t M, int64_t N, int64_t K, int64_t lda, int64_t ldb,
                                int64_t ldp, int64_t batch, int64_t strideA, int64_t strideB, int64_t strideP, float alpha,
                                hipStream_t st)
 {
-    constexpr int kStages = wide_own(NT) ? 32 * NW * NT * kRowBytes : 2 * (32 * NW * NT + 32) * kRowBytes, kOut = wide_rows_out(NT) * 128 * NT * NW;
+    constexpr int kStages = OWN ? 32 * NW * NT * kRowBytes : wide_stages(NT) * (32 * NW * NT + 32) * kRowBytes, kOut = wide_rows_out(NT) * 128 * NT * NW;
     constexpr int kLds = kStages > kOut ? kStages : kOut;
-    auto kern = gemm_softmax_wide_kernel<NT, PT, NW, FEW>;
+    auto kern = gemm_softmax_wide_kernel<NT, PT, NW, OWN, FEW>;
     static std::atomic<bool> attr_done{false};  // (idempotent per-function setting)
     if (!attr_done) {
         if (hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, kLds) != hipSuccess)
@@ -550,10 +550,15 @@ extern "C" perf_status perf_gemm_softmax(const void *A, const void *B, void *P, 
     const bool few = strips * N <= (p_dt == PERF_F32 ? 40960 : 65536);
 #define PERF_WIDE(...) return launch_wide<__VA_ARGS__>(A, B, P, M, N, K, lda, ldb, ldp, batch, strideA, strideB, strideP, alpha, st)
     if (loads_ok && lda <= (1 << 21) && ldb <= (1 << 21) && p_dt == PERF_BF16 && N <= 512 && (K == 64 || K == 128)) {
-        if (N <= 128 && few) PERF_WIDE(1, uint16_t, 4, true);
+        if (N <= 128 && few) PERF_WIDE(1, uint16_t, 4, false, true);
         if (N <= 128) PERF_WIDE(1, uint16_t, 4);
         if (N <= 256) PERF_WIDE(2, uint16_t, 4);
-        PERF_WIDE(4, uint16_t);
+        // (us, with the four tiles of four waves on their own stages, now: 481 x (32x434x128) 18.6, 16.1, 10 x (679x440x128) 9.1, 7.9;
+        // for more than the chip holds at a time 304 x (512x289x128) 82.0, 64.1, 168 x (320x477x64) 26.7, 24.6)
+        if (N <= 384 && strips <= 512) PERF_WIDE(3, uint16_t, 4, true);
+        if (N <= 384) PERF_WIDE(3, uint16_t, 4);
+        if (strips <= 512) PERF_WIDE(2, uint16_t, 8);
+        PERF_WIDE(4, uint16_t, 4);
     }
     // A few strips of long rows or long reductions are faster as two launches, which spread the columns over the chip and
     // pipeline deeper (in us, strips on this kernel against two launches): 100x769x128 13 against 8, up to more strips where the
@@ -567,16 +572,40 @@ extern "C" perf_status perf_gemm_softmax(const void *A, const void *B, void *P, 
         least = least > more ? least : more;
     }
     if (loads_ok && lda <= (1 << 20) && ldb <= (1 << 20) && p_dt == PERF_F32 && N <= 1024 && K <= 512 && strips >= least) {
-        if (N <= 64 && few) PERF_WIDE(1, float, 2, true);
+        if (N <= 64 && few) PERF_WIDE(1, float, 2, false, true);
         if (N <= 64) PERF_WIDE(1, float, 2);
-        if (N <= 128 && few) PERF_WIDE(1, float, 4, true);
+        if (N <= 128 && few) PERF_WIDE(1, float, 4, false, true);
         if (N <= 128) PERF_WIDE(1, float, 4);
         if (N <= 256) PERF_WIDE(2, float, 4);
-        if (N <= 384) PERF_WIDE(3, float);
-        if (N <= 512) PERF_WIDE(2, float, 8);
-        if (N <= 640) PERF_WIDE(5, float);
-        if (N <= 768) PERF_WIDE(3, float, 8);
-        PERF_WIDE(4, float, 8);
+        // Eight waves, or own stages, for what two workgroups per CU hold at a time (512 strips); the shared stages, whose kernels leave
+        // room for three and more, for more strips if the reduction is long or the last of the chip's rounds would be nearly
+        // empty otherwise.  Us, without these lines, now: 160 x (759x359x384) 145.7, 127.3; 192 x (424x416x512) 137.8, 127.9;
+        // 224 x (101x424x16) 14.2, 13.4; 112 x (576x592x384) 116.5, 112.6; 308 x (48x653x8) 16.8, 15.7 (768 strips in one
+        // round); 330 x (176x760x192) 100, 89; but 94 x (384x490x72) 25.8 against 27.8, 40 x (514x716x192) 31.4 against 33.2.
+        // Four waves with twice the tiles for long reductions of wider rows (242 x (111x800x320) 90, 83; 320 x (32x896x128) 34.5, 31.8;
+        // 208 x (224x992x320) 145, 134), and eight for few strips of 513 to 640 columns (64 x (2x616x80) 8.1, 7.8).
+        if (N <= 384) {
+            if ((strips > 512 && K > 96) || (strips > 256 && K > 256)) PERF_WIDE(3, float, 4);
+            PERF_WIDE(3, float, 4, true);
+        }
+        if (N <= 512) {
+            if (strips > 512 && (strips <= 1024 ? K <= 160 : K > 96)) PERF_WIDE(4, float, 4);
+            PERF_WIDE(2, float, 8);
+        }
+        if (N <= 640) {
+            if (strips <= 256 && K <= 96) PERF_WIDE(3, float, 8, true);
+            if (strips > 768 && K > 256) PERF_WIDE(5, float, 4);
+            PERF_WIDE(5, float, 4, true);
+        }
+        if (N <= 768) {
+            if (strips > 512 && (strips <= 768 ? K <= 160 : K > 160)) PERF_WIDE(6, float, 4);
+            PERF_WIDE(3, float, 8, true);
+        }
+        if (strips > 256 && K > (N <= 896 ? 96 : 160)) {
+            if (N <= 896) PERF_WIDE(7, float, 4, true);
+            PERF_WIDE(8, float, 4, true);
+        }
+        PERF_WIDE(4, float, 8, true);
     }
 #undef PERF_WIDE
     // Unfused: scores into P, then the row softmax in place (fp32 P only).

@@ -135,6 +135,20 @@ def test_strip_kernel_bf16_output_few_and_many(M, N, K, batch):
     _check(M, N, K, batch=batch, p_bf16=True)
 
 
+@pytest.mark.parametrize("M,N,K,batch,ldp", [
+    (33, 383, 72, 257, 383), (2, 300, 168, 257, 300), (33, 509, 40, 257, 509),   # shared stages: three and four tiles
+    (1, 640, 168, 513, 643), (33, 700, 24, 257, 700), (1, 768, 168, 769, 768),   # ... five and six
+    (3, 577, 64, 257, 577), (17, 895, 104, 257, 896), (1, 1001, 168, 257, 1001),  # a wave's own: five, seven and eight
+])
+def test_strip_kernel_more_strips_than_the_chip_holds(M, N, K, batch, ldp):
+    test_strip_kernel_edges(M, N, K, batch, ldp)
+
+
+@pytest.mark.parametrize("M,N,K,batch", [(40, 384, 128, 3), (33, 381, 64, 257), (33, 385, 128, 3), (33, 499, 64, 257)])
+def test_strip_kernel_bf16_output_tiles_and_waves(M, N, K, batch):
+    _check(M, N, K, batch=batch, p_bf16=True)
+
+
 def test_argmax_matches_scores():
     M, N, K = 256, 512, 64
     a, b = _inputs(M, N, K, 1, seed=7)
