@@ -271,7 +271,7 @@ __global__ __launch_bounds__(256) void bn_apply_kernel(const XT *__restrict__ x,
     else write(std::true_type{});
 }
 
-// Channels of up to 4096 chunks, which a workgroup holds in registers: a workgroup per channel, one launch, x is read once.
+// Channels of up to 4096 chunks (but see `spread` in launch_bn), which a workgroup holds in registers: a workgroup per channel, one launch, x is read once.
 // Bound by latency (launch, loads, block sums, stores) and the vector work of one CU per channel; two launches took (us, now):
 // 8x232x128x8 bf16 9.5 (4.3), 32x256x7x7 fp32 8.1 (4.2), 8x224x76x16 fp32 10.2 (6.4), 1x40x104x286 bf16 8.6 (6.5).  Larger channels
 // use more CUs in two launches (16x39x65x42 bf16, 5472 chunks, 8.1 against 11.0; 10x16x12x194 fp32, 5820, 6.9 against 7.4).
@@ -469,7 +469,11 @@ static void launch_bn(const BnArgs &a, bool vec)
         return;
     }
     const int64_t cpp = (a.HW + E - 1) / E;
-    if (a.N * cpp <= 4096) {
+    // (bf16 has twice the elements to a chunk, and ragged ones are masked one by one: with few planes, each a small workgroup's, two launches
+    // share that among more CUs.  us, one launch, two: 32x16x7x127 8.4, 6.6; 37x4x7x101 7.6, 6.2; 16x8x112x18 6.5, 5.8; but with
+    // 2000 ragged chunks 0.86 of the two, 3500 whole ones 0.98, more than 512 planes 0.9, 7x48x32x136 with 544 chunks in each 6.5, 7.6)
+    const bool spread = E == 8 && a.N * cpp > (vec ? 3520 : 2048) && a.N * a.C <= 512 && cpp <= (vec ? 256 : 560);
+    if (a.N * cpp <= 4096 && !spread) {
         const BnGeom g{a.HW, (int)a.C, (int)a.N, cpp, (int)a.N, 0, 1, div_magic(cpp)};
         auto go = [&](auto nj, auto threads) {
             constexpr int NJ = decltype(nj)::value, THREADS = decltype(threads)::value;

@@ -118,6 +118,17 @@ def test_channels_in_one_workgroup(N, C, H, W, x_bf16, y_bf16):
     _check(N, C, H, W, x_bf16=x_bf16, y_bf16=y_bf16, seed=N + W, offsets=[30.0] * C, inplace=x_bf16 == y_bf16, want_stats=False)
 
 
+@pytest.mark.parametrize("y_bf16", [True, False])
+@pytest.mark.parametrize("N,C,H,W", [
+    (16, 2, 40, 44), (16, 2, 112, 18),             # whole chunks, the most in one launch and more
+    (16, 2, 31, 33), (17, 2, 31, 33),              # ragged ones
+    (32, 16, 7, 127), (32, 17, 7, 127),            # the most planes that are spread
+    (14, 2, 32, 64), (13, 2, 33, 72), (4, 2, 63, 71), (4, 2, 63, 73),   # the longest, whole and ragged
+])
+def test_bf16_channels_in_one_launch_or_two(N, C, H, W, y_bf16):
+    _check(N, C, H, W, x_bf16=True, y_bf16=y_bf16, seed=N + W, inplace=y_bf16)
+
+
 @pytest.mark.parametrize("ratio", [1e4, 1e5, 1e6, 3e6])
 @pytest.mark.parametrize("N,C,H,W", [(2, 16, 16, 32), (4, 16, 31, 33), (4, 16, 64, 64)])   # 256 and 1024 threads, whole and ragged
 def test_one_workgroup_large_offsets(N, C, H, W, ratio):
