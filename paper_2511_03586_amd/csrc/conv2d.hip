@@ -1712,8 +1712,9 @@ static perf_status conv2d_impl(const void *x, const void *w, void *y, int64_t N,
     if (variant == kConvAuto && one_tap && !few_macs && K <= 64 * kMaxGridYZ && !(xw_dt == PERF_F32 && y_dt == PERF_BF16) &&
         (mfma_ok ? K >= 256 && tiles128 >= 192 : K > 64 || px < (xw_dt == PERF_F32 ? 65536 : 16384)))
         return perf_gemm(x, w, y, N * P * Q, K, C, PERF_ROW_MAJOR, C, PERF_COL_MAJOR, C, K, 1, 0, 0, 0, 1.0f, xw_dt, y_dt, stream);
-    // few tiles with a long reduction: the staged kernel's wave groups share it (8x28x28 256->128 12.8 us against 16.5 on the
-    // shared main loop, 20x20 256->256 12.2 against 16.1, 14x14 128->64 with 5x5 taps about even at 1600)
+    // few tiles with a long reduction: the staged kernel's wave groups share it.  What reaches this has 32 taps and more, or operands
+    // that launch_waves_conv refuses (us, against the shared main loop: 8x28x28x64 -> 64 7x7 15.3, 21.3; 20x20 256 -> 256 6x6 36,
+    // 56; 48x48x64 -> 96 x2 6x6, 2304 long, 12.1, 16.6; 40x33x32 -> 64 x3 7x7, 1568 long, 11.3, 12.0)
     const bool few_long = mfma_ok && staged_ok && R * S * C >= 1600 && ((N * P * Q + 63) / 64) * ((K + 63) / 64) <= 256;
     const StagedConv staged{x, w, y, g.N, g.H, g.W, g.C, g.K, g.R, g.S, g.sh, g.sw, g.ph, g.pw, g.P, g.Q, st};
     perf_status waves_status;

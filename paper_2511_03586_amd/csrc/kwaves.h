@@ -275,7 +275,8 @@ struct WavesShape {
     static constexpr int kWave = ASrc::kLds + BSrc::kLds > kSum ? ASrc::kLds + BSrc::kLds : kSum;
     static constexpr int kLds = kWave * W + 8 * W;  // (and a flag and a value per wave)
     static_assert(kLds <= 160 * 1024, "LDS of one CU");
-    // registers: 256 for 64 x 64 (and all but the smallest fp32 tile), 168 and 128 for the smaller ones
+    // registers: 256 for 64 x 64 (and all but the smallest fp32 tile), 168 and 128 for the smaller ones (fp32 64 x 64 spills 1 to 4
+    // of them if B is WaveRows, 11 if A is WaveConv, which spills 1 at 32 x 32)
     static constexpr int kWavesPerSimd = TM * TN == 1 ? 4 : TM * TN == 2 && sizeof(T) == 2 ? 3 : 2;
 };
 

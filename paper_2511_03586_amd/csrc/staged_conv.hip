@@ -53,9 +53,10 @@ static perf_status launch_typed(const StagedConv &c)
     }
     // Tile by size (us): fp32 takes 128 x 64 from 192 of them on (8x56x56x64->64 21.3 against 22.4 with 64 x 64,
     // 8x28x28x128->256 37.1 against 39.3); two groups of waves where 64 x 64 tiles leave CUs idle and the reduction
-    // is long (bf16 20x20x256->256 13.5 against 16.2).  Larger tiles were never ahead: the pixels' addresses take registers.
+    // is long (8x28x28x64->128 fp32 13.3 against 15.6; bf16 with more than 31 taps, 28x28x16->64 x2 7x7 8.1 against 9.3,
+    // 28x28x16->64 x8 6x6, 576 long, 7.2 against 7.1).  Larger tiles were never ahead: the pixels' addresses take registers.
     if (sizeof(T) == 4 && K <= (1 << 21) && tiles_of(c, 128, 64) >= 192) return launch_whole<T, CT, 2, 1, 2, 2, 1, 2>(c);
-    if constexpr (sizeof(T) == 2)  // ... four groups from 1600 on (20x20 256->256 12.2 against 13.6 with two)
+    if constexpr (sizeof(T) == 2)  // ... four groups from 1600 on (8x28x28x64->64 7x7 15.3 against 17.7 with two)
         if (K >= 1600 && tiles_of(c, 64, 64) <= 256) return launch_whole<T, CT, 1, 1, 2, 2, 4, 1>(c);
     if (K >= 512 && tiles_of(c, 64, 64) <= 256) return launch_whole<T, CT, 1, 1, 2, 2, 2, sizeof(T) == 2 ? 2 : 4>(c);
     return launch_whole<T, CT, 1, 1, 2, 2, 1, 4>(c);

@@ -68,8 +68,9 @@ static int64_t tiles_of(const GemmArgs &g, int64_t bm, int64_t bn) { return ((g.
 //     for its start: 2999x5003x2048 72 against 80 with 128 x 128; 120 x (125x357x112) 14.7 against 12.8 without it.
 //   * 128 x 128 (4 waves, two workgroups per CU) from 192 such tiles on: 952x3562x489 13.6 against 17.4 with 64 x 64.
 //   * 64 x 64, four register sets of loads in flight; with few tiles and a long reduction instead two groups of waves
-//     that share the K-steps: 336x640x1000 7.8 against 9.2 (8.7 with four groups), 256x256x4096 16.2 against 20.4 (16.3),
-//     512x512x512 even; one register set up to K = 64, where the loads for steps that do not exist cost more than the
+//     that share the K-steps, where launch_waves_gemm leaves such calls: 960x1000x600 row-major 8.2 against 8.7 (9.0 with four
+//     groups), 640x1024x896 7.2 against 8.1 (8.6), 999x901x520 with K contiguous 6.6 against 6.9 (7.5), but 1003x1003x513
+//     7.6 against 7.4 (8.6), 16 x (256x256x512) 7.2 against 7.1 (8.3); one register set up to K = 64, where the loads for steps that do not exist cost more than the
 //     latency they hide (1000x1000x20 6.2 against 5.6, 100x100x36 5.5 against 4.9).
 template <typename CT>
 static perf_status launch_bf16(const GemmArgs &g, bool big_ok)

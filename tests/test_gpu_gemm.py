@@ -127,18 +127,20 @@ def test_general_kernel_layouts_exact_integers(a_col, b_col, M, N, K):
 @pytest.mark.parametrize("a_col,b_col", [(False, False), (True, False), (True, True), (False, True)])
 @pytest.mark.parametrize("M,N,K,batch,pad", [
     (1, 1, 1, 1, 0), (7, 3, 5, 2, 0), (3, 300, 7, 1, 1),       # extents below a 16-byte load: element loads
-    (8, 9, 8, 1, 0), (64, 64, 64, 1, 0), (65, 71, 130, 2, 3),    # 64 x 64 tile: exact, ragged in every extent, odd ld
+    (8, 9, 8, 1, 0), (64, 64, 64, 1, 0), (65, 71, 130, 2, 3),    # one tile; exact, ragged in every extent, odd ld (the waves' kernel)
     (100, 70, 643, 1, 1), (64, 130, 1024, 1, 0), (9, 10, 257, 3, 1),   # long reductions on few tiles (the waves' kernel)
     (64, 72, 704, 1, 0), (72, 64, 288, 1, 0), (64, 64, 1216, 1, 0),
-    (705, 641, 577, 1, 1), (704, 648, 704, 1, 0), (704, 648, 1088, 1, 0),   # two groups of waves (bf16, row-major): K-steps that they
+    (705, 741, 577, 1, 1), (704, 744, 704, 1, 0), (704, 744, 1088, 1, 0),   # two groups of waves (bf16, row-major): K-steps that they
                                                                  # do not divide, with edges and without
     (70, 65, 96, 65, 1), (100, 66, 67, 100, 0),                  # 64 x 64 (fp32), one register set
     (64, 61, 300, 641, 0),                                       # ... four
     (257, 131, 97, 64, 0), (130, 250, 64, 96, 5),                # 128 x 128 (bf16), 256 x 128 (fp32)
     (40, 33, 521, 200, 1), (300, 261, 512, 100, 0),              # 256 x 256 (bf16): ragged first and second tiles
     (500, 250, 70, 40, 1), (128, 120, 65, 130, 0), (33, 65, 20, 128, 0),   # 256 x 128 (fp32), full and half full; 64 x 64 instead
-    (3, 70, 130, 2, 1), (70, 2, 77, 3, 0), (1, 9, 8, 1, 0),      # element loads for the short operand only
-    (70, 130, 64, 1, 1), (70, 130, 65, 1, 0), (70, 130, 97, 1, 0),   # one register set for short reductions
+    (3, 70, 40, 2, 1), (70, 2, 20, 3, 0), (1, 9, 8, 1, 0),       # element loads for the short operand only
+    (3, 70, 130, 2, 1), (70, 2, 77, 3, 0),                       # ... short operands of the waves' kernel
+    (70, 130, 40, 1, 1), (70, 130, 31, 1, 0),                    # one register set for short reductions (bf16, fp32)
+    (70, 130, 64, 1, 1), (70, 130, 65, 1, 0), (70, 130, 97, 1, 0),   # ... of the waves' kernel
 ])
 def test_staged_kernel_edges(M, N, K, batch, pad, a_col, b_col, ab_bf16, c_bf16):
     """Every layout and type of the register-staged contraction at the edges of its tiles, K-steps and loads."""
@@ -169,9 +171,9 @@ def test_staged_kernel_edges(M, N, K, batch, pad, a_col, b_col, ab_bf16, c_bf16)
     (700, 600, 40, 1, 1), (577, 450, 66, 1, 0),                  # 32 x 32 with four waves (fp32), pairs of tiles (bf16); an odd row alone
     (450, 577, 127, 1, 1), (450, 577, 513, 1, 1),                # in the last pair, an odd column (row-major)
     (20, 9000, 130, 1, 1), (9000, 20, 513, 1, 0),                # pairs along the only operand with more than a tile
-    (705, 641, 64, 1, 1), (705, 641, 100, 1, 0), (705, 641, 128, 1, 1),   # two waves: one K-step, the last overlapping, one each
-    (705, 641, 200, 1, 1), (705, 641, 400, 1, 0),                # one round of 64 x 64: 32 x 32 and pairs
-    (705, 641, 1030, 1, 0), (705, 741, 2113, 1, 1), (768, 768, 2080, 1, 0),   # ... 64 x 64 with eight waves; the direct kernels' shapes
+    (705, 741, 64, 1, 1), (705, 741, 100, 1, 0), (705, 741, 128, 1, 1),   # two waves: one K-step, the last overlapping, one each
+    (705, 741, 200, 1, 1), (705, 741, 400, 1, 0),                # one round of 64 x 64: 32 x 32 and pairs
+    (705, 741, 1030, 1, 0), (705, 741, 2113, 1, 1), (768, 768, 2080, 1, 0),   # ... 64 x 64 with eight waves; the direct kernels' shapes
     (1030, 1090, 70, 1, 0), (1030, 1090, 130, 1, 1), (1030, 1090, 300, 1, 1),   # several rounds: two waves; pairs with two and four
     (1025, 1089, 515, 1, 0), (1025, 1089, 1100, 1, 1),           # ... 64 x 64, ragged by one
     (100, 70, 130, 37, 3), (65, 33, 200, 11, 0), (64, 64, 520, 300, 0),   # batches that 8 does not divide, tiles that it does not
