@@ -170,6 +170,7 @@ def test_staged_kernel_edges(M, N, K, batch, pad, a_col, b_col, ab_bf16, c_bf16)
     (33, 65, 32, 1, 0), (33, 65, 63, 3, 1),                      # fp32: one K-step, one and most of another
     (700, 600, 40, 1, 1), (577, 450, 66, 1, 0),                  # 32 x 32 with four waves (fp32), pairs of tiles (bf16); an odd row alone
     (450, 577, 127, 1, 1), (450, 577, 513, 1, 1),                # in the last pair, an odd column (row-major)
+    (705, 641, 1030, 1, 0),                                      # ... the longest of a few tiles; 64 x 64 with eight waves (fp32)
     (20, 9000, 130, 1, 1), (9000, 20, 513, 1, 0),                # pairs along the only operand with more than a tile
     (705, 741, 64, 1, 1), (705, 741, 100, 1, 0), (705, 741, 128, 1, 1),   # two waves: one K-step, the last overlapping, one each
     (705, 741, 200, 1, 1), (705, 741, 400, 1, 0),                # one round of 64 x 64: 32 x 32 and pairs
