@@ -110,7 +110,8 @@ def test_strip_kernel_edges(M, N, K, batch, ldp):
 
 @pytest.mark.parametrize("M,N,K,batch,ldp", [
     (33, 384, 72, 9, 384), (31, 385, 80, 9, 385), (17, 449, 128, 16, 452),      # three tiles per wave, then two with eight waves
-    (33, 545, 96, 32, 545), (16, 673, 64, 64, 675), (32, 800, 136, 64, 800),    # three and four, whose last waves have none
+    (33, 545, 96, 32, 545), (16, 673, 64, 64, 675), (32, 800, 128, 64, 800),    # three and four, whose last waves have none
+    (32, 800, 136, 64, 800),                                                    # (two launches)
 ])
 def test_strip_kernel_waves_and_tiles(M, N, K, batch, ldp):
     # both forms of the K-loop and of the write-out at the counts where they change, rows of 4 and 16 bytes' alignment
@@ -136,8 +137,8 @@ def test_strip_kernel_bf16_output_few_and_many(M, N, K, batch):
 
 
 @pytest.mark.parametrize("M,N,K,batch,ldp", [
-    (33, 383, 72, 257, 383), (2, 300, 168, 257, 300), (33, 509, 40, 257, 509),   # shared stages: three and four tiles
-    (1, 640, 168, 513, 643), (33, 700, 24, 257, 700), (1, 768, 168, 769, 768),   # ... five and six
+    (33, 383, 104, 257, 383), (1, 300, 264, 401, 300), (33, 509, 40, 257, 509),  # shared stages: three and four tiles
+    (1, 514, 264, 769, 517), (33, 700, 24, 257, 700), (1, 768, 168, 769, 768),   # ... five and six
     (3, 577, 64, 257, 577), (17, 895, 104, 257, 896), (1, 1001, 168, 257, 1001),  # a wave's own: five, seven and eight
 ])
 def test_strip_kernel_more_strips_than_the_chip_holds(M, N, K, batch, ldp):
