@@ -312,8 +312,8 @@ def test_rows_shared_by_two_tiles_have_one_writer(M, N, K, tiny_row, tiny_col):
 
 @pytest.mark.parametrize("M,N,K,tiny_row,tiny_col", [(1061, 1030, 40, 1040, None), (1061, 1030, 96, None, 1026), (1633, 1630, 130, 1605, 1626)])
 def test_rows_shared_by_two_tiles_have_one_writer_staged(M, N, K, tiny_row, tiny_col):
-    """As above on shapes that the staged kernel runs, with 64 x 64 tiles: there a ragged last tile starts early and reads rows and columns that its neighbour stores. A tile's bits alone come from a batch of
-    it that the same kernel runs."""
+    """As above on shapes that the staged kernel runs, with 64 x 64 tiles: there a ragged last tile starts early and reads rows
+    and columns that its neighbour stores. A tile's bits alone come from a batch of it that the same kernel runs."""
     g = np.random.default_rng(M + N)
     a, b = g.uniform(-1, 1, (K, M)).astype(np.float32), g.uniform(-1, 1, (K, N)).astype(np.float32)
     if tiny_row is not None:
